@@ -4,11 +4,28 @@
 // Per row: z_i = logit_i / T, e_i = exp(z_i - max z).  The nucleus is {i : e_i >= tau}, tau being the largest of the e
 // values for which the members' sum reaches top_p * sum of all e (elements equal to tau are all in).  The token is drawn
 // by the inverse CDF over the nucleus taken in index order: the first member whose running sum exceeds u * (nucleus sum),
-// u in [0, 1) supplied by the caller.  No sort: tau is found by bisection on the bit pattern of a non-negative float
-// (31 passes over the row's e values, which stay in L2), every sum has a fixed order, so a call is reproducible.
+// u in [0, 1) supplied by the caller.
+//
+// No sort, and no pass over the row per bit of tau.  The scores t = log2(e) * z are dropped into 256 bins of an eighth of
+// an octave below the largest one, with the mass of each bin; the bins alone tell which one holds tau, and only that
+// bin's elements (one to three per cent of a row) are looked at individually.  All masses are integers - units of 2^-44 of
+// a power of two at the largest score, so every fp32 probability above 2^-20 enters with all its bits - and integer sums
+// do not depend on their order: a call is reproducible although the bins are filled with LDS atomics.
+//
+// A row is 501 KB at 128 256 tokens and one compute unit fetches some 120 GB/s, so one workgroup per row is bound by its
+// compute unit's loads and exponentials whatever it does (the 33 passes of the bisection that stood here: 849 us for 64
+// rows, 25 us a pass, against 6.4 us to read the logits once at the rate of a copy).  Long rows are therefore cut into
+// chunks of at most 8192 tokens, one workgroup each (1024 workgroups for 64 rows), in three launches: bins of every chunk;
+// probabilities and members of the decisive bin of every chunk; tau and the token of every row.  What the launches hand
+// on lies in the first RESERVED floats of every chunk's part of the scratch buffer, which receive their probabilities
+// last.
+// Measured at 64 rows of 128 256 tokens: 849 -> 45 us (12 + 18 + 15; the 99 MB the first two launches cannot avoid moving
+// take 19 us), 39 us for one row.  Rows of up to 8192 tokens fit one workgroup's registers and take one launch: 21 us at
+// 8192 tokens, where the three launches take 28 (64 rows; 43 against 47 us for 512 rows).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "../../include/www.h"
@@ -19,117 +36,572 @@ void set_error(const char* fmt, ...);
 
 namespace {
 
+constexpr int BINS = 256, BINS_PER_OCTAVE_LOG2 = 3;
+constexpr int SUB = 8192;            // elements a workgroup of 256 threads holds in registers at a time
+constexpr int MAX_CHUNKS = 1024;     // chunks of a row (longer rows take longer chunks)
+constexpr int HEAD = 2 + 2 * BINS;   // start of a chunk's scratch: largest bin, candidates found, bin masses (low words, high words)
+constexpr int CAND_MAX = 510;        // room for a chunk's candidates behind that
+constexpr int RESERVED = HEAD + CAND_MAX;
+constexpr int ROW_CAND = 8192;       // candidates of a row that are looked at in LDS
 constexpr int TPB = 1024;
+constexpr int WAVES = TPB / 64;
 
-// sum of v over the workgroup, added in a fixed order (lanes by halving, then wavefronts in index order); all threads get it
-__device__ float block_sum(float v, float* red) {
-#pragma unroll
-  for (int s = 32; s >= 1; s >>= 1) v += __shfl_xor(v, s);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  __syncthreads();  // red may still be read from the previous call
-  if (lane == 0) red[wave] = v;
-  __syncthreads();
-  float t = 0.f;
-#pragma unroll
-  for (int w = 0; w < TPB / 64; ++w) t += red[w];
-  return t;
+typedef unsigned long long u64;
+
+// bin of a score, clamped far outside the range of finite scores (NaN falls to the bottom)
+__device__ __forceinline__ int bin_of(float t) {
+  return (int)floorf(fminf(fmaxf(t * (float)(1 << BINS_PER_OCTAVE_LOG2), -536870912.f), 536870912.f));
+}
+// power of two above every probability of a row or chunk whose largest score lies in bin `top`
+__device__ __forceinline__ int ref_of(int top) { return (top >> BINS_PER_OCTAVE_LOG2) + 1; }
+__device__ __forceinline__ float prob(float logit, float c, int ref) { return __builtin_amdgcn_exp2f(__builtin_fmaf(logit, c, -(float)ref)); }
+// e in [0, 1] in units of 2^-44
+__device__ __forceinline__ u64 mass_of(float e) {
+  const float s = e * 1048576.f;
+  const uint32_t hi = (uint32_t)s;
+  const uint32_t lo = (uint32_t)((s - (float)hi) * 16777216.f);
+  return ((u64)hi << 24) + lo;
+}
+__device__ __forceinline__ u64 shifted(u64 v, int k) { return k < 64 ? v >> k : 0ull; }
+// order-preserving integer of a float
+__device__ __forceinline__ uint32_t key_of(float x) {
+  const uint32_t b = __float_as_uint(x);
+  return (b & 0x80000000u) ? ~b : b | 0x80000000u;
 }
 
+__device__ __forceinline__ u64 wave_sum(u64 v) {
+#pragma unroll
+  for (int s = 32; s >= 1; s >>= 1) v += __shfl_xor(v, s);
+  return v;
+}
+__device__ __forceinline__ u64 wave_scan(u64 v) {  // inclusive
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int s = 1; s < 64; s <<= 1) {
+    const u64 up = __shfl_up(v, s);
+    if (lane >= s) v += up;
+  }
+  return v;
+}
+
+template <int NT>
 __device__ float block_max(float v, float* red) {
 #pragma unroll
   for (int s = 32; s >= 1; s >>= 1) v = fmaxf(v, __shfl_xor(v, s));
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  __syncthreads();
-  if (lane == 0) red[wave] = v;
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
   float t = red[0];
 #pragma unroll
-  for (int w = 1; w < TPB / 64; ++w) t = fmaxf(t, red[w]);
+  for (int w = 1; w < NT / 64; ++w) t = fmaxf(t, red[w]);
   return t;
 }
 
-__global__ __launch_bounds__(TPB) void sample_top_p_kernel(const float* __restrict__ logits, int V, float inv_T, float top_p,
-                                                           const float* __restrict__ u01, float* __restrict__ scratch,
-                                                           int32_t* __restrict__ tokens) {
-  __shared__ float red[TPB / 64];
-  __shared__ float part[TPB];
-  __shared__ int s_owner;
-  __shared__ float s_before;
-  const int row = blockIdx.x, tid = threadIdx.x;
-  const float* lg = logits + (int64_t)row * V;
-  float* e = scratch + (int64_t)row * V;
-
-  float m = -INFINITY;
-  for (int i = tid; i < V; i += TPB) m = fmaxf(m, lg[i] * inv_T);
-  m = block_max(m, red);
-  float acc = 0.f;
-  for (int i = tid; i < V; i += TPB) {
-    const float x = exp2f((lg[i] * inv_T - m) * 1.4426950408889634f);
-    e[i] = x;
-    acc += x;
+// The first of BINS bins, largest elements first, at which the mass so far reaches `share` of the total (want < 0) or
+// `want`; `need` is what its own members have to contribute.  Called by one whole wavefront.
+__device__ void find_boundary(const u64* hist, float share, double want, int* bin, double* need) {
+  const int lane = threadIdx.x & 63;
+  u64 h[4], s = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) { h[i] = hist[lane * 4 + i]; s += h[i]; }
+  const u64 incl = wave_scan(s);
+  const double total = (double)__shfl(incl, 63);
+  want = want < 0. ? (double)share * total : fmin(want, total);
+  const u64 reached = __ballot((double)incl >= want);
+  if (lane == (reached ? __ffsll((long long)reached) - 1 : 63)) {
+    u64 before = incl - s;
+    int i = 0;
+    while (i < 3 && (double)(before + h[i]) < want) before += h[i++];
+    *bin = lane * 4 + i;
+    *need = fmin(want - (double)before, (double)h[i]);  // (sums beyond 2^53 are rounded: never more than the bin holds)
   }
-  const float total = block_sum(acc, red);  // the barriers inside also make every thread's e[] visible to the workgroup
-  const float need = top_p * total;
+}
 
-  // largest threshold (as a bit pattern; non-negative floats order like their bits) whose members' sum still reaches `need`
-  uint32_t lo = 0u, hi = 0x3F800001u;  // sum(e >= 0) = total >= need;  no e exceeds 1
-  while (hi - lo > 1u) {
-    const uint32_t mid = lo + (hi - lo) / 2u;
-    const float thr = __uint_as_float(mid);
-    float s = 0.f;
-    for (int i = tid; i < V; i += TPB) {
-      const float x = e[i];
-      s += x >= thr ? x : 0.f;
+// tau among n candidates: the largest key whose members' mass reaches `need` (the smallest key if rounding keeps even
+// that from it).  A search with sixteen thresholds a round, one per wavefront.
+__device__ uint32_t find_tau(const uint32_t* keys, const u64* mass, int n, double need, uint32_t lo, uint32_t hi, int* reached) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int turn = 0;  // two sets of answers, so that a round needs one barrier
+  while (hi - lo > 1u) {  // members of lo suffice, members of hi do not
+    const uint32_t step = (hi - lo - 1u) / (WAVES + 1) + 1u;
+    const u64 at = (u64)lo + (u64)step * (wave + 1);
+    bool ok = false;
+    if (at < hi) {
+      u64 s = 0;
+      for (int i = lane; i < n; i += 64) s += keys[i] >= (uint32_t)at ? mass[i] : 0ull;
+      ok = (double)wave_sum(s) >= need;
     }
-    s = block_sum(s, red);
-    if (s >= need) lo = mid; else hi = mid;  // the same value in every thread
+    if (lane == 0) reached[turn + wave] = ok;
+    __syncthreads();
+    int c = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) c += reached[turn + w];  // (monotone: the first c thresholds reach it)
+    turn = WAVES - turn;
+    const uint32_t l = lo + step * c;
+    if (c < WAVES && hi - l > step) hi = l + step;
+    lo = l;
   }
-  const float tau = __uint_as_float(lo);
+  return lo;
+}
 
-  // inverse CDF over the nucleus in index order: contiguous segment per thread, running sums across threads by thread 0
-  const int seg = (V + TPB - 1) / TPB;
-  const int i0 = min(tid * seg, V), i1 = min(i0 + seg, V);
-  float mine = 0.f;
+// The token: the first member (key >= tau) among elements [0, n) of x whose running mass exceeds `target`.  Each thread
+// takes a contiguous run, so that the running masses of the threads follow index order.  All threads of the workgroup
+// call it; `base` is added to the index.
+__device__ void pick(const float* x, int n, float c, int ref, uint32_t tau, u64 target, int base, u64* wave_tot, int32_t* token) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int per = (n + TPB - 1) / TPB;
+  const int i0 = min(tid * per, n), i1 = min(i0 + per, n);
+  u64 mine = 0;
+#pragma unroll 8
   for (int i = i0; i < i1; ++i) {
-    const float x = e[i];
-    mine += x >= tau ? x : 0.f;
+    const float v = x[i];
+    mine += key_of(v) >= tau ? mass_of(prob(v, c, ref)) : 0ull;
   }
-  part[tid] = mine;
+  const u64 incl = wave_scan(mine);
+  if (lane == 63) wave_tot[wave] = incl;
   __syncthreads();
-  if (tid == 0) {
-    float nuc = 0.f;
-    for (int t = 0; t < TPB; ++t) nuc += part[t];
-    const float target = u01[row] * nuc;
-    float run = 0.f;
-    int owner = -1;
-    for (int t = 0; t < TPB && owner < 0; ++t) {
-      if (part[t] > 0.f && target < run + part[t]) { owner = t; s_before = run; }
-      else run += part[t];
+  u64 before = incl - mine;
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) before += w < wave ? wave_tot[w] : 0ull;
+  if (before <= target && target < before + mine) {
+    u64 run = before;
+    int at = i0;
+    for (int i = i0; i < i1; ++i) {
+      const float v = x[i];
+      if (key_of(v) >= tau) run += mass_of(prob(v, c, ref));
+      if (target < run) { at = i; break; }
     }
-    if (owner < 0) {  // rounding at the very end of the range: the last thread that holds a member
-      for (int t = TPB - 1; t >= 0 && owner < 0; --t)
-        if (part[t] > 0.f) owner = t;
-      s_before = -INFINITY;  // marks the fallback: take the owner's last member
+    *token = base + at;
+  }
+}
+
+// target of the draw inside a nucleus of mass `nucleus`
+__device__ __forceinline__ u64 draw_target(float u, u64 nucleus) {
+  const u64 t = (u64)((double)fmaxf(u, 0.f) * (double)nucleus);
+  return t < nucleus ? t : (nucleus ? nucleus - 1 : 0ull);
+}
+
+// ---- rows of up to SUB tokens: one workgroup per row, everything in LDS
+struct SmallLds {
+  uint32_t keys[ROW_CAND];
+  u64 mass[ROW_CAND];
+  u64 hist[BINS];
+  u64 wave_tot[WAVES];
+  double need;
+  float red[WAVES];
+  int reached[2 * WAVES];
+  int bin, count;
+};
+
+__global__ __launch_bounds__(TPB) void sample_row_kernel(const float* __restrict__ logits, int V, float c, float top_p,
+                                                         const float* __restrict__ u01, float* __restrict__ scratch,
+                                                         int32_t* __restrict__ tokens) {
+  extern __shared__ __align__(16) char smem[];
+  SmallLds& S = *reinterpret_cast<SmallLds*>(smem);
+  const int tid = threadIdx.x, row = blockIdx.x;
+  const float* lg = logits + (int64_t)row * V;
+  constexpr int PER = SUB / TPB;
+  float x[PER];
+  float m = -INFINITY;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int i = k * TPB + tid;
+    x[k] = i < V ? lg[i] : -INFINITY;
+    m = fmaxf(m, x[k]);
+  }
+  if (tid < BINS) S.hist[tid] = 0;
+  if (tid == 0) S.count = 0;
+  const int top = bin_of(block_max<TPB>(m, S.red) * c), ref = ref_of(top);
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int i = k * TPB + tid;
+    if (i < V) {
+      const float e = prob(x[k], c, ref);
+      scratch[(int64_t)row * V + i] = e;
+      const u64 w = mass_of(e);
+      if (w) atomicAdd(&S.hist[min(BINS - 1, top - bin_of(x[k] * c))], w);
     }
-    s_owner = owner;
-    part[0] = target;
   }
   __syncthreads();
-  if (tid == s_owner) {
-    const float target = part[0];
-    float run = s_before;
-    int pick = -1, last = -1;
-    for (int i = i0; i < i1 && pick < 0; ++i) {
-      const float x = e[i];
-      if (!(x >= tau)) continue;
-      last = i;
-      if (s_before != -INFINITY) {
-        run += x;
-        if (target < run) pick = i;
+  if (tid < 64) find_boundary(S.hist, top_p, -1., &S.bin, &S.need);
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int i = k * TPB + tid;
+    if (i < V && min(BINS - 1, top - bin_of(x[k] * c)) == S.bin) {
+      const int at = atomicAdd(&S.count, 1);
+      S.keys[at] = key_of(x[k]);
+      S.mass[at] = mass_of(prob(x[k], c, ref));
+    }
+  }
+  __syncthreads();
+  const uint32_t tau = find_tau(S.keys, S.mass, S.count, S.need, 0u, 0xFFFFFFFFu, S.reached);
+  // mass of the nucleus
+  u64 mine = 0;
+#pragma unroll
+  for (int k = 0; k < PER; ++k)
+    if (k * TPB + tid < V && key_of(x[k]) >= tau) mine += mass_of(prob(x[k], c, ref));
+  mine = wave_sum(mine);
+  if ((tid & 63) == 0) S.wave_tot[tid >> 6] = mine;
+  __syncthreads();
+  u64 nucleus = 0;
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) nucleus += S.wave_tot[w];
+  __syncthreads();
+  if (nucleus) pick(lg, V, c, ref, tau, draw_target(u01[row], nucleus), 0, S.wave_tot, tokens + row);
+  else if (tid == 0) tokens[row] = 0;  // (a row without any finite logit)
+}
+
+// ---- longer rows, first launch: largest score and bin masses of every chunk
+__global__ __launch_bounds__(256) void sample_bins_kernel(const float* __restrict__ logits, int V, int chunk, float c, float* __restrict__ scratch) {
+  constexpr int COPIES = 16;  // of the bins, by lane, so that the lanes of a wavefront seldom meet in one
+  __shared__ u64 hist[BINS * COPIES];
+  __shared__ float red[4];
+  const int tid = threadIdx.x, first = blockIdx.y * chunk, n = min(chunk, V - first);
+  const float* lg = logits + (int64_t)blockIdx.x * V + first;
+  float x[SUB / 256];
+  auto load = [&](int base) __attribute__((always_inline)) {
+#pragma unroll
+    for (int k = 0; k < SUB / 256; ++k) {
+      const int i = base + k * 256 + tid;
+      x[k] = i < n ? lg[i] : -INFINITY;
+    }
+  };
+  float m = -INFINITY;
+  for (int base = 0; base < n; base += SUB) {
+    load(base);
+#pragma unroll
+    for (int k = 0; k < SUB / 256; ++k) m = fmaxf(m, x[k]);
+  }
+#pragma unroll
+  for (int k = 0; k < COPIES; ++k) hist[k * 256 + tid] = 0;
+  const int top = bin_of(block_max<256>(m, red) * c), ref = ref_of(top);
+  for (int base = 0; base < n; base += SUB) {
+    if (n > SUB) load(base);
+#pragma unroll
+    for (int k = 0; k < SUB / 256; ++k) {
+      const u64 w = mass_of(prob(x[k], c, ref));  // (0 for the -inf behind the end)
+      if (w) atomicAdd(&hist[min(BINS - 1, top - bin_of(x[k] * c)) * COPIES + (tid & (COPIES - 1))], w);
+    }
+  }
+  __syncthreads();
+  u64 s = 0;
+#pragma unroll
+  for (int k = 0; k < COPIES; ++k) s += hist[tid * COPIES + ((k + tid) & (COPIES - 1))];
+  float* region = scratch + (int64_t)blockIdx.x * V + first;
+  region[2 + tid] = __uint_as_float((uint32_t)s);
+  region[2 + BINS + tid] = __uint_as_float((uint32_t)(s >> 32));
+  if (tid == 0) region[0] = __int_as_float(top);
+}
+
+// Largest bin of a row, from its chunks' headers (called by every thread, the same value everywhere).
+__device__ __forceinline__ int row_top(const float* row, int chunk, int n_chunks) {
+  int top = -0x7fffffff;
+  for (int k = threadIdx.x & 63; k < n_chunks; k += 64) top = max(top, __float_as_int(row[(int64_t)k * chunk]));
+#pragma unroll
+  for (int s = 32; s >= 1; s >>= 1) top = max(top, __shfl_xor(top, s));
+  return top;
+}
+__device__ __forceinline__ u64 chunk_bin(const float* region, int bin) {
+  return ((u64)__float_as_uint(region[2 + BINS + bin]) << 32) | __float_as_uint(region[2 + bin]);
+}
+// ---- second launch: probabilities of every chunk (but its reserved head) and its members of the bin that holds tau
+__global__ __launch_bounds__(256) void sample_split_kernel(const float* __restrict__ logits, int V, int chunk, float c, float top_p, float* scratch) {
+  __shared__ u64 hist[BINS];
+  __shared__ double need;
+  __shared__ int bin, count;
+  const int tid = threadIdx.x, first = blockIdx.y * chunk, n = min(chunk, V - first);
+  const float* lg = logits + (int64_t)blockIdx.x * V + first;
+  float* row = scratch + (int64_t)blockIdx.x * V;
+  float* region = row + first;
+  float x[SUB / 256];
+  auto load = [&](int base) __attribute__((always_inline)) {
+#pragma unroll
+    for (int k = 0; k < SUB / 256; ++k) {
+      const int i = base + k * 256 + tid;
+      x[k] = i < n ? lg[i] : -INFINITY;
+    }
+  };
+  load(0);
+  hist[tid] = 0;
+  if (tid == 0) count = 0;
+  // bins of the row's chunks, one bin a thread, sixteen chunks in flight: they and the headers arrive together
+  constexpr int NB = 16;
+  u64 w[NB];
+  const int n_chunks = gridDim.y;
+  auto load_bins = [&](int k0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int k = 0; k < NB; ++k) w[k] = chunk_bin(row + (int64_t)min(k0 + k, n_chunks - 1) * chunk, tid);
+  };
+  load_bins(0);
+  const int top = row_top(row, chunk, n_chunks), ref = ref_of(top);
+  __syncthreads();
+  for (int k0 = 0; k0 < n_chunks; k0 += NB) {
+    if (k0) load_bins(k0);
+    const int mine = __float_as_int(row[(int64_t)min(k0 + (tid & 63), n_chunks - 1) * chunk]);
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      const int t = __builtin_amdgcn_readlane(mine, k);
+      const u64 v = k0 + k < n_chunks ? shifted(w[k], ref_of(top) - ref_of(t)) : 0ull;
+      if (v) atomicAdd(&hist[min(BINS - 1, tid + (top - t))], v);
+    }
+  }
+  __syncthreads();
+  if (tid < 64) find_boundary(hist, top_p, -1., &bin, &need);
+  __syncthreads();
+  const int b = bin;
+  for (int base = 0; base < n; base += SUB) {
+    if (base) load(base);
+#pragma unroll
+    for (int k = 0; k < SUB / 256; ++k) {
+      const int i = base + k * 256 + tid;
+      if (i >= RESERVED && i < n) region[i] = prob(x[k], c, ref);
+      const bool cand = i < n && min(BINS - 1, top - bin_of(x[k] * c)) == b;
+      const u64 who = __ballot(cand);
+      if (who) {  // one LDS addition per wavefront; the order of the list does not matter
+        const int lane = tid & 63, leader = __ffsll((long long)who) - 1;
+        int at = 0;
+        if (lane == leader) at = atomicAdd(&count, __popcll(who));
+        at = __shfl(at, leader) + __popcll(who & ((1ull << lane) - 1));
+        if (cand && at < CAND_MAX) region[HEAD + at] = x[k];
       }
     }
-    tokens[row] = pick >= 0 ? pick : last;
   }
+  __syncthreads();
+  if (tid == 0) region[1] = __int_as_float(count);
+}
+
+// ---- third launch: tau and the token of every row, and the probabilities of the reserved heads
+struct PickLds {
+  uint32_t keys[ROW_CAND];
+  u64 mass[ROW_CAND];
+  u64 hist[BINS];
+  u64 chunk_mass[MAX_CHUNKS];
+  int chunk_at[MAX_CHUNKS];  // first candidate of a chunk in the lists above
+  u64 wave_tot[WAVES];
+  u64 target;
+  double need;
+  int reached[2 * WAVES];
+  uint32_t klo[WAVES], khi[WAVES];
+  int bin, n_cand, overflow, chunk;
+};
+
+__global__ __launch_bounds__(TPB) void sample_pick_kernel(const float* __restrict__ logits, int V, int chunk, int n_chunks, float c, float top_p,
+                                                          const float* __restrict__ u01, float* scratch, int32_t* __restrict__ tokens) {
+  extern __shared__ __align__(16) char smem[];
+  PickLds& S = *reinterpret_cast<PickLds*>(smem);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const float* lg = logits + (int64_t)blockIdx.x * V;
+  float* row = scratch + (int64_t)blockIdx.x * V;
+  // A wavefront looks after chunk number `wave` (and every sixteenth from there): its bins, and the logits of its reserved
+  // head, are requested before anything else and kept, so that the chain of dependent reads below starts with one round trip.
+  constexpr int HREG = RESERVED / 64;
+  float hx[HREG];
+  u64 hb[BINS / 64];
+  {
+    const int64_t f = (int64_t)min(wave, n_chunks - 1) * chunk;
+#pragma unroll
+    for (int i = 0; i < BINS / 64; ++i) hb[i] = chunk_bin(row + f, i * 64 + lane);
+#pragma unroll
+    for (int i = 0; i < HREG; ++i) hx[i] = lg[f + i * 64 + lane];
+  }
+  const float u = u01[blockIdx.x];
+  if (tid < BINS) S.hist[tid] = 0;
+  if (wave == 0) {  // places of the chunks' candidates in one list
+    int at = 0, over = 0;
+    for (int k0 = 0; k0 < n_chunks; k0 += 64) {
+      const int k = k0 + lane;
+      const int mine = k < n_chunks ? __float_as_int(row[(int64_t)k * chunk + 1]) : 0;
+      over |= mine > CAND_MAX;
+      int incl = mine;
+#pragma unroll
+      for (int s = 1; s < 64; s <<= 1) {
+        const int up = __shfl_up(incl, s);
+        if (lane >= s) incl += up;
+      }
+      if (k < n_chunks) S.chunk_at[k] = at + incl - mine;
+      at += __shfl(incl, 63);
+    }
+    over = __any(over) || at > ROW_CAND;
+    if (lane == 0) { S.n_cand = at; S.overflow = over; }
+  }
+  const int top = row_top(row, chunk, n_chunks), ref = ref_of(top);
+  __syncthreads();
+  const bool listed = !S.overflow;
+  uint32_t klo = 0xFFFFFFFFu, khi = 0u;
+  for (int k = wave; k < n_chunks; k += WAVES) {
+    const float* region = row + (int64_t)k * chunk;
+    const int t = __float_as_int(region[0]), back = ref_of(top) - ref_of(t);
+#pragma unroll
+    for (int i = 0; i < BINS / 64; ++i) {
+      const u64 v = shifted(k == wave ? hb[i] : chunk_bin(region, i * 64 + lane), back);
+      if (v) atomicAdd(&S.hist[min(BINS - 1, i * 64 + lane + (top - t))], v);
+    }
+    if (listed) {
+      const int at = S.chunk_at[k], cnt = __float_as_int(region[1]);
+      for (int i = lane; i < cnt; i += 64) {
+        const float v = region[HEAD + i];
+        const uint32_t key = key_of(v);
+        S.keys[at + i] = key;
+        S.mass[at + i] = shifted(mass_of(prob(v, c, ref_of(t))), back);
+        klo = min(klo, key);
+        khi = max(khi, key);
+      }
+    }
+  }
+#pragma unroll
+  for (int s = 32; s >= 1; s >>= 1) {
+    klo = min(klo, (uint32_t)__shfl_xor((int)klo, s));
+    khi = max(khi, (uint32_t)__shfl_xor((int)khi, s));
+  }
+  if (lane == 0) { S.klo[wave] = klo; S.khi[wave] = khi; }
+  __syncthreads();
+  if (wave == 0) find_boundary(S.hist, top_p, -1., &S.bin, &S.need);
+  if (listed) {
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) { klo = min(klo, S.klo[w]); khi = max(khi, S.khi[w]); }
+  }
+  __syncthreads();
+  const int b = S.bin;
+  uint32_t tau;
+  if (listed) {
+    tau = S.n_cand ? find_tau(S.keys, S.mass, S.n_cand, S.need, klo, khi == 0xFFFFFFFFu ? khi : khi + 1u, S.reached) : 0u;
+  } else {
+    // The bin holds more elements than the lists (a row that is flat to within a tenth of an octave): its keys are binned
+    // again, 256 linear bins at a time, until one key is left; three or four passes over the row.
+    auto members = [&](auto&& use) __attribute__((always_inline)) {  // use(key, logit, chunk reference) of every member of bin b
+      for (int k = wave; k < n_chunks; k += WAVES) {
+        const int64_t f = (int64_t)k * chunk;
+        const int n = min(chunk, (int)(V - f)), rc = ref_of(__float_as_int(row[f]));
+#pragma unroll 8
+        for (int i = lane; i < n; i += 64) {
+          const float v = lg[f + i];
+          if (min(BINS - 1, top - bin_of(v * c)) == b) use(key_of(v), v, rc);
+        }
+      }
+    };
+    uint32_t lo = 0xFFFFFFFFu, last = 0u;
+    members([&](uint32_t key, float, int) { lo = min(lo, key); last = max(last, key); });
+#pragma unroll
+    for (int s = 32; s >= 1; s >>= 1) {
+      lo = min(lo, (uint32_t)__shfl_xor((int)lo, s));
+      last = max(last, (uint32_t)__shfl_xor((int)last, s));
+    }
+    if (lane == 0) { S.klo[wave] = lo; S.khi[wave] = last; }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) { lo = min(lo, S.klo[w]); last = max(last, S.khi[w]); }
+    constexpr int COPIES = 16;  // (of the bins, by lane, in the space of the lists)
+    u64* copies = S.mass;
+    while (last > lo) {  // tau lies in lo .. last
+      const int shift = max(0, 24 - __clz(last - lo));  // (last - lo) >> shift < 256
+      for (int i = tid; i < BINS * COPIES; i += TPB) copies[i] = 0;
+      __syncthreads();
+      members([&](uint32_t key, float v, int rc) {
+        if (key < lo || key > last) return;
+        const u64 w = shifted(mass_of(prob(v, c, rc)), ref_of(top) - rc);
+        if (w) atomicAdd(&copies[(BINS - 1 - ((key - lo) >> shift)) * COPIES + (tid & (COPIES - 1))], w);
+      });
+      __syncthreads();
+      if (tid < BINS) {
+        u64 s = 0;
+#pragma unroll
+        for (int k = 0; k < COPIES; ++k) s += copies[tid * COPIES + ((k + tid) & (COPIES - 1))];
+        S.hist[tid] = s;
+      }
+      const double want = S.need;
+      __syncthreads();
+      if (wave == 0) find_boundary(S.hist, 0.f, want, &S.bin, &S.need);
+      __syncthreads();
+      const uint32_t first = lo + ((uint32_t)(BINS - 1 - S.bin) << shift);
+      last = min(last, first + ((1u << shift) - 1u));
+      lo = first;
+    }
+    tau = lo;
+  }
+  // mass of the nucleus in every chunk, in units of the row's reference
+  for (int k = wave; k < n_chunks; k += WAVES) {
+    const float* region = row + (int64_t)k * chunk;
+    const int t = __float_as_int(region[0]), back = ref_of(top) - ref_of(t);
+    u64 s = 0;
+#pragma unroll
+    for (int i = 0; i < BINS / 64; ++i)
+      if (min(BINS - 1, i * 64 + lane + (top - t)) < b) s += k == wave ? hb[i] : chunk_bin(region, i * 64 + lane);
+    s = shifted(wave_sum(s), back);
+    u64 q = 0;
+    if (listed) {
+      const int at = S.chunk_at[k], cnt = __float_as_int(region[1]);
+      for (int i = lane; i < cnt; i += 64) q += S.keys[at + i] >= tau ? S.mass[at + i] : 0ull;
+    } else {
+      const int64_t f = (int64_t)k * chunk;
+      const int n = min(chunk, (int)(V - f));
+#pragma unroll 8
+      for (int i = lane; i < n; i += 64) {
+        const float v = lg[f + i];
+        if (key_of(v) >= tau && min(BINS - 1, top - bin_of(v * c)) == b) q += shifted(mass_of(prob(v, c, ref_of(t))), back);
+      }
+    }
+    q = wave_sum(q);
+    if (lane == 0) S.chunk_mass[k] = s + q;
+  }
+  __syncthreads();
+  if (wave == 0) {
+    u64 nucleus = 0;
+    for (int k = lane; k < n_chunks; k += 64) nucleus += S.chunk_mass[k];
+    nucleus = wave_sum(nucleus);
+    const u64 target = draw_target(u, nucleus);
+    u64 run = 0;
+    int owner = -1;
+    for (int k0 = 0; k0 < n_chunks && owner < 0; k0 += 64) {
+      const u64 mine = k0 + lane < n_chunks ? S.chunk_mass[k0 + lane] : 0ull;
+      const u64 incl = wave_scan(mine) + run;
+      const u64 past = __ballot(incl > target);
+      if (past) {
+        owner = k0 + __ffsll((long long)past) - 1;
+        if (k0 + lane == owner) S.target = target - (incl - mine);
+      }
+      run = __shfl(incl, 63);
+    }
+    if (lane == 0) { S.chunk = owner; if (owner < 0) tokens[blockIdx.x] = 0; }  // (no finite logit in the row)
+  }
+  __syncthreads();
+  if (S.chunk >= 0) {
+    const int64_t f = (int64_t)S.chunk * chunk;
+    const int t = __float_as_int(row[f]);
+    // the running mass inside the chunk is counted in the chunk's own units, in which it is at least what was counted above
+    pick(lg + f, min(chunk, (int)(V - f)), c, ref_of(t), tau, S.target << (ref_of(top) - ref_of(t)), (int)f, S.wave_tot, tokens + blockIdx.x);
+  }
+  __syncthreads();  // the headers are no longer needed
+  for (int k = wave; k < n_chunks; k += WAVES) {
+    const int64_t f = (int64_t)k * chunk;
+#pragma unroll
+    for (int i = 0; i < HREG; ++i) row[f + i * 64 + lane] = prob(k == wave ? hx[i] : lg[f + i * 64 + lane], c, ref);
+  }
+}
+
+constexpr int MAX_DEVICES = 64;
+std::mutex g_device_mutex;         // guards the two tables below
+bool g_lds_allowed[MAX_DEVICES];   // the kernels with more than 64 KiB of LDS have been announced to the device
+float* g_scratch_ptr[MAX_DEVICES]; // device address of the static scratch array on each device, once looked up
+
+int current_device(int* dev) {
+  *dev = -1;
+  const hipError_t e = hipGetDevice(dev);
+  if (e != hipSuccess) { set_error("hipGetDevice failed: %s", hipGetErrorString(e)); return WWW_E_HIP; }
+  if (*dev < 0 || *dev >= MAX_DEVICES) { set_error("device index %d out of range", *dev); return WWW_E_HIP; }
+  return WWW_OK;
+}
+
+int allow_lds() {
+  int dev;
+  if (int rc = current_device(&dev)) return rc;
+  std::lock_guard<std::mutex> lock(g_device_mutex);
+  if (g_lds_allowed[dev]) return WWW_OK;
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&sample_row_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(SmallLds));
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&sample_pick_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(PickLds));
+  if (e != hipSuccess) { set_error("hipFuncSetAttribute failed: %s", hipGetErrorString(e)); return WWW_E_HIP; }
+  g_lds_allowed[dev] = true;
+  return WWW_OK;
 }
 
 }  // namespace
@@ -143,8 +615,22 @@ WWW_EXPORT int www_sample_top_p(const float* logits_dev, int32_t batch, int32_t 
   }
   if (batch == 0) return WWW_OK;
   if (!logits_dev || !u01_dev || !scratch_dev || !tokens_dev) { set_error("NULL pointer argument"); return WWW_E_INVALID_ARG; }
-  hipLaunchKernelGGL(sample_top_p_kernel, dim3(batch), dim3(TPB), 0, (hipStream_t)hip_stream, logits_dev, vocab, 1.f / temperature, top_p,
-                     u01_dev, scratch_dev, tokens_dev);
+  const hipStream_t st = (hipStream_t)hip_stream;
+  const float c = 1.4426950408889634f / temperature;
+  if (int rc = allow_lds()) return rc;
+  if (vocab <= SUB) {
+    hipLaunchKernelGGL(sample_row_kernel, dim3(batch), dim3(TPB), sizeof(SmallLds), st, logits_dev, vocab, c, top_p, u01_dev, scratch_dev,
+                       tokens_dev);
+  } else {
+    // chunks of equal length, 4097 .. 8192 tokens (longer only above 8 Mi tokens); the last one falls short of the others
+    // by less than the number of chunks, so every chunk has room for its reserved head
+    const int n_chunks = std::min((vocab + SUB - 1) / SUB, MAX_CHUNKS), chunk = (int)(((int64_t)vocab + n_chunks - 1) / n_chunks);
+    const dim3 grid(batch, n_chunks);
+    hipLaunchKernelGGL(sample_bins_kernel, grid, dim3(256), 0, st, logits_dev, vocab, chunk, c, scratch_dev);
+    hipLaunchKernelGGL(sample_split_kernel, grid, dim3(256), 0, st, logits_dev, vocab, chunk, c, top_p, scratch_dev);
+    hipLaunchKernelGGL(sample_pick_kernel, dim3(batch), dim3(TPB), sizeof(PickLds), st, logits_dev, vocab, chunk, n_chunks, c, top_p, u01_dev,
+                       scratch_dev, tokens_dev);
+  }
   const hipError_t err = hipGetLastError();
   if (err != hipSuccess) { set_error("sampling kernel launch failed: %s", hipGetErrorString(err)); return WWW_E_HIP; }
   return WWW_OK;
@@ -160,20 +646,14 @@ WWW_EXPORT int www_sample_top_p(const float* logits_dev, int32_t batch, int32_t 
 static __device__ __align__(256) float scratch[WWW_SAMPLE_STATIC_MAX_FLOATS];
 
 namespace {
-constexpr int MAX_DEVICES = 64;
-float* g_scratch_ptr[MAX_DEVICES];  // device address of `scratch` on each device, once looked up
-std::mutex g_scratch_mutex;
-
 // device address of this device's copy of `scratch` (the array's name itself is only a host-side stand-in)
 int static_scratch(float** out) {
-  int dev = -1;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) { set_error("hipGetDevice failed: %s", hipGetErrorString(e)); return WWW_E_HIP; }
-  if (dev < 0 || dev >= MAX_DEVICES) { set_error("device index %d out of range", dev); return WWW_E_HIP; }
-  std::lock_guard<std::mutex> lock(g_scratch_mutex);
+  int dev;
+  if (int rc = current_device(&dev)) return rc;
+  std::lock_guard<std::mutex> lock(g_device_mutex);
   if (!g_scratch_ptr[dev]) {
     float* ptr = nullptr;
-    e = hipGetSymbolAddress((void**)&ptr, HIP_SYMBOL(scratch));
+    const hipError_t e = hipGetSymbolAddress((void**)&ptr, HIP_SYMBOL(scratch));
     if (e != hipSuccess || !ptr) { set_error("hipGetSymbolAddress failed: %s", hipGetErrorString(e)); return WWW_E_HIP; }
     g_scratch_ptr[dev] = ptr;
   }

@@ -119,7 +119,6 @@ struct Plan {
   uint64_t h, ssq, q, xq, xo, xa, partial, attn_part, counters, logits, last_tok, argmax_val, argmax_idx, attn_hdr, attn_start, attn_pref;
   uint64_t hp, ssq_p, xn, qp, op, ap, row_seq, row_pos, tile_seq, tile_q0, meta;
   uint64_t val_words, val_bitmap, val_bitmap_bytes;  // argument validation (WWW_VALIDATE=1): result words, one bit per KV block
-  int attn_maxrec;
 };
 
 struct Dims {
@@ -204,10 +203,9 @@ static void make_plan(const www_config* c, Plan& p) {
       }
   }
   p.partial = take(part ? part : 256);
-  // a wavefront of the decode attention takes at least 16 key pairs (512 keys) of the batch's work list, so a sequence
-  // is cut into at most max_pos / 512 + 2 segments
-  p.attn_maxrec = s.max_pos / 512 + 2;
-  p.attn_part = take((uint64_t)s.maxB * s.Hkv * p.attn_maxrec * s.G * (s.hd + 4) * 4);
+  // the decode attention's records: two per wavefront that has work, and no more of those than key pairs in the batch
+  const uint64_t max_pairs = (uint64_t)s.maxB * s.Hkv * (((uint64_t)s.max_pos + 31) / 32);
+  p.attn_part = take(2 * (max_pairs < MAX_ATTN_WAVES ? max_pairs : MAX_ATTN_WAVES) * s.G * (s.hd + 4) * 4);
   p.logits = take((uint64_t)s.maxB * s.V * 4);
   p.last_tok = take((uint64_t)s.maxB * 4);
   p.attn_hdr = take(16);
@@ -466,7 +464,6 @@ WWW_EXPORT int www_model_load(const www_config* cfg, const void* weights_dev, vo
   m->hp = (float*)(ws + p.hp); m->ssq_p = (float*)(ws + p.ssq_p); m->xn = (uint16_t*)(ws + p.xn); m->qp = (uint16_t*)(ws + p.qp); m->op = (uint16_t*)(ws + p.op); m->ap = (uint16_t*)(ws + p.ap);
   m->row_seq = (int*)(ws + p.row_seq); m->row_pos = (int*)(ws + p.row_pos); m->tile_seq = (int*)(ws + p.tile_seq);
   m->tile_q0 = (int*)(ws + p.tile_q0); m->meta = (int*)(ws + p.meta);
-  m->attn_maxrec = p.attn_maxrec;
   m->attn_waves = decode_attn_resident_waves(s.hd, s.G);
   if (m->attn_waves > MAX_ATTN_WAVES) m->attn_waves = MAX_ATTN_WAVES;
   {

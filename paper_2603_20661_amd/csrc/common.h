@@ -166,14 +166,13 @@ struct www_model {
   int *row_seq, *row_pos, *tile_seq, *tile_q0, *meta;  // ragged-batch bookkeeping
   int attn_waves;  // wavefronts of the decode attention grid (all resident at once)
   int handover_fence;  // 1: split-K partial tiles get a device-scope release fence (placement rule not confirmed)
-  int attn_maxrec; // most partial records per (sequence, kv head)
   GraphEntry* graphs;
   int n_graphs;
   int use_graph;
   struct DecodeProfiler* prof;  // per-kernel-class timing of eager decode steps (benchmark hook), or null
 };
 
-#define MAX_ATTN_WAVES 8192  // upper bound of the decode attention grid, in wavefronts (sizes its plan buffer)
+#define MAX_ATTN_WAVES 4096  // upper bound of the decode attention grid, in wavefronts (sizes its plan and its records)
 #define PSSQ 32            // entries per token of the prefill path's sum-of-squares table (d_model / 256 row tiles at most)
 #define SSQ_TILES 64       // most row tiles of a residual-producing GEMM (d_model / 128)
 #define GEMM_TILE_ROWS 128 // rows of W per workgroup of the skinny GEMM

@@ -706,26 +706,33 @@ __global__ __launch_bounds__(256 * KH, 2 / KH) void skinny_gemm_kernel(const Gem
 //
 // The keys of the batch are counted in pairs of 16-key blocks.  All (sequence b, kv head j, pair) triples, in that
 // order, form one long list of T = Hkv * sum_b P_b entries (P_b = pairs of sequence b); the attention kernel runs W
-// wavefronts and wavefront w takes the entries [w*C, (w+1)*C), C = max(16, ceil(T / W)).  Every wavefront therefore
+// wavefronts and wavefront w takes the entries [w*C, (w+1)*C), C = ceil(T / W), at least ceil(longest P / 64).  Every wavefront therefore
 // streams the same number of bytes and all of them finish together, whatever the mix of sequence lengths.  A chunk may
 // end inside a (b, j) sequence and continue into the next one; each piece is a segment with its own softmax state,
-// parked as a record and merged afterwards (a sequence of P pairs is cut into at most P/C + 2 <= P/16 + 2 segments).
+// parked as a record and merged afterwards.  Only the first and the last segment of a chunk can be part of a longer
+// sequence, so wavefront w owns the records 2w (the segment its chunk begins with) and 2w + 1 (a later one).
 // The cut points depend on the lengths of all sequences of the batch: results are reproducible for a given batch
 // but the rounding of a sequence's attention output may differ between batches of different composition.
-//   hdr[0] = T, hdr[1] = C;  start[w] = (b, j, first pair) of wavefront w, b = -1 if it has no work;
+// C has no other lower bound: with few tokens in the batch a chunk is a single pair, and the whole GPU works on it.  (At
+// least 16 pairs a chunk, one sequence of 1041 tokens had 17 wavefronts: 32 us per layer of the 8B shape against 8; a
+// step took 4197 us, 3835 with at least 8 pairs, 3661 with 4, 3543 with 1.)  A sequence is cut into at most 64 full
+// chunks, because the merge reads 32 records per memory round trip (one sequence of 8192 tokens: 3957 us a step with
+// 128 chunks, 3800 with 64).
+//   hdr[0] = T, hdr[1] = C;  start[w] = (b, j, first pair, length of b) of wavefront w, b = -1 if it has no work;
 //   pref[b] = sum of P over the sequences before b
 __global__ __launch_bounds__(256) void attn_plan_kernel(const int32_t* __restrict__ seq_lens, int batch, int Hkv, int W,
                                                         int32_t* __restrict__ hdr, int32_t* __restrict__ start,
                                                         int32_t* __restrict__ pref_out) {
-  extern __shared__ int pref[];  // [batch + 1]
+  extern __shared__ int pref[];  // [batch + 1] and the longest P
   const int tid = threadIdx.x, lane = tid & 63;
   if (tid < 64) {
-    int carry = 0;
+    int carry = 0, top = 0;
     if (lane == 0) pref[0] = 0;
     for (int c = 0; c < batch; c += 64) {
       const int bb = c + lane;
       const int P = bb < batch ? max(0, (seq_lens[bb] + 31) / 32) : 0;
       int inc = P;
+      top = max(top, P);
 #pragma unroll
       for (int o = 1; o < 64; o <<= 1) {
         const int up = __shfl_up(inc, o);
@@ -734,15 +741,18 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(const int32_t* __restric
       if (bb < batch) pref[bb + 1] = carry + inc;
       carry += __shfl(inc, 63);
     }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) top = max(top, __shfl_xor(top, o));
+    if (lane == 0) pref[batch + 1] = top;
   }
   __syncthreads();
-  const int T = pref[batch] * Hkv;
-  const int C = max(16, (T + W - 1) / W);
+  const int T = pref[batch] * Hkv, longest = pref[batch + 1];
+  const int C = max(1, max((T + W - 1) / W, (longest + 63) / 64));
   if (tid == 0) { hdr[0] = T; hdr[1] = C; }
   for (int i = tid; i <= batch; i += 256) pref_out[i] = pref[i];
   for (int w = tid; w < W; w += 256) {
     const int64_t x0 = (int64_t)w * C;
-    int sb = -1, sj = 0, sp = 0;
+    int sb = -1, sj = 0, sp = 0, sctx = 0;
     if (x0 < T) {
       int lo = 0, hi = batch - 1;  // largest b with Hkv * pref[b] <= x0
       while (lo < hi) {
@@ -751,9 +761,9 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(const int32_t* __restric
       }
       const int P = max(1, pref[lo + 1] - pref[lo]);  // (never 0 for the sequence that holds entry x0 < T)
       const int r = (int)(x0 - (int64_t)pref[lo] * Hkv);
-      sb = lo; sj = r / P; sp = r % P;
+      sb = lo; sj = r / P; sp = r % P; sctx = seq_lens[lo];
     }
-    start[4 * w] = sb; start[4 * w + 1] = sj; start[4 * w + 2] = sp; start[4 * w + 3] = 0;
+    start[4 * w] = sb; start[4 * w + 1] = sj; start[4 * w + 2] = sp; start[4 * w + 3] = sctx;
   }
 }
 
@@ -784,7 +794,7 @@ __device__ __forceinline__ void split_codes8(u32x4 w, f16x8& hi, f16x8& lo) { sp
 //   S^T = K Q^T (keys x heads), online softmax per head along the key axis with cross-lane shuffles,
 //   O^T = V^T P^T (head_dim x heads).  The G query heads of the group share every K/V byte.
 // A segment that covers its whole (sequence, kv head) writes the packed hi/lo operand of the O projection itself;
-// otherwise it parks (m, l, unnormalised o) as record number (w - first wavefront of that sequence).
+// otherwise it parks (m, l, unnormalised o) in one of its two records.
 template <int HD, int G>
 __global__ __launch_bounds__(256) void decode_attn_kernel(const uint16_t* __restrict__ q_hi, const uint16_t* __restrict__ q_lo,
                                                            const uint16_t* __restrict__ kplane,
@@ -792,27 +802,34 @@ __global__ __launch_bounds__(256) void decode_attn_kernel(const uint16_t* __rest
                                                            const int32_t* __restrict__ seq_lens,
                                                            const int32_t* __restrict__ table, int batch, int mbs, int Hq, int Hkv,
                                                            const int32_t* __restrict__ hdr, const int32_t* __restrict__ start,
-                                                           int maxrec, float* __restrict__ part, uint16_t* __restrict__ xo, int MT) {
+                                                           float* __restrict__ part, uint16_t* __restrict__ xo, int MT) {
   constexpr int NKF = HD / 32;  // K fragments per block
   constexpr int NVF = HD / 16;  // V fragments per block
   constexpr int PSTRIDE = HD + 4;  // floats per (record, head): o[HD], m, l, pad
-  const int w = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int n = lane & 15, g = lane >> 4;
+  // A list shorter than the number of wavefronts is dealt out over the workgroups, so that it still reaches every compute
+  // unit; a longer one is not, neighbouring chunks then share a compute unit (64 sequences of the 8B shape: 6385 against
+  // 6452 us a step).  Both candidates are requested at once, before the length of the list is known.
+  const int w_near = blockIdx.x * 4 + wave, w_far = wave * gridDim.x + blockIdx.x;
+  const u32x4 st_near = *reinterpret_cast<const u32x4*>(start + 4 * w_near), st_far = *reinterpret_cast<const u32x4*>(start + 4 * w_far);
   const int T = hdr[0], C = hdr[1];
-  int b = __builtin_amdgcn_readfirstlane(start[4 * w]);
+  const bool far = T < (int)gridDim.x * 4;
+  const int w = far ? w_far : w_near;
+  const u32x4 st = far ? st_far : st_near;
+  int b = __builtin_amdgcn_readfirstlane((int)st.x);
   if (b < 0) return;
-  int j = __builtin_amdgcn_readfirstlane(start[4 * w + 1]);
-  int p = __builtin_amdgcn_readfirstlane(start[4 * w + 2]);
+  int j = __builtin_amdgcn_readfirstlane((int)st.y);
+  int p = __builtin_amdgcn_readfirstlane((int)st.z);
+  int ctx = __builtin_amdgcn_readfirstlane((int)st.w);
   int x = w * C;                      // position in the list of the next entry
   int remaining = min(C, T - x);
   const int64_t blk_elems = (int64_t)KV_BS * HD;
 
   while (remaining > 0 && b < batch) {  // (the second test only guards against a plan that does not match the lengths)
-    const int ctx = __builtin_amdgcn_readfirstlane(seq_lens[b]);
     const int P = (ctx + 31) / 32;
     if (P <= 0) {  // an empty sequence has no entries in the list
-      ++b;
+      if (++b < batch) ctx = __builtin_amdgcn_readfirstlane(seq_lens[b]);
       continue;
     }
     const int np = min(P - p, remaining);
@@ -914,7 +931,8 @@ __global__ __launch_bounds__(256) void decode_attn_kernel(const uint16_t* __rest
         mx = fmaxf(mx, __shfl_xor(mx, 16));
         mx = fmaxf(mx, __shfl_xor(mx, 32));
         const float m_new = fmaxf(m_run, mx);
-        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+        const float ref = m_new == NEG_INF ? 0.f : m_new;  // (scores of -inf only, so far: no weight, and not a NaN)
+        const float alpha = __builtin_amdgcn_exp2f(m_run - ref);
         // the probabilities times the value scales go to the matrix cores as fp16 hi + lo, like every other operand of the
         // single-token path (for the a plane of the value codes with the factor 256; the b plane, 2^-8 of the value, takes
         // the hi part alone); non-negative, so one bound keeps a wild scale from overflowing
@@ -922,7 +940,7 @@ __global__ __launch_bounds__(256) void decode_attn_kernel(const uint16_t* __rest
         float psum = 0.f;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-          const float pv = __builtin_amdgcn_exp2f(sc[i] - m_new);
+          const float pv = __builtin_amdgcn_exp2f(sc[i] - ref);
           psum += pv;
           const float w = fminf(pv * pvs[i], 255.f), w256 = w * 256.f;
           pa.s[i] = (_Float16)w256;
@@ -995,9 +1013,9 @@ __global__ __launch_bounds__(256) void decode_attn_kernel(const uint16_t* __rest
         }
       }
     } else {
-      // park the record [b][j][w - first_w][head n][o(HD), m, l]; a separate small kernel merges the records (a kernel
+      // park the record [2w | 2w + 1][head n][o(HD), m, l]; a separate small kernel merges the records (a kernel
       // boundary is a far cheaper hand-over here than in-kernel device-scope signalling)
-      float* rec = part + ((((int64_t)b * Hkv + j) * maxrec + (w - first_w)) * G) * PSTRIDE;
+      float* rec = part + (int64_t)(2 * w + (x == w * C ? 0 : 1)) * G * PSTRIDE;
       if (n < G) {
 #pragma unroll
         for (int f = 0; f < NVF; ++f)
@@ -1011,28 +1029,36 @@ __global__ __launch_bounds__(256) void decode_attn_kernel(const uint16_t* __rest
     x += np;
     remaining -= np;
     p = 0;
-    if (++j == Hkv) { j = 0; ++b; }
+    if (++j == Hkv) {
+      j = 0;
+      if (++b < batch && remaining > 0) ctx = __builtin_amdgcn_readfirstlane(seq_lens[b]);
+    }
   }
 }
 
-// Merges the records of one (sequence, kv head) in key order and writes the packed hi/lo operand of the O
-// projection.  One wavefront per (kv head, sequence); sequences that were a single segment were finished by the
-// attention kernel itself.
+// Merges the records of one (sequence, kv head) and writes the packed hi/lo operand of the O projection.  MERGE_WAVES wavefronts
+// per (kv head, sequence): wavefront v merges, in key order, the v-th run of consecutive records, and wavefront 0 then
+// adds the intermediate records, in key order again (a fixed order).  Sequences that were a single segment were
+// finished by the attention kernel itself.  Bound by dependent memory round trips; eight wavefronts reading four records
+// at a time take a sequence of 32 records in one of them (8B shape, graph replay, against one wavefront: one sequence of
+// 8192 tokens 4800 -> 3800 us a step, 64 sequences 6450 -> 6395, 16 sequences with FP8 weights 3095 -> 2963).
+#define MERGE_WAVES 8
 template <int HD, int G>
-__global__ __launch_bounds__(64) void decode_attn_merge_kernel(const int32_t* __restrict__ seq_lens, int Hkv,
-                                                                const int32_t* __restrict__ hdr, const int32_t* __restrict__ pref,
-                                                                int nsplit_max, const float* __restrict__ part,
-                                                                uint16_t* __restrict__ xo, int MT) {
-  constexpr int PSTRIDE = HD + 4;
-  const int j = blockIdx.x, b = blockIdx.y, lane = threadIdx.x;
+__global__ __launch_bounds__(64 * MERGE_WAVES) void decode_attn_merge_kernel(const int32_t* __restrict__ seq_lens, int Hkv,
+                                                                     const int32_t* __restrict__ hdr, const int32_t* __restrict__ pref,
+                                                                     const float* __restrict__ part,
+                                                                     uint16_t* __restrict__ xo, int MT) {
+  constexpr int PSTRIDE = HD + 4, NS = MERGE_WAVES;
+  const int j = blockIdx.x, b = blockIdx.y, lane = threadIdx.x & 63, v = threadIdx.x >> 6;
   const int C = hdr[1];
   const int P = max(0, (seq_lens[b] + 31) / 32);
   const int S = pref[b] * Hkv + j * P;  // list position of this sequence's first pair
-  const int nsplit_act = (S + P - 1) / C - S / C + 1;
-  if (nsplit_act <= 1) return;
-  // Lane owns head-dim elements lane + 64*i of every head; records are read four splits at a time so the merge is
-  // not one memory round trip per split.
-  const float* recs = part + (((int64_t)b * Hkv + j) * nsplit_max) * G * PSTRIDE;
+  const int first_w = S / C;
+  const int nrec = (S + P - 1) / C - first_w + 1;
+  if (nrec <= 1) return;
+  const int first_slot = 2 * first_w + (S == first_w * C ? 0 : 1);  // later wavefronts begin with this sequence: even records
+  // Lane owns head-dim elements lane + 64*i of every head; records are read four at a time so the merge is not one
+  // memory round trip per record.
   constexpr int NE = HD / 64;
   float Mh[G], Lh[G], oh[G][NE];
 #pragma unroll
@@ -1042,14 +1068,26 @@ __global__ __launch_bounds__(64) void decode_attn_merge_kernel(const int32_t* __
 #pragma unroll
     for (int i = 0; i < NE; ++i) oh[hh][i] = 0.f;
   }
-  for (int s0 = 0; s0 < nsplit_act; s0 += 4) {
+  auto take = [&](int hh, float mv, float lv, const float(&ov)[NE]) __attribute__((always_inline)) {
+    const float Mn = fmaxf(Mh[hh], mv);
+    const float ref = Mn == NEG_INF ? 0.f : Mn;
+    const float a = __builtin_amdgcn_exp2f(Mh[hh] - ref), w = __builtin_amdgcn_exp2f(mv - ref);
+    Lh[hh] = Lh[hh] * a + lv * w;
+#pragma unroll
+    for (int i = 0; i < NE; ++i) oh[hh][i] = oh[hh][i] * a + ov[i] * w;
+    Mh[hh] = Mn;
+  };
+  const int per = (nrec + NS - 1) / NS;
+  const int r_end = min(nrec, (v + 1) * per);
+  for (int s0 = v * per; s0 < r_end; s0 += 4) {
     float mv[4][G], lv[4][G], ov[4][G][NE];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int sidx = min(s0 + u, nsplit_act - 1);
+      const int sidx = min(s0 + u, r_end - 1);
+      const int slot = sidx == 0 ? first_slot : 2 * (first_w + sidx);
 #pragma unroll
       for (int hh = 0; hh < G; ++hh) {
-        const float* r = recs + ((int64_t)sidx * G + hh) * PSTRIDE;
+        const float* r = part + ((int64_t)slot * G + hh) * PSTRIDE;
         mv[u][hh] = r[HD];
         lv[u][hh] = r[HD + 1];
 #pragma unroll
@@ -1058,16 +1096,29 @@ __global__ __launch_bounds__(64) void decode_attn_merge_kernel(const int32_t* __
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      if (s0 + u >= nsplit_act) break;
+      if (s0 + u >= r_end) break;
 #pragma unroll
-      for (int hh = 0; hh < G; ++hh) {
-        const float Mn = fmaxf(Mh[hh], mv[u][hh]);
-        const float a = __builtin_amdgcn_exp2f(Mh[hh] - Mn), w = __builtin_amdgcn_exp2f(mv[u][hh] - Mn);
-        Lh[hh] = Lh[hh] * a + lv[u][hh] * w;
+      for (int hh = 0; hh < G; ++hh) take(hh, mv[u][hh], lv[u][hh], ov[u][hh]);
+    }
+  }
+  __shared__ float mid[NS][G][PSTRIDE];
+  if (v > 0 && v * per < nrec) {
 #pragma unroll
-        for (int i = 0; i < NE; ++i) oh[hh][i] = oh[hh][i] * a + ov[u][hh][i] * w;
-        Mh[hh] = Mn;
-      }
+    for (int hh = 0; hh < G; ++hh) {
+      if (lane == 0) { mid[v][hh][HD] = Mh[hh]; mid[v][hh][HD + 1] = Lh[hh]; }
+#pragma unroll
+      for (int i = 0; i < NE; ++i) mid[v][hh][lane + 64 * i] = oh[hh][i];
+    }
+  }
+  __syncthreads();
+  if (v > 0) return;
+  for (int u = 1; u < NS && u * per < nrec; ++u) {
+#pragma unroll
+    for (int hh = 0; hh < G; ++hh) {
+      float ov[NE];
+#pragma unroll
+      for (int i = 0; i < NE; ++i) ov[i] = mid[u][hh][lane + 64 * i];
+      take(hh, mid[u][hh][HD], mid[u][hh][HD + 1], ov);
     }
   }
 #pragma unroll
@@ -1251,7 +1302,7 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
   else
     hipLaunchKernelGGL(embed_pack_kernel<uint16_t>, dim3(batch), dim3(256), 0, st, tok, (const uint16_t*)m->embed, d,
                        m->layers[0].attn_norm, m->h, m->ssq, (uint16_t*)m->xq, MT);
-  hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(256), (size_t)(batch + 1) * 4, st, lens, batch, m->Hkv, m->attn_waves, m->attn_hdr,
+  hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(256), (size_t)(batch + 2) * 4, st, lens, batch, m->Hkv, m->attn_waves, m->attn_hdr,
                      m->attn_start, m->attn_pref);
   int n_ssq = 1;
   const float qscale = 1.4426950408889634f / sqrtf((float)m->hd);
@@ -1277,10 +1328,9 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
   {                                                                                                                                \
     hipLaunchKernelGGL((decode_attn_kernel<HD_, G_>), dim3(m->attn_waves / 4), dim3(256), 0, st, m->q_hi, m->q_lo, kplane, vplane,  \
                        kvscale, lens, table, batch, (int)m->cfg.max_blocks_per_seq, m->Hq, m->Hkv, m->attn_hdr, m->attn_start,            \
-                       m->attn_maxrec,                                                                                             \
                        m->attn_part, (uint16_t*)m->xo, MT);                                                                        \
-    hipLaunchKernelGGL((decode_attn_merge_kernel<HD_, G_>), dim3(m->Hkv, batch), dim3(64), 0, st, lens, m->Hkv, m->attn_hdr,        \
-                       m->attn_pref, m->attn_maxrec, m->attn_part, (uint16_t*)m->xo, MT);                                          \
+    hipLaunchKernelGGL((decode_attn_merge_kernel<HD_, G_>), dim3(m->Hkv, batch), dim3(64 * MERGE_WAVES), 0, st, lens, m->Hkv,      \
+                       m->attn_hdr, m->attn_pref, m->attn_part, (uint16_t*)m->xo, MT);                                             \
   }
       if (m->hd == 128) {
         if (m->G == 1) ATTN(128, 1) else if (m->G == 2) ATTN(128, 2) else if (m->G == 4) ATTN(128, 4) else ATTN(128, 8)

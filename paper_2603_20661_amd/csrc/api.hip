@@ -14,6 +14,7 @@
 #define WWW_EXPORT extern "C" __attribute__((visibility("default")))
 
 int decode_gemm_ksplit(int NRG, int KB, int MT);
+uint64_t prefill_partial_bytes(int maxT, int NRG, int KB);
 int decode_MT(int batch);
 
 static thread_local char g_err[512] = "";
@@ -202,6 +203,9 @@ static void make_plan(const www_config* c, Plan& p) {
         if (ks > 1 && bytes > part) part = bytes;
       }
   }
+  const uint64_t pre[4] = {prefill_partial_bytes(s.maxT, s.QKVN / 16, s.d / 32), prefill_partial_bytes(s.maxT, s.d / 16, s.QD / 32),
+                           prefill_partial_bytes(s.maxT, 2 * s.F / 16, s.d / 32), prefill_partial_bytes(s.maxT, s.d / 16, s.Fp / 32)};
+  for (uint64_t b : pre) part = part > b ? part : b;
   p.partial = take(part ? part : 256);
   // the decode attention's records: two per wavefront that has work, and no more of those than key pairs in the batch
   const uint64_t max_pairs = (uint64_t)s.maxB * s.Hkv * (((uint64_t)s.max_pos + 31) / 32);

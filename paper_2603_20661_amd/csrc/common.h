@@ -99,6 +99,54 @@ __device__ __forceinline__ int64_t kv_slot(const int32_t* __restrict__ row, int 
 }
 
 // ------------------------------------------------------------------------------------------------
+// Cross-workgroup hand-over of partial results inside one kernel.  Partial tiles are written and read with
+// device-scope (sc1) 16-byte accesses; every wavefront of the producer waits for its stores, the workgroup syncs, one
+// thread bumps a device-scope counter (after a device-scope release fence when the splits of a tile are not known to
+// share an L2); the workgroup that sees the last count reads the tiles back.  Only that one thread per workgroup
+// fences: a device-scope fence in every wavefront (write-back of the whole L2) costs tens of microseconds per kernel.
+// 16-byte accesses with device scope (cache-policy bit 4 = sc1 on gfx942/gfx950) through a raw buffer descriptor
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t shared_rsrc(const void* base) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0x7fffffff, 0x00020000);
+}
+__device__ __forceinline__ void store_shared_f32x4(__amdgpu_buffer_rsrc_t r, uint32_t byte_off, f32x4 v) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, byte_off, 0, 16);
+}
+__device__ __forceinline__ f32x4 load_shared_f32x4(__amdgpu_buffer_rsrc_t r, uint32_t byte_off) {
+  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, byte_off, 0, 16));
+}
+__device__ __forceinline__ void store_shared_f32(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ float load_shared_f32(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// All of this wavefront's earlier vector memory operations have completed (stores: acknowledged by L2).  Written as the
+// wait itself: a workgroup-scope release fence compiles to no vector-memory wait here (the wavefronts of a workgroup
+// share one L1, so for ordering inside the workgroup none is needed), and then the partial-tile stores of a slow
+// wavefront could still be on their way when the arrival counter moved: once in some ten thousand launches the last
+// workgroup read the previous launch's values of a few cache lines.
+__device__ __forceinline__ void wait_own_memory_ops() {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+}
+
+// One thread of each of the ksplit workgroups of a tile, behind wait_own_memory_ops() and a barrier: counts the arrival
+// and returns true in the workgroup that came last.
+__device__ __forceinline__ bool arrive_last(unsigned long long* counter, int ksplit, int fence_handover, int* fault_flag) {
+  // Conservative path for partial tiles that may have to cross to another XCD: a device-scope release (L2
+  // write-back) before the counter moves.  The barrier in front orders every wavefront's completed stores before
+  // this thread's fence.
+  if (fence_handover) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  // the counter also records on which XCD each split ran, so that the last workgroup can tell whether the
+  // placement rule held for this tile (the unfenced hand-over is only sound if it did)
+  const unsigned xcc = __builtin_amdgcn_s_getreg((3 << 11) | 20) & 15u;  // HW_REG_XCC_ID
+  const unsigned long long mine = 1ull + (xcc < 8 ? 1ull << (8 + 5 * xcc) : 0ull);
+  const unsigned long long old = __hip_atomic_fetch_add(counter, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const bool last = (int)(old & 0xff) == ksplit - 1;
+  if (last && !fence_handover) {
+    const unsigned same = xcc < 8 ? (unsigned)(((old + mine) >> (8 + 5 * xcc)) & 31u) : 0u;
+    if ((int)same != ksplit) *fault_flag = 1;
+  }
+  return last;
+}
+
+// ------------------------------------------------------------------------------------------------
 struct LayerW {
   const uint16_t *wqkv, *wqkv_lo, *wo, *wo_lo, *wgu, *wgu_lo, *wd, *wd_lo;  // packed fp16 (lo planes only for fp32 sources)
   const uint8_t *wqkv8, *wo8, *wgu8, *wd8;  // weight-only quantised models: packed codes for the decode path ...
@@ -158,7 +206,7 @@ struct www_model {
   int* last_tok;      // [maxB] tokens of the last prompt position (prefill)
   // prefill-path buffers
   float* hp;       // residual stream of the prefill path in 256 x 256 blocks of accumulator order (see prefill.hip)
-  float* ssq_p;    // [d/256][maxT rounded to 256] partial sums of squares of hp
+  float* ssq_p;    // [maxT rounded to 256][PSSQ] partial sums of squares of hp, one per row tile of the producing GEMM
   uint16_t* xn;        // packed [maxT][d] normalised activations
   uint16_t* qp;    // [maxT][QD] rotated queries, fp16 (interleaved head-dim order)
   uint16_t* op;        // packed [maxT][QD] attention output
@@ -173,7 +221,7 @@ struct www_model {
 };
 
 #define MAX_ATTN_WAVES 4096  // upper bound of the decode attention grid, in wavefronts (sizes its plan and its records)
-#define PSSQ 32            // entries per token of the prefill path's sum-of-squares table (d_model / 256 row tiles at most)
+#define PSSQ 64            // entries per token of the prefill path's sum-of-squares table (d_model / 128 row tiles at most)
 #define SSQ_TILES 64       // most row tiles of a residual-producing GEMM (d_model / 128)
 #define GEMM_TILE_ROWS 128 // rows of W per workgroup of the skinny GEMM
 #define MAX_KSPLIT 16

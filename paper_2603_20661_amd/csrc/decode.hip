@@ -12,33 +12,6 @@
 
 __device__ __forceinline__ f16x8 as_f16x8(u32x4 v) { return __builtin_bit_cast(f16x8, v); }
 
-// Cross-workgroup hand-over of partial results inside one kernel.  Partial tiles are written and read with
-// device-scope (sc1) 16-byte accesses; every wavefront of the producer waits for its stores, the workgroup syncs, one
-// thread bumps a device-scope counter (after a device-scope release fence when the splits of a tile are not known to
-// share an L2); the workgroup that sees the last count reads the tiles back.  Only that one thread per workgroup
-// fences: a device-scope fence in every wavefront (write-back of the whole L2) costs tens of microseconds per kernel.
-// 16-byte accesses with device scope (cache-policy bit 4 = sc1 on gfx942/gfx950) through a raw buffer descriptor
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t shared_rsrc(const void* base) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0x7fffffff, 0x00020000);
-}
-__device__ __forceinline__ void store_shared_f32x4(__amdgpu_buffer_rsrc_t r, uint32_t byte_off, f32x4 v) {
-  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, byte_off, 0, 16);
-}
-__device__ __forceinline__ f32x4 load_shared_f32x4(__amdgpu_buffer_rsrc_t r, uint32_t byte_off) {
-  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, byte_off, 0, 16));
-}
-__device__ __forceinline__ void store_shared_f32(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ float load_shared_f32(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-// All of this wavefront's earlier vector memory operations have completed (stores: acknowledged by L2).  Written as the
-// wait itself: a workgroup-scope release fence compiles to no vector-memory wait here (the wavefronts of a workgroup
-// share one L1, so for ordering inside the workgroup none is needed), and then the partial-tile stores of a slow
-// wavefront could still be on their way when the arrival counter moved: once in some ten thousand launches the last
-// workgroup read the previous launch's values of a few cache lines.
-__device__ __forceinline__ void wait_own_memory_ops() {
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-}
-
 // offset (in elements) of column k of token t in a packed activation buffer with MT token groups
 __device__ __forceinline__ int64_t packed_x_offset(int k, int t, int MT, int hl) {
   int kb = k >> 5, g = (k & 31) >> 3, e = k & 7;
@@ -183,8 +156,8 @@ __global__ __launch_bounds__(256 * KH, 2 / KH) void skinny_gemm_kernel(const Gem
   // ids: id = c + 8 * ((zb * tiles_per_xcd + lt) * ksplit + split) for row tile c + 8 * lt.  Their partial tiles then
   // meet in one L2 and the split-K hand-over needs no L2 write-back.  The host checks this placement rule with a probe
   // kernel when a model is loaded and sets fence_handover when it does not hold.
-  const int tiles_per_xcd = (p.row_tiles + 7) / 8;
   const int slot = blockIdx.x >> 3;
+  const int tiles_per_xcd = (p.row_tiles + 7) / 8;
   const int split = slot % p.ksplit;
   const int lt = (slot / p.ksplit) % tiles_per_xcd, zb = slot / (p.ksplit * tiles_per_xcd);
   const int tile = (blockIdx.x & 7) + 8 * lt;
@@ -466,23 +439,7 @@ __global__ __launch_bounds__(256 * KH, 2 / KH) void skinny_gemm_kernel(const Gem
       for (int tb = 0; tb < MTK; ++tb) store_shared_f32x4(prs, punit(split, r, tb), acc[r][tb]);
     wait_own_memory_ops();
     __syncthreads();
-    if (tid == 0) {
-      // Conservative path for partial tiles that may have to cross to another XCD: a device-scope release (L2
-      // write-back) before the counter moves.  The barrier above orders every wavefront's completed stores before
-      // this thread's fence.
-      if (p.fence_handover) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-      // the counter also records on which XCD each split ran, so that the last workgroup can tell whether the
-      // placement rule held for this tile (the unfenced hand-over is only sound if it did)
-      const unsigned xcc = __builtin_amdgcn_s_getreg((3 << 11) | 20) & 15u;  // HW_REG_XCC_ID
-      const unsigned long long mine = 1ull + (xcc < 8 ? 1ull << (8 + 5 * xcc) : 0ull);
-      const unsigned long long old = __hip_atomic_fetch_add(&p.counters[zb * p.row_tiles + tile], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const bool last = (int)(old & 0xff) == p.ksplit - 1;
-      *s_last = last;
-      if (last && !p.fence_handover) {
-        const unsigned same = xcc < 8 ? (unsigned)(((old + mine) >> (8 + 5 * xcc)) & 31u) : 0u;
-        if ((int)same != p.ksplit) *p.fault_flag = 1;
-      }
-    }
+    if (tid == 0) *s_last = arrive_last(&p.counters[zb * p.row_tiles + tile], p.ksplit, p.fence_handover, p.fault_flag);
     __syncthreads();
     if (!*s_last) return;
     // the fenced hand-over's other half: the partial tiles may come from another L2, so everything this workgroup has

@@ -3,6 +3,8 @@
 // paged flash attention over cached prefix + new tokens.  This pass fills the KV cache; the logits
 // of each sequence's last position are produced afterwards by the decode path, which keeps the
 // activations of that one row in hi/lo precision.
+#include <type_traits>
+
 #include "common.h"
 
 #define NEG_INF (-__builtin_inff())
@@ -118,7 +120,7 @@ struct PGemmP {
   int NRG, KB;
   const u32x4* X;  // packed activations
   int T;
-  int n_tt, n_rt;  // token tiles, row tiles
+  int n_tt, n_rt;  // token tiles, row tiles of 256 x 256
   // QKV epilogue
   const float* qk_gain;  // models with normalised query / key heads: [2][hd] gains in packed row order; null otherwise
   uint16_t* qp;
@@ -140,6 +142,12 @@ struct PGemmP {
   // SwiGLU epilogue
   uint16_t* ap;
   int Fp;
+  // the kernel of smaller tiles: its tile counts, splits of the k range, and their hand-over (as in the decode GEMMs)
+  int n_ttS, n_rt128, ksplit, kb_per_split;
+  float* partial;
+  unsigned long long* counters;
+  int fence_handover;
+  int* fault_flag;
 };
 
 // Workgroup id -> tile of the prefill GEMM.  Workgroup ids are dealt round-robin to the 8 XCDs and dispatched in order,
@@ -173,6 +181,245 @@ __host__ __device__ __forceinline__ void pgemm_tile_of(int id, int n_tt, int n_r
   }
 }
 
+// Epilogue of the prefill GEMMs for TB groups of 32 tokens of one wavefront: its 128 rows are row half wn, its tokens the
+// groups tb0 .. tb0 + TB - 1 of token half wt of the 256 x 256 tile (tt, rt).
+//   acc[rb][tb][i] = Y^T[row][token]: row = (rg_w + rb*2)*16 + (i/4)*8 + (lane/32)*4 + i%4, token = t_w + tb*32 + lane%32
+// sum_out(tb, s) receives the sum of squares of a token's new residual over the wavefront's rows (residual epilogue).
+template <int EPI, bool QKN, int TB, typename SUM>
+__device__ __forceinline__ void pgemm_epilogue(const PGemmP& p, f32x16 (&acc)[4][TB], int tt, int rt, int wn, int wt, int tb0, SUM sum_out) {
+  const int lane = threadIdx.x & 63, wave = wn * 2 + wt;  // (position of the wavefront's rows and tokens in the 256 x 256 tile)
+  const int rg_w = rt * 16 + wn * 8, t_w = tt * 256 + wt * 128 + tb0 * 32;
+  const int hsel = lane >> 5;
+  // Everything the epilogue needs from memory per token is requested up front for all token groups (one memory
+  // round trip, two for the KV block ids), and the per-element operands of a token group (residual rows, rotary
+  // factors) in one batch per group: a wavefront has no partner on its SIMD to hide a chain of dependent loads behind.
+  // Addresses of tokens past the end are clamped; their results are dropped.
+  int tcl[TB];
+  bool tok_ok[TB];
+  float scale[TB];
+  int pos[TB], blk[TB];
+#pragma unroll
+  for (int tb = 0; tb < TB; ++tb) {
+    const int t = t_w + tb * 32 + (lane & 31);
+    tok_ok[tb] = t < p.T;
+    tcl[tb] = min(t, p.T - 1);
+    scale[tb] = p.wfactor;
+    pos[tb] = 0;
+    blk[tb] = 0;
+  }
+  if constexpr (EPI != PEPI_RESID) {
+    if constexpr (EPI == PEPI_QKV) {
+      int seq[TB];
+#pragma unroll
+      for (int tb = 0; tb < TB; ++tb) {
+        pos[tb] = p.row_pos[tcl[tb]];
+        seq[tb] = p.row_seq[tcl[tb]];
+      }
+#pragma unroll
+      for (int tb = 0; tb < TB; ++tb) blk[tb] = kv_block_id(p.table + (int64_t)seq[tb] * p.mbs, pos[tb]);
+    }
+    // the tokens' rows of the sum-of-squares table, [token][PSSQ], two token groups and 32 entries at a time (64
+    // registers); entries past n_ssq_in are masked, the rest is added in tile order
+    constexpr int TH = TB < 2 ? TB : 2;
+#pragma unroll
+    for (int t0 = 0; t0 < TB; t0 += TH) {
+      if (!p.ssq_in) break;  // no normalisation requested: the scales stay 1
+      float ss[TH];
+#pragma unroll
+      for (int u = 0; u < TH; ++u) ss[u] = 0.f;
+      for (int e0 = 0; e0 < p.n_ssq_in; e0 += 32) {
+        f32x4 sq[TH][8];
+#pragma unroll
+        for (int u = 0; u < TH; ++u)
+#pragma unroll
+          for (int c = 0; c < 8; ++c) sq[u][c] = *reinterpret_cast<const f32x4*>(p.ssq_in + (int64_t)tcl[t0 + u] * PSSQ + e0 + c * 4);
+#pragma unroll
+        for (int u = 0; u < TH; ++u)
+#pragma unroll
+          for (int c = 0; c < 8; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) ss[u] += (e0 + c * 4 + e < p.n_ssq_in) ? sq[u][c][e] : 0.f;
+      }
+#pragma unroll
+      for (int u = 0; u < TH; ++u) scale[t0 + u] = rsqrtf(ss[u] * p.inv_dim + p.eps) * p.wfactor;
+    }
+  }
+  f32x4 gv[4][4];  // next norm's gain for this lane's 16 x 4 rows (residual epilogue); gains of the head normalisation (QKV)
+  if constexpr (EPI == PEPI_QKV && QKN) {
+#pragma unroll
+    for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const int rg = min(rg_w + rb * 2 + (q4 >> 1), p.NRG - 1);
+        const int n0 = rg * 16 + (q4 & 1) * 8 + hsel * 4;
+        gv[rb][q4] = *reinterpret_cast<const f32x4*>(p.qk_gain + (n0 / p.hd < p.Hq ? 0 : p.hd) + n0 % p.hd);  // (value rows: unused)
+      }
+  }
+  if constexpr (EPI == PEPI_RESID) {
+#pragma unroll
+    for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const int rg = min(rg_w + rb * 2 + (q4 >> 1), p.NRG - 1);
+        gv[rb][q4] = *reinterpret_cast<const f32x4*>(p.gain_next + rg * 16 + (q4 & 1) * 8 + hsel * 4);
+      }
+  }
+#pragma unroll
+  for (int tb = 0; tb < TB; ++tb) {
+    __builtin_amdgcn_sched_barrier(0);  // one token group at a time: keeps the accumulator copies of the others out of the way
+    const int t = tcl[tb];
+    const bool ok = tok_ok[tb];
+    const int64_t slot = kv_slot_in_block(blk[tb], pos[tb]);
+    const int64_t kvbase = (slot / KV_BS) * p.Hkv;
+    const int tok = (int)(slot % KV_BS);
+    // one batch of loads for this token group: residual rows (RESID) or rotary factors (QKV)
+    f32x4 pre[4][4];
+    if constexpr (EPI != PEPI_SWIGLU) {
+#pragma unroll
+      for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const int rg = min(rg_w + rb * 2 + (q4 >> 1), p.NRG - 1);
+          const int n0 = rg * 16 + (q4 & 1) * 8 + hsel * 4;
+          if constexpr (EPI == PEPI_RESID)  // (whole tiles are allocated: in bounds also for tokens and rows past the end)
+            pre[rb][q4] = *reinterpret_cast<const f32x4*>(p.hp + hp_image_offset(tt, rt, p.n_rt, wave, rb, tb0 + tb, q4, lane));
+          else pre[rb][q4] = *reinterpret_cast<const f32x4*>(p.rope + (int64_t)pos[tb] * (p.hd / 2) + ((n0 % p.hd) >> 1));
+        }
+    }
+    float ssq_tok = 0.f;
+    // Normalised query / key heads: a wavefront's 128 rows are one head of 128 or two heads of 64 (row blocks 0,1 and
+    // 2,3), and a token's values of these rows sit in the two lanes l, l + 32: 1 / rms per head from the lane's own
+    // squares and one cross-lane exchange.
+    float head_rs[2] = {1.f, 1.f};
+    if constexpr (EPI == PEPI_QKV && QKN) {
+      float ss[2] = {0.f, 0.f};
+#pragma unroll
+      for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const float v = acc[rb][tb][i] * scale[tb];
+          ss[rb >> 1] += v * v;
+        }
+      if (p.hd == 128) ss[0] = ss[1] = ss[0] + ss[1];
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh) {
+        ss[hh] += __shfl_xor(ss[hh], 32);
+        head_rs[hh] = rsqrtf(ss[hh] / (float)p.hd + p.eps);
+      }
+    }
+    // QKV: finish the values in place (RMSNorm factor, head normalisation, rotation) and take the largest magnitude of
+    // each head's vector for this token: the scale of its key / value codes.  A wavefront's 128 rows are one head of
+    // 128 or two of 64 (row blocks 0,1 and 2,3); the token's values sit in the lanes l and l + 32.
+    float head_amax[2] = {0.f, 0.f};
+    if constexpr (EPI == PEPI_QKV) {
+      const int rot_rows = (p.Hq + p.Hkv) * p.hd;
+#pragma unroll
+      for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const int rg = rg_w + rb * 2 + (q4 >> 1);
+          const int n0 = rg * 16 + (q4 & 1) * 8 + hsel * 4;
+          float v4[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) v4[i] = acc[rb][tb][q4 * 4 + i] * scale[tb];
+          if (n0 < rot_rows) {
+            if constexpr (QKN) {
+#pragma unroll
+              for (int i = 0; i < 4; ++i) v4[i] *= head_rs[rb >> 1] * gv[rb][q4][i];
+            }
+            const f32x4 cs = pre[rb][q4];  // (cos, sin) of the two rotary pairs held here
+#pragma unroll
+            for (int pr = 0; pr < 2; ++pr) {
+              float a = v4[2 * pr], b = v4[2 * pr + 1];
+              v4[2 * pr] = a * cs[2 * pr] - b * cs[2 * pr + 1];
+              v4[2 * pr + 1] = b * cs[2 * pr] + a * cs[2 * pr + 1];
+            }
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            acc[rb][tb][q4 * 4 + i] = v4[i];
+            head_amax[rb >> 1] = fmaxf(head_amax[rb >> 1], __builtin_fabsf(v4[i]));
+          }
+        }
+      if (p.hd == 128) head_amax[0] = head_amax[1] = fmaxf(head_amax[0], head_amax[1]);
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh) head_amax[hh] = fmaxf(head_amax[hh], __shfl_xor(head_amax[hh], 32));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int rb = 0; rb < 4; ++rb) {
+      const int rgb = rg_w + rb * 2;  // first of the two row groups of this 32-row block
+      if constexpr (EPI == PEPI_SWIGLU) {
+        if (!ok || rgb + 1 >= p.NRG) continue;
+#pragma unroll
+        for (int q4 = 0; q4 < 2; ++q4) {
+          int f0 = (rgb >> 1) * 16 + q4 * 8 + hsel * 4;
+          union { uint16_t s[4]; u32x2 v; } o;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            float g = acc[rb][tb][q4 * 4 + i] * scale[tb], u = acc[rb][tb][(q4 + 2) * 4 + i] * scale[tb];
+            // (hardware reciprocal, 1 ulp: the result is rounded to fp16 right away; a correctly rounded fp32 division
+            // costs ten instructions per element of the widest GEMM's epilogue)
+            o.s[i] = f32_to_f16_sat(g * __builtin_amdgcn_rcpf(1.f + __expf(-g)) * u);
+          }
+          *reinterpret_cast<u32x2*>(p.ap + packed_p_offset(t, f0, p.Fp >> 4)) = o.v;
+        }
+      } else {
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const int rg = rgb + (q4 >> 1);
+          if (!ok || rg >= p.NRG) continue;
+          const int n0 = rg * 16 + (q4 & 1) * 8 + hsel * 4;
+          float v4[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) v4[i] = acc[rb][tb][q4 * 4 + i] * scale[tb];
+          if constexpr (EPI == PEPI_RESID) {
+            const f32x4 hv = pre[rb][q4], g4 = gv[rb][q4];
+            const float hn[4] = {hv[0] + v4[0], hv[1] + v4[1], hv[2] + v4[2], hv[3] + v4[3]};
+            *reinterpret_cast<float4*>(p.hp + hp_image_offset(tt, rt, p.n_rt, wave, rb, tb0 + tb, q4, lane)) = make_float4(hn[0], hn[1], hn[2], hn[3]);
+            union { uint16_t s[4]; u32x2 v; } o;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              ssq_tok += hn[i] * hn[i];
+              o.s[i] = f32_to_f16_sat(hn[i] * g4[i]);
+            }
+            *reinterpret_cast<u32x2*>(p.xn_out + packed_p_offset(t, n0, p.d >> 4)) = o.v;
+          } else {  // PEPI_QKV: the values were finished in place above
+            const int head = n0 / p.hd, c0 = n0 % p.hd;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v4[i] = acc[rb][tb][q4 * 4 + i];
+            union { uint16_t s[4]; u32x2 v; } o;
+            if (head < p.Hq) {
+#pragma unroll
+              for (int i = 0; i < 4; ++i) o.s[i] = f32_to_f16_sat(v4[i]);  // queries feed the fp16 attention kernel
+              *reinterpret_cast<u32x2*>(p.qp + (int64_t)t * (p.Hq * p.hd) + n0) = o.v;
+            } else {
+              // keys and values go to the cache as 16-bit codes with the scale of their (token, head) vector
+              const bool is_v = head >= p.Hq + p.Hkv;
+              const int j = head - p.Hq - (is_v ? p.Hkv : 0);
+              const float amax = head_amax[rb >> 1], inv = kv_code_inv(amax);
+#pragma unroll
+              for (int i = 0; i < 4; ++i) o.s[i] = kv_code(v4[i], inv);
+              if (!is_v) {
+                *reinterpret_cast<u32x2*>(p.kplane + (kvbase + j) * (int64_t)(KV_BS * p.hd) + k_cache_offset(tok, c0)) = o.v;
+              } else {
+                uint16_t* dst = p.vplane + (kvbase + j) * (int64_t)(KV_BS * p.hd);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) dst[v_cache_offset(tok, c0 + i)] = o.s[i];
+              }
+              if (c0 == 0) p.kvscale[kv_scale_offset(slot / KV_BS, p.Hkv, j) + (is_v ? 16 : 0) + tok] = kv_code_scale(amax);
+            }
+          }
+        }
+      }
+    }
+    if constexpr (EPI == PEPI_RESID) {
+      ssq_tok += __shfl_xor(ssq_tok, 32);  // the two lane halves hold different rows of the same token
+      sum_out(tb, ssq_tok);
+    }
+  }
+}
+
 // QKN: the QKV epilogue also normalises the query and key heads (an instantiation of its own, so that the plain model's
 // kernel carries none of its registers)
 template <int EPI, bool QKN = false>
@@ -186,7 +433,6 @@ __global__ __launch_bounds__(256) void prefill_gemm_kernel(const PGemmP p) {
   pgemm_tile_of((int)blockIdx.x, p.n_tt, p.n_rt, &tt, &rt);
 
   const int rg_tile = rt * 16;
-  const int t_tile = tt * 256;
   const int K16 = p.KB * 2;
 
   f32x16 acc[4][4];
@@ -306,238 +552,210 @@ __global__ __launch_bounds__(256) void prefill_gemm_kernel(const PGemmP p) {
   float(*red_ssq)[256] = reinterpret_cast<float(*)[256]>(smem);
   (void)red_ssq;
 
-  // acc[rb][tb][i] = Y^T[row][token]: row = (rg_tile + wn*8 + rb*2)*16 + (i/4)*8 + (lane/32)*4 + i%4, token = t_tile + wt*128 + tb*32 + lane%32
-  const int hsel = lane >> 5;
-  // Everything the epilogue needs from memory per token is requested up front for all four token groups (one memory
-  // round trip, two for the KV block ids), and the per-element operands of a token group (residual rows, rotary
-  // factors) in one batch per group: a wavefront has no partner on its SIMD to hide a chain of dependent loads behind.
-  // Addresses of tokens past the end are clamped; their results are dropped.
-  int tcl[4];
-  bool tok_ok[4];
-  float scale[4];
-  int pos[4], blk[4];
-#pragma unroll
-  for (int tb = 0; tb < 4; ++tb) {
-    const int t = t_tile + wt * 128 + tb * 32 + (lane & 31);
-    tok_ok[tb] = t < p.T;
-    tcl[tb] = min(t, p.T - 1);
-    scale[tb] = p.wfactor;
-    pos[tb] = 0;
-    blk[tb] = 0;
-  }
-  if constexpr (EPI != PEPI_RESID) {
-    if constexpr (EPI == PEPI_QKV) {
-      int seq[4];
-#pragma unroll
-      for (int tb = 0; tb < 4; ++tb) {
-        pos[tb] = p.row_pos[tcl[tb]];
-        seq[tb] = p.row_seq[tcl[tb]];
-      }
-#pragma unroll
-      for (int tb = 0; tb < 4; ++tb) blk[tb] = kv_block_id(p.table + (int64_t)seq[tb] * p.mbs, pos[tb]);
-    }
-    // the tokens' rows of the sum-of-squares table, [token][PSSQ], two token groups at a time (64 registers);
-    // entries past n_ssq_in are masked, the rest is added in tile order
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      if (!p.ssq_in) break;  // no normalisation requested: the scales stay 1
-      f32x4 sq[2][PSSQ / 4];
-#pragma unroll
-      for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int c = 0; c < PSSQ / 4; ++c)
-          sq[u][c] = *reinterpret_cast<const f32x4*>(p.ssq_in + (int64_t)tcl[half * 2 + u] * PSSQ + c * 4);
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        float ss = 0.f;
-#pragma unroll
-        for (int c = 0; c < PSSQ / 4; ++c)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) ss += (c * 4 + e < p.n_ssq_in) ? sq[u][c][e] : 0.f;
-        scale[half * 2 + u] = rsqrtf(ss * p.inv_dim + p.eps) * p.wfactor;
-      }
-    }
-  }
-  f32x4 gv[4][4];  // next norm's gain for this lane's 16 x 4 rows (residual epilogue); gains of the head normalisation (QKV)
-  if constexpr (EPI == PEPI_QKV && QKN) {
-#pragma unroll
-    for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const int rg = min(rg_tile + wn * 8 + rb * 2 + (q4 >> 1), p.NRG - 1);
-        const int n0 = rg * 16 + (q4 & 1) * 8 + hsel * 4;
-        gv[rb][q4] = *reinterpret_cast<const f32x4*>(p.qk_gain + (n0 / p.hd < p.Hq ? 0 : p.hd) + n0 % p.hd);  // (value rows: unused)
-      }
-  }
-  if constexpr (EPI == PEPI_RESID) {
-#pragma unroll
-    for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const int rg = min(rg_tile + wn * 8 + rb * 2 + (q4 >> 1), p.NRG - 1);
-        gv[rb][q4] = *reinterpret_cast<const f32x4*>(p.gain_next + rg * 16 + (q4 & 1) * 8 + hsel * 4);
-      }
-  }
-#pragma unroll
-  for (int tb = 0; tb < 4; ++tb) {
-    __builtin_amdgcn_sched_barrier(0);  // one token group at a time: keeps the accumulator copies of the others out of the way
-    const int t = tcl[tb];
-    const bool ok = tok_ok[tb];
-    const int64_t slot = kv_slot_in_block(blk[tb], pos[tb]);
-    const int64_t kvbase = (slot / KV_BS) * p.Hkv;
-    const int tok = (int)(slot % KV_BS);
-    // one batch of loads for this token group: residual rows (RESID) or rotary factors (QKV)
-    f32x4 pre[4][4];
-    if constexpr (EPI != PEPI_SWIGLU) {
-#pragma unroll
-      for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          const int rg = min(rg_tile + wn * 8 + rb * 2 + (q4 >> 1), p.NRG - 1);
-          const int n0 = rg * 16 + (q4 & 1) * 8 + hsel * 4;
-          if constexpr (EPI == PEPI_RESID)  // (whole tiles are allocated: in bounds also for tokens and rows past the end)
-            pre[rb][q4] = *reinterpret_cast<const f32x4*>(p.hp + hp_image_offset(tt, rt, p.n_rt, wave, rb, tb, q4, lane));
-          else pre[rb][q4] = *reinterpret_cast<const f32x4*>(p.rope + (int64_t)pos[tb] * (p.hd / 2) + ((n0 % p.hd) >> 1));
-        }
-    }
-    float ssq_tok = 0.f;
-    // Normalised query / key heads: a wavefront's 128 rows are one head of 128 or two heads of 64 (row blocks 0,1 and
-    // 2,3), and a token's values of these rows sit in the two lanes l, l + 32: 1 / rms per head from the lane's own
-    // squares and one cross-lane exchange.
-    float head_rs[2] = {1.f, 1.f};
-    if constexpr (EPI == PEPI_QKV && QKN) {
-      float ss[2] = {0.f, 0.f};
-#pragma unroll
-      for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const float v = acc[rb][tb][i] * scale[tb];
-          ss[rb >> 1] += v * v;
-        }
-      if (p.hd == 128) ss[0] = ss[1] = ss[0] + ss[1];
-#pragma unroll
-      for (int hh = 0; hh < 2; ++hh) {
-        ss[hh] += __shfl_xor(ss[hh], 32);
-        head_rs[hh] = rsqrtf(ss[hh] / (float)p.hd + p.eps);
-      }
-    }
-    // QKV: finish the values in place (RMSNorm factor, head normalisation, rotation) and take the largest magnitude of
-    // each head's vector for this token: the scale of its key / value codes.  A wavefront's 128 rows are one head of
-    // 128 or two of 64 (row blocks 0,1 and 2,3); the token's values sit in the lanes l and l + 32.
-    float head_amax[2] = {0.f, 0.f};
-    if constexpr (EPI == PEPI_QKV) {
-      const int rot_rows = (p.Hq + p.Hkv) * p.hd;
-#pragma unroll
-      for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          const int rg = rg_tile + wn * 8 + rb * 2 + (q4 >> 1);
-          const int n0 = rg * 16 + (q4 & 1) * 8 + hsel * 4;
-          float v4[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) v4[i] = acc[rb][tb][q4 * 4 + i] * scale[tb];
-          if (n0 < rot_rows) {
-            if constexpr (QKN) {
-#pragma unroll
-              for (int i = 0; i < 4; ++i) v4[i] *= head_rs[rb >> 1] * gv[rb][q4][i];
-            }
-            const f32x4 cs = pre[rb][q4];  // (cos, sin) of the two rotary pairs held here
-#pragma unroll
-            for (int pr = 0; pr < 2; ++pr) {
-              float a = v4[2 * pr], b = v4[2 * pr + 1];
-              v4[2 * pr] = a * cs[2 * pr] - b * cs[2 * pr + 1];
-              v4[2 * pr + 1] = b * cs[2 * pr] + a * cs[2 * pr + 1];
-            }
-          }
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            acc[rb][tb][q4 * 4 + i] = v4[i];
-            head_amax[rb >> 1] = fmaxf(head_amax[rb >> 1], __builtin_fabsf(v4[i]));
-          }
-        }
-      if (p.hd == 128) head_amax[0] = head_amax[1] = fmaxf(head_amax[0], head_amax[1]);
-#pragma unroll
-      for (int hh = 0; hh < 2; ++hh) head_amax[hh] = fmaxf(head_amax[hh], __shfl_xor(head_amax[hh], 32));
-    }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int rb = 0; rb < 4; ++rb) {
-      const int rgb = rg_tile + wn * 8 + rb * 2;  // first of the two row groups of this 32-row block
-      if constexpr (EPI == PEPI_SWIGLU) {
-        if (!ok || rgb + 1 >= p.NRG) continue;
-#pragma unroll
-        for (int q4 = 0; q4 < 2; ++q4) {
-          int f0 = (rgb >> 1) * 16 + q4 * 8 + hsel * 4;
-          union { uint16_t s[4]; u32x2 v; } o;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            float g = acc[rb][tb][q4 * 4 + i] * scale[tb], u = acc[rb][tb][(q4 + 2) * 4 + i] * scale[tb];
-            // (hardware reciprocal, 1 ulp: the result is rounded to fp16 right away; a correctly rounded fp32 division
-            // costs ten instructions per element of the widest GEMM's epilogue)
-            o.s[i] = f32_to_f16_sat(g * __builtin_amdgcn_rcpf(1.f + __expf(-g)) * u);
-          }
-          *reinterpret_cast<u32x2*>(p.ap + packed_p_offset(t, f0, p.Fp >> 4)) = o.v;
-        }
-      } else {
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          const int rg = rgb + (q4 >> 1);
-          if (!ok || rg >= p.NRG) continue;
-          const int n0 = rg * 16 + (q4 & 1) * 8 + hsel * 4;
-          float v4[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) v4[i] = acc[rb][tb][q4 * 4 + i] * scale[tb];
-          if constexpr (EPI == PEPI_RESID) {
-            const f32x4 hv = pre[rb][q4], g4 = gv[rb][q4];
-            const float hn[4] = {hv[0] + v4[0], hv[1] + v4[1], hv[2] + v4[2], hv[3] + v4[3]};
-            *reinterpret_cast<float4*>(p.hp + hp_image_offset(tt, rt, p.n_rt, wave, rb, tb, q4, lane)) = make_float4(hn[0], hn[1], hn[2], hn[3]);
-            union { uint16_t s[4]; u32x2 v; } o;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              ssq_tok += hn[i] * hn[i];
-              o.s[i] = f32_to_f16_sat(hn[i] * g4[i]);
-            }
-            *reinterpret_cast<u32x2*>(p.xn_out + packed_p_offset(t, n0, p.d >> 4)) = o.v;
-          } else {  // PEPI_QKV: the values were finished in place above
-            const int head = n0 / p.hd, c0 = n0 % p.hd;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) v4[i] = acc[rb][tb][q4 * 4 + i];
-            union { uint16_t s[4]; u32x2 v; } o;
-            if (head < p.Hq) {
-#pragma unroll
-              for (int i = 0; i < 4; ++i) o.s[i] = f32_to_f16_sat(v4[i]);  // queries feed the fp16 attention kernel
-              *reinterpret_cast<u32x2*>(p.qp + (int64_t)t * (p.Hq * p.hd) + n0) = o.v;
-            } else {
-              // keys and values go to the cache as 16-bit codes with the scale of their (token, head) vector
-              const bool is_v = head >= p.Hq + p.Hkv;
-              const int j = head - p.Hq - (is_v ? p.Hkv : 0);
-              const float amax = head_amax[rb >> 1], inv = kv_code_inv(amax);
-#pragma unroll
-              for (int i = 0; i < 4; ++i) o.s[i] = kv_code(v4[i], inv);
-              if (!is_v) {
-                *reinterpret_cast<u32x2*>(p.kplane + (kvbase + j) * (int64_t)(KV_BS * p.hd) + k_cache_offset(tok, c0)) = o.v;
-              } else {
-                uint16_t* dst = p.vplane + (kvbase + j) * (int64_t)(KV_BS * p.hd);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) dst[v_cache_offset(tok, c0 + i)] = o.s[i];
-              }
-              if (c0 == 0) p.kvscale[kv_scale_offset(slot / KV_BS, p.Hkv, j) + (is_v ? 16 : 0) + tok] = kv_code_scale(amax);
-            }
-          }
-        }
-      }
-    }
-    if constexpr (EPI == PEPI_RESID) {
-      ssq_tok += __shfl_xor(ssq_tok, 32);  // the two lane halves hold different rows of the same token
-      if (lane < 32) red_ssq[wn][wt * 128 + tb * 32 + lane] = ssq_tok;  // (slots of tokens past the end are never read)
-    }
-  }
+  pgemm_epilogue<EPI, QKN, 4>(p, acc, tt, rt, wn, wt, 0, [&](int tb, float ssq_tok) __attribute__((always_inline)) {
+    if (lane < 32) red_ssq[wn][wt * 128 + tb * 32 + lane] = ssq_tok;  // (slots of tokens past the end are never read)
+  });
   if constexpr (EPI == PEPI_RESID) {
     // per (row tile, token) sum of squares of the new residual, the two row halves added in a fixed order
     __syncthreads();
-    const int t = t_tile + tid;
+    const int t = tt * 256 + tid;
     if (t < p.T) p.ssq_out[(int64_t)t * PSSQ + rt] = red_ssq[0][tid] + red_ssq[1][tid];
   }
+}
+
+// ------------------------------------------------------------------------------------------------
+// The same GEMM with tiles of 128 rows x 128 TB tokens: four wavefronts of 128 rows x 32 TB tokens, and the k range of a
+// tile cut over ksplit workgroups where the tiles alone leave compute units idle.
+// The four wavefronts share the weight fragments (through LDS, copied as above) but no activations: those go from memory
+// straight into the registers of the one wavefront that needs them, PSG_D / TB blocks of 64 columns ahead.
+// Bound by what one compute unit takes in, 50 - 55 KB per us: a k block of 32 columns takes 0.29 us (TB = 1, 16 KB) or 0.43
+// us (TB = 2, 24 KB) with few or many workgroups, with the activations through LDS as well, and with two or five blocks in
+// flight; the 256 x 256 tiles (32 KB) take 0.7 - 0.76 us.  Up to 128 tokens the weights are read once: 4096 x 14336 weights,
+// 128 tokens, 8 splits: 37 us against 256 with 16 workgroups of 256 x 256 tiles.  (The wavefront's waits: 48 % of its
+// cycles at 512 tokens, matrix cores busy 49 %, bank conflicts none.)
+// All splits of a tile get workgroup ids that are equal modulo 8 and hand their partial tiles over like the decode GEMMs
+// (device-scope accesses, explicit wait, counter; the last one adds them in split order).  Token tiles are innermost, in
+// groups of 8: they run side by side behind one L2 and share the weights.
+#define PSG_NB 8  // stage buffers of 64 columns of the tile's weights (16 KiB each)
+#define PSG_D 8
+#define PSG_LDS_BYTES (PSG_NB * 1024 * 16)
+template <int EPI, bool QKN, int TB>
+__global__ __launch_bounds__(256, 1) void prefill_gemm_small_kernel(const PGemmP p) {
+  extern __shared__ u32x4 smem[];  // per stage 1024 units: [2 k blocks][8 row groups][64]
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int slot = blockIdx.x >> 3;
+  const int per_group = (p.n_rt128 + 7) / 8 * p.ksplit * 8;
+  const int group = slot / per_group, in_group = slot - group * per_group;
+  const int gsz = min(8, p.n_ttS - group * 8);  // (only the last group is narrower)
+  const int tt1 = group * 8 + in_group % gsz, split = (in_group / gsz) % p.ksplit;
+  const int rt1 = (blockIdx.x & 7) + 8 * (in_group / (gsz * p.ksplit));
+  if (rt1 >= p.n_rt128) return;  // grid padding when the row tiles are not a multiple of 8
+  const int rg_tile = rt1 * 8, K16 = p.KB * 2;
+  const int kb_begin = split * p.kb_per_split, nkb = min(p.KB, kb_begin + p.kb_per_split) - kb_begin;
+  // token groups of this wavefront that hold tokens of the call; one without any only helps with the copies
+  const int t_w = tt1 * 128 * TB + __builtin_amdgcn_readfirstlane(wave) * 32 * TB;
+  const int n_act = min(TB, max(0, (p.T - t_w + 31) >> 5));
+
+  f32x16 acc[4][TB];
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int b = 0; b < TB; ++b)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
+
+  // Stage copies, buffers and waits as in prefill_gemm_kernel, in blocks of 64 columns (four steps of 16); a wavefront
+  // moves 4 of a block's 16 units, one per step.  The activations are ordinary loads, whose waits the compiler places; they
+  // count in vmcnt too, so the hand-placed waits, which allow for the copies alone, wait for somewhat more than they need.
+  constexpr int NB = PSG_NB, D = PSG_D / TB;
+  static_assert(NB % D == 0, "the register sets rotate with the unrolled loop");
+  const int nsb = (nkb + 1) >> 1;  // blocks; the last one may be half empty
+  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+  const u32x4* srcA[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) srcA[i] = p.W + ((int64_t)kb_begin * p.NRG + min(rg_tile + wave_u + 4 * i, p.NRG - 1)) * 64;
+  const u32x4* srcB[TB];
+#pragma unroll
+  for (int tb = 0; tb < TB; ++tb) srcB[tb] = p.X + ((int64_t)((tt1 * 4 + wave_u) * TB + tb) * K16 + (int64_t)kb_begin * 2) * 64;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)smem;
+  const uint32_t voff = lane * 16;
+  u32x4 fa[2][4], fb[D][4][TB];
+  const int fm = lane & 31, fh = lane >> 5;
+  auto stage1 = [&](int sb, int buf, int i) __attribute__((always_inline)) {
+    const u32x4* g = srcA[i & 1] + (int64_t)min(sb * 2 + (i >> 1), nkb - 1) * p.NRG * 64;
+    const uint32_t lds_addr = lds0 + (uint32_t)(buf * 1024 + (i >> 1) * 512 + (wave_u + 4 * (i & 1)) * 64) * 16u;
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(g), "s"(lds_addr) : "memory", "m0");
+  };
+  auto load_b = [&](u32x4(&f)[TB], int sb, int t) __attribute__((always_inline)) {
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) f[tb] = srcB[tb][(int64_t)min(sb * 4 + t, nkb * 2 - 1) * 64 + lane];
+  };
+  auto fetch1 = [&](u32x4(&f)[4], int buf, int t, int rb) __attribute__((always_inline)) {
+    f[rb] = smem[buf * 1024 + (t >> 1) * 512 + (rb * 2 + (fm >> 4)) * 64 + (((t & 1) * 2 + fh) << 4) + (fm & 15)];
+  };
+  auto lds_barrier = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+  };
+  // requests that may still be outstanding when block s+1 (the first block) has to have landed
+  constexpr int VM_MID = (NB - 3) * 4 + 3, VM_PRO = (NB - 2) * 4;
+  constexpr int WAIT_MID = 0x0F70 | (VM_MID & 15) | ((VM_MID >> 4) << 14);
+  constexpr int WAIT_PRO = 0x0F70 | (VM_PRO & 15) | ((VM_PRO >> 4) << 14);
+  auto loop = [&](auto act) __attribute__((always_inline)) {
+    constexpr bool ACT = decltype(act)::value;  // this wavefront has tokens
+    // block s in buffer r, activations in register set r % D.  Per step: the MFMAs of its 16 columns, the weight fragments
+    // of the next step behind the first four, then the activations of block s + D into the registers just used, and
+    // one stage copy of block s + NB - 1 into the buffer of block s - 1.
+    auto block = [&](int s, int r, auto tail) __attribute__((always_inline)) {
+      const int buf1 = r == NB - 1 ? 0 : r + 1, bufp = r == 0 ? NB - 1 : r - 1;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        if (t == 3) {
+          __builtin_amdgcn_s_waitcnt(WAIT_MID);  // this wavefront's units of block s+1 have landed
+          lds_barrier();                         // ... everybody's
+        }
+        if (ACT) {
+          const bool skip = decltype(tail)::value && t >= 2 && s * 2 + 2 > nkb;  // the empty half of the last block
+#pragma unroll
+          for (int i = 0; i < 4 * TB; ++i) {
+            const int rb = i & 3, tb = i >> 2;
+            if (!skip) acc[rb][tb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_f16x8(fa[t & 1][rb]), as_f16x8(fb[r % D][t][tb]), acc[rb][tb], 0, 0, 0);
+            if (i < 4) fetch1(fa[(t + 1) & 1], t == 3 ? buf1 : r, (t + 1) & 3, i);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          load_b(fb[r % D][t], s + D, t);
+        }
+        stage1(s + NB - 1, bufp, t);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    if (ACT) {
+#pragma unroll
+      for (int s = 0; s < D; ++s)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) load_b(fb[s][t], s, t);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int b = 0; b < NB - 1; ++b)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) stage1(b, b, i);
+    __builtin_amdgcn_s_waitcnt(WAIT_PRO);
+    lds_barrier();
+    if (ACT) {
+#pragma unroll
+      for (int rb = 0; rb < 4; ++rb) fetch1(fa[0], 0, 0, rb);
+    }
+    int s = 0;
+    for (; s + NB < nsb; s += NB) {
+#pragma unroll
+      for (int r = 0; r < NB; ++r) block(s + r, r, std::false_type{});
+    }
+#pragma unroll
+    for (int r = 0; r < NB; ++r)
+      if (s + r < nsb) block(s + r, r, std::true_type{});
+  };
+  if (n_act) loop(std::true_type{});
+  else loop(std::false_type{});
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // the redirected copies past the last k block have landed too
+  __syncthreads();                     // the staging buffers are dead from here on
+
+  if (p.ksplit > 1) {
+    volatile int* s_last = reinterpret_cast<volatile int*>(smem);
+    const __amdgpu_buffer_rsrc_t prs = shared_rsrc(p.partial);
+    const int tile = tt1 * p.n_rt128 + rt1;
+    // register image: [split][tile][wavefront][token group][16 units][lane] of 16 bytes
+    auto punit = [&](int sp, int tb, int u) __attribute__((always_inline)) {
+      return (uint32_t)(((((sp * (p.n_ttS * p.n_rt128) + tile) * 4 + wave) * TB + tb) * 16 + u) * 64 + lane) * 16u;
+    };
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) {
+      if (tb >= n_act) break;
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        const int i = (u & 3) * 4;
+        const f32x4 v = {acc[u >> 2][tb][i], acc[u >> 2][tb][i + 1], acc[u >> 2][tb][i + 2], acc[u >> 2][tb][i + 3]};
+        store_shared_f32x4(prs, punit(split, tb, u), v);
+      }
+    }
+    wait_own_memory_ops();
+    __syncthreads();
+    if (tid == 0) *s_last = arrive_last(&p.counters[tile], p.ksplit, p.fence_handover, p.fault_flag);
+    __syncthreads();
+    if (!*s_last) return;
+    if (p.fence_handover) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    if (tid == 0) __hip_atomic_store(&p.counters[tile], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // added in split order (reproducible), the loads of two splits in flight together
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) {
+      if (tb >= n_act) break;
+#pragma unroll
+      for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[rb][tb][i] = 0.f;
+      for (int s0 = 0; s0 < p.ksplit; s0 += 2) {
+        f32x4 pv[2][16];
+#pragma unroll
+        for (int w = 0; w < 2; ++w)
+#pragma unroll
+          for (int u = 0; u < 16; ++u) pv[w][u] = load_shared_f32x4(prs, punit(min(s0 + w, p.ksplit - 1), tb, u));
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+          if (s0 + w >= p.ksplit) break;
+#pragma unroll
+          for (int u = 0; u < 16; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[u >> 2][tb][(u & 3) * 4 + e] += pv[w][u][e];
+        }
+      }
+    }
+  }
+  if (n_act == 0) return;
+  const int g32 = tt1 * 4 * TB + wave * TB;  // the wavefront's first group of 32 tokens; 8 of them make a 256-token tile
+  pgemm_epilogue<EPI, QKN, TB>(p, acc, g32 >> 3, rt1 >> 1, rt1 & 1, (g32 >> 2) & 1, g32 & 3, [&](int tb, float ssq_tok) __attribute__((always_inline)) {
+    if (lane < 32 && t_w + tb * 32 + lane < p.T) p.ssq_out[(int64_t)(t_w + tb * 32 + lane) * PSSQ + rt1] = ssq_tok;
+  });
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -801,21 +1019,84 @@ __global__ __launch_bounds__(256 * HG, 2 / HG) void prefill_attn_kernel(const ui
 // ------------------------------------------------------------------------------------------------
 // Host side
 
+// Which kernel a prefill GEMM of T tokens, NRG row groups and KB k blocks uses: tb = 0: 256 x 256 tiles, otherwise tiles of
+// 128 rows x 128 tb tokens whose k range is shared by ks workgroups.  The choice is the least of the times in us that a
+// fit of all three kernels gives: rounds of one workgroup per compute unit, a time per k block, a fixed time per round
+// (fill and epilogue) and, for a split range, the hand-over, whose last workgroup reads ks partial tiles.  Large calls
+// keep the 256 x 256 tiles, which read least per product; small ones would leave most compute units idle with them.
+// Measured at the 8B shape (us, 256 x 256 tiles against the choice): 333 tokens QKV 100 / 41 (128 tokens, no split), O 91 /
+// 28 (128, 2 splits), gate/up 91 / 91 (256 x 256), down 256 / 59 (256 tokens, 4 splits); 1024 tokens 106 / 67, 93 / 44,
+// 195 / 195, 261 / 117; 2048 tokens O 108 / 71, down 282 / 204; 8192 tokens: always 256 x 256 (gate/up 1388, the others 1660
+// and 2030).
+struct PGemmChoice { int tb, ks; };
+static PGemmChoice choose_pgemm(int T, int NRG, int KB) {
+  constexpr int CUS = 256;
+  const float per_kb[3] = {0.76f, 0.29f, 0.43f}, per_round[3] = {12.f, 5.f, 8.f}, hand0[3] = {0.f, 7.f, 9.f}, hand1[3] = {0.f, 1.4f, 3.f};
+  PGemmChoice best = {0, 1};
+  float least = 0.f;
+  for (int tb = 0; tb <= 2; ++tb) {
+    const int rows = tb ? 8 : 16, tokens = tb ? 128 * tb : 256;
+    const int64_t tiles = (int64_t)((T + tokens - 1) / tokens) * ((NRG + rows - 1) / rows);
+    for (int ks = 1; ks <= 8; ++ks) {
+      if (ks > 1 && (!tb || tiles * ks > CUS || KB < 8 * ks)) break;  // (parked tiles and counters are sized by this line)
+      const float us = (float)((tiles * ks + CUS - 1) / CUS) * (per_kb[tb] * (float)((KB + ks - 1) / ks) + per_round[tb]) +
+                       (ks > 1 ? hand0[tb] + hand1[tb] * ks : 0.f);
+      if ((!tb && ks == 1) || us < least) {
+        least = us;
+        best = {tb, ks};
+      }
+    }
+  }
+  return best;
+}
+
+// bytes of parked partial tiles the splits of any call of up to maxT tokens need
+uint64_t prefill_partial_bytes(int maxT, int NRG, int KB) {
+  uint64_t most = 0;
+  for (int64_t T = 128; T < (int64_t)maxT + 128; T += 128) {
+    const PGemmChoice c = choose_pgemm((int)T, NRG, KB);
+    if (c.ks > 1) {
+      const uint64_t tiles = (uint64_t)((T + 128 * c.tb - 1) / (128 * c.tb)) * ((NRG + 7) / 8);
+      if (tiles * c.ks * c.tb * 65536 > most) most = tiles * c.ks * c.tb * 65536;
+    }
+    if ((T / 256) * ((NRG + 7) / 8) > 256) break;  // more tiles than compute units from here on: never split
+  }
+  return most;
+}
+
+template <typename K>
+static void enable_lds(K kernel, int bytes) { (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes); }
+
+// returns the number of entries per token a residual epilogue wrote into the sum-of-squares table
 template <int EPI, bool QKN = false>
-static void launch_pgemm(PGemmP& p, hipStream_t st) {
+static int launch_pgemm(www_model* m, PGemmP& p, hipStream_t st) {
   if constexpr (EPI == PEPI_QKV && !QKN) {
-    if (p.qk_gain) return launch_pgemm<EPI, true>(p, st);
+    if (p.qk_gain) return launch_pgemm<EPI, true>(m, p, st);
   }
   p.n_tt = (p.T + 255) / 256;
   p.n_rt = (p.NRG + 15) / 16;
   if (p.wfactor == 0.f) p.wfactor = 1.f;  // not set: an unscaled matrix
-  static bool lds_enabled = false;  // per instantiation: allow 128 KiB of dynamic LDS
+  static bool lds_enabled = false;  // per instantiation: allow more than 64 KiB of dynamic LDS
   if (!lds_enabled) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&prefill_gemm_kernel<EPI, QKN>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              PGEMM_LDS_BYTES);
+    enable_lds(&prefill_gemm_kernel<EPI, QKN>, PGEMM_LDS_BYTES);
+    enable_lds(&prefill_gemm_small_kernel<EPI, QKN, 1>, PSG_LDS_BYTES);
+    enable_lds(&prefill_gemm_small_kernel<EPI, QKN, 2>, PSG_LDS_BYTES);
     lds_enabled = true;
   }
-  hipLaunchKernelGGL((prefill_gemm_kernel<EPI, QKN>), dim3(p.n_tt * p.n_rt), dim3(256), PGEMM_LDS_BYTES, st, p);
+  const PGemmChoice c = choose_pgemm(p.T, p.NRG, p.KB);
+  if (c.tb == 0) {
+    hipLaunchKernelGGL((prefill_gemm_kernel<EPI, QKN>), dim3(p.n_tt * p.n_rt), dim3(256), PGEMM_LDS_BYTES, st, p);
+    return p.n_rt;
+  }
+  p.n_ttS = (p.T + 128 * c.tb - 1) / (128 * c.tb);
+  p.n_rt128 = (p.NRG + 7) / 8;
+  p.kb_per_split = (p.KB + c.ks - 1) / c.ks;
+  p.ksplit = (p.KB + p.kb_per_split - 1) / p.kb_per_split;
+  p.partial = m->partial; p.counters = m->counters; p.fence_handover = m->handover_fence; p.fault_flag = m->fault_dev;
+  const dim3 grid(8 * ((p.n_rt128 + 7) / 8) * p.ksplit * p.n_ttS);
+  if (c.tb == 1) hipLaunchKernelGGL((prefill_gemm_small_kernel<EPI, QKN, 1>), grid, dim3(256), PSG_LDS_BYTES, st, p);
+  else hipLaunchKernelGGL((prefill_gemm_small_kernel<EPI, QKN, 2>), grid, dim3(256), PSG_LDS_BYTES, st, p);
+  return p.n_rt128;
 }
 
 template <int HD>
@@ -856,7 +1137,6 @@ int run_prefill(www_model* m, const int32_t* tok, const int32_t* qlens, const in
     hipLaunchKernelGGL(embed_rows_kernel<uint16_t>, dim3(T), dim3(256), 0, st, tok, (const uint16_t*)m->embed, d, m->layers[0].attn_norm,
                        m->hp, (uint16_t*)m->xn, m->ssq_p);
   int n_ssq = 1;
-  const int n_rt_d = (d / 16 + 15) / 16;  // row tiles of a GEMM with d output rows
   const int max_tiles = T / ATTN_TQ + batch;
   for (int l = 0; l < m->L; ++l) {
     const LayerW& w = m->layers[l];
@@ -869,7 +1149,7 @@ int run_prefill(www_model* m, const int32_t* tok, const int32_t* qlens, const in
       p.ssq_in = m->ssq_p; p.n_ssq_in = n_ssq; p.inv_dim = 1.f / d; p.eps = m->cfg.rms_eps;
       p.qp = (uint16_t*)m->qp; p.kplane = kplane; p.vplane = vplane; p.kvscale = kvscale; p.row_seq = m->row_seq; p.row_pos = m->row_pos; p.table = table;
       p.mbs = m->cfg.max_blocks_per_seq; p.hd = m->hd; p.Hq = m->Hq; p.Hkv = m->Hkv; p.rope = m->rope; p.qk_gain = w.qk_gain;
-      launch_pgemm<PEPI_QKV>(p, st);
+      launch_pgemm<PEPI_QKV>(m, p, st);
     }
     if (l == m->L - 1) break;  // only this layer's keys and values are still needed
     if (m->hd == 128) launch_pattn<128>(m, kplane, vplane, kvscale, qlens, lens, table, max_tiles, st);
@@ -878,21 +1158,20 @@ int run_prefill(www_model* m, const int32_t* tok, const int32_t* qlens, const in
       PGemmP p = {};
       p.W = (const u32x4*)w.wo; p.wfactor = w.so; p.NRG = d / 16; p.KB = m->QD / 32; p.X = (const u32x4*)m->op; p.T = T;
       p.hp = m->hp; p.d = d; p.gain_next = w.ffn_norm; p.xn_out = (uint16_t*)m->xn; p.ssq_out = m->ssq_p;
-      launch_pgemm<PEPI_RESID>(p, st);
-      n_ssq = n_rt_d;
+      n_ssq = launch_pgemm<PEPI_RESID>(m, p, st);
     }
     {
       PGemmP p = {};
       p.W = (const u32x4*)w.wgu; p.wfactor = w.sgu; p.NRG = 2 * m->F / 16; p.KB = d / 32; p.X = (const u32x4*)m->xn; p.T = T;
       p.ssq_in = m->ssq_p; p.n_ssq_in = n_ssq; p.inv_dim = 1.f / d; p.eps = m->cfg.rms_eps;
       p.ap = (uint16_t*)m->ap; p.Fp = m->Fp;
-      launch_pgemm<PEPI_SWIGLU>(p, st);
+      launch_pgemm<PEPI_SWIGLU>(m, p, st);
     }
     {
       PGemmP p = {};
       p.W = (const u32x4*)w.wd; p.wfactor = w.sd; p.NRG = d / 16; p.KB = m->Fp / 32; p.X = (const u32x4*)m->ap; p.T = T;
       p.hp = m->hp; p.d = d; p.gain_next = m->layers[l + 1].attn_norm; p.xn_out = (uint16_t*)m->xn; p.ssq_out = m->ssq_p;
-      launch_pgemm<PEPI_RESID>(p, st);
+      n_ssq = launch_pgemm<PEPI_RESID>(m, p, st);
     }
   }
   hipError_t e = hipGetLastError();

@@ -53,7 +53,7 @@ __global__ __launch_bounds__(256) void embed_pack_kernel(const int32_t* __restri
 }
 
 // ------------------------------------------------------------------------------------------------
-// Skinny GEMM: Y^T[n][t] = sum_k W[n][k] X[t][k] for up to 64 tokens per workgroup pass.
+// Skinny GEMM: Y^T[n][t] = sum_k W[n][k] X[t][k] for up to 128 tokens per workgroup pass.
 enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LOGITS = 3 };
 
 struct GemmP {
@@ -67,7 +67,7 @@ struct GemmP {
   int kb_per_split, ksplit;
   int row_tiles, zbs;  // grid: 8 * ceil(row_tiles / 8) * ksplit * zbs workgroups
   int fence_handover;  // 1: workgroups of one row tile may sit behind different L2s
-  float* partial;    // [ksplit][zbs][row_tiles] tiles of 128 rows x 64 tokens
+  float* partial;    // [ksplit][zbs][row_tiles] tiles of 128 rows x 16 MTK tokens
   unsigned long long* counters;  // [zbs][row_tiles]: arrivals in bits 0-7, arrivals per XCD in eight 5-bit fields above
   int* fault_flag;   // host-visible; set when the splits of a row tile turn out to sit on different XCDs
   const float* ssq_in;  // [token][SSQ_TILES]; row scale = rsqrt(sum of the first n_ssq_in entries / dim + eps); null: no scale
@@ -135,7 +135,7 @@ enum { WMODE_F16 = 0, WMODE_SPLIT = 1, WMODE_FP8 = 2, WMODE_INT4 = 3 };
 // chunk, so each issues half of the MFMAs and one can issue while its SIMD partner waits for memory; the two partial
 // tiles are added through LDS behind the loop and wavefronts 4..7 retire.
 template <int MTK, int WMODE, int EPI, int KH>
-__global__ __launch_bounds__(256 * KH, 2 / KH) void skinny_gemm_kernel(const GemmP p) {
+__global__ __launch_bounds__(256 * KH, MTK == 8 ? 1 : 2 / KH) void skinny_gemm_kernel(const GemmP p) {
   constexpr bool WSPLIT = WMODE == WMODE_SPLIT, W8 = WMODE == WMODE_FP8, W4 = WMODE == WMODE_INT4;
   constexpr int R = 2, KC = 4, WP = WSPLIT ? 2 : 1;
   constexpr int NT = 256 * KH;                     // threads
@@ -144,25 +144,31 @@ __global__ __launch_bounds__(256 * KH, 2 / KH) void skinny_gemm_kernel(const Gem
   constexpr int CHUNK_UNITS = KC * MTK * 128;      // 16-byte units of activations per k chunk
   constexpr int NSTG = (CHUNK_UNITS + NT - 1) / NT;
   __shared__ u32x4 lds[2][CHUNK_UNITS];
-  __shared__ float s_scale[64];
+  __shared__ float s_scale[MTK * 16];
   // after the main loop the staging buffers are dead and are reused for the epilogue's small reductions
-  float(*red)[64] = reinterpret_cast<float(*)[64]>(&lds[0][0]);
+  float(*red)[MTK * 16] = reinterpret_cast<float(*)[MTK * 16]>(&lds[0][0]);
   volatile int* s_last = reinterpret_cast<volatile int*>(&lds[1][0]);
 
   const int tid = threadIdx.x, wave = (tid >> 6) & 3, khalf = KH == 1 ? 0 : tid >> 8, lane = tid & 63;
   const int k_first = khalf * KPW;                 // first k block of a chunk this wavefront multiplies
   // Workgroup id -> work item.  Consecutive workgroup ids are dealt round-robin to the XCDs (8 here; any power of two
   // up to 8 divides 8), so ids that are equal modulo 8 run behind the same L2.  All k splits of a row tile get such
-  // ids: id = c + 8 * ((zb * tiles_per_xcd + lt) * ksplit + split) for row tile c + 8 * lt.  Their partial tiles then
-  // meet in one L2 and the split-K hand-over needs no L2 write-back.  The host checks this placement rule with a probe
+  // ids: id = c + 8 * slot for row tile c + 8 * lt.  Their partial tiles then meet in one L2 and the split-K hand-over
+  // needs no L2 write-back.  Order of the slots: token groups (zb) outermost, then row tiles, then splits; in the two wide
+  // GEMMs (gate/up, output head), whose grids are several rounds long, token groups innermost: they run side by side behind
+  // one L2 and share the weights (128 tokens in two groups of 64: output head of the 8B shape 407 -> 308 us).
+  // The host checks this placement rule with a probe
   // kernel when a model is loaded and sets fence_handover when it does not hold.
   const int slot = blockIdx.x >> 3;
+  constexpr bool WIDE = EPI == EPI_SWIGLU || EPI == EPI_LOGITS;
   const int tiles_per_xcd = (p.row_tiles + 7) / 8;
-  const int split = slot % p.ksplit;
-  const int lt = (slot / p.ksplit) % tiles_per_xcd, zb = slot / (p.ksplit * tiles_per_xcd);
+  const int zb = WIDE ? slot % p.zbs : slot / (p.ksplit * tiles_per_xcd);
+  const int in_zb = WIDE ? slot / p.zbs : slot % (p.ksplit * tiles_per_xcd);
+  const int split = in_zb % p.ksplit, lt = in_zb / p.ksplit;
   const int tile = (blockIdx.x & 7) + 8 * lt;
   if (tile >= p.row_tiles) return;  // grid padding when the row tiles are not a multiple of 8
-  const int tb0 = zb * 4;
+  const int tb0 = zb * MTK;
+  if (tb0 * 16 >= p.M) return;  // a group of padding only (all splits of it leave here)
   const int rg0 = tile * 8 + wave * R;
   const int kb_begin = split * p.kb_per_split;
   const int kb_end = min(p.KB, kb_begin + p.kb_per_split);
@@ -181,11 +187,12 @@ __global__ __launch_bounds__(256 * KH, 2 / KH) void skinny_gemm_kernel(const Gem
   // Inputs of the epilogue that hang off dependent loads (RMSNorm scale; position and KV block of each token) are
   // requested at kernel entry together with the first weights and activations, and only touched once that first chunk
   // has arrived, so they never put a memory round trip in front of the streaming loop.
-  // Sum of squares of a token: wavefront w owns token group w (every workgroup of the grid reads the same small table,
+  // Sum of squares of a token: wavefront w owns token group w (and w + 4; every workgroup of the grid reads the same small table,
   // so each reads it once, not once per wavefront).  Lane group g = lane/16 reads entries 16g .. 16g+15 of the token's
   // row (four 16-byte loads, always in bounds; entries past n_ssq_in are masked), adds them in index order, and the
   // four groups are combined by two cross-lane exchanges: a fixed order, so the scale is the same in every workgroup.
-  f32x4 ssq_raw[4];
+  constexpr int NSQ = (MTK + 3) / 4;
+  f32x4 ssq_raw[NSQ][4];
   int pos_pre[MTK];
   int tok_c[MTK];
 #pragma unroll
@@ -195,24 +202,30 @@ __global__ __launch_bounds__(256 * KH, 2 / KH) void skinny_gemm_kernel(const Gem
     if constexpr (EPI == EPI_QKV) pos_pre[tb] = p.seq_lens[tok_c[tb]] - 1;
   }
   if (p.ssq_in && wave < MTK && khalf == 0) {
-    const int t = min((tb0 + wave) * 16 + (lane & 15), p.M - 1);
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
-      ssq_raw[c] = *reinterpret_cast<const f32x4*>(p.ssq_in + (int64_t)t * SSQ_TILES + (lane >> 4) * 16 + c * 4);
+    for (int q = 0; q < NSQ; ++q) {
+      const int t = min((tb0 + wave + 4 * q) * 16 + (lane & 15), p.M - 1);
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        ssq_raw[q][c] = *reinterpret_cast<const f32x4*>(p.ssq_in + (int64_t)t * SSQ_TILES + (lane >> 4) * 16 + c * 4);
+    }
   }
   float scale_pre[MTK];
   int blk_pre[MTK];
   // before the first barrier: reduce the sums and publish the scales; table loads for the KV slots go out
   auto finish_prefetch = [&]() __attribute__((always_inline)) {
     if (p.ssq_in && wave < MTK && khalf == 0) {
-      float s = 0.f;
 #pragma unroll
-      for (int c = 0; c < 4; ++c)
+      for (int q = 0; q < NSQ; ++q) {
+        float s = 0.f;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) s += ((lane >> 4) * 16 + c * 4 + e < p.n_ssq_in) ? ssq_raw[c][e] : 0.f;
-      s += __shfl_xor(s, 16);
-      s += __shfl_xor(s, 32);
-      if (lane < 16) s_scale[wave * 16 + lane] = rsqrtf(s * p.inv_dim + p.eps);
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) s += ((lane >> 4) * 16 + c * 4 + e < p.n_ssq_in) ? ssq_raw[q][c][e] : 0.f;
+        s += __shfl_xor(s, 16);
+        s += __shfl_xor(s, 32);
+        if (lane < 16) s_scale[(wave + 4 * q) * 16 + lane] = rsqrtf(s * p.inv_dim + p.eps);
+      }
     }
 #pragma unroll
     for (int tb = 0; tb < MTK; ++tb) {
@@ -230,6 +243,7 @@ __global__ __launch_bounds__(256 * KH, 2 / KH) void skinny_gemm_kernel(const Gem
   };
 
   u32x4 wA[KC][R][WP], wB[KC][R][WP], stg[NSTG];
+  const int last_tb = (p.M - 1) / 16 - tb0;  // last token group of this workgroup that holds a sequence
 
   // Loads past the end of this split's k range are redirected to its last valid block (in bounds) and the
   // matching MFMAs are skipped in compute(): no per-element selects in the streaming loop.
@@ -271,7 +285,8 @@ __global__ __launch_bounds__(256 * KH, 2 / KH) void skinny_gemm_kernel(const Gem
 #pragma unroll
     for (int i = 0; i < NSTG; ++i) {
       const int u = min(tid + i * NT, CHUNK_UNITS - 1);  // (more threads than units when MTK = 1 and KH = 2)
-      const int kk = u / (MTK * 128), within = u % (MTK * 128);
+      // (token groups past the last sequence: its group again, in L1 by then; their columns of the result are dropped)
+      const int kk = u / (MTK * 128), within = min(u % (MTK * 128) / 128, last_tb) * 128 + u % 128;
       const int kbc = min(kb_begin + c * KC + kk, kb_end - 1);
       stg[i] = p.X[((int64_t)kbc * p.MT + tb0) * 128 + within];
     }
@@ -281,51 +296,59 @@ __global__ __launch_bounds__(256 * KH, 2 / KH) void skinny_gemm_kernel(const Gem
     for (int i = 0; i < NSTG; ++i) lds[buf][min(tid + i * NT, CHUNK_UNITS - 1)] = stg[i];
   };
   // nvalid = k blocks of the chunk that lie inside the range: KC for every chunk but possibly the last.
-  // The B fragments (activations) of k block kk+1 are fetched from LDS while the MFMAs of k block kk run.
+  // The B fragments (activations) of the next up to four token groups are fetched from LDS while the MFMAs of the current
+  // ones run.
   auto compute = [&](u32x4(&w)[KC][R][WP], int buf, int nvalid) __attribute__((always_inline)) {
-    u32x4 bq[2][MTK][2];
-    auto fetch = [&](int set, int kk) __attribute__((always_inline)) {
+    constexpr int TG = MTK < 4 ? MTK : 4, NG = MTK / TG;
+    u32x4 bq[2][TG][2];
+    auto fetch = [&](int set, int kk, int grp) __attribute__((always_inline)) {
 #pragma unroll
-      for (int tb = 0; tb < MTK; ++tb) {
-        bq[set][tb][0] = lds[buf][(kk * MTK + tb) * 128 + lane];
-        bq[set][tb][1] = lds[buf][(kk * MTK + tb) * 128 + 64 + lane];
+      for (int tb = 0; tb < TG; ++tb) {
+        bq[set][tb][0] = lds[buf][(kk * MTK + grp * TG + tb) * 128 + lane];
+        bq[set][tb][1] = lds[buf][(kk * MTK + grp * TG + tb) * 128 + 64 + lane];
       }
     };
-    fetch(0, k_first);
+    fetch(0, k_first, 0);
+    f16x8 a8[R];
 #pragma unroll
-    for (int j = 0; j < KPW; ++j) {  // k block k_first + j of the chunk, operands in register slot j
+    for (int st = 0; st < KPW * NG; ++st) {
+      const int j = st / NG, grp = st % NG;  // k block k_first + j of the chunk, operands in register slot j; token groups TG grp ..
       if (k_first + j >= nvalid) break;
-      if (j + 1 < KPW) fetch((j + 1) & 1, k_first + j + 1);
+      if (st + 1 < KPW * NG) fetch((st + 1) & 1, k_first + (st + 1) / NG, (st + 1) % NG);
       __builtin_amdgcn_sched_barrier(0);
-      f16x8 a8[R];
       if constexpr (W8) {
+        if (grp == 0) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const u32x4 raw = w[j & ~1][r][0];
-          a8[r] = (j & 1) ? fp8x8_to_f16x8(raw.z, raw.w) : fp8x8_to_f16x8(raw.x, raw.y);
+          for (int r = 0; r < R; ++r) {
+            const u32x4 raw = w[j & ~1][r][0];
+            a8[r] = (j & 1) ? fp8x8_to_f16x8(raw.z, raw.w) : fp8x8_to_f16x8(raw.x, raw.y);
+          }
         }
       }
       if constexpr (W4) {  // (KH = 1: j is the k block)
+        if (grp == 0) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const u32x4 raw = w[0][r][0], sc = w[1][r][0];
-          const uint32_t word = j == 0 ? raw.x : j == 1 ? raw.y : j == 2 ? raw.z : raw.w;
-          const uint32_t s2 = j < 2 ? sc.x : sc.y;
-          const uint32_t s16 = (j & 1) ? (s2 >> 16) : (s2 & 0xFFFFu);
-          a8[r] = int4x8_to_f16x8(word, __builtin_bit_cast(f16x2, s16 | (s16 << 16)));
+          for (int r = 0; r < R; ++r) {
+            const u32x4 raw = w[0][r][0], sc = w[1][r][0];
+            const uint32_t word = j == 0 ? raw.x : j == 1 ? raw.y : j == 2 ? raw.z : raw.w;
+            const uint32_t s2 = j < 2 ? sc.x : sc.y;
+            const uint32_t s16 = (j & 1) ? (s2 >> 16) : (s2 & 0xFFFFu);
+            a8[r] = int4x8_to_f16x8(word, __builtin_bit_cast(f16x2, s16 | (s16 << 16)));
+          }
         }
       }
 #pragma unroll
-      for (int tb = 0; tb < MTK; ++tb) {
-        const f16x8 bhi = as_f16x8(bq[j & 1][tb][0]), blo = as_f16x8(bq[j & 1][tb][1]);
+      for (int tb = 0; tb < TG; ++tb) {
+        const f16x8 bhi = as_f16x8(bq[st & 1][tb][0]), blo = as_f16x8(bq[st & 1][tb][1]);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
+          f32x4& c = acc[r][grp * TG + tb];
           f16x8 a;
           if constexpr (W8 || W4) a = a8[r];
           else a = as_f16x8(w[j][r][0]);
-          acc[r][tb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, bhi, acc[r][tb], 0, 0, 0);
-          acc[r][tb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, blo, acc[r][tb], 0, 0, 0);
-          if constexpr (WSPLIT) acc[r][tb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(w[j][r][1]), bhi, acc[r][tb], 0, 0, 0);
+          c = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, bhi, c, 0, 0, 0);
+          c = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, blo, c, 0, 0, 0);
+          if constexpr (WSPLIT) c = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(w[j][r][1]), bhi, c, 0, 0, 0);
         }
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -451,12 +474,13 @@ __global__ __launch_bounds__(256 * KH, 2 / KH) void skinny_gemm_kernel(const Gem
     for (int r = 0; r < R; ++r)
 #pragma unroll
       for (int tb = 0; tb < MTK; ++tb) acc[r][tb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // partial tiles are added in split order (reproducible); loads are issued four splits at a time so that
-    // the reduction is not one memory round trip per split
-    for (int s0 = 0; s0 < p.ksplit; s0 += 4) {
-      f32x4 pv[4][R][MTK];
+    // partial tiles are added in split order (reproducible); loads are issued four splits (two of 128 tokens: registers)
+    // at a time so that the reduction is not one memory round trip per split
+    constexpr int NSP = MTK == 8 ? 2 : 4;
+    for (int s0 = 0; s0 < p.ksplit; s0 += NSP) {
+      f32x4 pv[NSP][R][MTK];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < NSP; ++u) {
         const int sidx = min(s0 + u, p.ksplit - 1);
 #pragma unroll
         for (int r = 0; r < R; ++r)
@@ -464,7 +488,7 @@ __global__ __launch_bounds__(256 * KH, 2 / KH) void skinny_gemm_kernel(const Gem
           for (int tb = 0; tb < MTK; ++tb) pv[u][r][tb] = load_shared_f32x4(prs, punit(sidx, r, tb));
       }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < NSP; ++u) {
         if (s0 + u >= p.ksplit) break;
 #pragma unroll
         for (int r = 0; r < R; ++r)
@@ -1171,16 +1195,25 @@ static void choose_split(int row_tiles, int zb, int KB, int* ksplit, int* kb_per
 
 // split factor the decode path will use for a GEMM with NRG row groups and KB k blocks (for workspace sizing)
 int decode_gemm_ksplit(int NRG, int KB, int MT) {
-  int zb = MT > 4 ? MT / 4 : 1, ks, per;
-  choose_split((NRG + 7) / 8, zb, KB, &ks, &per);
-  return ks;
+  int most = 1;
+  for (int mtk = 4; mtk <= 8; mtk += 4) {  // token groups per workgroup, see launch_gemm
+    int ks, per;
+    choose_split((NRG + 7) / 8, MT > mtk ? MT / mtk : 1, KB, &ks, &per);
+    if (ks > most) most = ks;
+  }
+  return most;
 }
 
 template <int EPI>
 static void launch_gemm(www_model* m, GemmP& p, int MT, hipStream_t st) {
   const int row_tiles = (p.NRG + 7) / 8;
-  const int zb = MT > 4 ? MT / 4 : 1;
-  const int mtk = MT > 4 ? 4 : MT;
+  // Above 64 tokens the two wide GEMMs take 128 tokens per workgroup: every compute unit takes in about 55 KB per us, and
+  // 128 rows x 128 tokens need 24 KB per k block where two workgroups of 64 tokens need 32 (8B shape, 128 tokens: gate/up 84 ->
+  // 73 us, output head 308 -> 298).  The split-K GEMMs, whose epilogues then exceed the registers, are slower that way (QKV
+  // 36 -> 52 us), and so are int4 weights (a step of 100 sequences 7250 -> 7700 us).
+  constexpr bool wide_epi = EPI == EPI_SWIGLU || EPI == EPI_LOGITS;
+  const int mtk = MT < 8 ? MT : wide_epi && !m->int4_group && !m->wsplit ? 8 : 4;
+  const int zb = MT / mtk;
   choose_split(row_tiles, zb, p.KB, &p.ksplit, &p.kb_per_split);
   p.MT = MT;
   p.partial = m->partial;
@@ -1192,6 +1225,7 @@ static void launch_gemm(www_model* m, GemmP& p, int MT, hipStream_t st) {
   if (p.wfactor == 0.f) p.wfactor = 1.f;  // not set: an unscaled matrix
   dim3 grid(8 * ((row_tiles + 7) / 8) * p.ksplit * zb);
 #define LAUNCH(MTK_, WM_, KH_) hipLaunchKernelGGL((skinny_gemm_kernel<MTK_, WM_, EPI, KH_>), grid, dim3(256 * KH_), 0, st, p);
+#define LAUNCH8(WM_) { if constexpr (wide_epi) LAUNCH(8, WM_, 2) }
   // With more than 32 tokens the MFMAs of a chunk take a third of a wavefront's time; in the gate/up GEMM (no split-K,
   // 32 chunks per workgroup) two wavefronts per SIMD (KH = 2) hide them behind each other's waits: 53 -> 49.5 us at 64
   // tokens of the 8B shape.  The split-K GEMMs walk 4 - 14 chunks and are bound by their fixed costs; the hand-over
@@ -1200,12 +1234,13 @@ static void launch_gemm(www_model* m, GemmP& p, int MT, hipStream_t st) {
   if (m->int4_group) {
     if (mtk == 1) LAUNCH(1, WMODE_INT4, 1) else if (mtk == 2) LAUNCH(2, WMODE_INT4, 1) else LAUNCH(4, WMODE_INT4, 1)
   } else if (m->fp8) {
-    if (mtk == 1) LAUNCH(1, WMODE_FP8, 1) else if (mtk == 2) LAUNCH(2, WMODE_FP8, 1) else LAUNCH(4, WMODE_FP8, kh4)
+    if (mtk == 1) LAUNCH(1, WMODE_FP8, 1) else if (mtk == 2) LAUNCH(2, WMODE_FP8, 1) else if (mtk == 4) LAUNCH(4, WMODE_FP8, kh4) else LAUNCH8(WMODE_FP8)
   } else if (m->wsplit) {
     if (mtk == 1) LAUNCH(1, WMODE_SPLIT, 1) else if (mtk == 2) LAUNCH(2, WMODE_SPLIT, 1) else LAUNCH(4, WMODE_SPLIT, 1)
   } else {
-    if (mtk == 1) LAUNCH(1, WMODE_F16, 1) else if (mtk == 2) LAUNCH(2, WMODE_F16, 1) else LAUNCH(4, WMODE_F16, kh4)
+    if (mtk == 1) LAUNCH(1, WMODE_F16, 1) else if (mtk == 2) LAUNCH(2, WMODE_F16, 1) else if (mtk == 4) LAUNCH(4, WMODE_F16, kh4) else LAUNCH8(WMODE_F16)
   }
+#undef LAUNCH8
 #undef LAUNCH
 }
 
@@ -1246,7 +1281,7 @@ int decode_probe_placement(int32_t* scratch_dev, int n, hipStream_t st) {
   return 1;
 }
 
-int decode_MT(int batch) { return batch <= 16 ? 1 : batch <= 32 ? 2 : ((batch + 63) / 64) * 4; }
+int decode_MT(int batch) { return batch <= 16 ? 1 : batch <= 32 ? 2 : batch <= 64 ? 4 : ((batch + 127) / 128) * 8; }
 
 int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int32_t* table, int batch, float* logits, int32_t* next,
                hipStream_t st) {

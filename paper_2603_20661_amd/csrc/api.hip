@@ -15,6 +15,7 @@
 
 int decode_gemm_ksplit(int NRG, int KB, int MT);
 uint64_t prefill_partial_bytes(int maxT, int NRG, int KB);
+uint64_t prefill_attn_part_bytes(int hd, int Hkv, int G, int maxT, int maxB, int max_pos);
 int decode_MT(int batch);
 
 static thread_local char g_err[512] = "";
@@ -206,6 +207,8 @@ static void make_plan(const www_config* c, Plan& p) {
   const uint64_t pre[4] = {prefill_partial_bytes(s.maxT, s.QKVN / 16, s.d / 32), prefill_partial_bytes(s.maxT, s.d / 16, s.QD / 32),
                            prefill_partial_bytes(s.maxT, 2 * s.F / 16, s.d / 32), prefill_partial_bytes(s.maxT, s.d / 16, s.Fp / 32)};
   for (uint64_t b : pre) part = part > b ? part : b;
+  const uint64_t states = prefill_attn_part_bytes(s.hd, s.Hkv, s.G, s.maxT, s.maxB, s.max_pos);  // same buffer, other kernels
+  part = part > states ? part : states;
   p.partial = take(part ? part : 256);
   // the decode attention's records: two per wavefront that has work, and no more of those than key pairs in the batch
   const uint64_t max_pairs = (uint64_t)s.maxB * s.Hkv * (((uint64_t)s.max_pos + 31) / 32);

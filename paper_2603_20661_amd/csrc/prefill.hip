@@ -769,6 +769,20 @@ __global__ __launch_bounds__(256, 1) void prefill_gemm_small_kernel(const PGemmP
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
+// Key range of a tile: a call with few tiles leaves compute units idle, so the key pairs of a tile are cut into up to
+// max_splits ranges of at least PATTN_MIN_PAIRS pairs, each walked by a workgroup of its own that parks its softmax state;
+// prefill_attn_merge_kernel then combines them.  A walk takes about 1.2 us per pair whatever the other compute units do: 16
+// tokens over 6000 cached ones, 8 workgroups: 225 us per layer of the 8B shape, the call 26.4 ms; with 16 ranges (and the
+// GEMMs of small calls) 8.4 ms.  At least 4, 8 or 16 pairs per range: 8.44, 8.60, 8.70 ms.
+#define PATTN_MIN_PAIRS 4
+#define PATTN_MAX_ITEMS 256  // calls with more workgroups than this are not cut
+__host__ __device__ __forceinline__ int pattn_splits(int npairs, int max_splits) {
+  const int n = npairs / PATTN_MIN_PAIRS;
+  return n < 1 ? 1 : n < max_splits ? n : max_splits;
+}
+// floats a workgroup parks: [wavefront][query head][HD / 16][lane][4] unnormalised outputs, then [wavefront][query head][lane] (m, l)
+constexpr int pattn_record(int HD, int GH, int HG) { return 4 * HG * GH * 64 * (HD / 4 + 2); }
+
 template <int HD, int GH, int HG>
 __global__ __launch_bounds__(256 * HG, 2 / HG) void prefill_attn_kernel(const uint16_t* __restrict__ qp, const uint16_t* __restrict__ kplane,
                                                             const uint16_t* __restrict__ vplane, const float* __restrict__ kvscale,
@@ -777,13 +791,14 @@ __global__ __launch_bounds__(256 * HG, 2 / HG) void prefill_attn_kernel(const ui
                                                             int mbs, int Hq, int Hkv, int G, const int32_t* __restrict__ tile_seq,
                                                             const int32_t* __restrict__ tile_q0, const int32_t* __restrict__ meta,
                                                             const int32_t* __restrict__ cum_rows, float scale_log2,
-                                                            uint16_t* __restrict__ op, int max_tiles) {
+                                                            uint16_t* __restrict__ op, int max_tiles, int max_splits,
+                                                            float* __restrict__ part) {
   constexpr int NKF = HD / 32, NVF = HD / 16;
   constexpr int CH = NKF * 64;         // 16-byte units of one block's keys (and of one block's values)
   constexpr int NT = 256 * HG;         // threads: HG groups of four wavefronts, each group with its own GH query heads
   constexpr int NLD = 4 * CH / NT;     // units each thread moves per pair
   __shared__ u32x4 kv[2][4 * CH];      // per pair: keys of block 0, keys of block 1, values of block 0, values of block 1
-  // Work items in the order (head group, kv head, tile), tiles fastest; workgroup ids are dealt round-robin to the 8
+  // Work items in the order (head group, kv head, key range, tile), tiles fastest; workgroup ids are dealt round-robin to the 8
   // XCDs, so the ids are transposed: XCD x gets the x-th eighth of that order, i.e. the consecutive tiles of a
   // sequence and kv head run behind one L2 and fetch its keys and values into it once (with 8 kv heads: one per XCD).
   int item = blockIdx.x;
@@ -791,9 +806,10 @@ __global__ __launch_bounds__(256 * HG, 2 / HG) void prefill_attn_kernel(const ui
   if (n_items % 8 == 0) item = (item & 7) * (n_items >> 3) + (item >> 3);
   const int tile = item % max_tiles;
   if (tile >= meta[0]) return;
-  const int j = (item / max_tiles) % Hkv;
+  const int split = (item / max_tiles) % max_splits, jh = item / (max_tiles * max_splits);  // (kv head, then head group)
+  const int j = jh % Hkv;
   const int tid = threadIdx.x, wave = (tid >> 6) & 3, lane = tid & 63;
-  const int h0 = j * G + ((item / (max_tiles * Hkv)) * HG + (tid >> 8)) * GH;  // first query head handled by this wavefront
+  const int h0 = j * G + ((jh / Hkv) * HG + (tid >> 8)) * GH;  // first query head handled by this wavefront
   const int n = lane & 15, g = lane >> 4;
   const int b = tile_seq[tile];
   const int qlen = q_lens[b], ctx = seq_lens[b];
@@ -807,7 +823,12 @@ __global__ __launch_bounds__(256 * HG, 2 / HG) void prefill_attn_kernel(const ui
   const int qpos = prefix + qw0 + my_q;   // this lane's query position
   const int kmax = active ? prefix + qw0 + nq : 0;  // keys 0 .. kmax-1 are visible to some query of the wavefront
   const int npairs = (kmax + 31) / 32;
-  const int npairs_wg = (prefix + min(qlen, tq0 + 64) + 31) / 32;  // pairs the workgroup walks through
+  const int npairs_tile = (prefix + min(qlen, tq0 + 64) + 31) / 32;  // pairs of the tile ...
+  const int nsplit = pattn_splits(npairs_tile, max_splits);
+  if (split >= nsplit) return;
+  const int per_split = (npairs_tile + nsplit - 1) / nsplit;
+  const int pr_first = split * per_split;                            // ... and the ones this workgroup walks through
+  const int npairs_wg = min(npairs_tile, pr_first + per_split);
   const int last_blk = (ctx - 1) / KV_BS;
   const int32_t* trow = table + (int64_t)b * mbs;
   const int QD = Hq * HD;
@@ -836,10 +857,10 @@ __global__ __launch_bounds__(256 * HG, 2 / HG) void prefill_attn_kernel(const ui
   float ksc[NLD / 2];
   f32x4 vsc[NLD / 2];
   // Block ids are fetched one pair ahead of the request that uses them, so the request never waits for the table.
-  // A pair past the workgroup's last one is redirected to the last one (in bounds, never used).
+  // A pair past the tile's last one is redirected to the last one (in bounds, never used).
   int id0 = 0, id1 = 0;
   auto fetch_ids = [&](int pr) __attribute__((always_inline)) {
-    const int prc = min(pr, npairs_wg - 1);
+    const int prc = min(pr, npairs_tile - 1);
     id0 = trow[min(prc * 2, last_blk)];
     id1 = trow[min(prc * 2 + 1, last_blk)];
   };
@@ -912,7 +933,7 @@ __global__ __launch_bounds__(256 * HG, 2 / HG) void prefill_attn_kernel(const ui
     // necessarily the running maximum: the result o / l does not depend on it.  The common case takes no maximum at
     // all: the exponentials are formed against the current reference, and only if some lane's sum of its eight
     // numerators exceeds 256 (so a numerator might not fit fp16 comfortably; also true for a NaN or an infinity) or
-    // on the first pair (no reference yet) the wavefront takes the exact maxima, moves the reference up, rescales o
+    // while a query has no reference yet (on the first pair, or as long as it has seen hidden keys only) the wavefront takes the exact maxima, moves the reference up, rescales o
     // and l and forms the exponentials again.  After the first pairs of a sequence that is rare, and the 4 * NVF
     // accumulator registers per head are then left alone.  Hidden keys (later than the query, or slots past the end
     // of the sequence, which may hold anything) enter as -inf and get p = 0.
@@ -933,7 +954,7 @@ __global__ __launch_bounds__(256 * HG, 2 / HG) void prefill_attn_kernel(const ui
         pv[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sr[i], scale_log2, neg_m));
         psum += pv[i];
       }
-      if (pr == 0 || __any(!(psum <= 256.f))) {
+      if (pr == pr_first || __any(!(psum <= 256.f) || (masked && m_run[hh] == NEG_INF))) {
         float scl[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) scl[i] = sr[i] * scale_log2;
@@ -982,12 +1003,12 @@ __global__ __launch_bounds__(256 * HG, 2 / HG) void prefill_attn_kernel(const ui
     }
   };
 
-  fetch_ids(0);
+  fetch_ids(pr_first);
   request();
-  fetch_ids(1);
-  copy_in(0);
+  fetch_ids(pr_first + 1);
+  copy_in(pr_first & 1);
   __syncthreads();
-  for (int pr = 0; pr < npairs_wg; ++pr) {
+  for (int pr = pr_first; pr < npairs_wg; ++pr) {
     request();          // pair pr + 1
     fetch_ids(pr + 2);
     __builtin_amdgcn_sched_barrier(0);
@@ -998,6 +1019,22 @@ __global__ __launch_bounds__(256 * HG, 2 / HG) void prefill_attn_kernel(const ui
     __builtin_amdgcn_sched_barrier(0);
     copy_in((pr + 1) & 1);
     __syncthreads();
+  }
+  if (nsplit > 1) {
+    // a wavefront without visible keys in this range parks m = -inf, l = 0, o = 0
+    float* rec = part + ((int64_t)(jh * max_tiles + tile) * max_splits + split) * pattn_record(HD, GH, HG);
+    float* ml = rec + 4 * HG * GH * 64 * (HD / 4);
+    const int w = tid >> 6;
+#pragma unroll
+    for (int hh = 0; hh < GH; ++hh) {
+      float l = l_run[hh];
+      l += __shfl_xor(l, 16);
+      l += __shfl_xor(l, 32);
+#pragma unroll
+      for (int f = 0; f < NVF; ++f) *reinterpret_cast<f32x4*>(rec + (((w * GH + hh) * NVF + f) * 64 + lane) * 4) = oacc[hh][f];
+      *reinterpret_cast<float2*>(ml + ((w * GH + hh) * 64 + lane) * 2) = make_float2(m_run[hh], l);
+    }
+    return;
   }
   if (!active || n >= nq) return;
 #pragma unroll
@@ -1013,6 +1050,62 @@ __global__ __launch_bounds__(256 * HG, 2 / HG) void prefill_attn_kernel(const ui
       for (int i = 0; i < 4; ++i) o.s[i] = f32_to_f16_sat(oacc[hh][f][i] * inv);
       *reinterpret_cast<u32x2*>(op + packed_p_offset(row0 + n, (h0 + hh) * HD + f * 16 + g * 4, QD >> 4)) = o.v;
     }
+  }
+}
+
+// Combines the key ranges of a tile, in key order: one workgroup per (tile, kv head and head group, query head of the
+// wavefront, half of the head's dims), lanes as in the attention kernel.
+template <int HD, int GH, int HG>
+__global__ __launch_bounds__(256 * HG) void prefill_attn_merge_kernel(const int32_t* __restrict__ q_lens, const int32_t* __restrict__ seq_lens,
+                                                                      int Hq, int Hkv, int G, const int32_t* __restrict__ tile_seq,
+                                                                      const int32_t* __restrict__ tile_q0, const int32_t* __restrict__ meta,
+                                                                      const int32_t* __restrict__ cum_rows, uint16_t* __restrict__ op,
+                                                                      int max_tiles, int max_splits, const float* __restrict__ part) {
+  constexpr int NVF = HD / 16, NF = NVF / 2;
+  const int tile = blockIdx.x, jh = blockIdx.y, hh = blockIdx.z >> 1, f0 = (blockIdx.z & 1) * NF;
+  if (tile >= meta[0]) return;
+  const int b = tile_seq[tile], tq0 = tile_q0[tile], qlen = q_lens[b];
+  const int prefix = seq_lens[b] - qlen;
+  const int nsplit = pattn_splits((prefix + min(qlen, tq0 + 64) + 31) / 32, max_splits);
+  if (nsplit <= 1) return;
+  const int tid = threadIdx.x, w = tid >> 6, wave = w & 3, lane = tid & 63, n = lane & 15, g = lane >> 4;
+  if (tq0 + wave * 16 + n >= qlen) return;
+  const int head = (jh % Hkv) * G + ((jh / Hkv) * HG + (w >> 2)) * GH + hh;
+  const float* rec0 = part + (int64_t)(jh * max_tiles + tile) * max_splits * pattn_record(HD, GH, HG);
+  const int o_at = (((w * GH + hh) * NVF + f0) * 64 + lane) * 4, ml_at = 4 * HG * GH * 64 * (HD / 4) + ((w * GH + hh) * 64 + lane) * 2;
+  float M = NEG_INF, L = 0.f;
+  f32x4 o[NF];
+#pragma unroll
+  for (int f = 0; f < NF; ++f) o[f] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int s0 = 0; s0 < nsplit; s0 += 4) {  // four ranges per memory round trip
+    float2 ml[4];
+    f32x4 v[4][NF];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const float* rec = rec0 + (int64_t)min(s0 + u, nsplit - 1) * pattn_record(HD, GH, HG);
+      ml[u] = *reinterpret_cast<const float2*>(rec + ml_at);
+#pragma unroll
+      for (int f = 0; f < NF; ++f) v[u][f] = *reinterpret_cast<const f32x4*>(rec + o_at + f * 256);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (s0 + u >= nsplit) break;
+      const float Mn = fmaxf(M, ml[u].x), ref = Mn == NEG_INF ? 0.f : Mn;
+      const float a = __builtin_amdgcn_exp2f(M - ref), c = __builtin_amdgcn_exp2f(ml[u].x - ref);
+      L = L * a + ml[u].y * c;
+#pragma unroll
+      for (int f = 0; f < NF; ++f) o[f] = o[f] * a + v[u][f] * c;
+      M = Mn;
+    }
+  }
+  const float inv = 1.f / L;
+  const int64_t row = (int64_t)cum_rows[b] + tq0 + wave * 16 + n;
+#pragma unroll
+  for (int f = 0; f < NF; ++f) {
+    union { uint16_t s[4]; u32x2 v; } out;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) out.s[i] = f32_to_f16_sat(o[f][i] * inv);
+    *reinterpret_cast<u32x2*>(op + packed_p_offset(row, head * HD + (f0 + f) * 16 + g * 4, (Hq * HD) >> 4)) = out.v;
   }
 }
 
@@ -1099,28 +1192,58 @@ static int launch_pgemm(www_model* m, PGemmP& p, hipStream_t st) {
   return p.n_rt128;
 }
 
+// Shape of the attention workgroups: two query heads per wavefront pass, since their accumulators and operands fit 256
+// registers, so two workgroups share a compute unit and one hides the other's softmax and LDS latencies (four heads per
+// pass at one workgroup per unit: 1.5x slower).  With 128-wide heads two such head groups form one workgroup of eight
+// wavefronts (still two per SIMD) and share the copy of the keys and values into LDS, which halves the code-to-fp16
+// conversions per query head.  max_splits: most key ranges per tile, for up to two workgroups per compute unit (half of the
+// tiles the host has to provide for are usually empty or short; limits of 128, 256 and 512 workgroups: 16 sequences of 16 -
+// 32 tokens over mixed prefixes 13.0, 12.6, 12.6 ms, 4 x 512 over 2000 33.4, 33.3, 34.4, one prompt of 2000 32.1, 32.4, 32.6).
+struct PAttnShape { int GH, HG, items, max_splits; };
+static PAttnShape pattn_shape(int hd, int Hkv, int G, int max_tiles, int max_pos) {
+  PAttnShape a;
+  a.GH = (G % 2 == 0) ? 2 : 1;
+  a.HG = (hd == 128 && (G / a.GH) % 2 == 0) ? 2 : 1;
+  a.items = max_tiles * Hkv * (G / a.GH / a.HG);
+  a.max_splits = a.items <= PATTN_MAX_ITEMS ? 2 * PATTN_MAX_ITEMS / a.items : 1;
+  if (a.max_splits > 16) a.max_splits = 16;
+  a.max_splits = pattn_splits((max_pos + 31) / 32, a.max_splits);
+  return a;
+}
+
+// bytes of parked softmax states any call needs
+uint64_t prefill_attn_part_bytes(int hd, int Hkv, int G, int maxT, int maxB, int max_pos) {
+  uint64_t most = 0;
+  for (int tiles = 1; tiles <= maxT / ATTN_TQ + maxB; ++tiles) {
+    const PAttnShape a = pattn_shape(hd, Hkv, G, tiles, max_pos);
+    if (a.items > PATTN_MAX_ITEMS) break;
+    const uint64_t bytes = a.max_splits > 1 ? (uint64_t)a.items * a.max_splits * pattn_record(hd, a.GH, a.HG) * 4 : 0;
+    if (bytes > most) most = bytes;
+  }
+  return most;
+}
+
 template <int HD>
 static void launch_pattn(www_model* m, const uint16_t* kplane, const uint16_t* vplane, const float* kvscale, const int32_t* qlens, const int32_t* lens,
                          const int32_t* table, int max_tiles, hipStream_t st) {
-  const int G = m->G;
-  // two query heads per workgroup pass: their accumulators and operands fit 256 registers, so two workgroups share a
-  // compute unit and one hides the other's softmax and LDS latencies (four heads per pass at one workgroup per unit: 1.5x slower)
-  const int GH = (G % 2 == 0) ? 2 : 1;
-  // with 128-wide heads two such head groups form one workgroup of eight wavefronts (still two per SIMD) and share
-  // the copy of the keys and values into LDS, which halves the code-to-fp16 conversions per query head
-  const int HG = (HD == 128 && (G / GH) % 2 == 0) ? 2 : 1;
-  dim3 grid(max_tiles * m->Hkv * (G / GH / HG)), block(256 * HG);
+  const PAttnShape a = pattn_shape(HD, m->Hkv, m->G, max_tiles, m->max_pos);
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)HD);
   const int32_t* cum_rows = m->meta + 16;
 #define PATTN(GH_, HG_)                                                                                                            \
-  hipLaunchKernelGGL((prefill_attn_kernel<HD, GH_, HG_>), grid, block, 0, st, (const uint16_t*)m->qp, kplane, vplane, kvscale, qlens, lens, \
-                     table,                                                                                                        \
-                     (int)m->cfg.max_blocks_per_seq, m->Hq, m->Hkv, G, m->tile_seq, m->tile_q0, m->meta, cum_rows, scale_log2,      \
-                     (uint16_t*)m->op, max_tiles)
-  if constexpr (HD == 128) {
-    if (HG == 2) { PATTN(2, 2); return; }
+  {                                                                                                                                \
+    hipLaunchKernelGGL((prefill_attn_kernel<HD, GH_, HG_>), dim3(a.items * a.max_splits), dim3(256 * HG_), 0, st,                  \
+                       (const uint16_t*)m->qp, kplane, vplane, kvscale, qlens, lens, table, (int)m->cfg.max_blocks_per_seq, m->Hq, \
+                       m->Hkv, m->G, m->tile_seq, m->tile_q0, m->meta, cum_rows, scale_log2, (uint16_t*)m->op, max_tiles,          \
+                       a.max_splits, m->partial);                                                                                  \
+    if (a.max_splits > 1)                                                                                                          \
+      hipLaunchKernelGGL((prefill_attn_merge_kernel<HD, GH_, HG_>), dim3(max_tiles, m->Hkv * (m->G / GH_ / HG_), GH_ * 2),         \
+                         dim3(256 * HG_), 0, st, qlens, lens, m->Hq, m->Hkv, m->G, m->tile_seq, m->tile_q0, m->meta, cum_rows,     \
+                         (uint16_t*)m->op, max_tiles, a.max_splits, m->partial);                                                   \
   }
-  if (GH == 2) PATTN(2, 1); else PATTN(1, 1);
+  if constexpr (HD == 128) {
+    if (a.HG == 2) { PATTN(2, 2) return; }
+  }
+  if (a.GH == 2) PATTN(2, 1) else PATTN(1, 1)
 #undef PATTN
 }
 

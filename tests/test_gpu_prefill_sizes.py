@@ -20,3 +20,13 @@ DEEP_QKN = dataclasses.replace(DEEP, name="deepkqkn", qk_norm=1, seed=403)
 @pytest.mark.parametrize("lens", [[1], [31, 1], [33], [127], [128, 1], [255, 2], [513], [200, 900]], ids=str)
 def test_edges(shape, lens):
     check(run_job(shape, lens, 1, seed=sum(lens)), f"{shape.name} {lens}")
+
+
+@pytest.mark.parametrize("hd,group", [(64, 1), (64, 2), (64, 8), (128, 1), (128, 2), (128, 4), (128, 8)])
+@pytest.mark.parametrize("lens,chunk", [([700, 3, 129], 40), ([1100, 260], 130)], ids=str)
+def test_key_ranges_of_the_attention(hd, group, lens, chunk):
+    """chunks over a cached prefix in calls of few tiles: the keys of a tile are cut into ranges, the last of them with
+    queries that see none of its keys or only part of its first pair"""
+    n_kv = 2 if group <= 4 else 1
+    shape = synth.ModelShape(f"rng{hd}g{group}", 2, 256, n_kv * group, n_kv, hd, 352, 512, 1e-5, 1e4, synth.WDTYPE_BF16, seed=420 + hd + group)
+    check(run_job(shape, lens, 1, seed=430 + group, chunk=chunk), f"{shape.name} {lens} chunk {chunk}")

@@ -140,7 +140,7 @@ __global__ __launch_bounds__(256 * KH, MTK == 8 ? 1 : 2 / KH) void skinny_gemm_k
   constexpr int R = 2, KC = 4, WP = WSPLIT ? 2 : 1;
   constexpr int NT = 256 * KH;                     // threads
   constexpr int KPW = KC / KH;                     // k blocks of a chunk per wavefront
-  static_assert(KH == 1 || (KH == 2 && !W4), "the int4 unit spans the whole chunk");
+  static_assert(KH == 1 || KH == 2);
   constexpr int CHUNK_UNITS = KC * MTK * 128;      // 16-byte units of activations per k chunk
   constexpr int NSTG = (CHUNK_UNITS + NT - 1) / NT;
   __shared__ u32x4 lds[2][CHUNK_UNITS];
@@ -253,9 +253,16 @@ __global__ __launch_bounds__(256 * KH, MTK == 8 ? 1 : 2 / KH) void skinny_gemm_k
       const int chunk = min((kb_begin + c * KC) >> 2, (kb_end - 1) >> 2);
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        w[0][r][0] = p.W[((int64_t)chunk * p.NRG + rgc[r]) * 64 + lane];
-        const u32x2 sc = p.Wscale[((int64_t)chunk * p.NRG + rgc[r]) * 16 + (lane & 15)];
-        w[1][r][0] = u32x4{sc.x, sc.y, 0u, 0u};
+        const int64_t unit = ((int64_t)chunk * p.NRG + rgc[r]) * 64 + lane, scale = ((int64_t)chunk * p.NRG + rgc[r]) * 16 + (lane & 15);
+        if constexpr (KH == 1) {
+          w[0][r][0] = p.W[unit];
+          const u32x2 sc = p.Wscale[scale];
+          w[1][r][0] = u32x4{sc.x, sc.y, 0u, 0u};
+        } else {  // only the half of the unit (two k blocks) and the two scales this wavefront multiplies
+          const u32x2 half = reinterpret_cast<const u32x2*>(p.W)[unit * 2 + khalf];
+          w[0][r][0] = u32x4{half.x, half.y, 0u, 0u};
+          w[1][r][0] = u32x4{reinterpret_cast<const uint32_t*>(p.Wscale)[scale * 2 + khalf], 0u, 0u, 0u};
+        }
       }
       return;
     }
@@ -325,7 +332,7 @@ __global__ __launch_bounds__(256 * KH, MTK == 8 ? 1 : 2 / KH) void skinny_gemm_k
           }
         }
       }
-      if constexpr (W4) {  // (KH = 1: j is the k block)
+      if constexpr (W4) {  // (j is the k block of the unit, or of its half)
         if (grp == 0) {
 #pragma unroll
           for (int r = 0; r < R; ++r) {
@@ -1232,7 +1239,15 @@ static void launch_gemm(www_model* m, GemmP& p, int MT, hipStream_t st) {
   // between the wavefront halves costs them as much as it saves, so they stay at KH = 1.
   constexpr int kh4 = EPI == EPI_SWIGLU ? 2 : 1;
   if (m->int4_group) {
-    if (mtk == 1) LAUNCH(1, WMODE_INT4, 1) else if (mtk == 2) LAUNCH(2, WMODE_INT4, 1) else LAUNCH(4, WMODE_INT4, 1)
+    // unpacking the codes takes longer than the weight stream, so from 17 tokens on two wavefronts per SIMD share it (8B shape,
+    // gate/up at 30 tokens 31.8 -> 29.8 us, at 60 47.7 -> 42.4; QKV and the residual GEMMs 1 - 3 us at 60 - 100).  Not with up to
+    // 16 tokens (each chunk is then over before the next has arrived: 23.8 -> 31.0 us), not in the output head (145 -> 166)
+    // and not in the gate/up GEMM with two token groups side by side (70 -> 80)
+    constexpr int ki = EPI == EPI_LOGITS ? 1 : 2;
+    if (mtk == 1) LAUNCH(1, WMODE_INT4, 1)
+    else if (mtk == 2) LAUNCH(2, WMODE_INT4, ki)
+    else if (EPI == EPI_SWIGLU && zb > 1) LAUNCH(4, WMODE_INT4, 1)
+    else LAUNCH(4, WMODE_INT4, ki)
   } else if (m->fp8) {
     if (mtk == 1) LAUNCH(1, WMODE_FP8, 1) else if (mtk == 2) LAUNCH(2, WMODE_FP8, 1) else if (mtk == 4) LAUNCH(4, WMODE_FP8, kh4) else LAUNCH8(WMODE_FP8)
   } else if (m->wsplit) {

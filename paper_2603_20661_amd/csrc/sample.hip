@@ -11,6 +11,10 @@
 // bin's elements (one to three per cent of a row) are looked at individually.  All masses are integers - units of 2^-44 of
 // a power of two at the largest score, so every fp32 probability above 2^-20 enters with all its bits - and integer sums
 // do not depend on their order: a call is reproducible although the bins are filled with LDS atomics.
+// Probabilities are formed from the difference to the largest logit of the row or chunk, never from the score itself, which
+// is as large as the temperature is small.  The bins take the score as it is, rounded and clamped: all they have to be is a
+// monotone function of the logit alone, the same in every chunk.  Scores beyond 2^21 share bins, at worst all of a row,
+// whose members are then told apart by their logits like those of any other bin.
 //
 // A row is 501 KB at 128 256 tokens and one compute unit fetches some 120 GB/s, so one workgroup per row is bound by its
 // compute unit's loads and exponentials whatever it does (the 33 passes of the bisection that stood here: 849 us for 64
@@ -26,6 +30,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <cfloat>
 #include <mutex>
 
 #include "../../include/www.h"
@@ -39,7 +44,7 @@ namespace {
 constexpr int BINS = 256, BINS_PER_OCTAVE_LOG2 = 3;
 constexpr int SUB = 8192;            // elements a workgroup of 256 threads holds in registers at a time
 constexpr int MAX_CHUNKS = 1024;     // chunks of a row (longer rows take longer chunks)
-constexpr int HEAD = 2 + 2 * BINS;   // start of a chunk's scratch: largest bin, candidates found, bin masses (low words, high words)
+constexpr int HEAD = 2 + 2 * BINS;   // start of a chunk's scratch: largest logit, candidates found, bin masses (low words, high words)
 constexpr int CAND_MAX = 510;        // room for a chunk's candidates behind that
 constexpr int RESERVED = HEAD + CAND_MAX;
 constexpr int ROW_CAND = 8192;       // candidates of a row that are looked at in LDS
@@ -48,13 +53,23 @@ constexpr int WAVES = TPB / 64;
 
 typedef unsigned long long u64;
 
-// bin of a score, clamped far outside the range of finite scores (NaN falls to the bottom)
+// bin of a score, clamped far outside the range of ordinary scores (NaN falls to the bottom)
 __device__ __forceinline__ int bin_of(float t) {
   return (int)floorf(fminf(fmaxf(t * (float)(1 << BINS_PER_OCTAVE_LOG2), -536870912.f), 536870912.f));
 }
-// power of two above every probability of a row or chunk whose largest score lies in bin `top`
-__device__ __forceinline__ int ref_of(int top) { return (top >> BINS_PER_OCTAVE_LOG2) + 1; }
-__device__ __forceinline__ float prob(float logit, float c, int ref) { return __builtin_amdgcn_exp2f(__builtin_fmaf(logit, c, -(float)ref)); }
+// number of a bin, counted down from bin `top`; the last one takes everything below
+__device__ __forceinline__ int bin_number(int top, int bin) { return min(BINS - 1, max(0, top - bin)); }
+// Reference of the masses of a row or chunk with largest logit m (made finite, so that differences to it are numbers):
+// 2^oct lies at most one octave above the largest probability, and r (-1 .. 0) is the way down from there.  Octaves are whole
+// numbers, in double because a score may exceed any integer, so that masses of different chunks differ by shifts.
+__device__ __forceinline__ float finite(float m) { return fminf(fmaxf(m, -FLT_MAX), FLT_MAX); }
+__device__ __forceinline__ double octave_of(float m, float c) { return floor((double)m * (double)c) + 1.; }
+__device__ __forceinline__ float way_down(float m, float c) { return (float)((double)m * (double)c - octave_of(m, c)); }
+__device__ __forceinline__ int octaves_between(double row, double chunk) { return (int)fmin(row - chunk, 64.); }
+// 2^(r + score - largest score), in [0, 1] (+inf: as FLT_MAX; NaN: 0)
+__device__ __forceinline__ float prob(float logit, float c, float m, float r) {
+  return __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(__builtin_fmaf(logit - m, c, r)), 0.f, 1.f);
+}
 // e in [0, 1] in units of 2^-44
 __device__ __forceinline__ u64 mass_of(float e) {
   const float s = e * 1048576.f;
@@ -146,7 +161,7 @@ __device__ uint32_t find_tau(const uint32_t* keys, const u64* mass, int n, doubl
 // The token: the first member (key >= tau) among elements [0, n) of x whose running mass exceeds `target`.  Each thread
 // takes a contiguous run, so that the running masses of the threads follow index order.  All threads of the workgroup
 // call it; `base` is added to the index.
-__device__ void pick(const float* x, int n, float c, int ref, uint32_t tau, u64 target, int base, u64* wave_tot, int32_t* token) {
+__device__ void pick(const float* x, int n, float c, float m, float r, uint32_t tau, u64 target, int base, u64* wave_tot, int32_t* token) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int per = (n + TPB - 1) / TPB;
   const int i0 = min(tid * per, n), i1 = min(i0 + per, n);
@@ -154,7 +169,7 @@ __device__ void pick(const float* x, int n, float c, int ref, uint32_t tau, u64 
 #pragma unroll 8
   for (int i = i0; i < i1; ++i) {
     const float v = x[i];
-    mine += key_of(v) >= tau ? mass_of(prob(v, c, ref)) : 0ull;
+    mine += key_of(v) >= tau ? mass_of(prob(v, c, m, r)) : 0ull;
   }
   const u64 incl = wave_scan(mine);
   if (lane == 63) wave_tot[wave] = incl;
@@ -167,7 +182,7 @@ __device__ void pick(const float* x, int n, float c, int ref, uint32_t tau, u64 
     int at = i0;
     for (int i = i0; i < i1; ++i) {
       const float v = x[i];
-      if (key_of(v) >= tau) run += mass_of(prob(v, c, ref));
+      if (key_of(v) >= tau) run += mass_of(prob(v, c, m, r));
       if (target < run) { at = i; break; }
     }
     *token = base + at;
@@ -210,15 +225,16 @@ __global__ __launch_bounds__(TPB) void sample_row_kernel(const float* __restrict
   }
   if (tid < BINS) S.hist[tid] = 0;
   if (tid == 0) S.count = 0;
-  const int top = bin_of(block_max<TPB>(m, S.red) * c), ref = ref_of(top);
+  m = finite(block_max<TPB>(m, S.red));
+  const int top = bin_of(m * c);
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
     const int i = k * TPB + tid;
     if (i < V) {
-      const float e = prob(x[k], c, ref);
+      const float e = prob(x[k], c, m, 0.f);
       scratch[(int64_t)row * V + i] = e;
       const u64 w = mass_of(e);
-      if (w) atomicAdd(&S.hist[min(BINS - 1, top - bin_of(x[k] * c))], w);
+      if (w) atomicAdd(&S.hist[bin_number(top, bin_of(x[k] * c))], w);
     }
   }
   __syncthreads();
@@ -227,10 +243,10 @@ __global__ __launch_bounds__(TPB) void sample_row_kernel(const float* __restrict
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
     const int i = k * TPB + tid;
-    if (i < V && min(BINS - 1, top - bin_of(x[k] * c)) == S.bin) {
+    if (i < V && bin_number(top, bin_of(x[k] * c)) == S.bin) {
       const int at = atomicAdd(&S.count, 1);
       S.keys[at] = key_of(x[k]);
-      S.mass[at] = mass_of(prob(x[k], c, ref));
+      S.mass[at] = mass_of(prob(x[k], c, m, 0.f));
     }
   }
   __syncthreads();
@@ -239,7 +255,7 @@ __global__ __launch_bounds__(TPB) void sample_row_kernel(const float* __restrict
   u64 mine = 0;
 #pragma unroll
   for (int k = 0; k < PER; ++k)
-    if (k * TPB + tid < V && key_of(x[k]) >= tau) mine += mass_of(prob(x[k], c, ref));
+    if (k * TPB + tid < V && key_of(x[k]) >= tau) mine += mass_of(prob(x[k], c, m, 0.f));
   mine = wave_sum(mine);
   if ((tid & 63) == 0) S.wave_tot[tid >> 6] = mine;
   __syncthreads();
@@ -247,11 +263,11 @@ __global__ __launch_bounds__(TPB) void sample_row_kernel(const float* __restrict
 #pragma unroll
   for (int w = 0; w < WAVES; ++w) nucleus += S.wave_tot[w];
   __syncthreads();
-  if (nucleus) pick(lg, V, c, ref, tau, draw_target(u01[row], nucleus), 0, S.wave_tot, tokens + row);
+  if (nucleus) pick(lg, V, c, m, 0.f, tau, draw_target(u01[row], nucleus), 0, S.wave_tot, tokens + row);
   else if (tid == 0) tokens[row] = 0;  // (a row without any finite logit)
 }
 
-// ---- longer rows, first launch: largest score and bin masses of every chunk
+// ---- longer rows, first launch: largest logit and bin masses of every chunk
 __global__ __launch_bounds__(256) void sample_bins_kernel(const float* __restrict__ logits, int V, int chunk, float c, float* __restrict__ scratch) {
   constexpr int COPIES = 16;  // of the bins, by lane, so that the lanes of a wavefront seldom meet in one
   __shared__ u64 hist[BINS * COPIES];
@@ -274,13 +290,15 @@ __global__ __launch_bounds__(256) void sample_bins_kernel(const float* __restric
   }
 #pragma unroll
   for (int k = 0; k < COPIES; ++k) hist[k * 256 + tid] = 0;
-  const int top = bin_of(block_max<256>(m, red) * c), ref = ref_of(top);
+  m = finite(block_max<256>(m, red));
+  const int top = bin_of(m * c);
+  const float r = way_down(m, c);
   for (int base = 0; base < n; base += SUB) {
     if (n > SUB) load(base);
 #pragma unroll
     for (int k = 0; k < SUB / 256; ++k) {
-      const u64 w = mass_of(prob(x[k], c, ref));  // (0 for the -inf behind the end)
-      if (w) atomicAdd(&hist[min(BINS - 1, top - bin_of(x[k] * c)) * COPIES + (tid & (COPIES - 1))], w);
+      const u64 w = mass_of(prob(x[k], c, m, r));  // (0 for the -inf behind the end)
+      if (w) atomicAdd(&hist[bin_number(top, bin_of(x[k] * c)) * COPIES + (tid & (COPIES - 1))], w);
     }
   }
   __syncthreads();
@@ -290,16 +308,16 @@ __global__ __launch_bounds__(256) void sample_bins_kernel(const float* __restric
   float* region = scratch + (int64_t)blockIdx.x * V + first;
   region[2 + tid] = __uint_as_float((uint32_t)s);
   region[2 + BINS + tid] = __uint_as_float((uint32_t)(s >> 32));
-  if (tid == 0) region[0] = __int_as_float(top);
+  if (tid == 0) region[0] = m;
 }
 
-// Largest bin of a row, from its chunks' headers (called by every thread, the same value everywhere).
-__device__ __forceinline__ int row_top(const float* row, int chunk, int n_chunks) {
-  int top = -0x7fffffff;
-  for (int k = threadIdx.x & 63; k < n_chunks; k += 64) top = max(top, __float_as_int(row[(int64_t)k * chunk]));
+// Largest logit of a row, from its chunks' headers (called by every thread, the same value everywhere).
+__device__ __forceinline__ float row_max(const float* row, int chunk, int n_chunks) {
+  float m = -FLT_MAX;
+  for (int k = threadIdx.x & 63; k < n_chunks; k += 64) m = fmaxf(m, row[(int64_t)k * chunk]);
 #pragma unroll
-  for (int s = 32; s >= 1; s >>= 1) top = max(top, __shfl_xor(top, s));
-  return top;
+  for (int s = 32; s >= 1; s >>= 1) m = fmaxf(m, __shfl_xor(m, s));
+  return m;
 }
 __device__ __forceinline__ u64 chunk_bin(const float* region, int bin) {
   return ((u64)__float_as_uint(region[2 + BINS + bin]) << 32) | __float_as_uint(region[2 + bin]);
@@ -333,16 +351,18 @@ __global__ __launch_bounds__(256) void sample_split_kernel(const float* __restri
     for (int k = 0; k < NB; ++k) w[k] = chunk_bin(row + (int64_t)min(k0 + k, n_chunks - 1) * chunk, tid);
   };
   load_bins(0);
-  const int top = row_top(row, chunk, n_chunks), ref = ref_of(top);
+  const float m = row_max(row, chunk, n_chunks);
+  const int top = bin_of(m * c);
+  const double oct = octave_of(m, c);
   __syncthreads();
   for (int k0 = 0; k0 < n_chunks; k0 += NB) {
     if (k0) load_bins(k0);
-    const int mine = __float_as_int(row[(int64_t)min(k0 + (tid & 63), n_chunks - 1) * chunk]);
+    const float mc = row[(int64_t)min(k0 + (tid & 63), n_chunks - 1) * chunk];  // lane k: chunk k0 + k
+    const int down = top - bin_of(mc * c), back = octaves_between(oct, octave_of(mc, c));
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
-      const int t = __builtin_amdgcn_readlane(mine, k);
-      const u64 v = k0 + k < n_chunks ? shifted(w[k], ref_of(top) - ref_of(t)) : 0ull;
-      if (v) atomicAdd(&hist[min(BINS - 1, tid + (top - t))], v);
+      const u64 v = k0 + k < n_chunks ? shifted(w[k], __builtin_amdgcn_readlane(back, k)) : 0ull;
+      if (v) atomicAdd(&hist[min(BINS - 1, tid + __builtin_amdgcn_readlane(down, k))], v);
     }
   }
   __syncthreads();
@@ -354,8 +374,8 @@ __global__ __launch_bounds__(256) void sample_split_kernel(const float* __restri
 #pragma unroll
     for (int k = 0; k < SUB / 256; ++k) {
       const int i = base + k * 256 + tid;
-      if (i >= RESERVED && i < n) region[i] = prob(x[k], c, ref);
-      const bool cand = i < n && min(BINS - 1, top - bin_of(x[k] * c)) == b;
+      if (i >= RESERVED && i < n) region[i] = prob(x[k], c, m, 0.f);
+      const bool cand = i < n && bin_number(top, bin_of(x[k] * c)) == b;
       const u64 who = __ballot(cand);
       if (who) {  // one LDS addition per wavefront; the order of the list does not matter
         const int lane = tid & 63, leader = __ffsll((long long)who) - 1;
@@ -424,17 +444,20 @@ __global__ __launch_bounds__(TPB) void sample_pick_kernel(const float* __restric
     over = __any(over) || at > ROW_CAND;
     if (lane == 0) { S.n_cand = at; S.overflow = over; }
   }
-  const int top = row_top(row, chunk, n_chunks), ref = ref_of(top);
+  const float m = row_max(row, chunk, n_chunks);
+  const int top = bin_of(m * c);
+  const double oct = octave_of(m, c);
   __syncthreads();
   const bool listed = !S.overflow;
   uint32_t klo = 0xFFFFFFFFu, khi = 0u;
   for (int k = wave; k < n_chunks; k += WAVES) {
     const float* region = row + (int64_t)k * chunk;
-    const int t = __float_as_int(region[0]), back = ref_of(top) - ref_of(t);
+    const float mc = region[0], r = way_down(mc, c);
+    const int down = top - bin_of(mc * c), back = octaves_between(oct, octave_of(mc, c));
 #pragma unroll
     for (int i = 0; i < BINS / 64; ++i) {
       const u64 v = shifted(k == wave ? hb[i] : chunk_bin(region, i * 64 + lane), back);
-      if (v) atomicAdd(&S.hist[min(BINS - 1, i * 64 + lane + (top - t))], v);
+      if (v) atomicAdd(&S.hist[min(BINS - 1, i * 64 + lane + down)], v);
     }
     if (listed) {
       const int at = S.chunk_at[k], cnt = __float_as_int(region[1]);
@@ -442,7 +465,7 @@ __global__ __launch_bounds__(TPB) void sample_pick_kernel(const float* __restric
         const float v = region[HEAD + i];
         const uint32_t key = key_of(v);
         S.keys[at + i] = key;
-        S.mass[at + i] = shifted(mass_of(prob(v, c, ref_of(t))), back);
+        S.mass[at + i] = shifted(mass_of(prob(v, c, mc, r)), back);
         klo = min(klo, key);
         khi = max(khi, key);
       }
@@ -468,19 +491,21 @@ __global__ __launch_bounds__(TPB) void sample_pick_kernel(const float* __restric
   } else {
     // The bin holds more elements than the lists (a row that is flat to within a tenth of an octave): its keys are binned
     // again, 256 linear bins at a time, until one key is left; three or four passes over the row.
-    auto members = [&](auto&& use) __attribute__((always_inline)) {  // use(key, logit, chunk reference) of every member of bin b
+    auto members = [&](auto&& use) __attribute__((always_inline)) {  // use(key, mass) of every member of bin b
       for (int k = wave; k < n_chunks; k += WAVES) {
         const int64_t f = (int64_t)k * chunk;
-        const int n = min(chunk, (int)(V - f)), rc = ref_of(__float_as_int(row[f]));
+        const int n = min(chunk, (int)(V - f));
+        const float mc = row[f], r = way_down(mc, c);
+        const int back = octaves_between(oct, octave_of(mc, c));
 #pragma unroll 8
         for (int i = lane; i < n; i += 64) {
           const float v = lg[f + i];
-          if (min(BINS - 1, top - bin_of(v * c)) == b) use(key_of(v), v, rc);
+          if (bin_number(top, bin_of(v * c)) == b) use(key_of(v), [&] { return shifted(mass_of(prob(v, c, mc, r)), back); });
         }
       }
     };
     uint32_t lo = 0xFFFFFFFFu, last = 0u;
-    members([&](uint32_t key, float, int) { lo = min(lo, key); last = max(last, key); });
+    members([&](uint32_t key, auto&&) { lo = min(lo, key); last = max(last, key); });
 #pragma unroll
     for (int s = 32; s >= 1; s >>= 1) {
       lo = min(lo, (uint32_t)__shfl_xor((int)lo, s));
@@ -496,9 +521,9 @@ __global__ __launch_bounds__(TPB) void sample_pick_kernel(const float* __restric
       const int shift = max(0, 24 - __clz(last - lo));  // (last - lo) >> shift < 256
       for (int i = tid; i < BINS * COPIES; i += TPB) copies[i] = 0;
       __syncthreads();
-      members([&](uint32_t key, float v, int rc) {
+      members([&](uint32_t key, auto&& mass) {
         if (key < lo || key > last) return;
-        const u64 w = shifted(mass_of(prob(v, c, rc)), ref_of(top) - rc);
+        const u64 w = mass();
         if (w) atomicAdd(&copies[(BINS - 1 - ((key - lo) >> shift)) * COPIES + (tid & (COPIES - 1))], w);
       });
       __syncthreads();
@@ -521,11 +546,12 @@ __global__ __launch_bounds__(TPB) void sample_pick_kernel(const float* __restric
   // mass of the nucleus in every chunk, in units of the row's reference
   for (int k = wave; k < n_chunks; k += WAVES) {
     const float* region = row + (int64_t)k * chunk;
-    const int t = __float_as_int(region[0]), back = ref_of(top) - ref_of(t);
+    const float mc = region[0], r = way_down(mc, c);
+    const int down = top - bin_of(mc * c), back = octaves_between(oct, octave_of(mc, c));
     u64 s = 0;
 #pragma unroll
     for (int i = 0; i < BINS / 64; ++i)
-      if (min(BINS - 1, i * 64 + lane + (top - t)) < b) s += k == wave ? hb[i] : chunk_bin(region, i * 64 + lane);
+      if (min(BINS - 1, i * 64 + lane + down) < b) s += k == wave ? hb[i] : chunk_bin(region, i * 64 + lane);
     s = shifted(wave_sum(s), back);
     u64 q = 0;
     if (listed) {
@@ -537,7 +563,7 @@ __global__ __launch_bounds__(TPB) void sample_pick_kernel(const float* __restric
 #pragma unroll 8
       for (int i = lane; i < n; i += 64) {
         const float v = lg[f + i];
-        if (key_of(v) >= tau && min(BINS - 1, top - bin_of(v * c)) == b) q += shifted(mass_of(prob(v, c, ref_of(t))), back);
+        if (key_of(v) >= tau && bin_number(top, bin_of(v * c)) == b) q += shifted(mass_of(prob(v, c, mc, r)), back);
       }
     }
     q = wave_sum(q);
@@ -566,15 +592,16 @@ __global__ __launch_bounds__(TPB) void sample_pick_kernel(const float* __restric
   __syncthreads();
   if (S.chunk >= 0) {
     const int64_t f = (int64_t)S.chunk * chunk;
-    const int t = __float_as_int(row[f]);
+    const float mc = row[f];
     // the running mass inside the chunk is counted in the chunk's own units, in which it is at least what was counted above
-    pick(lg + f, min(chunk, (int)(V - f)), c, ref_of(t), tau, S.target << (ref_of(top) - ref_of(t)), (int)f, S.wave_tot, tokens + blockIdx.x);
+    pick(lg + f, min(chunk, (int)(V - f)), c, mc, way_down(mc, c), tau, S.target << octaves_between(oct, octave_of(mc, c)), (int)f, S.wave_tot,
+         tokens + blockIdx.x);
   }
   __syncthreads();  // the headers are no longer needed
   for (int k = wave; k < n_chunks; k += WAVES) {
     const int64_t f = (int64_t)k * chunk;
 #pragma unroll
-    for (int i = 0; i < HREG; ++i) row[f + i * 64 + lane] = prob(k == wave ? hx[i] : lg[f + i * 64 + lane], c, ref);
+    for (int i = 0; i < HREG; ++i) row[f + i * 64 + lane] = prob(k == wave ? hx[i] : lg[f + i * 64 + lane], c, m, 0.f);
   }
 }
 
@@ -616,7 +643,7 @@ WWW_EXPORT int www_sample_top_p(const float* logits_dev, int32_t batch, int32_t 
   if (batch == 0) return WWW_OK;
   if (!logits_dev || !u01_dev || !scratch_dev || !tokens_dev) { set_error("NULL pointer argument"); return WWW_E_INVALID_ARG; }
   const hipStream_t st = (hipStream_t)hip_stream;
-  const float c = 1.4426950408889634f / temperature;
+  const float c = std::min(1.4426950408889634f / temperature, FLT_MAX);  // (finite: no 0 * inf at the largest logit)
   if (int rc = allow_lds()) return rc;
   if (vocab <= SUB) {
     hipLaunchKernelGGL(sample_row_kernel, dim3(batch), dim3(TPB), sizeof(SmallLds), st, logits_dev, vocab, c, top_p, u01_dev, scratch_dev,

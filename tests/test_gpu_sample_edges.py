@@ -1,0 +1,75 @@
+"""GPU: sampling where the scores leave the ordinary range: temperatures at which log2(e) * logit / T exceeds any table of
+scores (nearly greedy draws), rows that lie far below zero (every token masked with a finite value).  Checked against the
+fp64 oracle: the token is a nucleus member, the draw falls into its interval of the running mass, and the scratch buffer
+holds the probabilities up to one factor per row.
+
+Bound: a probability is 2^a with a = (x - max) * log2(e) / T; the difference, the factor and the product are each rounded to
+fp32 (2^-24 relative), so a is off by at most 3 * 2^-24 * |a| and 2^a by 1.3e-7 * |a| of itself, which is at most 7e-8 of the
+largest probability.  A running mass of members down to 2^-44 is then off by less than 6e-6 of the total; 1e-5 is allowed."""
+import numpy as np
+import pytest
+
+from oracle import sample as S
+from paper_2603_20661_amd import synth
+from test_gpu_sample_sizes import run
+
+pytestmark = pytest.mark.gpu
+
+BOUND = 1e-5
+ROW, CHUNKS = 1000, 20011      # a row of one workgroup, and one that is cut into chunks
+
+
+def check(lg, temperature, top_p, u):
+    T = float(np.float32(temperature))
+    tok, e_gpu = run(lg, temperature, top_p, u)
+    for b in range(len(lg)):
+        want, e, mask, cum, target = S.sample(lg[b], T, top_p, float(u[b]))
+        t = int(tok[b])
+        assert 0 <= t < lg.shape[1]
+        assert e[t] >= e[mask].min() * (1 - BOUND), f"row {b}: token {t} outside the nucleus (oracle's {want})"
+        before, eps = cum[t] - (e[t] if mask[t] else 0.0), BOUND * cum[-1]
+        assert before - eps <= target <= cum[t] + eps, f"row {b}: token {t}, oracle's {want}"
+        ratio = e_gpu[b].astype(np.float64) / e_gpu[b].max()
+        assert np.abs(ratio - e).max() <= BOUND, f"row {b}: scratch is not the unnormalised probabilities"
+    return tok
+
+
+U = np.array([0.0, 0.3, 0.6, 0.999], np.float32)
+
+
+@pytest.mark.parametrize("vocab", [ROW, 8192, 8193, CHUNKS, 128256])
+@pytest.mark.parametrize("temperature", [1e-3, 1e-6, 1e-7, 1e-8, 1e-20, 1e-39])
+def test_low_temperatures(vocab, temperature):
+    lg = synth.normal_f32(84, vocab, 4 * vocab, std=3.0).reshape(4, vocab).copy()
+    lg[1] = np.abs(lg[1]) + 0.5                  # positive only
+    lg[2] = -np.abs(lg[2]) - 0.5                 # negative only
+    lg[3, [5, vocab - 3]] = lg[3].max() + 1.0    # two equal ones at the top
+    tok = check(lg, temperature, 0.9, U)
+    if temperature < 1e-6:
+        assert [int(t) for t in tok[:3]] == [int(r.argmax()) for r in lg[:3]]
+        assert tok[3] == vocab - 3
+
+
+@pytest.mark.parametrize("vocab", [ROW, CHUNKS])
+@pytest.mark.parametrize("value", [-1e8, -1e9, -3e38, np.finfo(np.float32).min], ids=str)
+def test_rows_far_below_zero(vocab, value):
+    """equal masked tokens: a uniform draw, as over any row of equal logits; and one token a little above the others"""
+    lg = np.full((4, vocab), value, np.float32)
+    lg[2, vocab - 2] *= np.float32(0.5)
+    lg[3, ::3] = -np.inf
+    tok = check(lg, 1.0, 0.9, U)
+    assert tok[0] == 0 and tok[2] == vocab - 2
+    assert abs(int(tok[1]) - 0.3 * vocab) <= 2
+
+
+@pytest.mark.parametrize("vocab", [ROW, CHUNKS])
+def test_infinite_and_unordered_logits(vocab):
+    """+inf is the certain token (two of them: one of the two); a NaN is never drawn"""
+    lg = synth.normal_f32(85, vocab, 4 * vocab, std=3.0).reshape(4, vocab).copy()
+    lg[0, vocab - 5] = np.inf
+    lg[1, [3, vocab - 5]] = np.inf
+    lg[2, 1:] = np.nan
+    lg[3, ::2] = np.nan
+    tok, e = run(lg, 1.0, 0.9, np.array([0.999, 0.6, 0.5, 0.5], np.float32))
+    assert tok[0] == vocab - 5 and tok[1] == vocab - 5 and tok[2] == 0 and tok[3] % 2 == 1
+    assert not np.isnan(e).any()

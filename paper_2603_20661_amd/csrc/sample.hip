@@ -10,7 +10,8 @@
 // an octave below the largest one, with the mass of each bin; the bins alone tell which one holds tau, and only that
 // bin's elements (one to three per cent of a row) are looked at individually.  All masses are integers - units of 2^-44 of
 // a power of two at the largest score, so every fp32 probability above 2^-20 enters with all its bits - and integer sums
-// do not depend on their order: a call is reproducible although the bins are filled with LDS atomics.
+// do not depend on their order: a call is reproducible although the bins are filled with LDS atomics.  Rows of more than
+// 2^19 tokens take a unit twice as large per doubling (mass_unit), so that the masses of a row add up to 2^63 at most.
 // Probabilities are formed from the difference to the largest logit of the row or chunk, never from the score itself, which
 // is as large as the temperature is small.  The bins take the score as it is, rounded and clamped: all they have to be is a
 // monotone function of the logit alone, the same in every chunk.  Scores beyond 2^21 share bins, at worst all of a row,
@@ -70,9 +71,9 @@ __device__ __forceinline__ int octaves_between(double row, double chunk) { retur
 __device__ __forceinline__ float prob(float logit, float c, float m, float r) {
   return __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(__builtin_fmaf(logit - m, c, r)), 0.f, 1.f);
 }
-// e in [0, 1] in units of 2^-44
-__device__ __forceinline__ u64 mass_of(float e) {
-  const float s = e * 1048576.f;
+// e in [0, 1] in units of 2^-24 / unit
+__device__ __forceinline__ u64 mass_of(float e, float unit) {
+  const float s = e * unit;
   const uint32_t hi = (uint32_t)s;
   const uint32_t lo = (uint32_t)((s - (float)hi) * 16777216.f);
   return ((u64)hi << 24) + lo;
@@ -161,7 +162,7 @@ __device__ uint32_t find_tau(const uint32_t* keys, const u64* mass, int n, doubl
 // The token: the first member (key >= tau) among elements [0, n) of x whose running mass exceeds `target`.  Each thread
 // takes a contiguous run, so that the running masses of the threads follow index order.  All threads of the workgroup
 // call it; `base` is added to the index.
-__device__ void pick(const float* x, int n, float c, float m, float r, uint32_t tau, u64 target, int base, u64* wave_tot, int32_t* token) {
+__device__ void pick(const float* x, int n, float c, float m, float r, float unit, uint32_t tau, u64 target, int base, u64* wave_tot, int32_t* token) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int per = (n + TPB - 1) / TPB;
   const int i0 = min(tid * per, n), i1 = min(i0 + per, n);
@@ -169,7 +170,7 @@ __device__ void pick(const float* x, int n, float c, float m, float r, uint32_t 
 #pragma unroll 8
   for (int i = i0; i < i1; ++i) {
     const float v = x[i];
-    mine += key_of(v) >= tau ? mass_of(prob(v, c, m, r)) : 0ull;
+    mine += key_of(v) >= tau ? mass_of(prob(v, c, m, r), unit) : 0ull;
   }
   const u64 incl = wave_scan(mine);
   if (lane == 63) wave_tot[wave] = incl;
@@ -182,7 +183,7 @@ __device__ void pick(const float* x, int n, float c, float m, float r, uint32_t 
     int at = i0;
     for (int i = i0; i < i1; ++i) {
       const float v = x[i];
-      if (key_of(v) >= tau) run += mass_of(prob(v, c, m, r));
+      if (key_of(v) >= tau) run += mass_of(prob(v, c, m, r), unit);
       if (target < run) { at = i; break; }
     }
     *token = base + at;
@@ -207,7 +208,7 @@ struct SmallLds {
   int bin, count;
 };
 
-__global__ __launch_bounds__(TPB) void sample_row_kernel(const float* __restrict__ logits, int V, float c, float top_p,
+__global__ __launch_bounds__(TPB) void sample_row_kernel(const float* __restrict__ logits, int V, float c, float unit, float top_p,
                                                          const float* __restrict__ u01, float* __restrict__ scratch,
                                                          int32_t* __restrict__ tokens) {
   extern __shared__ __align__(16) char smem[];
@@ -233,7 +234,7 @@ __global__ __launch_bounds__(TPB) void sample_row_kernel(const float* __restrict
     if (i < V) {
       const float e = prob(x[k], c, m, 0.f);
       scratch[(int64_t)row * V + i] = e;
-      const u64 w = mass_of(e);
+      const u64 w = mass_of(e, unit);
       if (w) atomicAdd(&S.hist[bin_number(top, bin_of(x[k] * c))], w);
     }
   }
@@ -246,7 +247,7 @@ __global__ __launch_bounds__(TPB) void sample_row_kernel(const float* __restrict
     if (i < V && bin_number(top, bin_of(x[k] * c)) == S.bin) {
       const int at = atomicAdd(&S.count, 1);
       S.keys[at] = key_of(x[k]);
-      S.mass[at] = mass_of(prob(x[k], c, m, 0.f));
+      S.mass[at] = mass_of(prob(x[k], c, m, 0.f), unit);
     }
   }
   __syncthreads();
@@ -255,7 +256,7 @@ __global__ __launch_bounds__(TPB) void sample_row_kernel(const float* __restrict
   u64 mine = 0;
 #pragma unroll
   for (int k = 0; k < PER; ++k)
-    if (k * TPB + tid < V && key_of(x[k]) >= tau) mine += mass_of(prob(x[k], c, m, 0.f));
+    if (k * TPB + tid < V && key_of(x[k]) >= tau) mine += mass_of(prob(x[k], c, m, 0.f), unit);
   mine = wave_sum(mine);
   if ((tid & 63) == 0) S.wave_tot[tid >> 6] = mine;
   __syncthreads();
@@ -263,12 +264,12 @@ __global__ __launch_bounds__(TPB) void sample_row_kernel(const float* __restrict
 #pragma unroll
   for (int w = 0; w < WAVES; ++w) nucleus += S.wave_tot[w];
   __syncthreads();
-  if (nucleus) pick(lg, V, c, m, 0.f, tau, draw_target(u01[row], nucleus), 0, S.wave_tot, tokens + row);
+  if (nucleus) pick(lg, V, c, m, 0.f, unit, tau, draw_target(u01[row], nucleus), 0, S.wave_tot, tokens + row);
   else if (tid == 0) tokens[row] = 0;  // (a row without any finite logit)
 }
 
 // ---- longer rows, first launch: largest logit and bin masses of every chunk
-__global__ __launch_bounds__(256) void sample_bins_kernel(const float* __restrict__ logits, int V, int chunk, float c, float* __restrict__ scratch) {
+__global__ __launch_bounds__(256) void sample_bins_kernel(const float* __restrict__ logits, int V, int chunk, float c, float unit, float* __restrict__ scratch) {
   constexpr int COPIES = 16;  // of the bins, by lane, so that the lanes of a wavefront seldom meet in one
   __shared__ u64 hist[BINS * COPIES];
   __shared__ float red[4];
@@ -297,7 +298,7 @@ __global__ __launch_bounds__(256) void sample_bins_kernel(const float* __restric
     if (n > SUB) load(base);
 #pragma unroll
     for (int k = 0; k < SUB / 256; ++k) {
-      const u64 w = mass_of(prob(x[k], c, m, r));  // (0 for the -inf behind the end)
+      const u64 w = mass_of(prob(x[k], c, m, r), unit);  // (0 for the -inf behind the end)
       if (w) atomicAdd(&hist[bin_number(top, bin_of(x[k] * c)) * COPIES + (tid & (COPIES - 1))], w);
     }
   }
@@ -405,7 +406,7 @@ struct PickLds {
   int bin, n_cand, overflow, chunk;
 };
 
-__global__ __launch_bounds__(TPB) void sample_pick_kernel(const float* __restrict__ logits, int V, int chunk, int n_chunks, float c, float top_p,
+__global__ __launch_bounds__(TPB) void sample_pick_kernel(const float* __restrict__ logits, int V, int chunk, int n_chunks, float c, float unit, float top_p,
                                                           const float* __restrict__ u01, float* scratch, int32_t* __restrict__ tokens) {
   extern __shared__ __align__(16) char smem[];
   PickLds& S = *reinterpret_cast<PickLds*>(smem);
@@ -465,7 +466,7 @@ __global__ __launch_bounds__(TPB) void sample_pick_kernel(const float* __restric
         const float v = region[HEAD + i];
         const uint32_t key = key_of(v);
         S.keys[at + i] = key;
-        S.mass[at + i] = shifted(mass_of(prob(v, c, mc, r)), back);
+        S.mass[at + i] = shifted(mass_of(prob(v, c, mc, r), unit), back);
         klo = min(klo, key);
         khi = max(khi, key);
       }
@@ -500,7 +501,7 @@ __global__ __launch_bounds__(TPB) void sample_pick_kernel(const float* __restric
 #pragma unroll 8
         for (int i = lane; i < n; i += 64) {
           const float v = lg[f + i];
-          if (bin_number(top, bin_of(v * c)) == b) use(key_of(v), [&] { return shifted(mass_of(prob(v, c, mc, r)), back); });
+          if (bin_number(top, bin_of(v * c)) == b) use(key_of(v), [&] { return shifted(mass_of(prob(v, c, mc, r), unit), back); });
         }
       }
     };
@@ -563,7 +564,7 @@ __global__ __launch_bounds__(TPB) void sample_pick_kernel(const float* __restric
 #pragma unroll 8
       for (int i = lane; i < n; i += 64) {
         const float v = lg[f + i];
-        if (key_of(v) >= tau && bin_number(top, bin_of(v * c)) == b) q += shifted(mass_of(prob(v, c, mc, r)), back);
+        if (key_of(v) >= tau && bin_number(top, bin_of(v * c)) == b) q += shifted(mass_of(prob(v, c, mc, r), unit), back);
       }
     }
     q = wave_sum(q);
@@ -594,7 +595,7 @@ __global__ __launch_bounds__(TPB) void sample_pick_kernel(const float* __restric
     const int64_t f = (int64_t)S.chunk * chunk;
     const float mc = row[f];
     // the running mass inside the chunk is counted in the chunk's own units, in which it is at least what was counted above
-    pick(lg + f, min(chunk, (int)(V - f)), c, mc, way_down(mc, c), tau, S.target << octaves_between(oct, octave_of(mc, c)), (int)f, S.wave_tot,
+    pick(lg + f, min(chunk, (int)(V - f)), c, mc, way_down(mc, c), unit, tau, S.target << octaves_between(oct, octave_of(mc, c)), (int)f, S.wave_tot,
          tokens + blockIdx.x);
   }
   __syncthreads();  // the headers are no longer needed
@@ -603,6 +604,13 @@ __global__ __launch_bounds__(TPB) void sample_pick_kernel(const float* __restric
 #pragma unroll
     for (int i = 0; i < HREG; ++i) row[f + i * 64 + lane] = prob(k == wave ? hx[i] : lg[f + i * 64 + lane], c, m, 0.f);
   }
+}
+
+// factor that turns a probability into the high part of its mass: 2^20, and half of that per doubling of the row beyond 2^19
+float mass_unit(int vocab) {
+  float unit = 1048576.f;
+  for (int64_t n = 1 << 19; n < vocab; n *= 2) unit *= 0.5f;
+  return unit;
 }
 
 constexpr int MAX_DEVICES = 64;
@@ -644,18 +652,19 @@ WWW_EXPORT int www_sample_top_p(const float* logits_dev, int32_t batch, int32_t 
   if (!logits_dev || !u01_dev || !scratch_dev || !tokens_dev) { set_error("NULL pointer argument"); return WWW_E_INVALID_ARG; }
   const hipStream_t st = (hipStream_t)hip_stream;
   const float c = std::min(1.4426950408889634f / temperature, FLT_MAX);  // (finite: no 0 * inf at the largest logit)
+  const float unit = mass_unit(vocab);
   if (int rc = allow_lds()) return rc;
   if (vocab <= SUB) {
-    hipLaunchKernelGGL(sample_row_kernel, dim3(batch), dim3(TPB), sizeof(SmallLds), st, logits_dev, vocab, c, top_p, u01_dev, scratch_dev,
+    hipLaunchKernelGGL(sample_row_kernel, dim3(batch), dim3(TPB), sizeof(SmallLds), st, logits_dev, vocab, c, unit, top_p, u01_dev, scratch_dev,
                        tokens_dev);
   } else {
     // chunks of equal length, 4097 .. 8192 tokens (longer only above 8 Mi tokens); the last one falls short of the others
     // by less than the number of chunks, so every chunk has room for its reserved head
     const int n_chunks = std::min((vocab + SUB - 1) / SUB, MAX_CHUNKS), chunk = (int)(((int64_t)vocab + n_chunks - 1) / n_chunks);
     const dim3 grid(batch, n_chunks);
-    hipLaunchKernelGGL(sample_bins_kernel, grid, dim3(256), 0, st, logits_dev, vocab, chunk, c, scratch_dev);
+    hipLaunchKernelGGL(sample_bins_kernel, grid, dim3(256), 0, st, logits_dev, vocab, chunk, c, unit, scratch_dev);
     hipLaunchKernelGGL(sample_split_kernel, grid, dim3(256), 0, st, logits_dev, vocab, chunk, c, top_p, scratch_dev);
-    hipLaunchKernelGGL(sample_pick_kernel, dim3(batch), dim3(TPB), sizeof(PickLds), st, logits_dev, vocab, chunk, n_chunks, c, top_p, u01_dev,
+    hipLaunchKernelGGL(sample_pick_kernel, dim3(batch), dim3(TPB), sizeof(PickLds), st, logits_dev, vocab, chunk, n_chunks, c, unit, top_p, u01_dev,
                        scratch_dev, tokens_dev);
   }
   const hipError_t err = hipGetLastError();

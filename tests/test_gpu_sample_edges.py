@@ -73,3 +73,14 @@ def test_infinite_and_unordered_logits(vocab):
     tok, e = run(lg, 1.0, 0.9, np.array([0.999, 0.6, 0.5, 0.5], np.float32))
     assert tok[0] == vocab - 5 and tok[1] == vocab - 5 and tok[2] == 0 and tok[3] % 2 == 1
     assert not np.isnan(e).any()
+
+
+@pytest.mark.parametrize("vocab", [1 << 19, (1 << 20) + 1, 1_800_000, 1 << 21, 9_000_001], ids=str)
+def test_long_flat_rows(vocab):
+    """every token near the largest: the masses of a row together are many times one token's.  The fp64 oracle's sums are
+    exact for equal tokens; the other row's are off by no more than its probabilities are."""
+    lg = np.zeros((3, vocab), np.float32)
+    lg[1] = 0.25
+    lg[2] = synth.normal_f32(86, vocab & 0xffff, vocab, std=1e-3)
+    tok = check(lg, 1.0, 0.9, np.array([0.999, 0.37, 0.62], np.float32))
+    assert abs(int(tok[0]) - 0.999 * vocab) <= 2e-5 * vocab

@@ -337,6 +337,7 @@ int www_get_stats(const www_sched* sched, www_stats* out);
  * rounding of a decision point.
  *   logits_dev fp32 [batch][vocab]; u01_dev fp32 [batch], the caller's uniform numbers in [0, 1);
  *   scratch_dev fp32 [batch][vocab], overwritten (unnormalised probabilities); tokens_dev int32 [batch].
+ *   scratch_dev may be logits_dev itself (slower for rows of more than 8192 tokens); otherwise the two may not overlap.
  * temperature > 0, 0 < top_p <= 1; batch == 0 is a no-op.  Errors: INVALID_ARG, HIP. */
 int www_sample_top_p(const float* logits_dev, int32_t batch, int32_t vocab, float temperature, float top_p, const float* u01_dev,
                      float* scratch_dev, int32_t* tokens_dev, void* hip_stream);

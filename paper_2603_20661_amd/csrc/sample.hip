@@ -159,6 +159,40 @@ __device__ uint32_t find_tau(const uint32_t* keys, const u64* mass, int n, doubl
   return lo;
 }
 
+// tau among the keys lo .. last: 256 linear bins a round until one key is left (four rounds at most).  members(use) calls
+// use(key, mass) for every element in question; share and want as for find_boundary.  `copies` holds COPIES sets of bins, by
+// lane, so that the lanes of a wavefront seldom meet in one.
+constexpr int COPIES = 16;
+template <typename M>
+__device__ uint32_t search_keys(M&& members, uint32_t lo, uint32_t last, float share, double want, u64* copies, u64* hist, int* bin, double* need) {
+  const int tid = threadIdx.x;
+  while (last > lo) {
+    const int shift = max(0, 24 - __clz(last - lo));  // (last - lo) >> shift < 256
+    for (int i = tid; i < BINS * COPIES; i += TPB) copies[i] = 0;
+    __syncthreads();
+    members([&](uint32_t key, auto&& mass) {
+      if (key < lo || key > last) return;
+      const u64 w = mass();
+      if (w) atomicAdd(&copies[(BINS - 1 - ((key - lo) >> shift)) * COPIES + (tid & (COPIES - 1))], w);
+    });
+    __syncthreads();
+    if (tid < BINS) {
+      u64 s = 0;
+#pragma unroll
+      for (int k = 0; k < COPIES; ++k) s += copies[tid * COPIES + ((k + tid) & (COPIES - 1))];
+      hist[tid] = s;
+    }
+    __syncthreads();
+    if (tid < 64) find_boundary(hist, share, want, bin, need);
+    __syncthreads();
+    want = *need;
+    const uint32_t first = lo + ((uint32_t)(BINS - 1 - *bin) << shift);
+    last = min(last, first + ((1u << shift) - 1u));
+    lo = first;
+  }
+  return lo;
+}
+
 // The token: the first member (key >= tau) among elements [0, n) of x whose running mass exceeds `target`.  Each thread
 // takes a contiguous run, so that the running masses of the threads follow index order.  All threads of the workgroup
 // call it; `base` is added to the index.
@@ -208,12 +242,12 @@ struct SmallLds {
   int bin, count;
 };
 
-__global__ __launch_bounds__(TPB) void sample_row_kernel(const float* __restrict__ logits, int V, float c, float unit, float top_p,
-                                                         const float* __restrict__ u01, float* __restrict__ scratch,
-                                                         int32_t* __restrict__ tokens) {
+__global__ __launch_bounds__(TPB) void sample_row_kernel(const float* logits, int V, float c, float unit, float top_p, const float* __restrict__ u01,
+                                                         float* scratch, int32_t* __restrict__ tokens) {
   extern __shared__ __align__(16) char smem[];
   SmallLds& S = *reinterpret_cast<SmallLds*>(smem);
   const int tid = threadIdx.x, row = blockIdx.x;
+  const bool in_place = scratch == logits;  // the probabilities then wait until the logits have been read for the last time
   const float* lg = logits + (int64_t)row * V;
   constexpr int PER = SUB / TPB;
   float x[PER];
@@ -233,7 +267,7 @@ __global__ __launch_bounds__(TPB) void sample_row_kernel(const float* __restrict
     const int i = k * TPB + tid;
     if (i < V) {
       const float e = prob(x[k], c, m, 0.f);
-      scratch[(int64_t)row * V + i] = e;
+      if (!in_place) scratch[(int64_t)row * V + i] = e;
       const u64 w = mass_of(e, unit);
       if (w) atomicAdd(&S.hist[bin_number(top, bin_of(x[k] * c))], w);
     }
@@ -266,11 +300,56 @@ __global__ __launch_bounds__(TPB) void sample_row_kernel(const float* __restrict
   __syncthreads();
   if (nucleus) pick(lg, V, c, m, 0.f, unit, tau, draw_target(u01[row], nucleus), 0, S.wave_tot, tokens + row);
   else if (tid == 0) tokens[row] = 0;  // (a row without any finite logit)
+  if (!in_place) return;
+  __syncthreads();  // the logits have been read for the last time
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int i = k * TPB + tid;
+    if (i < V) scratch[(int64_t)row * V + i] = prob(x[k], c, m, 0.f);
+  }
+}
+
+// ---- longer rows whose probabilities are to replace the logits themselves: the launches below have no room for what they
+// hand on before the logits have been read for the last time, so one workgroup takes a row, in about nine passes over it
+// (64 rows of 128 256 tokens: 323 us, one row 212).
+__global__ __launch_bounds__(TPB) void sample_in_place_kernel(float* rows, int V, float c, float unit, float top_p, const float* __restrict__ u01,
+                                                              int32_t* __restrict__ tokens) {
+  __shared__ u64 copies[BINS * COPIES], hist[BINS], wave_tot[WAVES];
+  __shared__ double need;
+  __shared__ float red[WAVES];
+  __shared__ int bin;
+  const int tid = threadIdx.x;
+  float* x = rows + (int64_t)blockIdx.x * V;
+  float m = -INFINITY;
+#pragma unroll 8
+  for (int i = tid; i < V; i += TPB) m = fmaxf(m, x[i]);
+  m = finite(block_max<TPB>(m, red));
+  auto members = [&](auto&& use) __attribute__((always_inline)) {
+#pragma unroll 8
+    for (int i = tid; i < V; i += TPB) {
+      const float v = x[i];
+      use(key_of(v), [&] { return mass_of(prob(v, c, m, 0.f), unit); });
+    }
+  };
+  const uint32_t tau = search_keys(members, 0u, 0xFFFFFFFFu, top_p, -1., copies, hist, &bin, &need);
+  u64 mine = 0;
+  members([&](uint32_t key, auto&& mass) { mine += key >= tau ? mass() : 0ull; });
+  mine = wave_sum(mine);
+  if ((tid & 63) == 0) wave_tot[tid >> 6] = mine;
+  __syncthreads();
+  u64 nucleus = 0;
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) nucleus += wave_tot[w];
+  __syncthreads();
+  if (nucleus) pick(x, V, c, m, 0.f, unit, tau, draw_target(u01[blockIdx.x], nucleus), 0, wave_tot, tokens + blockIdx.x);
+  else if (tid == 0) tokens[blockIdx.x] = 0;
+  __syncthreads();  // the logits have been read for the last time
+#pragma unroll 8
+  for (int i = tid; i < V; i += TPB) x[i] = prob(x[i], c, m, 0.f);
 }
 
 // ---- longer rows, first launch: largest logit and bin masses of every chunk
 __global__ __launch_bounds__(256) void sample_bins_kernel(const float* __restrict__ logits, int V, int chunk, float c, float unit, float* __restrict__ scratch) {
-  constexpr int COPIES = 16;  // of the bins, by lane, so that the lanes of a wavefront seldom meet in one
   __shared__ u64 hist[BINS * COPIES];
   __shared__ float red[4];
   const int tid = threadIdx.x, first = blockIdx.y * chunk, n = min(chunk, V - first);
@@ -516,33 +595,7 @@ __global__ __launch_bounds__(TPB) void sample_pick_kernel(const float* __restric
     __syncthreads();
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) { lo = min(lo, S.klo[w]); last = max(last, S.khi[w]); }
-    constexpr int COPIES = 16;  // (of the bins, by lane, in the space of the lists)
-    u64* copies = S.mass;
-    while (last > lo) {  // tau lies in lo .. last
-      const int shift = max(0, 24 - __clz(last - lo));  // (last - lo) >> shift < 256
-      for (int i = tid; i < BINS * COPIES; i += TPB) copies[i] = 0;
-      __syncthreads();
-      members([&](uint32_t key, auto&& mass) {
-        if (key < lo || key > last) return;
-        const u64 w = mass();
-        if (w) atomicAdd(&copies[(BINS - 1 - ((key - lo) >> shift)) * COPIES + (tid & (COPIES - 1))], w);
-      });
-      __syncthreads();
-      if (tid < BINS) {
-        u64 s = 0;
-#pragma unroll
-        for (int k = 0; k < COPIES; ++k) s += copies[tid * COPIES + ((k + tid) & (COPIES - 1))];
-        S.hist[tid] = s;
-      }
-      const double want = S.need;
-      __syncthreads();
-      if (wave == 0) find_boundary(S.hist, 0.f, want, &S.bin, &S.need);
-      __syncthreads();
-      const uint32_t first = lo + ((uint32_t)(BINS - 1 - S.bin) << shift);
-      last = min(last, first + ((1u << shift) - 1u));
-      lo = first;
-    }
-    tau = lo;
+    tau = search_keys(members, lo, last, 0.f, S.need, S.mass, S.hist, &S.bin, &S.need);  // (copies of the bins in the space of the lists)
   }
   // mass of the nucleus in every chunk, in units of the row's reference
   for (int k = wave; k < n_chunks; k += WAVES) {
@@ -650,6 +703,11 @@ WWW_EXPORT int www_sample_top_p(const float* logits_dev, int32_t batch, int32_t 
   }
   if (batch == 0) return WWW_OK;
   if (!logits_dev || !u01_dev || !scratch_dev || !tokens_dev) { set_error("NULL pointer argument"); return WWW_E_INVALID_ARG; }
+  const uint64_t from = (uint64_t)logits_dev, to = (uint64_t)scratch_dev, bytes = (uint64_t)batch * (uint64_t)vocab * sizeof(float);
+  if (from != to && from < to + bytes && to < from + bytes) {
+    set_error("scratch_dev overlaps logits_dev (it may be the same buffer, or one that does not overlap)");
+    return WWW_E_INVALID_ARG;
+  }
   const hipStream_t st = (hipStream_t)hip_stream;
   const float c = std::min(1.4426950408889634f / temperature, FLT_MAX);  // (finite: no 0 * inf at the largest logit)
   const float unit = mass_unit(vocab);
@@ -657,6 +715,8 @@ WWW_EXPORT int www_sample_top_p(const float* logits_dev, int32_t batch, int32_t 
   if (vocab <= SUB) {
     hipLaunchKernelGGL(sample_row_kernel, dim3(batch), dim3(TPB), sizeof(SmallLds), st, logits_dev, vocab, c, unit, top_p, u01_dev, scratch_dev,
                        tokens_dev);
+  } else if (scratch_dev == logits_dev) {
+    hipLaunchKernelGGL(sample_in_place_kernel, dim3(batch), dim3(TPB), 0, st, scratch_dev, vocab, c, unit, top_p, u01_dev, tokens_dev);
   } else {
     // chunks of equal length, 4097 .. 8192 tokens (longer only above 8 Mi tokens); the last one falls short of the others
     // by less than the number of chunks, so every chunk has room for its reserved head

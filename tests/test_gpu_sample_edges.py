@@ -19,7 +19,7 @@ BOUND = 1e-5
 ROW, CHUNKS = 1000, 20011      # a row of one workgroup, and one that is cut into chunks
 
 
-def check(lg, temperature, top_p, u):
+def check(lg, temperature, top_p, u, run=run):
     T = float(np.float32(temperature))
     tok, e_gpu = run(lg, temperature, top_p, u)
     for b in range(len(lg)):
@@ -84,3 +84,39 @@ def test_long_flat_rows(vocab):
     lg[2] = synth.normal_f32(86, vocab & 0xffff, vocab, std=1e-3)
     tok = check(lg, 1.0, 0.9, np.array([0.999, 0.37, 0.62], np.float32))
     assert abs(int(tok[0]) - 0.999 * vocab) <= 2e-5 * vocab
+
+
+@pytest.mark.parametrize("vocab", [1, 63, ROW, 8192, 8193, CHUNKS, 128256])
+@pytest.mark.parametrize("temperature,top_p", [(1.0, 0.9), (0.6, 1.0), (1e-8, 0.9)])
+def test_probabilities_replace_the_logits(vocab, temperature, top_p):
+    """the same buffer as logits and scratch"""
+    import torch
+    from paper_2603_20661_amd import binding as B
+    lg = synth.normal_f32(87, vocab, 4 * vocab, std=3.0).reshape(4, vocab).copy()
+    lg[1, :] = 0.25
+    lg[2, 1::2] = -np.inf
+    lg[3] *= 1e-3
+    print(f"vocab {vocab} T {temperature}", flush=True)
+    dev = torch.device("cuda:0")
+
+    def in_place(lg, temperature, top_p, u):
+        buf, tok = torch.from_numpy(lg).to(dev), torch.full((4,), -1, dtype=torch.int32, device=dev)
+        B.www_sample_top_p(buf, temperature, top_p, torch.from_numpy(u).to(dev), buf, tok)
+        torch.cuda.synchronize()
+        return tok.cpu().numpy(), buf.cpu().numpy()
+
+    check(lg, temperature, top_p, U, in_place)
+
+
+def test_buffers_that_overlap_in_part_are_refused():
+    import torch
+    from paper_2603_20661_amd import binding as B
+    dev = torch.device("cuda:0")
+    buf = torch.zeros(3 * 64, dtype=torch.float32, device=dev)
+    u, tok = torch.zeros(2, dtype=torch.float32, device=dev), torch.full((2,), -1, dtype=torch.int32, device=dev)
+    for a, b in ((0, 64), (64, 0), (1, 0), (0, 1)):
+        with pytest.raises(B.WwwError) as e:
+            B.www_sample_top_p(buf[a:a + 128].view(2, 64), 1.0, 0.9, u, buf[b:b + 128].view(2, 64), tok)
+        assert e.value.code == B.E_INVALID_ARG
+    torch.cuda.synchronize()
+    assert tok.cpu().tolist() == [-1, -1] and not buf.cpu().numpy().any()

@@ -79,10 +79,10 @@ __device__ __forceinline__ u64 mass_of(float e, float unit) {
   return ((u64)hi << 24) + lo;
 }
 __device__ __forceinline__ u64 shifted(u64 v, int k) { return k < 64 ? v >> k : 0ull; }
-// order-preserving integer of a float
+// order-preserving integer of a float, the same for both zeros
 __device__ __forceinline__ uint32_t key_of(float x) {
   const uint32_t b = __float_as_uint(x);
-  return (b & 0x80000000u) ? ~b : b | 0x80000000u;
+  return (b & 0x80000000u) ? 0u - b : b | 0x80000000u;
 }
 
 __device__ __forceinline__ u64 wave_sum(u64 v) {

@@ -120,3 +120,13 @@ def test_buffers_that_overlap_in_part_are_refused():
         assert e.value.code == B.E_INVALID_ARG
     torch.cuda.synchronize()
     assert tok.cpu().tolist() == [-1, -1] and not buf.cpu().numpy().any()
+
+
+@pytest.mark.parametrize("vocab", [2, ROW, CHUNKS])
+def test_zeros_of_either_sign_are_equal(vocab):
+    """equal probabilities enter the nucleus together, whatever the sign of the zero they come from"""
+    lg = np.full((4, vocab), -1.0, np.float32)
+    lg[:, :2] = [0.0, -0.0]
+    lg[1, :2] = lg[2, :2] = [-0.0, 0.0]
+    tok = check(lg, 0.02, 0.5, np.array([0.9, 0.9, 0.2, 0.2], np.float32))
+    assert tok.tolist() == [1, 1, 0, 0]

@@ -710,6 +710,7 @@ WWW_EXPORT int www_sample_top_p(const float* logits_dev, int32_t batch, int32_t 
   }
   const hipStream_t st = (hipStream_t)hip_stream;
   const float c = std::min(1.4426950408889634f / temperature, FLT_MAX);  // (finite: no 0 * inf at the largest logit)
+  if (c == 0.f) top_p = 1.f;  // infinite temperature: equal probabilities, which enter the nucleus together
   const float unit = mass_unit(vocab);
   if (int rc = allow_lds()) return rc;
   if (vocab <= SUB) {

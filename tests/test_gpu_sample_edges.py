@@ -130,3 +130,11 @@ def test_zeros_of_either_sign_are_equal(vocab):
     lg[1, :2] = lg[2, :2] = [-0.0, 0.0]
     tok = check(lg, 0.02, 0.5, np.array([0.9, 0.9, 0.2, 0.2], np.float32))
     assert tok.tolist() == [1, 1, 0, 0]
+
+
+@pytest.mark.parametrize("vocab", [ROW, 8192, CHUNKS])
+def test_infinite_temperature(vocab):
+    """all tokens equally probable, so all in the nucleus, whatever their logits"""
+    lg = synth.normal_f32(88, vocab, 4 * vocab, std=3.0).reshape(4, vocab)
+    tok, _ = run(lg, float("inf"), 0.5, U)
+    assert tok.tolist() == [int(np.float64(u) * vocab) for u in U]

@@ -45,8 +45,9 @@ namespace {
 constexpr int BINS = 256, BINS_PER_OCTAVE_LOG2 = 3;
 constexpr int SUB = 8192;            // elements a workgroup of 256 threads holds in registers at a time
 constexpr int MAX_CHUNKS = 1024;     // chunks of a row (longer rows take longer chunks)
-constexpr int HEAD = 2 + 2 * BINS;   // start of a chunk's scratch: largest logit, candidates found, bin masses (low words, high words)
-constexpr int CAND_MAX = 510;        // room for a chunk's candidates behind that
+constexpr int HEAD = 4 + 2 * BINS;   // start of a chunk's scratch: largest logit, candidates found, their least and largest key if they
+                                     // are too many, bin masses (low words, high words)
+constexpr int CAND_MAX = 508;        // room for a chunk's candidates behind that
 constexpr int RESERVED = HEAD + CAND_MAX;
 constexpr int ROW_CAND = 8192;       // candidates of a row that are looked at in LDS
 constexpr int TPB = 1024;
@@ -98,6 +99,24 @@ __device__ __forceinline__ u64 wave_scan(u64 v) {  // inclusive
     if (lane >= s) v += up;
   }
   return v;
+}
+
+// least lo and largest hi of the wavefront
+__device__ __forceinline__ void wave_range(uint32_t& lo, uint32_t& hi) {
+#pragma unroll
+  for (int s = 32; s >= 1; s >>= 1) {
+    lo = min(lo, (uint32_t)__shfl_xor((int)lo, s));
+    hi = max(hi, (uint32_t)__shfl_xor((int)hi, s));
+  }
+}
+// place in a list, counted in LDS, for every lane that has something: one addition per wavefront (the order does not matter)
+__device__ __forceinline__ int list_place(bool has, int* count) {
+  const u64 who = __ballot(has);
+  if (!who) return 0;
+  const int lane = threadIdx.x & 63, leader = __ffsll((long long)who) - 1;
+  int at = 0;
+  if (lane == leader) at = atomicAdd(count, __popcll(who));
+  return __shfl(at, leader) + __popcll(who & ((1ull << lane) - 1));
 }
 
 template <int NT>
@@ -239,6 +258,7 @@ struct SmallLds {
   double need;
   float red[WAVES];
   int reached[2 * WAVES];
+  uint32_t klo, khi;
   int bin, count;
 };
 
@@ -259,7 +279,7 @@ __global__ __launch_bounds__(TPB) void sample_row_kernel(const float* logits, in
     m = fmaxf(m, x[k]);
   }
   if (tid < BINS) S.hist[tid] = 0;
-  if (tid == 0) S.count = 0;
+  if (tid == 0) { S.count = 0; S.klo = 0xFFFFFFFFu; S.khi = 0u; }
   m = finite(block_max<TPB>(m, S.red));
   const int top = bin_of(m * c);
 #pragma unroll
@@ -275,17 +295,26 @@ __global__ __launch_bounds__(TPB) void sample_row_kernel(const float* logits, in
   __syncthreads();
   if (tid < 64) find_boundary(S.hist, top_p, -1., &S.bin, &S.need);
   __syncthreads();
+  uint32_t klo = 0xFFFFFFFFu, khi = 0u;
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
-    const int i = k * TPB + tid;
-    if (i < V && bin_number(top, bin_of(x[k] * c)) == S.bin) {
-      const int at = atomicAdd(&S.count, 1);
-      S.keys[at] = key_of(x[k]);
+    const bool cand = k * TPB + tid < V && bin_number(top, bin_of(x[k] * c)) == S.bin;
+    const int at = list_place(cand, &S.count);
+    if (cand) {
+      const uint32_t key = key_of(x[k]);
+      S.keys[at] = key;
       S.mass[at] = mass_of(prob(x[k], c, m, 0.f), unit);
+      klo = min(klo, key);
+      khi = max(khi, key);
     }
   }
+  if (__any(khi)) {
+    wave_range(klo, khi);
+    if ((tid & 63) == 0) { atomicMin(&S.klo, klo); atomicMax(&S.khi, khi); }
+  }
   __syncthreads();
-  const uint32_t tau = find_tau(S.keys, S.mass, S.count, S.need, 0u, 0xFFFFFFFFu, S.reached);
+  klo = S.klo; khi = S.khi;
+  const uint32_t tau = S.count ? find_tau(S.keys, S.mass, S.count, S.need, klo, khi == 0xFFFFFFFFu ? khi : khi + 1u, S.reached) : 0u;
   // mass of the nucleus
   u64 mine = 0;
 #pragma unroll
@@ -386,26 +415,30 @@ __global__ __launch_bounds__(256) void sample_bins_kernel(const float* __restric
 #pragma unroll
   for (int k = 0; k < COPIES; ++k) s += hist[tid * COPIES + ((k + tid) & (COPIES - 1))];
   float* region = scratch + (int64_t)blockIdx.x * V + first;
-  region[2 + tid] = __uint_as_float((uint32_t)s);
-  region[2 + BINS + tid] = __uint_as_float((uint32_t)(s >> 32));
+  region[4 + tid] = __uint_as_float((uint32_t)s);
+  region[4 + BINS + tid] = __uint_as_float((uint32_t)(s >> 32));
   if (tid == 0) region[0] = m;
 }
 
-// Largest logit of a row, from its chunks' headers (called by every thread, the same value everywhere).
-__device__ __forceinline__ float row_max(const float* row, int chunk, int n_chunks) {
-  float m = -FLT_MAX;
-  for (int k = threadIdx.x & 63; k < n_chunks; k += 64) m = fmaxf(m, row[(int64_t)k * chunk]);
+// Largest logit of a row, from its chunks' headers (called by every thread, the same value everywhere); lane k keeps the one
+// of chunk k in `head`.
+__device__ __forceinline__ float row_max(const float* row, int chunk, int n_chunks, float& head) {
+  const int lane = threadIdx.x & 63;
+  head = lane < n_chunks ? row[(int64_t)lane * chunk] : -FLT_MAX;
+  float m = head;
+  for (int k = lane + 64; k < n_chunks; k += 64) m = fmaxf(m, row[(int64_t)k * chunk]);
 #pragma unroll
   for (int s = 32; s >= 1; s >>= 1) m = fmaxf(m, __shfl_xor(m, s));
   return m;
 }
 __device__ __forceinline__ u64 chunk_bin(const float* region, int bin) {
-  return ((u64)__float_as_uint(region[2 + BINS + bin]) << 32) | __float_as_uint(region[2 + bin]);
+  return ((u64)__float_as_uint(region[4 + BINS + bin]) << 32) | __float_as_uint(region[4 + bin]);
 }
 // ---- second launch: probabilities of every chunk (but its reserved head) and its members of the bin that holds tau
 __global__ __launch_bounds__(256) void sample_split_kernel(const float* __restrict__ logits, int V, int chunk, float c, float top_p, float* scratch) {
   __shared__ u64 hist[BINS];
   __shared__ double need;
+  __shared__ uint32_t klo[4], khi[4];
   __shared__ int bin, count;
   const int tid = threadIdx.x, first = blockIdx.y * chunk, n = min(chunk, V - first);
   const float* lg = logits + (int64_t)blockIdx.x * V + first;
@@ -431,13 +464,15 @@ __global__ __launch_bounds__(256) void sample_split_kernel(const float* __restri
     for (int k = 0; k < NB; ++k) w[k] = chunk_bin(row + (int64_t)min(k0 + k, n_chunks - 1) * chunk, tid);
   };
   load_bins(0);
-  const float m = row_max(row, chunk, n_chunks);
+  float head;
+  const float m = row_max(row, chunk, n_chunks, head);
   const int top = bin_of(m * c);
   const double oct = octave_of(m, c);
   __syncthreads();
   for (int k0 = 0; k0 < n_chunks; k0 += NB) {
     if (k0) load_bins(k0);
-    const float mc = row[(int64_t)min(k0 + (tid & 63), n_chunks - 1) * chunk];  // lane k: chunk k0 + k
+    const int k_lane = k0 + (tid & (NB - 1));  // lane k: chunk k0 + k
+    const float mc = k0 < 64 ? __shfl(head, k_lane) : row[(int64_t)min(k_lane, n_chunks - 1) * chunk];
     const int down = top - bin_of(mc * c), back = octaves_between(oct, octave_of(mc, c));
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
@@ -456,18 +491,28 @@ __global__ __launch_bounds__(256) void sample_split_kernel(const float* __restri
       const int i = base + k * 256 + tid;
       if (i >= RESERVED && i < n) region[i] = prob(x[k], c, m, 0.f);
       const bool cand = i < n && bin_number(top, bin_of(x[k] * c)) == b;
-      const u64 who = __ballot(cand);
-      if (who) {  // one LDS addition per wavefront; the order of the list does not matter
-        const int lane = tid & 63, leader = __ffsll((long long)who) - 1;
-        int at = 0;
-        if (lane == leader) at = atomicAdd(&count, __popcll(who));
-        at = __shfl(at, leader) + __popcll(who & ((1ull << lane) - 1));
-        if (cand && at < CAND_MAX) region[HEAD + at] = x[k];
-      }
+      const int at = list_place(cand, &count);
+      if (cand && at < CAND_MAX) region[HEAD + at] = x[k];
     }
   }
   __syncthreads();
   if (tid == 0) region[1] = __int_as_float(count);
+  if (count <= CAND_MAX) return;
+  // more than the list holds: the range of their keys, for the search that replaces it
+  uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+  for (int base = 0; base < n; base += SUB) {
+    if (n > SUB) load(base);
+#pragma unroll
+    for (int k = 0; k < SUB / 256; ++k)
+      if (base + k * 256 + tid < n && bin_number(top, bin_of(x[k] * c)) == b) { lo = min(lo, key_of(x[k])); hi = max(hi, key_of(x[k])); }
+  }
+  wave_range(lo, hi);
+  if ((tid & 63) == 0) { klo[tid >> 6] = lo; khi[tid >> 6] = hi; }
+  __syncthreads();
+  if (tid == 0) {
+    region[2] = __uint_as_float(min(min(klo[0], klo[1]), min(klo[2], klo[3])));
+    region[3] = __uint_as_float(max(max(khi[0], khi[1]), max(khi[2], khi[3])));
+  }
 }
 
 // ---- third launch: tau and the token of every row, and the probabilities of the reserved heads
@@ -524,104 +569,99 @@ __global__ __launch_bounds__(TPB) void sample_pick_kernel(const float* __restric
     over = __any(over) || at > ROW_CAND;
     if (lane == 0) { S.n_cand = at; S.overflow = over; }
   }
-  const float m = row_max(row, chunk, n_chunks);
+  float head;
+  const float m = row_max(row, chunk, n_chunks, head);
   const int top = bin_of(m * c);
   const double oct = octave_of(m, c);
+  struct Ref { float m, r; int down, back; };  // largest logit of a chunk, its way down, and how far bins and masses lie below the row's
+  auto ref_of = [&](float mc) __attribute__((always_inline)) { return Ref{mc, way_down(mc, c), top - bin_of(mc * c), octaves_between(oct, octave_of(mc, c))}; };
+  const Ref own = ref_of(__shfl(head, wave));
   __syncthreads();
   const bool listed = !S.overflow;
   uint32_t klo = 0xFFFFFFFFu, khi = 0u;
   for (int k = wave; k < n_chunks; k += WAVES) {
     const float* region = row + (int64_t)k * chunk;
-    const float mc = region[0], r = way_down(mc, c);
-    const int down = top - bin_of(mc * c), back = octaves_between(oct, octave_of(mc, c));
+    const Ref R = k == wave ? own : ref_of(region[0]);
 #pragma unroll
     for (int i = 0; i < BINS / 64; ++i) {
-      const u64 v = shifted(k == wave ? hb[i] : chunk_bin(region, i * 64 + lane), back);
-      if (v) atomicAdd(&S.hist[min(BINS - 1, i * 64 + lane + down)], v);
+      const u64 v = shifted(k == wave ? hb[i] : chunk_bin(region, i * 64 + lane), R.back);
+      if (v) atomicAdd(&S.hist[min(BINS - 1, i * 64 + lane + R.down)], v);
     }
-    if (listed) {
-      const int at = S.chunk_at[k], cnt = __float_as_int(region[1]);
+    const int cnt = __float_as_int(region[1]);
+    if (cnt <= CAND_MAX) {
+      const int at = S.chunk_at[k];
       for (int i = lane; i < cnt; i += 64) {
         const float v = region[HEAD + i];
         const uint32_t key = key_of(v);
-        S.keys[at + i] = key;
-        S.mass[at + i] = shifted(mass_of(prob(v, c, mc, r), unit), back);
+        if (listed) {
+          S.keys[at + i] = key;
+          S.mass[at + i] = shifted(mass_of(prob(v, c, R.m, R.r), unit), R.back);
+        }
         klo = min(klo, key);
         khi = max(khi, key);
       }
+    } else if (lane == 0) {
+      klo = min(klo, __float_as_uint(region[2]));
+      khi = max(khi, __float_as_uint(region[3]));
     }
   }
-#pragma unroll
-  for (int s = 32; s >= 1; s >>= 1) {
-    klo = min(klo, (uint32_t)__shfl_xor((int)klo, s));
-    khi = max(khi, (uint32_t)__shfl_xor((int)khi, s));
-  }
+  wave_range(klo, khi);
   if (lane == 0) { S.klo[wave] = klo; S.khi[wave] = khi; }
   __syncthreads();
   if (wave == 0) find_boundary(S.hist, top_p, -1., &S.bin, &S.need);
-  if (listed) {
 #pragma unroll
-    for (int w = 0; w < WAVES; ++w) { klo = min(klo, S.klo[w]); khi = max(khi, S.khi[w]); }
-  }
+  for (int w = 0; w < WAVES; ++w) { klo = min(klo, S.klo[w]); khi = max(khi, S.khi[w]); }
   __syncthreads();
   const int b = S.bin;
+  // Where the lists do not do, the row itself is read: by one wavefront per chunk, or several where there are fewer chunks (512
+  // rows of 32 000 near-equal tokens, 4 chunks: 530 -> 226 us)
+  int team = 1;
+  while (2 * team * n_chunks <= WAVES) team *= 2;
+  auto members_of = [&](int k, const Ref& R, auto&& use) __attribute__((always_inline)) {  // use(key, mass) of every member of bin b
+    const int64_t f = (int64_t)k * chunk;
+    const int n = min(chunk, (int)(V - f));
+#pragma unroll 8
+    for (int i = wave % team * 64 + lane; i < n; i += 64 * team) {
+      const float v = lg[f + i];
+      if (bin_number(top, bin_of(v * c)) == b) use(key_of(v), [&] { return shifted(mass_of(prob(v, c, R.m, R.r), unit), R.back); });
+    }
+  };
   uint32_t tau;
   if (listed) {
     tau = S.n_cand ? find_tau(S.keys, S.mass, S.n_cand, S.need, klo, khi == 0xFFFFFFFFu ? khi : khi + 1u, S.reached) : 0u;
   } else {
     // The bin holds more elements than the lists (a row that is flat to within a tenth of an octave): its keys are binned
     // again, 256 linear bins at a time, until one key is left; three or four passes over the row.
-    auto members = [&](auto&& use) __attribute__((always_inline)) {  // use(key, mass) of every member of bin b
-      for (int k = wave; k < n_chunks; k += WAVES) {
-        const int64_t f = (int64_t)k * chunk;
-        const int n = min(chunk, (int)(V - f));
-        const float mc = row[f], r = way_down(mc, c);
-        const int back = octaves_between(oct, octave_of(mc, c));
-#pragma unroll 8
-        for (int i = lane; i < n; i += 64) {
-          const float v = lg[f + i];
-          if (bin_number(top, bin_of(v * c)) == b) use(key_of(v), [&] { return shifted(mass_of(prob(v, c, mc, r), unit), back); });
-        }
-      }
+    auto members = [&](auto&& use) __attribute__((always_inline)) {
+      for (int k = wave / team; k < n_chunks; k += WAVES / team) members_of(k, ref_of(row[(int64_t)k * chunk]), use);
     };
-    uint32_t lo = 0xFFFFFFFFu, last = 0u;
-    members([&](uint32_t key, auto&&) { lo = min(lo, key); last = max(last, key); });
-#pragma unroll
-    for (int s = 32; s >= 1; s >>= 1) {
-      lo = min(lo, (uint32_t)__shfl_xor((int)lo, s));
-      last = max(last, (uint32_t)__shfl_xor((int)last, s));
-    }
-    if (lane == 0) { S.klo[wave] = lo; S.khi[wave] = last; }
-    __syncthreads();
-#pragma unroll
-    for (int w = 0; w < WAVES; ++w) { lo = min(lo, S.klo[w]); last = max(last, S.khi[w]); }
-    tau = search_keys(members, lo, last, 0.f, S.need, S.mass, S.hist, &S.bin, &S.need);  // (copies of the bins in the space of the lists)
+    tau = search_keys(members, klo, khi, 0.f, S.need, S.mass, S.hist, &S.bin, &S.need);  // (copies of the bins in the space of the lists)
   }
   // mass of the nucleus in every chunk, in units of the row's reference
   for (int k = wave; k < n_chunks; k += WAVES) {
     const float* region = row + (int64_t)k * chunk;
-    const float mc = region[0], r = way_down(mc, c);
-    const int down = top - bin_of(mc * c), back = octaves_between(oct, octave_of(mc, c));
+    const Ref R = k == wave ? own : ref_of(region[0]);
     u64 s = 0;
 #pragma unroll
     for (int i = 0; i < BINS / 64; ++i)
-      if (min(BINS - 1, i * 64 + lane + down) < b) s += k == wave ? hb[i] : chunk_bin(region, i * 64 + lane);
-    s = shifted(wave_sum(s), back);
+      if (min(BINS - 1, i * 64 + lane + R.down) < b) s += k == wave ? hb[i] : chunk_bin(region, i * 64 + lane);
+    s = shifted(wave_sum(s), R.back);
     u64 q = 0;
     if (listed) {
       const int at = S.chunk_at[k], cnt = __float_as_int(region[1]);
       for (int i = lane; i < cnt; i += 64) q += S.keys[at + i] >= tau ? S.mass[at + i] : 0ull;
-    } else {
-      const int64_t f = (int64_t)k * chunk;
-      const int n = min(chunk, (int)(V - f));
-#pragma unroll 8
-      for (int i = lane; i < n; i += 64) {
-        const float v = lg[f + i];
-        if (key_of(v) >= tau && bin_number(top, bin_of(v * c)) == b) q += shifted(mass_of(prob(v, c, mc, r), unit), back);
-      }
+      q = wave_sum(q);
     }
-    q = wave_sum(q);
     if (lane == 0) S.chunk_mass[k] = s + q;
+  }
+  if (!listed) {
+    __syncthreads();
+    for (int k = wave / team; k < n_chunks; k += WAVES / team) {
+      u64 q = 0;
+      members_of(k, ref_of(row[(int64_t)k * chunk]), [&](uint32_t key, auto&& mass) { q += key >= tau ? mass() : 0ull; });
+      q = wave_sum(q);
+      if (lane == 0) atomicAdd(&S.chunk_mass[k], q);
+    }
   }
   __syncthreads();
   if (wave == 0) {
@@ -646,10 +686,9 @@ __global__ __launch_bounds__(TPB) void sample_pick_kernel(const float* __restric
   __syncthreads();
   if (S.chunk >= 0) {
     const int64_t f = (int64_t)S.chunk * chunk;
-    const float mc = row[f];
+    const Ref R = ref_of(row[f]);
     // the running mass inside the chunk is counted in the chunk's own units, in which it is at least what was counted above
-    pick(lg + f, min(chunk, (int)(V - f)), c, mc, way_down(mc, c), unit, tau, S.target << octaves_between(oct, octave_of(mc, c)), (int)f, S.wave_tot,
-         tokens + blockIdx.x);
+    pick(lg + f, min(chunk, (int)(V - f)), c, R.m, R.r, unit, tau, S.target << R.back, (int)f, S.wave_tot, tokens + blockIdx.x);
   }
   __syncthreads();  // the headers are no longer needed
   for (int k = wave; k < n_chunks; k += WAVES) {

@@ -138,3 +138,15 @@ def test_infinite_temperature(vocab):
     lg = synth.normal_f32(88, vocab, 4 * vocab, std=3.0).reshape(4, vocab)
     tok, _ = run(lg, float("inf"), 0.5, U)
     assert tok.tolist() == [int(np.float64(u) * vocab) for u in U]
+
+
+@pytest.mark.parametrize("vocab", [8192, 8193, 24577])
+def test_members_of_the_decisive_bin_in_some_chunks_only(vocab):
+    """more members than a chunk's list holds in the first chunk, few, none or equal ones in the others"""
+    lg = synth.normal_f32(89, vocab, 4 * vocab, std=0.5).reshape(4, vocab) - 8.0
+    lg[:, :3000] = 0.01 * synth.normal_f32(90, vocab, 4 * 3000).reshape(4, 3000)
+    lg[1, 5000:5300] = lg[1, 17]
+    lg[2, 4500:] = -np.inf
+    lg[3, :3000] = 0.125
+    for u in (0.01, 0.5, 0.999):
+        check(lg, 1.0, 0.6, np.full(4, u, np.float32))

@@ -168,7 +168,6 @@ __global__ __launch_bounds__(256 * KH, MTK == 8 ? 1 : 2 / KH) void skinny_gemm_k
   const int tile = (blockIdx.x & 7) + 8 * lt;
   if (tile >= p.row_tiles) return;  // grid padding when the row tiles are not a multiple of 8
   const int tb0 = zb * MTK;
-  if (tb0 * 16 >= p.M) return;  // a group of padding only (all splits of it leave here)
   const int rg0 = tile * 8 + wave * R;
   const int kb_begin = split * p.kb_per_split;
   const int kb_end = min(p.KB, kb_begin + p.kb_per_split);
@@ -455,7 +454,7 @@ __global__ __launch_bounds__(256 * KH, MTK == 8 ? 1 : 2 / KH) void skinny_gemm_k
   };
 
   if (p.ksplit <= 1) request_epilogue_inputs();
-  if (p.ksplit > 1) {
+  if (MTK < 8 && p.ksplit > 1) {
     // split-K: park the partial tile, and let the workgroup that arrives last add all partial tiles in split order
     // parked as a register image: unit ((((split, zb, tile), wave), r), tb), lane -> one 16-byte store per lane,
     // 1 KiB contiguous per instruction; the last workgroup reads it back with the same thread mapping
@@ -481,9 +480,9 @@ __global__ __launch_bounds__(256 * KH, MTK == 8 ? 1 : 2 / KH) void skinny_gemm_k
     for (int r = 0; r < R; ++r)
 #pragma unroll
       for (int tb = 0; tb < MTK; ++tb) acc[r][tb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // partial tiles are added in split order (reproducible); loads are issued four splits (two of 128 tokens: registers)
-    // at a time so that the reduction is not one memory round trip per split
-    constexpr int NSP = MTK == 8 ? 2 : 4;
+    // partial tiles are added in split order (reproducible); loads are issued four splits at a time so that
+    // the reduction is not one memory round trip per split
+    constexpr int NSP = 4;
     for (int s0 = 0; s0 < p.ksplit; s0 += NSP) {
       f32x4 pv[NSP][R][MTK];
 #pragma unroll
@@ -1200,12 +1199,13 @@ static void choose_split(int row_tiles, int zb, int KB, int* ksplit, int* kb_per
   *ksplit = (KB + per - 1) / per;
 }
 
-// split factor the decode path will use for a GEMM with NRG row groups and KB k blocks (for workspace sizing)
+// largest split factor the decode path will use for a GEMM with NRG row groups, KB k blocks and MT token groups (for
+// workspace sizing)
 int decode_gemm_ksplit(int NRG, int KB, int MT) {
   int most = 1;
-  for (int mtk = 4; mtk <= 8; mtk += 4) {  // token groups per workgroup, see launch_gemm
+  for (int zb = MT > 8 ? MT / 8 : 1; zb <= (MT + 3) / 4; ++zb) {  // workgroups per row tile and split, see launch_gemm
     int ks, per;
-    choose_split((NRG + 7) / 8, MT > mtk ? MT / mtk : 1, KB, &ks, &per);
+    choose_split((NRG + 7) / 8, zb, KB, &ks, &per);
     if (ks > most) most = ks;
   }
   return most;
@@ -1214,13 +1214,19 @@ int decode_gemm_ksplit(int NRG, int KB, int MT) {
 template <int EPI>
 static void launch_gemm(www_model* m, GemmP& p, int MT, hipStream_t st) {
   const int row_tiles = (p.NRG + 7) / 8;
-  // Above 64 tokens the two wide GEMMs take 128 tokens per workgroup: every compute unit takes in about 55 KB per us, and
-  // 128 rows x 128 tokens need 24 KB per k block where two workgroups of 64 tokens need 32 (8B shape, 128 tokens: gate/up 84 ->
-  // 73 us, output head 308 -> 298).  The split-K GEMMs, whose epilogues then exceed the registers, are slower that way (QKV
-  // 36 -> 52 us), and so are int4 weights (a step of 100 sequences 7250 -> 7700 us).
+  // Above 64 tokens the two wide GEMMs may take 128 tokens per workgroup: every compute unit takes in about 55 KB per us, and
+  // 128 rows x 128 tokens need 24 KB per k block where two workgroups of 64 tokens need 32 (with FP8 weights 20 and 24).
+  // A round of 128 tokens on all compute units takes about 1.75 (FP8: 1.9) times as long as one of 64 (8B shape, gate/up 73
+  // and 42 us), so they are taken where they save that many rounds: 8B shape, 128 sequences 7000 -> 6670 us a step, 256:
+  // 11 840 -> 11 440.  Elsewhere they cost: 192 sequences 10 160 -> 10 850 us, with FP8 weights 9290 -> 10 400, 1B shape 65
+  // sequences 1456 -> 1530.  The split-K GEMMs, whose epilogues then exceed the registers, are slower that way (QKV
+  // 36 -> 52 us), and so are int4 weights (a step of 100 sequences 7250 -> 7700 us).  A range of k is never split there: more
+  // than half of the compute units have a row tile each, or there would be no round to save.
   constexpr bool wide_epi = EPI == EPI_SWIGLU || EPI == EPI_LOGITS;
-  const int mtk = MT < 8 ? MT : wide_epi && !m->int4_group && !m->wsplit ? 8 : 4;
-  const int zb = MT / mtk;
+  auto rounds = [&](int tokens) { return (float)((row_tiles * ((p.M + tokens - 1) / tokens) + wg_target() - 1) / wg_target()); };
+  const bool wide = wide_epi && !m->int4_group && !m->wsplit && rounds(128) * (m->fp8 ? 1.9f : 1.75f) < rounds(64);
+  const int mtk = MT < 8 ? MT : wide ? 8 : 4;
+  const int zb = MT < 8 ? 1 : (p.M + 16 * mtk - 1) / (16 * mtk);  // (not MT / mtk: the last 64 tokens may all be padding)
   choose_split(row_tiles, zb, p.KB, &p.ksplit, &p.kb_per_split);
   p.MT = MT;
   p.partial = m->partial;

@@ -1,6 +1,6 @@
-"""GPU: batches above 64 sequences, where the gate/up and output-head GEMMs take 128 tokens per workgroup (with a split k
-range too) and the others 64, and where the last group of tokens is nearly empty, full, or padding only.  Bounds of the
-parity tests."""
+"""GPU: batches above 64 sequences, which the decode GEMMs take in groups of 64 tokens per workgroup, or of 128 in gate/up
+GEMMs and output heads that fill the GPU in fewer rounds that way, and where the last group of tokens is nearly empty, full,
+or padding only.  Bounds of the parity tests."""
 import dataclasses
 
 import pytest
@@ -25,3 +25,20 @@ def test_large_batches(shape, batch):
 def test_groups_of_16_without_sequences(batch):
     lens = 3 + synth.uniform_i32(batch, 9, batch, 30)
     check(run_job(MID128, lens, 2, seed=170 + batch), f"batch {batch}")
+
+
+WIDE = dataclasses.replace(MID128, name="wide", n_layers=1, ffn_dim=8320, vocab=20000, seed=413)        # 130 and 157 row tiles
+WIDE_FP8 = dataclasses.replace(WIDE, name="widefp8", weight_dtype=synth.WDTYPE_FP8WO, seed=414)
+
+
+@pytest.mark.parametrize("shape", [WIDE, WIDE_FP8], ids=lambda s: s.name)
+@pytest.mark.parametrize("batch", [65, 100, 128, 129, 193])     # groups of 128 tokens up to 128 sequences, of 64 behind
+def test_wide_gemms(shape, batch):
+    lens = 3 + synth.uniform_i32(batch, 9, batch, 12)
+    check(run_job(shape, lens, 2, seed=180 + batch), f"{shape.name} batch {batch}")
+
+
+def test_wide_gemms_with_a_half_empty_group():
+    """86 row tiles, 250 sequences: two groups of 128 tokens in the gate/up GEMM, the second of them not full"""
+    shape = dataclasses.replace(WIDE, name="wide86", ffn_dim=5504, seed=415)
+    check(run_job(shape, 3 + synth.uniform_i32(250, 9, 250, 12), 2, seed=190), "wide86 batch 250")

@@ -14,6 +14,7 @@
 #define WWW_EXPORT extern "C" __attribute__((visibility("default")))
 
 int decode_gemm_ksplit(int NRG, int KB, int MT);
+hipError_t prefill_allow_lds();
 uint64_t prefill_partial_bytes(int maxT, int NRG, int KB);
 uint64_t prefill_attn_part_bytes(int hd, int Hkv, int G, int maxT, int maxB, int max_pos);
 int decode_MT(int batch);
@@ -471,6 +472,7 @@ WWW_EXPORT int www_model_load(const www_config* cfg, const void* weights_dev, vo
   m->hp = (float*)(ws + p.hp); m->ssq_p = (float*)(ws + p.ssq_p); m->xn = (uint16_t*)(ws + p.xn); m->qp = (uint16_t*)(ws + p.qp); m->op = (uint16_t*)(ws + p.op); m->ap = (uint16_t*)(ws + p.ap);
   m->row_seq = (int*)(ws + p.row_seq); m->row_pos = (int*)(ws + p.row_pos); m->tile_seq = (int*)(ws + p.tile_seq);
   m->tile_q0 = (int*)(ws + p.tile_q0); m->meta = (int*)(ws + p.meta);
+  LOAD_TRY(prefill_allow_lds());
   m->attn_waves = decode_attn_resident_waves(s.hd, s.G);
   if (m->attn_waves > MAX_ATTN_WAVES) m->attn_waves = MAX_ATTN_WAVES;
   {

@@ -1157,8 +1157,22 @@ uint64_t prefill_partial_bytes(int maxT, int NRG, int KB) {
   return most;
 }
 
-template <typename K>
-static void enable_lds(K kernel, int bytes) { (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes); }
+// Announces the GEMM kernels, which use more than 64 KiB of dynamic LDS, to the current device (when a model is loaded there).
+template <int EPI, bool QKN>
+static hipError_t allow_pgemm_lds() {
+  auto allow = [](const void* kernel, int bytes) { return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); };
+  hipError_t e = allow(reinterpret_cast<const void*>(&prefill_gemm_kernel<EPI, QKN>), PGEMM_LDS_BYTES);
+  if (e == hipSuccess) e = allow(reinterpret_cast<const void*>(&prefill_gemm_small_kernel<EPI, QKN, 1>), PSG_LDS_BYTES);
+  if (e == hipSuccess) e = allow(reinterpret_cast<const void*>(&prefill_gemm_small_kernel<EPI, QKN, 2>), PSG_LDS_BYTES);
+  return e;
+}
+hipError_t prefill_allow_lds() {
+  hipError_t e = allow_pgemm_lds<PEPI_QKV, false>();
+  if (e == hipSuccess) e = allow_pgemm_lds<PEPI_QKV, true>();
+  if (e == hipSuccess) e = allow_pgemm_lds<PEPI_RESID, false>();
+  if (e == hipSuccess) e = allow_pgemm_lds<PEPI_SWIGLU, false>();
+  return e;
+}
 
 // returns the number of entries per token a residual epilogue wrote into the sum-of-squares table
 template <int EPI, bool QKN = false>
@@ -1169,13 +1183,6 @@ static int launch_pgemm(www_model* m, PGemmP& p, hipStream_t st) {
   p.n_tt = (p.T + 255) / 256;
   p.n_rt = (p.NRG + 15) / 16;
   if (p.wfactor == 0.f) p.wfactor = 1.f;  // not set: an unscaled matrix
-  static bool lds_enabled = false;  // per instantiation: allow more than 64 KiB of dynamic LDS
-  if (!lds_enabled) {
-    enable_lds(&prefill_gemm_kernel<EPI, QKN>, PGEMM_LDS_BYTES);
-    enable_lds(&prefill_gemm_small_kernel<EPI, QKN, 1>, PSG_LDS_BYTES);
-    enable_lds(&prefill_gemm_small_kernel<EPI, QKN, 2>, PSG_LDS_BYTES);
-    lds_enabled = true;
-  }
   const PGemmChoice c = choose_pgemm(p.T, p.NRG, p.KB);
   if (c.tb == 0) {
     hipLaunchKernelGGL((prefill_gemm_kernel<EPI, QKN>), dim3(p.n_tt * p.n_rt), dim3(256), PGEMM_LDS_BYTES, st, p);

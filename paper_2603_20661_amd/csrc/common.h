@@ -114,8 +114,6 @@ __device__ __forceinline__ void store_shared_f32x4(__amdgpu_buffer_rsrc_t r, uin
 __device__ __forceinline__ f32x4 load_shared_f32x4(__amdgpu_buffer_rsrc_t r, uint32_t byte_off) {
   return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, byte_off, 0, 16));
 }
-__device__ __forceinline__ void store_shared_f32(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ float load_shared_f32(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 // All of this wavefront's earlier vector memory operations have completed (stores: acknowledged by L2).  Written as the
 // wait itself: a workgroup-scope release fence compiles to no vector-memory wait here (the wavefronts of a workgroup
 // share one L1, so for ordering inside the workgroup none is needed), and then the partial-tile stores of a slow

@@ -450,7 +450,6 @@ WWW_EXPORT int www_model_load(const www_config* cfg, const void* weights_dev, vo
     LOAD_TRY(hipMemcpyAsync(ws + p.rope, tab.data(), tab.size() * 4, hipMemcpyHostToDevice, st));
     LOAD_TRY(hipStreamSynchronize(st));  // tab is about to go out of scope; also fences the packing kernels
   }
-#undef LOAD_TRY
 
   m->embed = ws + p.embed;
   m->lm_head = (s.fp8 || s.int4_group) ? nullptr : (const uint16_t*)(ws + p.lm_head);
@@ -473,6 +472,7 @@ WWW_EXPORT int www_model_load(const www_config* cfg, const void* weights_dev, vo
   m->row_seq = (int*)(ws + p.row_seq); m->row_pos = (int*)(ws + p.row_pos); m->tile_seq = (int*)(ws + p.tile_seq);
   m->tile_q0 = (int*)(ws + p.tile_q0); m->meta = (int*)(ws + p.meta);
   LOAD_TRY(prefill_allow_lds());
+#undef LOAD_TRY
   m->attn_waves = decode_attn_resident_waves(s.hd, s.G);
   if (m->attn_waves > MAX_ATTN_WAVES) m->attn_waves = MAX_ATTN_WAVES;
   {

@@ -693,7 +693,7 @@ __global__ __launch_bounds__(256 * KH, MTK == 8 ? 1 : 2 / KH) void skinny_gemm_k
 //
 // The keys of the batch are counted in pairs of 16-key blocks.  All (sequence b, kv head j, pair) triples, in that
 // order, form one long list of T = Hkv * sum_b P_b entries (P_b = pairs of sequence b); the attention kernel runs W
-// wavefronts and wavefront w takes the entries [w*C, (w+1)*C), C = ceil(T / W), at least ceil(longest P / 64).  Every wavefront therefore
+// wavefronts and wavefront w takes the entries [w*C, (w+1)*C), C = ceil(T / W), at least min(16, ceil(longest P / 64)).  Every wavefront therefore
 // streams the same number of bytes and all of them finish together, whatever the mix of sequence lengths.  A chunk may
 // end inside a (b, j) sequence and continue into the next one; each piece is a segment with its own softmax state,
 // parked as a record and merged afterwards.  Only the first and the last segment of a chunk can be part of a longer
@@ -701,10 +701,12 @@ __global__ __launch_bounds__(256 * KH, MTK == 8 ? 1 : 2 / KH) void skinny_gemm_k
 // The cut points depend on the lengths of all sequences of the batch: results are reproducible for a given batch
 // but the rounding of a sequence's attention output may differ between batches of different composition.
 // C has no other lower bound: with few tokens in the batch a chunk is a single pair, and the whole GPU works on it.  (At
-// least 16 pairs a chunk, one sequence of 1041 tokens had 17 wavefronts: 32 us per layer of the 8B shape against 8; a
-// step took 4197 us, 3835 with at least 8 pairs, 3661 with 4, 3543 with 1.)  A sequence is cut into at most 64 full
-// chunks, because the merge reads 32 records per memory round trip (one sequence of 8192 tokens: 3957 us a step with
-// 128 chunks, 3800 with 64).
+// least 16 pairs a chunk, one sequence of 1041 tokens had 17 wavefronts: 32 us per layer of the 8B shape against 6; a
+// step took 4197 us, 3835 with at least 8 pairs, 3661 with 4, 3543 with 1.)  A sequence of up to 32 768 tokens is cut into
+// at most 64 full chunks, because the merge reads 32 records per memory round trip (a step of one sequence with 64 chunks
+// and with one per wavefront, us: 4096 tokens 3762 / 3877, 8192 3862 / 4014, 16 384 4058 / 4120, 32 768 4467 / 4475).  Beyond, the
+// wavefronts that this leaves without work cost more than a round trip (65 536: 5325 / 5122, 131 072: 7027 / 6410), so chunks
+// of 16 pairs are long enough.
 //   hdr[0] = T, hdr[1] = C;  start[w] = (b, j, first pair, length of b) of wavefront w, b = -1 if it has no work;
 //   pref[b] = sum of P over the sequences before b
 __global__ __launch_bounds__(256) void attn_plan_kernel(const int32_t* __restrict__ seq_lens, int batch, int Hkv, int W,
@@ -734,7 +736,7 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(const int32_t* __restric
   }
   __syncthreads();
   const int T = pref[batch] * Hkv, longest = pref[batch + 1];
-  const int C = max(1, max((T + W - 1) / W, (longest + 63) / 64));
+  const int C = max(1, max((T + W - 1) / W, min(16, (longest + 63) / 64)));
   if (tid == 0) { hdr[0] = T; hdr[1] = C; }
   for (int i = tid; i <= batch; i += 256) pref_out[i] = pref[i];
   for (int w = tid; w < W; w += 256) {

@@ -332,9 +332,10 @@ int www_get_stats(const www_sched* sched, www_stats* out);
  * use temperature 0, which is the greedy token www_decode_step already returns).  Definition used here, per row:
  * p = softmax(logits / temperature); the nucleus is {i : p_i >= tau} for the largest tau among the probabilities whose
  * members' mass reaches top_p (equal probabilities enter together); the token is the first member, in index order,
- * whose running mass exceeds u01[row] times the nucleus mass.  No sort is involved and every sum has a fixed order, so
- * a call is reproducible; against an exact evaluation the choice can differ only where a sum lies within fp32
- * rounding of a decision point.
+ * whose running mass exceeds u01[row] times the nucleus mass.  No sort is involved and masses are summed as integers,
+ * whose sums do not depend on their order, so a call is reproducible; against an exact evaluation the choice can differ
+ * only where a sum lies within fp32 rounding of a decision point.  A logit of +inf counts as the largest finite one, a
+ * NaN is never drawn, and a row without any logit above -inf yields token 0.
  *   logits_dev fp32 [batch][vocab]; u01_dev fp32 [batch], the caller's uniform numbers in [0, 1);
  *   scratch_dev fp32 [batch][vocab], overwritten (unnormalised probabilities); tokens_dev int32 [batch].
  *   scratch_dev may be logits_dev itself (slower for rows of more than 8192 tokens); otherwise the two may not overlap.
@@ -343,7 +344,7 @@ int www_sample_top_p(const float* logits_dev, int32_t batch, int32_t vocab, floa
                      float* scratch_dev, int32_t* tokens_dev, void* hip_stream);
 
 /* www_sample_top_p for callers that cannot allocate device memory (code under HIP graph capture, tight serving loops,
- * harnesses that forbid hipMalloc): the same kernel and the same results, with the [batch][vocab] buffer of
+ * harnesses that forbid hipMalloc): the same kernels and the same results, with the [batch][vocab] buffer of
  * unnormalised probabilities in an array built into the library (WWW_SAMPLE_STATIC_MAX_FLOATS floats = 32 MiB of
  * device memory on every GPU the library runs on, held until the process ends) instead of scratch_dev.  The call
  * allocates and frees nothing.  batch * vocab must not exceed WWW_SAMPLE_STATIC_MAX_FLOATS (enough for 64 rows of a

@@ -25,8 +25,8 @@
 // on lies in the first RESERVED floats of every chunk's part of the scratch buffer, which receive their probabilities
 // last.
 // Measured at 64 rows of 128 256 tokens: 849 -> 45 us (12 + 18 + 15; the 99 MB the first two launches cannot avoid moving
-// take 19 us), 39 us for one row.  Rows of up to 8192 tokens fit one workgroup's registers and take one launch: 21 us at
-// 8192 tokens, where the three launches take 28 (64 rows; 43 against 47 us for 512 rows).
+// take 19 us), 32 us for one row.  Rows of up to 8192 tokens fit one workgroup's registers and take one launch: 18 us at
+// 8192 tokens, where the three launches take 27 (64 rows; 36 against 45 us for 512 rows).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

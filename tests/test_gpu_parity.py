@@ -296,7 +296,7 @@ def test_results_do_not_depend_on_what_device_memory_held_before():
 # ------------------------------------------------------------------ the largest sizes a configuration may name
 def test_widest_model_the_configuration_allows():
     """d_model 8192, the documented maximum: every one of the 64 entries per token of the decode path's sum-of-squares
-    table and of the 32 of the prefill path's is in use, and the QKV matrix has 80 row tiles of 128"""
+    table and, in calls that take tiles of 128 rows, of the prefill path's is in use, and the QKV matrix has 80 row tiles of 128"""
     shape = synth.ModelShape("max8192", 2, 8192, 64, 8, 128, 2048, 1024, 1e-5, 5e5, synth.WDTYPE_BF16, seed=51)
     lens = 1 + synth.uniform_i32(51, 11, 40, 30)
     lens[0], lens[1] = 300, 1
@@ -304,7 +304,7 @@ def test_widest_model_the_configuration_allows():
 
 
 def test_largest_batch_the_configuration_allows():
-    """1024 sequences in one prefill call and in every decode step (16 groups of 64 tokens per decode GEMM)"""
+    """1024 sequences in one prefill call and in every decode step (the decode GEMMs take them in groups of 64 or 128 tokens)"""
     lens = 1 + synth.uniform_i32(52, 11, 1024, 20)
     check(run_job(MID64, lens, 2, seed=94, min_rows=WIDE_ROWS), "batch 1024")
 
@@ -313,7 +313,7 @@ def test_largest_batch_the_configuration_allows():
 def test_batches_so_large_that_no_decode_gemm_splits_k(shape):
     """576 sequences on the 1B-wide layers: nine groups of 64 tokens times the row tiles of every matrix exceed the
     number of compute units, so the QKV, O and down GEMMs run without split-K and finish in their own epilogues (no
-    hand-over), and the gate/up GEMM runs its eight-wavefront form once per token group"""
+    hand-over), and the gate/up GEMM runs its eight-wavefront form once per token group of 64 or 128"""
     lens = 1 + synth.uniform_i32(53, 11, 576, 6)
     check(run_job(shape, lens, 2, seed=95, gain_std=0.05, min_rows=WIDE_ROWS), f"{shape.name} batch 576")
 

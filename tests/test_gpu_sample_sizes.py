@@ -1,8 +1,10 @@
 """GPU: the sampling kernels at the sizes where their paths meet: one workgroup per row up to 8192 tokens, chunks beyond;
 rows whose decisive bin holds more elements than the lists (flat rows, ties over the whole row); masked tokens.  Checked
 against the fp64 oracle: the token is a nucleus member, the draw falls into its interval of the running mass, and the
-scratch buffer holds the probabilities up to one factor per row.  Bounds: a score log2(e) * logit / T of up to 60 is
-rounded to 2^-24 relative, an error of 60 * 6e-8 = 4e-6 in the exponent and of 2.5e-6 in a probability."""
+scratch buffer holds the probabilities up to one factor per row.  Bound: a probability is 2^a with a = (x - max) *
+log2(e) / T, whatever the size of the scores themselves; the difference, the factor and the product are each rounded to fp32, so a
+is off by at most 3 * 2^-24 * |a| and 2^a by 1.3e-7 * |a| of itself: at most 7e-8 of the largest probability, and less than
+6e-6 for a sum of members down to 2^-44 (scores far outside the ones here: test_gpu_sample_edges.py)."""
 import numpy as np
 import pytest
 

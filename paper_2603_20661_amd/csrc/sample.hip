@@ -55,9 +55,10 @@ constexpr int WAVES = TPB / 64;
 
 typedef unsigned long long u64;
 
-// bin of a score, clamped far outside the range of ordinary scores (NaN falls to the bottom)
-__device__ __forceinline__ int bin_of(float t) {
-  return (int)floorf(fminf(fmaxf(t * (float)(1 << BINS_PER_OCTAVE_LOG2), -536870912.f), 536870912.f));
+// bin of a score, clamped far outside the range of ordinary scores (NaN falls to the bottom: the median of a NaN is the least of
+// the others)
+__device__ __forceinline__ int bin_of(float logit, float c) {
+  return (int)floorf(__builtin_amdgcn_fmed3f(logit * (c * (float)(1 << BINS_PER_OCTAVE_LOG2)), -536870912.f, 536870912.f));
 }
 // number of a bin, counted down from bin `top`; the last one takes everything below
 __device__ __forceinline__ int bin_number(int top, int bin) { return min(BINS - 1, max(0, top - bin)); }
@@ -281,7 +282,7 @@ __global__ __launch_bounds__(TPB) void sample_row_kernel(const float* logits, in
   if (tid < BINS) S.hist[tid] = 0;
   if (tid == 0) { S.count = 0; S.klo = 0xFFFFFFFFu; S.khi = 0u; }
   m = finite(block_max<TPB>(m, S.red));
-  const int top = bin_of(m * c);
+  const int top = bin_of(m, c);
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
     const int i = k * TPB + tid;
@@ -289,7 +290,7 @@ __global__ __launch_bounds__(TPB) void sample_row_kernel(const float* logits, in
       const float e = prob(x[k], c, m, 0.f);
       if (!in_place) scratch[(int64_t)row * V + i] = e;
       const u64 w = mass_of(e, unit);
-      if (w) atomicAdd(&S.hist[bin_number(top, bin_of(x[k] * c))], w);
+      if (w) atomicAdd(&S.hist[bin_number(top, bin_of(x[k], c))], w);
     }
   }
   __syncthreads();
@@ -298,7 +299,7 @@ __global__ __launch_bounds__(TPB) void sample_row_kernel(const float* logits, in
   uint32_t klo = 0xFFFFFFFFu, khi = 0u;
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
-    const bool cand = k * TPB + tid < V && bin_number(top, bin_of(x[k] * c)) == S.bin;
+    const bool cand = k * TPB + tid < V && bin_number(top, bin_of(x[k], c)) == S.bin;
     const int at = list_place(cand, &S.count);
     if (cand) {
       const uint32_t key = key_of(x[k]);
@@ -400,14 +401,14 @@ __global__ __launch_bounds__(256) void sample_bins_kernel(const float* __restric
 #pragma unroll
   for (int k = 0; k < COPIES; ++k) hist[k * 256 + tid] = 0;
   m = finite(block_max<256>(m, red));
-  const int top = bin_of(m * c);
+  const int top = bin_of(m, c);
   const float r = way_down(m, c);
   for (int base = 0; base < n; base += SUB) {
     if (n > SUB) load(base);
 #pragma unroll
     for (int k = 0; k < SUB / 256; ++k) {
       const u64 w = mass_of(prob(x[k], c, m, r), unit);  // (0 for the -inf behind the end)
-      if (w) atomicAdd(&hist[bin_number(top, bin_of(x[k] * c)) * COPIES + (tid & (COPIES - 1))], w);
+      if (w) atomicAdd(&hist[bin_number(top, bin_of(x[k], c)) * COPIES + (tid & (COPIES - 1))], w);
     }
   }
   __syncthreads();
@@ -466,14 +467,14 @@ __global__ __launch_bounds__(256) void sample_split_kernel(const float* __restri
   load_bins(0);
   float head;
   const float m = row_max(row, chunk, n_chunks, head);
-  const int top = bin_of(m * c);
+  const int top = bin_of(m, c);
   const double oct = octave_of(m, c);
   __syncthreads();
   for (int k0 = 0; k0 < n_chunks; k0 += NB) {
     if (k0) load_bins(k0);
     const int k_lane = k0 + (tid & (NB - 1));  // lane k: chunk k0 + k
     const float mc = k0 < 64 ? __shfl(head, k_lane) : row[(int64_t)min(k_lane, n_chunks - 1) * chunk];
-    const int down = top - bin_of(mc * c), back = octaves_between(oct, octave_of(mc, c));
+    const int down = top - bin_of(mc, c), back = octaves_between(oct, octave_of(mc, c));
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
       const u64 v = k0 + k < n_chunks ? shifted(w[k], __builtin_amdgcn_readlane(back, k)) : 0ull;
@@ -490,7 +491,7 @@ __global__ __launch_bounds__(256) void sample_split_kernel(const float* __restri
     for (int k = 0; k < SUB / 256; ++k) {
       const int i = base + k * 256 + tid;
       if (i >= RESERVED && i < n) region[i] = prob(x[k], c, m, 0.f);
-      const bool cand = i < n && bin_number(top, bin_of(x[k] * c)) == b;
+      const bool cand = i < n && bin_number(top, bin_of(x[k], c)) == b;
       const int at = list_place(cand, &count);
       if (cand && at < CAND_MAX) region[HEAD + at] = x[k];
     }
@@ -504,7 +505,7 @@ __global__ __launch_bounds__(256) void sample_split_kernel(const float* __restri
     if (n > SUB) load(base);
 #pragma unroll
     for (int k = 0; k < SUB / 256; ++k)
-      if (base + k * 256 + tid < n && bin_number(top, bin_of(x[k] * c)) == b) { lo = min(lo, key_of(x[k])); hi = max(hi, key_of(x[k])); }
+      if (base + k * 256 + tid < n && bin_number(top, bin_of(x[k], c)) == b) { lo = min(lo, key_of(x[k])); hi = max(hi, key_of(x[k])); }
   }
   wave_range(lo, hi);
   if ((tid & 63) == 0) { klo[tid >> 6] = lo; khi[tid >> 6] = hi; }
@@ -571,10 +572,10 @@ __global__ __launch_bounds__(TPB) void sample_pick_kernel(const float* __restric
   }
   float head;
   const float m = row_max(row, chunk, n_chunks, head);
-  const int top = bin_of(m * c);
+  const int top = bin_of(m, c);
   const double oct = octave_of(m, c);
   struct Ref { float m, r; int down, back; };  // largest logit of a chunk, its way down, and how far bins and masses lie below the row's
-  auto ref_of = [&](float mc) __attribute__((always_inline)) { return Ref{mc, way_down(mc, c), top - bin_of(mc * c), octaves_between(oct, octave_of(mc, c))}; };
+  auto ref_of = [&](float mc) __attribute__((always_inline)) { return Ref{mc, way_down(mc, c), top - bin_of(mc, c), octaves_between(oct, octave_of(mc, c))}; };
   const Ref own = ref_of(__shfl(head, wave));
   __syncthreads();
   const bool listed = !S.overflow;
@@ -623,7 +624,7 @@ __global__ __launch_bounds__(TPB) void sample_pick_kernel(const float* __restric
 #pragma unroll 8
     for (int i = wave % team * 64 + lane; i < n; i += 64 * team) {
       const float v = lg[f + i];
-      if (bin_number(top, bin_of(v * c)) == b) use(key_of(v), [&] { return shifted(mass_of(prob(v, c, R.m, R.r), unit), R.back); });
+      if (bin_number(top, bin_of(v, c)) == b) use(key_of(v), [&] { return shifted(mass_of(prob(v, c, R.m, R.r), unit), R.back); });
     }
   };
   uint32_t tau;
@@ -748,7 +749,7 @@ WWW_EXPORT int www_sample_top_p(const float* logits_dev, int32_t batch, int32_t 
     return WWW_E_INVALID_ARG;
   }
   const hipStream_t st = (hipStream_t)hip_stream;
-  const float c = std::min(1.4426950408889634f / temperature, FLT_MAX);  // (finite: no 0 * inf at the largest logit)
+  const float c = std::min(1.4426950408889634f / temperature, FLT_MAX / 8.f);  // (finite, times the bins of an octave too: no 0 * inf)
   if (c == 0.f) top_p = 1.f;  // infinite temperature: equal probabilities, which enter the nucleus together
   const float unit = mass_unit(vocab);
   if (int rc = allow_lds()) return rc;

@@ -13,6 +13,7 @@
 // the library is built with hidden visibility; only the C ABI is exported
 #define WWW_EXPORT extern "C" __attribute__((visibility("default")))
 
+uint64_t small_gemm_partial_bytes(int NRG);
 int decode_gemm_ksplit(int NRG, int KB, int MT);
 hipError_t prefill_allow_lds();
 uint64_t prefill_partial_bytes(int maxT, int NRG, int KB);
@@ -119,7 +120,7 @@ struct Plan {
   std::vector<uint64_t> qk_gain;                // gains of the query / key head normalisation, in packed row order
   uint64_t lm_head8, g_lm;
   uint64_t zero_begin, zero_end;  // region cleared at load (counters, padded activation buffers)
-  uint64_t h, ssq, q, xq, xo, xa, partial, attn_part, counters, logits, last_tok, argmax_val, argmax_idx, attn_hdr, attn_start, attn_pref;
+  uint64_t h, ssq, ssq_rows, q, xq, xo, xa, partial, attn_part, counters, logits, last_tok, argmax_val, argmax_idx, attn_hdr, attn_start, attn_pref;
   uint64_t hp, ssq_p, xn, qp, op, ap, row_seq, row_pos, tile_seq, tile_q0, meta;
   uint64_t val_words, val_bitmap, val_bitmap_bytes;  // argument validation (WWW_VALIDATE=1): result words, one bit per KV block
 };
@@ -205,6 +206,7 @@ static void make_plan(const www_config* c, Plan& p) {
         if (ks > 1 && bytes > part) part = bytes;
       }
   }
+  for (int n : {s.QKVN, s.d}) part = part > small_gemm_partial_bytes(n / 16) ? part : small_gemm_partial_bytes(n / 16);
   const uint64_t pre[4] = {prefill_partial_bytes(s.maxT, s.QKVN / 16, s.d / 32), prefill_partial_bytes(s.maxT, s.d / 16, s.QD / 32),
                            prefill_partial_bytes(s.maxT, 2 * s.F / 16, s.d / 32), prefill_partial_bytes(s.maxT, s.d / 16, s.Fp / 32)};
   for (uint64_t b : pre) part = part > b ? part : b;
@@ -214,6 +216,7 @@ static void make_plan(const www_config* c, Plan& p) {
   // the decode attention's records: two per wavefront that has work, and no more of those than key pairs in the batch
   const uint64_t max_pairs = (uint64_t)s.maxB * s.Hkv * (((uint64_t)s.max_pos + 31) / 32);
   p.attn_part = take(2 * (max_pairs < MAX_ATTN_WAVES ? max_pairs : MAX_ATTN_WAVES) * s.G * (s.hd + 4) * 4);
+  p.ssq_rows = take((uint64_t)SSQ_ROWS * (s.maxB < 32 ? s.maxB : 32) * 4);
   p.logits = take((uint64_t)s.maxB * s.V * 4);
   p.last_tok = take((uint64_t)s.maxB * 4);
   p.attn_hdr = take(16);
@@ -462,7 +465,7 @@ WWW_EXPORT int www_model_load(const www_config* cfg, const void* weights_dev, vo
   m->kv_plane = (int64_t)cfg->num_kv_blocks * s.Hkv * KV_BS * s.hd;
   m->kv_scales = (float*)(m->kv + (int64_t)2 * s.L * m->kv_plane);
   m->kv_scale_plane = (int64_t)cfg->num_kv_blocks * s.Hkv * 32;
-  m->h = (float*)(ws + p.h); m->ssq = (float*)(ws + p.ssq); m->q_hi = (uint16_t*)(ws + p.q); m->q_lo = m->q_hi + (size_t)s.MTmax * 16 * s.QD;
+  m->h = (float*)(ws + p.h); m->ssq = (float*)(ws + p.ssq); m->ssq_rows = (float*)(ws + p.ssq_rows); m->q_hi = (uint16_t*)(ws + p.q); m->q_lo = m->q_hi + (size_t)s.MTmax * 16 * s.QD;
   m->xq = (uint16_t*)(ws + p.xq); m->xo = (uint16_t*)(ws + p.xo); m->xa = (uint16_t*)(ws + p.xa);
   m->partial = (float*)(ws + p.partial); m->attn_part = (float*)(ws + p.attn_part); m->counters = (unsigned long long*)(ws + p.counters);
   m->logits_buf = (float*)(ws + p.logits); m->last_tok = (int*)(ws + p.last_tok);

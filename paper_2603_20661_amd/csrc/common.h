@@ -184,6 +184,7 @@ struct www_model {
   // decode-path buffers
   float* h;        // [maxB][d] residual stream
   float* ssq;      // [maxB][SSQ_TILES] partial sums of squares of h, one per row tile of the producing GEMM
+  float* ssq_rows; // [up to 32 tokens][SSQ_ROWS] the same of a step of up to 32 tokens, one per row group
   uint16_t *q_hi, *q_lo;  // [maxB][QD] rotated, pre-scaled queries as fp16 hi + lo
   uint16_t* xq;        // packed activations feeding the QKV / gate-up / lm_head GEMMs (K = d)
   uint16_t* xo;        // packed attention output feeding the O projection (K = QD)
@@ -221,6 +222,7 @@ struct www_model {
 #define MAX_ATTN_WAVES 4096  // upper bound of the decode attention grid, in wavefronts (sizes its plan and its records)
 #define PSSQ 64            // entries per token of the prefill path's sum-of-squares table (d_model / 128 row tiles at most)
 #define SSQ_TILES 64       // most row tiles of a residual-producing GEMM (d_model / 128)
+#define SSQ_ROWS 512       // most row groups of one (d_model / 16)
 #define GEMM_TILE_ROWS 128 // rows of W per workgroup of the skinny GEMM
 #define MAX_KSPLIT 16
 

@@ -6,17 +6,7 @@
 
 #include <vector>
 
-#include "common.h"
-
-#define NEG_INF (-__builtin_inff())
-
-__device__ __forceinline__ f16x8 as_f16x8(u32x4 v) { return __builtin_bit_cast(f16x8, v); }
-
-// offset (in elements) of column k of token t in a packed activation buffer with MT token groups
-__device__ __forceinline__ int64_t packed_x_offset(int k, int t, int MT, int hl) {
-  int kb = k >> 5, g = (k & 31) >> 3, e = k & 7;
-  return ((((int64_t)kb * MT + (t >> 4)) * 2 + hl) * 64 + g * 16 + (t & 15)) * 8 + e;
-}
+#include "decode_gemm.h"
 
 // ------------------------------------------------------------------------------------------------
 // Embedding gather: h = E[token]; sum of squares; packed (h * gain) for the first QKV GEMM.
@@ -49,87 +39,11 @@ __global__ __launch_bounds__(256) void embed_pack_kernel(const int32_t* __restri
     if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
     __syncthreads();
   }
-  if (threadIdx.x == 0) ssq[(int64_t)t * SSQ_TILES] = red[0];  // row t of the [token][row tile] table; one entry in use
+  if (threadIdx.x == 0) ssq[(int64_t)t * (MT <= 2 ? SSQ_ROWS : SSQ_TILES)] = red[0];  // row t of the [token][row tile] table; one entry in use
 }
 
 // ------------------------------------------------------------------------------------------------
 // Skinny GEMM: Y^T[n][t] = sum_k W[n][k] X[t][k] for up to 128 tokens per workgroup pass.
-enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LOGITS = 3 };
-
-struct GemmP {
-  const u32x4* W;    // packed weights, 16-byte units (fp16 fragments, or FP8 codes of two k blocks)
-  const u32x4* Wlo;  // low-order plane (fp32 sources) or null
-  float wfactor;     // FP8 weights: the matrix's scale, applied to the result
-  const u32x2* Wscale;  // int4 weights: four fp16 group scales per (chunk of 4 k blocks, row)
-  int NRG, KB;       // row groups of 16, k blocks of 32
-  const u32x4* X;    // packed activations
-  int MT, M;         // token groups in X, valid tokens
-  int kb_per_split, ksplit;
-  int row_tiles, zbs;  // grid: 8 * ceil(row_tiles / 8) * ksplit * zbs workgroups
-  int fence_handover;  // 1: workgroups of one row tile may sit behind different L2s
-  float* partial;    // [ksplit][zbs][row_tiles] tiles of 128 rows x 16 MTK tokens
-  unsigned long long* counters;  // [zbs][row_tiles]: arrivals in bits 0-7, arrivals per XCD in eight 5-bit fields above
-  int* fault_flag;   // host-visible; set when the splits of a row tile turn out to sit on different XCDs
-  const float* ssq_in;  // [token][SSQ_TILES]; row scale = rsqrt(sum of the first n_ssq_in entries / dim + eps); null: no scale
-  int n_ssq_in;
-  float inv_dim, eps;
-  // QKV epilogue
-  uint16_t *q_hi, *q_lo;
-  float qscale;
-  uint16_t *kplane, *vplane;  // this layer's K and V planes of the pool (16-bit codes)
-  float* kvscale;             // and its plane of scales
-  const int32_t *seq_lens, *table;
-  int mbs, hd, Hq, Hkv;
-  const float2* rope;
-  const float* qk_gain;  // models with normalised query / key heads: [2][hd] gains in packed row order; null otherwise
-  // residual epilogue
-  float* h;
-  const float* gain_next;
-  uint16_t* xnext;
-  float* ssq_out;
-  int d;
-  // SwiGLU epilogue
-  uint16_t* xa;
-  int F;
-  // logits epilogue
-  float* logits;
-  int V;
-};
-
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-
-// 8 FP8 E4M3 codes (two 32-bit words, lowest byte first) -> 8 fp16 values, exact (|value| <= 448); the conversion
-// instruction widens two codes at a time.
-__device__ __forceinline__ f16x8 fp8x8_to_f16x8(uint32_t lo, uint32_t hi) {
-  const f16x2 a = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(lo, 1.0f, false), b = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(lo, 1.0f, true);
-  const f16x2 c = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(hi, 1.0f, false), d = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(hi, 1.0f, true);
-  return __builtin_shufflevector(__builtin_shufflevector(a, b, 0, 1, 2, 3), __builtin_shufflevector(c, d, 0, 1, 2, 3), 0, 1, 2, 3, 4, 5, 6, 7);
-}
-
-typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
-
-// 8 four-bit codes (one 32-bit word, the code of column e in nibble e) -> 8 fp16 values (code - 8) * scale.  A code n
-// is planted in the mantissa of the fp16 number 1024 (0x6400 | n = 1024 + n, exact), 1032 is subtracted and the result
-// multiplied by the group's scale, two values per instruction; with a scale of 8 significant bits (bf16) the product
-// is exact.
-__device__ __forceinline__ f16x8 int4x8_to_f16x8(uint32_t w, f16x2 scale) {
-  const uint32_t even = w & 0x0F0F0F0Fu, odd = (w >> 4) & 0x0F0F0F0Fu;  // codes of columns 0,2,4,6 / 1,3,5,7, one per byte
-  const f16x2 off = {(_Float16)1032.f, (_Float16)1032.f};
-  f16x2 v[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    // low half: byte i of `even`, high half: byte i of `odd`
-    const uint32_t pair = __builtin_amdgcn_perm(odd, even, 0x0C040C00u + 0x00010001u * i) | 0x64006400u;
-    v[i] = (__builtin_bit_cast(f16x2, pair) - off) * scale;
-  }
-  return __builtin_shufflevector(__builtin_shufflevector(v[0], v[1], 0, 1, 2, 3), __builtin_shufflevector(v[2], v[3], 0, 1, 2, 3), 0, 1, 2, 3, 4, 5, 6, 7);
-}
-
-// WMODE: 0 = fp16 weights; 1 = fp16 hi + lo planes (fp32 sources); 2 = FP8 codes, two k blocks per 16-byte unit, widened
-// to fp16 in registers just before the MFMAs (the matrix's scale multiplies the result in the epilogue); 3 = int4 codes,
-// four k blocks (one chunk) per 16-byte unit, widened and multiplied by their group's scale in registers
-enum { WMODE_F16 = 0, WMODE_SPLIT = 1, WMODE_FP8 = 2, WMODE_INT4 = 3 };
-
 // KH = 1: four wavefronts, each multiplies its two row groups with all four k blocks of a chunk.  KH = 2: eight
 // wavefronts (two per SIMD); wavefront w and w + 4 own the same two row groups and take k blocks 0,1 / 2,3 of every
 // chunk, so each issues half of the MFMAs and one can issue while its SIMD partner waits for memory; the two partial
@@ -186,12 +100,16 @@ __global__ __launch_bounds__(256 * KH, MTK == 8 ? 1 : 2 / KH) void skinny_gemm_k
   // Inputs of the epilogue that hang off dependent loads (RMSNorm scale; position and KV block of each token) are
   // requested at kernel entry together with the first weights and activations, and only touched once that first chunk
   // has arrived, so they never put a memory round trip in front of the streaming loop.
-  // Sum of squares of a token: wavefront w owns token group w (and w + 4; every workgroup of the grid reads the same small table,
-  // so each reads it once, not once per wavefront).  Lane group g = lane/16 reads entries 16g .. 16g+15 of the token's
-  // row (four 16-byte loads, always in bounds; entries past n_ssq_in are masked), adds them in index order, and the
-  // four groups are combined by two cross-lane exchanges: a fixed order, so the scale is the same in every workgroup.
+  // Sum of squares of a token, the same in every workgroup (a fixed order).  More than 32 tokens (at most 64 entries, one per
+  // 128-row tile): wavefront w owns token group w (and w + 4), lane group g = lane/16 reads entries 16g .. 16g+15 of the
+  // token's row (four 16-byte loads, always in bounds; entries past n_ssq_in are masked), adds them in index order, and the
+  // four groups are combined by two cross-lane exchanges.  Up to 32 tokens (one entry per row group of 16, from
+  // small_gemm_kernel): 16 / MTK neighbouring threads read a token's entries, 4 MTK 16-byte pieces each, which covers
+  // d_model = 4096, and exchange their sums.
+  constexpr bool SQ_ROWS = MTK <= 2;
+  constexpr int SUB = 16 / (SQ_ROWS ? MTK : 1), NPC = SQ_ROWS ? 4 * MTK : 1;
   constexpr int NSQ = (MTK + 3) / 4;
-  f32x4 ssq_raw[NSQ][4];
+  f32x4 ssq_raw[NSQ][4], sq_rows[NPC];
   int pos_pre[MTK];
   int tok_c[MTK];
 #pragma unroll
@@ -200,7 +118,13 @@ __global__ __launch_bounds__(256 * KH, MTK == 8 ? 1 : 2 / KH) void skinny_gemm_k
     pos_pre[tb] = 0;
     if constexpr (EPI == EPI_QKV) pos_pre[tb] = p.seq_lens[tok_c[tb]] - 1;
   }
-  if (p.ssq_in && wave < MTK && khalf == 0) {
+  const float* sq_row = p.ssq_in + (int64_t)min(tb0 * 16 + tid / SUB, p.M - 1) * SSQ_ROWS;
+  if constexpr (SQ_ROWS) {
+    if (p.ssq_in && khalf == 0) {
+#pragma unroll
+      for (int i = 0; i < NPC; ++i) sq_rows[i] = *reinterpret_cast<const f32x4*>(sq_row + (i * SUB + tid % SUB) * 4);
+    }
+  } else if (p.ssq_in && wave < MTK && khalf == 0) {
 #pragma unroll
     for (int q = 0; q < NSQ; ++q) {
       const int t = min((tb0 + wave + 4 * q) * 16 + (lane & 15), p.M - 1);
@@ -213,7 +137,22 @@ __global__ __launch_bounds__(256 * KH, MTK == 8 ? 1 : 2 / KH) void skinny_gemm_k
   int blk_pre[MTK];
   // before the first barrier: reduce the sums and publish the scales; table loads for the KV slots go out
   auto finish_prefetch = [&]() __attribute__((always_inline)) {
-    if (p.ssq_in && wave < MTK && khalf == 0) {
+    if constexpr (SQ_ROWS) {
+      if (p.ssq_in && khalf == 0) {
+        float s = 0.f;
+        auto add = [&](f32x4 v, int e0) __attribute__((always_inline)) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) s += e0 + e < p.n_ssq_in ? v[e] : 0.f;
+        };
+#pragma unroll
+        for (int i = 0; i < NPC; ++i) add(sq_rows[i], (i * SUB + tid % SUB) * 4);
+        for (int i = NPC; i * SUB * 4 < p.n_ssq_in; ++i)
+          add(*reinterpret_cast<const f32x4*>(sq_row + (i * SUB + tid % SUB) * 4), (i * SUB + tid % SUB) * 4);
+#pragma unroll
+        for (int o = SUB / 2; o > 0; o >>= 1) s += __shfl_xor(s, o);
+        if (tid % SUB == 0) s_scale[tid / SUB] = rsqrtf(s * p.inv_dim + p.eps);
+      }
+    } else if (p.ssq_in && wave < MTK && khalf == 0) {
 #pragma unroll
       for (int q = 0; q < NSQ; ++q) {
         float s = 0.f;
@@ -683,7 +622,7 @@ __global__ __launch_bounds__(256 * KH, MTK == 8 ? 1 : 2 / KH) void skinny_gemm_k
     __syncthreads();
     if (tid < MTK * 16) {
       int t = tb0 * 16 + tid;
-      if (t < p.M) p.ssq_out[(int64_t)t * SSQ_TILES + tile] = red[0][tid] + red[1][tid] + red[2][tid] + red[3][tid];
+      if (t < p.M) p.ssq_out[(int64_t)t * (SQ_ROWS ? SSQ_ROWS : SSQ_TILES) + tile] = red[0][tid] + red[1][tid] + red[2][tid] + red[3][tid];
     }
   }
 }
@@ -1173,7 +1112,7 @@ __global__ __launch_bounds__(64) void argmax_final_kernel(const float* __restric
 // Workgroups a skinny GEMM should spread over (split-K is used when the row tiles alone are fewer): one per compute
 // unit, so that no compute unit carries two of a kernel's workgroups while others carry one.  Tunable through the
 // environment variable WWW_GEMM_WG_TARGET, read once.
-static int wg_target() {
+int decode_wg_target() {
   static int v = 0;
   if (!v) {
     const char* e = getenv("WWW_GEMM_WG_TARGET");
@@ -1191,7 +1130,7 @@ static int wg_target() {
 }
 
 static void choose_split(int row_tiles, int zb, int KB, int* ksplit, int* kb_per_split) {
-  int want = wg_target() / (row_tiles * zb);
+  int want = decode_wg_target() / (row_tiles * zb);
   if (want < 1) want = 1;
   if (want > MAX_KSPLIT) want = MAX_KSPLIT;
   int per = (KB + want - 1) / want;
@@ -1215,6 +1154,7 @@ int decode_gemm_ksplit(int NRG, int KB, int MT) {
 
 template <int EPI>
 static void launch_gemm(www_model* m, GemmP& p, int MT, hipStream_t st) {
+  if (small_gemm_takes(m, EPI, p.NRG, p.KB, p.M)) return launch_small_gemm<EPI>(m, p, st);
   const int row_tiles = (p.NRG + 7) / 8;
   // Above 64 tokens the two wide GEMMs may take 128 tokens per workgroup: every compute unit takes in about 55 KB per us, and
   // 128 rows x 128 tokens need 24 KB per k block where two workgroups of 64 tokens need 32 (with FP8 weights 20 and 24).
@@ -1225,7 +1165,7 @@ static void launch_gemm(www_model* m, GemmP& p, int MT, hipStream_t st) {
   // 36 -> 52 us), and so are int4 weights (a step of 100 sequences 7250 -> 7700 us).  A range of k is never split there: more
   // than half of the compute units have a row tile each, or there would be no round to save.
   constexpr bool wide_epi = EPI == EPI_SWIGLU || EPI == EPI_LOGITS;
-  auto rounds = [&](int tokens) { return (float)((row_tiles * ((p.M + tokens - 1) / tokens) + wg_target() - 1) / wg_target()); };
+  auto rounds = [&](int tokens) { return (float)((row_tiles * ((p.M + tokens - 1) / tokens) + decode_wg_target() - 1) / decode_wg_target()); };
   const bool wide = wide_epi && !m->int4_group && !m->wsplit && rounds(128) * (m->fp8 ? 1.9f : 1.75f) < rounds(64);
   const int mtk = MT < 8 ? MT : wide ? 8 : 4;
   const int zb = MT < 8 ? 1 : (p.M + 16 * mtk - 1) / (16 * mtk);  // (not MT / mtk: the last 64 tokens may all be padding)
@@ -1240,6 +1180,7 @@ static void launch_gemm(www_model* m, GemmP& p, int MT, hipStream_t st) {
   if (p.wfactor == 0.f) p.wfactor = 1.f;  // not set: an unscaled matrix
   dim3 grid(8 * ((row_tiles + 7) / 8) * p.ksplit * zb);
 #define LAUNCH(MTK_, WM_, KH_) hipLaunchKernelGGL((skinny_gemm_kernel<MTK_, WM_, EPI, KH_>), grid, dim3(256 * KH_), 0, st, p);
+#define LAUNCH2(WM_, KH_) { if constexpr (wide_epi) LAUNCH(2, WM_, KH_) }  // (the others: small_gemm_kernel)
 #define LAUNCH8(WM_) { if constexpr (wide_epi) LAUNCH(8, WM_, 2) }
   // With more than 32 tokens the MFMAs of a chunk take a third of a wavefront's time; in the gate/up GEMM (no split-K,
   // 32 chunks per workgroup) two wavefronts per SIMD (KH = 2) hide them behind each other's waits: 53 -> 49.5 us at 64
@@ -1253,16 +1194,17 @@ static void launch_gemm(www_model* m, GemmP& p, int MT, hipStream_t st) {
     // and not in the gate/up GEMM with two token groups side by side (70 -> 80)
     constexpr int ki = EPI == EPI_LOGITS ? 1 : 2;
     if (mtk == 1) LAUNCH(1, WMODE_INT4, 1)
-    else if (mtk == 2) LAUNCH(2, WMODE_INT4, ki)
+    else if (mtk == 2) LAUNCH2(WMODE_INT4, ki)
     else if (EPI == EPI_SWIGLU && zb > 1) LAUNCH(4, WMODE_INT4, 1)
     else LAUNCH(4, WMODE_INT4, ki)
   } else if (m->fp8) {
-    if (mtk == 1) LAUNCH(1, WMODE_FP8, 1) else if (mtk == 2) LAUNCH(2, WMODE_FP8, 1) else if (mtk == 4) LAUNCH(4, WMODE_FP8, kh4) else LAUNCH8(WMODE_FP8)
+    if (mtk == 1) LAUNCH(1, WMODE_FP8, 1) else if (mtk == 2) LAUNCH2(WMODE_FP8, 1) else if (mtk == 4) LAUNCH(4, WMODE_FP8, kh4) else LAUNCH8(WMODE_FP8)
   } else if (m->wsplit) {
-    if (mtk == 1) LAUNCH(1, WMODE_SPLIT, 1) else if (mtk == 2) LAUNCH(2, WMODE_SPLIT, 1) else LAUNCH(4, WMODE_SPLIT, 1)
+    if (mtk == 1) LAUNCH(1, WMODE_SPLIT, 1) else if (mtk == 2) LAUNCH2(WMODE_SPLIT, 1) else LAUNCH(4, WMODE_SPLIT, 1)
   } else {
-    if (mtk == 1) LAUNCH(1, WMODE_F16, 1) else if (mtk == 2) LAUNCH(2, WMODE_F16, 1) else if (mtk == 4) LAUNCH(4, WMODE_F16, kh4) else LAUNCH8(WMODE_F16)
+    if (mtk == 1) LAUNCH(1, WMODE_F16, 1) else if (mtk == 2) LAUNCH2(WMODE_F16, 1) else if (mtk == 4) LAUNCH(4, WMODE_F16, kh4) else LAUNCH8(WMODE_F16)
   }
+#undef LAUNCH2
 #undef LAUNCH8
 #undef LAUNCH
 }
@@ -1310,16 +1252,18 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
                hipStream_t st) {
   const int MT = decode_MT(batch);
   const int d = m->d;
+  float* const ssq = MT <= 2 ? m->ssq_rows : m->ssq;
   prof_mark(m, PK_EMBED, st);
   if (m->cfg.weight_dtype == WWW_DTYPE_F32)
     hipLaunchKernelGGL(embed_pack_kernel<float>, dim3(batch), dim3(256), 0, st, tok, (const float*)m->embed, d, m->layers[0].attn_norm,
-                       m->h, m->ssq, (uint16_t*)m->xq, MT);
+                       m->h, ssq, (uint16_t*)m->xq, MT);
   else
     hipLaunchKernelGGL(embed_pack_kernel<uint16_t>, dim3(batch), dim3(256), 0, st, tok, (const uint16_t*)m->embed, d,
-                       m->layers[0].attn_norm, m->h, m->ssq, (uint16_t*)m->xq, MT);
+                       m->layers[0].attn_norm, m->h, ssq, (uint16_t*)m->xq, MT);
   hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(256), (size_t)(batch + 2) * 4, st, lens, batch, m->Hkv, m->attn_waves, m->attn_hdr,
                      m->attn_start, m->attn_pref);
-  int n_ssq = 1;
+  int n_ssq = 1;  // entries per token of the sum-of-squares table: one per row group or per row tile of the GEMM that wrote it
+  auto resid_entries = [&](int KB) { return small_gemm_takes(m, EPI_RESID, d / 16, KB, batch) ? d / 16 : (d / 16 + 7) / 8; };
   const float qscale = 1.4426950408889634f / sqrtf((float)m->hd);
   for (int l = 0; l < m->L; ++l) {
     const LayerW& w = m->layers[l];
@@ -1331,7 +1275,7 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
       p.W = (const u32x4*)(w.wqkv8 ? (const void*)w.wqkv8 : (const void*)w.wqkv); p.Wlo = (const u32x4*)w.wqkv_lo; p.wfactor = w.sqkv; p.Wscale = (const u32x2*)w.gqkv;
       p.NRG = m->QKVN / 16; p.KB = d / 32;
       p.X = (const u32x4*)m->xq; p.M = batch;
-      p.ssq_in = m->ssq; p.n_ssq_in = n_ssq; p.inv_dim = 1.f / d; p.eps = m->cfg.rms_eps;
+      p.ssq_in = ssq; p.n_ssq_in = n_ssq; p.inv_dim = 1.f / d; p.eps = m->cfg.rms_eps;
       p.q_hi = m->q_hi; p.q_lo = m->q_lo; p.qscale = qscale; p.kplane = kplane; p.vplane = vplane; p.kvscale = kvscale; p.seq_lens = lens; p.table = table; p.mbs = m->cfg.max_blocks_per_seq;
       p.hd = m->hd; p.Hq = m->Hq; p.Hkv = m->Hkv; p.rope = m->rope; p.qk_gain = w.qk_gain;
       prof_mark(m, PK_QKV, st);
@@ -1359,17 +1303,17 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
       p.W = (const u32x4*)(w.wo8 ? (const void*)w.wo8 : (const void*)w.wo); p.Wlo = (const u32x4*)w.wo_lo; p.wfactor = w.so; p.Wscale = (const u32x2*)w.go;
       p.NRG = d / 16; p.KB = m->QD / 32;
       p.X = (const u32x4*)m->xo; p.M = batch;
-      p.h = m->h; p.gain_next = w.ffn_norm; p.xnext = (uint16_t*)m->xq; p.ssq_out = m->ssq; p.d = d;
+      p.h = m->h; p.gain_next = w.ffn_norm; p.xnext = (uint16_t*)m->xq; p.ssq_out = ssq; p.d = d;
       prof_mark(m, PK_OPROJ, st);
       launch_gemm<EPI_RESID>(m, p, MT, st);
-      n_ssq = (d / 16 + 7) / 8;
+      n_ssq = resid_entries(m->QD / 32);
     }
     {
       GemmP p = {};
       p.W = (const u32x4*)(w.wgu8 ? (const void*)w.wgu8 : (const void*)w.wgu); p.Wlo = (const u32x4*)w.wgu_lo; p.wfactor = w.sgu; p.Wscale = (const u32x2*)w.ggu;
       p.NRG = 2 * m->F / 16; p.KB = d / 32;
       p.X = (const u32x4*)m->xq; p.M = batch;
-      p.ssq_in = m->ssq; p.n_ssq_in = n_ssq; p.inv_dim = 1.f / d; p.eps = m->cfg.rms_eps;
+      p.ssq_in = ssq; p.n_ssq_in = n_ssq; p.inv_dim = 1.f / d; p.eps = m->cfg.rms_eps;
       p.xa = (uint16_t*)m->xa; p.F = m->F;
       prof_mark(m, PK_GATEUP, st);
       launch_gemm<EPI_SWIGLU>(m, p, MT, st);
@@ -1380,9 +1324,10 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
       p.NRG = d / 16; p.KB = m->Fp / 32;
       p.X = (const u32x4*)m->xa; p.M = batch;
       p.h = m->h; p.gain_next = (l + 1 < m->L) ? m->layers[l + 1].attn_norm : m->final_norm;
-      p.xnext = (uint16_t*)m->xq; p.ssq_out = m->ssq; p.d = d;
+      p.xnext = (uint16_t*)m->xq; p.ssq_out = ssq; p.d = d;
       prof_mark(m, PK_DOWN, st);
       launch_gemm<EPI_RESID>(m, p, MT, st);
+      n_ssq = resid_entries(m->Fp / 32);
     }
   }
   float* lg = logits ? logits : m->logits_buf;
@@ -1391,7 +1336,7 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
     p.W = (const u32x4*)(m->lm_head8 ? (const void*)m->lm_head8 : (const void*)m->lm_head); p.Wlo = (const u32x4*)m->lm_head_lo; p.wfactor = m->s_lm; p.Wscale = (const u32x2*)m->g_lm;
     p.NRG = m->V / 16; p.KB = d / 32;
     p.X = (const u32x4*)m->xq; p.M = batch;
-    p.ssq_in = m->ssq; p.n_ssq_in = n_ssq; p.inv_dim = 1.f / d; p.eps = m->cfg.rms_eps;
+    p.ssq_in = ssq; p.n_ssq_in = n_ssq; p.inv_dim = 1.f / d; p.eps = m->cfg.rms_eps;
     p.logits = lg; p.V = m->V;
     prof_mark(m, PK_LMHEAD, st);
     launch_gemm<EPI_LOGITS>(m, p, MT, st);

@@ -1,0 +1,516 @@
+// Decode GEMMs for up to 32 tokens: Y^T[n][t] = sum_k W[n][k] X[t][k] with the epilogues of the decode path.
+#include <math.h>
+
+#include "decode_gemm.h"
+
+// A workgroup owns 16 R RW rows and a range of k, which it cuts over its eight wavefronts: wavefront (rw, kw) takes R row
+// groups and every KW-th chunk of KC k blocks and loads weights and activations straight into registers, D chunks ahead; no
+// LDS and no barrier in the loop.  The partial tiles are added through LDS in wavefront order.
+//
+// What bounds it: the weight stream (6.2 TB/s at best) or what a compute unit takes in (about 52 KB per us, weights and
+// activations together), plus launch, first round trip and the sum at the end, about 4 us.  In skinny_gemm_kernel a
+// workgroup has 128 rows, so a narrow GEMM needs many k splits, whose tiles meet in memory (three dependent round trips and
+// ksplit tiles read by one workgroup), and four wavefronts with one chunk in flight each wait for every chunk.  With few
+// tokens the activations are small, so a workgroup can own few rows and a long k range instead.
+// XF: fragments of activations per k block.  1: up to 8 tokens, the hi parts are the columns 0 .. 7 and the lo parts the
+// columns 8 .. 15 of one fragment (half the products and half the loads); 2: up to 16 tokens, hi and lo; 4: up to 32.
+constexpr int SG_NW = 8;
+constexpr int sg_kc(int wmode, int XF) { return XF == 4 && wmode != WMODE_INT4 ? 2 : 4; }
+// registers of one chunk
+constexpr int sg_set(int wmode, int R, int XF) {
+  return sg_kc(wmode, XF) * (R * (wmode == WMODE_F16 ? 4 : wmode == WMODE_SPLIT ? 8 : 2) + 4 * XF) - (wmode == WMODE_INT4 ? 2 * R : 0);
+}
+// four wavefronts per SIMD (128 registers) where two chunks fit, two otherwise
+constexpr int sg_eu(int wmode, int R, int XF) { return sg_set(wmode, R, XF) + 4 * R * (XF / 4) <= 40 ? 4 : 2; }
+constexpr int sg_depth(int wmode, int R, int XF) {
+  const int set = sg_set(wmode, R, XF), d = (sg_eu(wmode, R, XF) == 4 ? 88 : 150) / set;
+  return d > 4 ? 4 : d < 2 ? 2 : d;
+}
+
+template <int WMODE, int EPI, int R, int RW, int XF>
+__global__ __launch_bounds__(64 * SG_NW, sg_eu(WMODE, R, XF)) void small_gemm_kernel(const GemmP p) {
+  constexpr bool WSPLIT = WMODE == WMODE_SPLIT, W8 = WMODE == WMODE_FP8, W4 = WMODE == WMODE_INT4;
+  constexpr int D = sg_depth(WMODE, R, XF), KC = sg_kc(WMODE, XF), KW = SG_NW / RW, RT = R * RW, TB = XF == 4 ? 2 : 1;
+  static_assert(EPI != EPI_SWIGLU || R % 2 == 0, "a gate row group sits in front of its up row group");
+  static_assert(EPI == EPI_LOGITS || RT <= SG_NW, "one wavefront per row group in the epilogue");
+  __shared__ f32x4 red[KW][RT][TB][64];
+  __shared__ float s_scale[16 * TB];
+  __shared__ float s_head[2][8][16 * TB];
+  __shared__ int s_last;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), kw = wave % KW, rw = wave / KW;
+
+  // Workgroup id -> work item.  Workgroups that hand partial results over (the k splits of a row tile; in the QKV GEMM also
+  // the row tiles of a head) form a group; the members of a group get ids that are equal modulo 8, so they run behind one L2.
+  // The key and value heads, which always end with a hand-over, come first.
+  const int slot = blockIdx.x >> 3, within = slot % p.zbs;
+  const int g0 = (blockIdx.x & 7) + 8 * (slot / p.zbs);
+  if (g0 >= p.row_tiles) return;  // grid padding when the groups are not a multiple of 8
+  const int group = EPI == EPI_QKV ? p.row_tiles - 1 - g0 : g0;
+  const int split = within % p.ksplit, member = within / p.ksplit;
+  const int hrg = EPI == EPI_QKV ? p.hd >> 4 : RT;  // row groups of a group
+  const int rg0 = group * hrg + member * RT;
+  const int kb_begin = split * p.kb_per_split, nkb = min(p.KB, kb_begin + p.kb_per_split) - kb_begin;
+  const int nch = (nkb + KC - 1) / KC;
+  const int n_w = (nch - kw + KW - 1) / KW;  // chunks of this wavefront (none: it only helps with the rest)
+  // do results of other workgroups enter the epilogue?
+  const bool handover = (EPI == EPI_QKV || EPI == EPI_RESID) && (p.ksplit > 1 || (EPI == EPI_QKV && p.zbs > 1 && (group >= p.Hq || p.qk_gain)));
+
+  // token of this lane's accumulators (XF == 1: of the sum of its hi and lo columns)
+  const int tsub = lane & 15, rsub = (lane >> 4) * 4;
+  const int tlow = XF == 1 ? lane & 7 : tsub;
+  // row group this wavefront finishes (SWIGLU: the gate's, its up rows are the next)
+  const int fin = EPI == EPI_SWIGLU ? 2 * wave : wave;
+  const int n_fin = EPI == EPI_SWIGLU ? RT / 2 : handover ? hrg : RT;
+  const int frg = (handover && EPI == EPI_QKV ? group * hrg : rg0) + fin, frgc = min(frg, p.NRG - 1);
+  const int n0 = frgc * 16 + rsub;
+
+  // Operands of the epilogue are requested first; they have arrived when the first weights have.  A token's sums of squares
+  // are read by 32 / TB threads, two (four) 16-byte pieces each, which covers d_model = 4096.
+  constexpr int SUB = 32 / TB, NSQ = 2 * TB;
+  f32x4 sq[NSQ];
+  const int sq_tok = tid / SUB, sq_sub = tid % SUB;
+  const float* sq_row = p.ssq_in + (int64_t)min(sq_tok, p.M - 1) * SSQ_ROWS;
+  if (p.ssq_in) {
+#pragma unroll
+    for (int i = 0; i < NSQ; ++i) sq[i] = *reinterpret_cast<const f32x4*>(sq_row + (i * SUB + sq_sub) * 4);
+  }
+  int tok[TB], pos[TB], blk[TB];
+  f32x4 hv[TB], gv, cs[TB];
+#pragma unroll
+  for (int tb = 0; tb < TB; ++tb) {
+    tok[tb] = min(tb * 16 + tlow, p.M - 1);
+    if constexpr (EPI == EPI_QKV) pos[tb] = p.seq_lens[tok[tb]] - 1;
+    if constexpr (EPI == EPI_RESID) hv[tb] = *reinterpret_cast<const f32x4*>(p.h + (int64_t)tok[tb] * p.d + n0);
+  }
+  if constexpr (EPI == EPI_QKV) {
+    if (p.qk_gain) gv = *reinterpret_cast<const f32x4*>(p.qk_gain + (n0 / p.hd < p.Hq ? 0 : p.hd) + n0 % p.hd);
+  }
+  if constexpr (EPI == EPI_RESID) gv = *reinterpret_cast<const f32x4*>(p.gain_next + n0);
+
+  struct Set {
+    u32x4 w[W4 ? 1 : W8 ? KC / 2 : WSPLIT ? 2 * KC : KC][R];
+    u32x2 sc[R];
+    u32x4 x[KC][XF];
+  };
+  // columns without a token read the last one's lines again
+  const int xl = XF == 1 ? ((lane >> 3) & 1) * 64 + (lane & 48) + min(lane & 7, p.M - 1) : (lane & 48) + min(tsub, min(p.M, 16) - 1);
+  const int xl2 = XF == 4 ? 128 + (lane & 48) + min(tsub, p.M - 17) : 0;  // the second group of 16 tokens
+  int rgc[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) rgc[r] = min(rg0 + rw * R + r, p.NRG - 1);
+  // (loads past the end of the k range are redirected to its last valid block, their products are skipped)
+  auto load = [&](Set& s, int i) __attribute__((always_inline)) {
+    const int kb0 = kb_begin + (kw + KW * i) * KC, last = kb_begin + nkb - 1;
+    if constexpr (W4) {
+      const int chunk = min(kb0 >> 2, last >> 2);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        s.w[0][r] = p.W[((int64_t)chunk * p.NRG + rgc[r]) * 64 + lane];
+        s.sc[r] = p.Wscale[((int64_t)chunk * p.NRG + rgc[r]) * 16 + tsub];
+      }
+    } else if constexpr (W8) {
+#pragma unroll
+      for (int j = 0; j < KC / 2; ++j) {
+        const int pair = min((kb0 >> 1) + j, last >> 1);
+#pragma unroll
+        for (int r = 0; r < R; ++r) s.w[j][r] = p.W[((int64_t)pair * p.NRG + rgc[r]) * 64 + lane];
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < KC; ++j) {
+        const int64_t kb = min(kb0 + j, last);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          s.w[j][r] = p.W[(kb * p.NRG + rgc[r]) * 64 + lane];
+          if constexpr (WSPLIT) s.w[KC + j][r] = p.Wlo[(kb * p.NRG + rgc[r]) * 64 + lane];
+        }
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < KC; ++j) {
+      const int64_t kb = min(kb0 + j, last);
+#pragma unroll
+      for (int f = 0; f < XF; ++f) s.x[j][f] = p.X[kb * (128 * TB) + (f & 1) * 64 + (f < 2 ? xl : xl2)];
+    }
+  };
+  f32x4 acc[R][TB];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) acc[r][tb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto compute = [&](Set& s, int nv) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < KC; ++j) {
+      if (j >= nv) break;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        f16x8 a;
+        if constexpr (W4) {
+          const u32x4 raw = s.w[0][r];
+          const uint32_t word = j == 0 ? raw.x : j == 1 ? raw.y : j == 2 ? raw.z : raw.w, s2 = j < 2 ? s.sc[r].x : s.sc[r].y;
+          const uint32_t s16 = (j & 1) ? (s2 >> 16) : (s2 & 0xFFFFu);
+          a = int4x8_to_f16x8(word, __builtin_bit_cast(f16x2, s16 | (s16 << 16)));
+        } else if constexpr (W8) {
+          const u32x4 raw = s.w[j >> 1][r];
+          a = (j & 1) ? fp8x8_to_f16x8(raw.z, raw.w) : fp8x8_to_f16x8(raw.x, raw.y);
+        } else {
+          a = as_f16x8(s.w[j][r]);
+        }
+#pragma unroll
+        for (int f = 0; f < XF; ++f) {
+          f32x4& c = acc[r][f >> 1];
+          c = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, as_f16x8(s.x[j][f]), c, 0, 0, 0);
+          if constexpr (WSPLIT)
+            if ((f & 1) == 0) c = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(s.w[KC + j][r]), as_f16x8(s.x[j][f]), c, 0, 0, 0);
+        }
+      }
+    }
+  };
+  auto valid = [&](int i) __attribute__((always_inline)) { return min(KC, nkb - (kw + KW * i) * KC); };
+
+  Set set[D];
+#pragma unroll
+  for (int s = 0; s < D; ++s) load(set[s], s);  // (a wavefront with fewer chunks reads the last blocks again)
+  __builtin_amdgcn_sched_barrier(0);
+  if (p.ssq_in) {  // the threads of a token add its entries in a fixed order
+    auto part = [&](f32x4 v, int e0) __attribute__((always_inline)) {
+      float s = 0.f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s += e0 + e < p.n_ssq_in ? v[e] : 0.f;
+      return s;
+    };
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < NSQ; ++i) s += part(sq[i], (i * SUB + sq_sub) * 4);
+    for (int i = NSQ; i * SUB * 4 < p.n_ssq_in; ++i) s += part(*reinterpret_cast<const f32x4*>(sq_row + (i * SUB + sq_sub) * 4), (i * SUB + sq_sub) * 4);
+#pragma unroll
+    for (int o = SUB / 2; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    if (sq_sub == 0) s_scale[sq_tok] = rsqrtf(s * p.inv_dim + p.eps) * p.wfactor;
+  } else if (tid < 16 * TB) {
+    s_scale[tid] = p.wfactor;
+  }
+  if constexpr (EPI == EPI_QKV) {
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) {
+      blk[tb] = kv_block_id(p.table + (int64_t)tok[tb] * p.mbs, pos[tb]);
+      cs[tb] = *reinterpret_cast<const f32x4*>(p.rope + (int64_t)pos[tb] * (p.hd / 2) + ((n0 % p.hd) >> 1));
+    }
+  }
+  int i = 0;
+  for (; i + 2 * D <= n_w; i += D) {
+#pragma unroll
+    for (int s = 0; s < D; ++s) {
+      compute(set[s], KC);
+      load(set[s], i + s + D);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < D; ++s) {
+    if (i + s < n_w) compute(set[s], valid(i + s));
+    if (i + s + D < n_w) load(set[s], i + s + D);
+  }
+#pragma unroll
+  for (int s = 0; s < D - 1; ++s)
+    if (i + s + D < n_w) compute(set[s], valid(i + s + D));
+
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) red[kw][rw * R + r][tb][lane] = acc[r][tb];
+  __syncthreads();
+  auto sum = [&](int r, int tb) __attribute__((always_inline)) {
+    f32x4 v = red[0][r][tb][lane];
+#pragma unroll
+    for (int w = 1; w < KW; ++w) v += red[w][r][tb][lane];
+    if constexpr (XF == 1) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] += __shfl_xor(v[e], 8);
+    }
+    return v;
+  };
+  auto valid_token = [&](int tb) __attribute__((always_inline)) { return tlow == tsub && tb * 16 + tlow < p.M; };
+
+  if constexpr (EPI == EPI_LOGITS) {
+    for (int q = wave; q < RT; q += SG_NW) {
+#pragma unroll
+      for (int tb = 0; tb < TB; ++tb) {
+        const f32x4 o = sum(q, tb);
+        if (valid_token(tb) && rg0 + q < p.NRG)
+          *reinterpret_cast<f32x4*>(p.logits + (int64_t)(tb * 16 + tlow) * p.V + (rg0 + q) * 16 + rsub) = o * s_scale[tb * 16 + tlow];
+      }
+    }
+    return;
+  }
+  f32x4 v[TB], up[TB];
+  if (wave < (EPI == EPI_SWIGLU ? RT / 2 : RT)) {
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) {
+      v[tb] = sum(fin, tb);
+      if constexpr (EPI == EPI_SWIGLU) up[tb] = sum(fin + 1, tb);
+    }
+  }
+  if constexpr (EPI == EPI_QKV || EPI == EPI_RESID) {
+    if (handover) {
+      // parked as [split][row group][tb][lane]; the workgroup of the group that comes last adds the splits in order
+      const __amdgpu_buffer_rsrc_t prs = shared_rsrc(p.partial);
+      auto unit = [&](int sp, int rg, int tb) __attribute__((always_inline)) { return (uint32_t)(((sp * p.NRG + rg) * TB + tb) * 64 + lane) * 16u; };
+      if (wave < RT && rg0 + wave < p.NRG) {
+#pragma unroll
+        for (int tb = 0; tb < TB; ++tb) store_shared_f32x4(prs, unit(split, rg0 + wave, tb), v[tb]);
+      }
+      wait_own_memory_ops();
+      __syncthreads();
+      if (tid == 0) s_last = arrive_last(&p.counters[group], p.zbs, p.fence_handover, p.fault_flag);
+      __syncthreads();
+      if (!s_last) return;
+      // the fenced hand-over's other half (acquire side of the producers' release fences)
+      if (p.fence_handover) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+      if (tid == 0) __hip_atomic_store(&p.counters[group], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (wave < n_fin) {
+#pragma unroll
+        for (int tb = 0; tb < TB; ++tb) v[tb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int s0 = 0; s0 < p.ksplit; s0 += 4) {
+          f32x4 pv[4][TB];
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int tb = 0; tb < TB; ++tb) pv[u][tb] = load_shared_f32x4(prs, unit(min(s0 + u, p.ksplit - 1), frgc, tb));
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int tb = 0; tb < TB; ++tb)
+              if (s0 + u < p.ksplit) v[tb] += pv[u][tb];
+        }
+      }
+    }
+  }
+  if (wave >= n_fin) return;  // (the barriers below count the wavefronts that are left)
+#pragma unroll
+  for (int tb = 0; tb < TB; ++tb) {
+    const float scale = s_scale[tb * 16 + tlow];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[tb][e] *= scale;
+    if constexpr (EPI == EPI_SWIGLU) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) up[tb][e] *= scale;
+    }
+  }
+  if constexpr (EPI == EPI_SWIGLU) {
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) {
+      union { uint16_t s[4]; u32x2 v; } hi, lo;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) split_f16(v[tb][e] / (1.f + __expf(-v[tb][e])) * up[tb][e], hi.s[e], lo.s[e]);
+      if (valid_token(tb) && frg + 1 < p.NRG) {
+        const int f0 = (frg >> 1) * 16 + rsub;
+        *reinterpret_cast<u32x2*>(p.xa + packed_x_offset(f0, tb * 16 + tlow, TB, 0)) = hi.v;
+        *reinterpret_cast<u32x2*>(p.xa + packed_x_offset(f0, tb * 16 + tlow, TB, 1)) = lo.v;
+      }
+    }
+  } else if constexpr (EPI == EPI_RESID) {
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) {
+      const int t = tb * 16 + tlow;
+      float s = 0.f;
+      union { uint16_t s[4]; u32x2 v; } hi, lo;
+      f32x4 hn;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        hn[e] = hv[tb][e] + v[tb][e];
+        s += hn[e] * hn[e];
+        split_f16(hn[e] * gv[e], hi.s[e], lo.s[e]);
+      }
+      s += __shfl_xor(s, 16);
+      s += __shfl_xor(s, 32);
+      if (valid_token(tb) && frg < p.NRG) {
+        *reinterpret_cast<f32x4*>(p.h + (int64_t)t * p.d + n0) = hn;
+        *reinterpret_cast<u32x2*>(p.xnext + packed_x_offset(n0, t, TB, 0)) = hi.v;
+        *reinterpret_cast<u32x2*>(p.xnext + packed_x_offset(n0, t, TB, 1)) = lo.v;
+        if (lane < 16) p.ssq_out[(int64_t)t * SSQ_ROWS + frg] = s;  // one entry per row group
+      }
+    }
+  } else if constexpr (EPI == EPI_QKV) {  // `group` is the head
+    const bool rotated = group < p.Hq + p.Hkv;
+    if (p.qk_gain) {  // 1 / rms of the head vector, its row groups added in order
+#pragma unroll
+      for (int tb = 0; tb < TB; ++tb) {
+        float s = v[tb][0] * v[tb][0] + v[tb][1] * v[tb][1] + v[tb][2] * v[tb][2] + v[tb][3] * v[tb][3];
+        s += __shfl_xor(s, 16);
+        s += __shfl_xor(s, 32);
+        if (lane < 16) s_head[0][wave][tb * 16 + lane] = s;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int tb = 0; tb < TB; ++tb) {
+        float tot = 0.f;
+        for (int w = 0; w < n_fin; ++w) tot += s_head[0][w][tb * 16 + tsub];
+        const float rs = rsqrtf(tot / (float)p.hd + p.eps);
+        if (rotated) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[tb][e] *= rs * gv[e];
+        }
+      }
+    }
+    const int c0 = n0 % p.hd;
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) {
+      if (rotated) {  // rows arrive with the rotary pair (i, i + hd/2) at neighbouring positions (2i, 2i+1)
+#pragma unroll
+        for (int pr = 0; pr < 2; ++pr) {
+          const float a = v[tb][2 * pr], b = v[tb][2 * pr + 1], c = cs[tb][2 * pr], s = cs[tb][2 * pr + 1];
+          v[tb][2 * pr] = a * c - b * s;
+          v[tb][2 * pr + 1] = b * c + a * s;
+        }
+      }
+      if (group < p.Hq) {
+        // queries leave as fp16 hi + lo, already multiplied by log2(e)/sqrt(hd), in the order the attention kernel loads them
+        union { uint16_t s[4]; u32x2 v; } qh, ql;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) split_f16(v[tb][e] * p.qscale, qh.s[e], ql.s[e]);
+        if (valid_token(tb)) {
+          *reinterpret_cast<u32x2*>(p.q_hi + (int64_t)(tb * 16 + tlow) * (p.Hq * p.hd) + n0) = qh.v;
+          *reinterpret_cast<u32x2*>(p.q_lo + (int64_t)(tb * 16 + tlow) * (p.Hq * p.hd) + n0) = ql.v;
+        }
+      }
+    }
+    if (group < p.Hq) return;
+    // keys and values go to the cache as 16-bit codes with the scale of their (token, head) vector
+    float amax[TB];
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) {
+      float am = fmaxf(fmaxf(__builtin_fabsf(v[tb][0]), __builtin_fabsf(v[tb][1])), fmaxf(__builtin_fabsf(v[tb][2]), __builtin_fabsf(v[tb][3])));
+      am = fmaxf(am, __shfl_xor(am, 16));
+      am = fmaxf(am, __shfl_xor(am, 32));
+      if (lane < 16) s_head[1][wave][tb * 16 + lane] = am;
+      amax[tb] = am;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) {
+      float am = amax[tb];
+      for (int w = 0; w < n_fin; ++w) am = fmaxf(am, s_head[1][w][tb * 16 + tsub]);
+      if (!valid_token(tb)) continue;
+      const int64_t slot_id = kv_slot_in_block(blk[tb], pos[tb]), kblk = slot_id / KV_BS;
+      const int at = (int)(slot_id % KV_BS);
+      const bool is_v = !rotated;
+      const int j = group - p.Hq - (is_v ? p.Hkv : 0);
+      const float inv = kv_code_inv(am);
+      union { uint16_t s[4]; u32x2 v; } code;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) code.s[e] = kv_code(v[tb][e], inv);
+      uint16_t* dst = (is_v ? p.vplane : p.kplane) + (kblk * p.Hkv + j) * (int64_t)(KV_BS * p.hd);
+      if (!is_v) {
+        *reinterpret_cast<u32x2*>(dst + k_cache_offset(at, c0)) = code.v;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dst[v_cache_offset(at, c0 + e)] = code.s[e];
+      }
+      if (c0 == 0) p.kvscale[kv_scale_offset(kblk, p.Hkv, j) + (is_v ? 16 : 0) + at] = kv_code_scale(am);
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
+// Host side
+// Rows and k splits of the QKV and residual GEMMs: the least of the times a model of two rates gives, the weight stream at
+// 6.2 TB/s and the intake of a compute unit at 52 KB per us (its weights, and the activations of its k range), the shorter of
+// the two hidden to three quarters behind the longer, plus 3 us and the reading of the parked tiles where results are handed
+// over (4 us with split k ranges).  Many rows save activations, few rows or more splits keep every compute unit at work.
+// 8B shape, us: down projection of FP8 weights, 16 tokens, 1 row group without splits 21.4, 2 x 2 splits 19.7, 4 x 4 16.6; O
+// projection of fp16 weights, 1 token, 1 x 1 8.5, 2 x 2 9.8, 4 x 4 11.2; QKV, 16 tokens, FP8: 1 x 1 15.8, 2 x 1 14.5, 4 x 2 12.5.
+struct SmallShape { int R, ks, per; };
+static SmallShape small_shape(int epi, int NRG, int KB, int hd, int xf, int wmode) {
+  const float CUS = (float)decode_wg_target();
+  const float wbytes = wmode == WMODE_INT4 ? 0.5f + 2.f / 32 : wmode == WMODE_FP8 ? 1.f : 2.f;
+  const int chunk = SG_NW * sg_kc(wmode, xf);  // k blocks of one chunk of every wavefront: an unfilled round costs a whole one
+  SmallShape best = {1, 1, (KB + 3) / 4 * 4};
+  float least = 0.f;
+  for (int R = 1; R <= 4; R *= 2)
+    for (int ks = 1; ks <= 8; ++ks) {
+      const int per = ((KB + ks - 1) / ks + 3) / 4 * 4, members = epi == EPI_QKV ? hd / 16 / R : 1;
+      if ((KB + per - 1) / per != ks || members < 1 || members * ks > 31) continue;  // (arrivals of a group: 5 bits per XCD)
+      if (ks > 1 && (per < chunk || (NRG + R - 1) / R * ks > decode_wg_target())) break;
+      const float groups = (float)((NRG + R - 1) / R) * (float)ks, fill = groups < CUS ? 1.f : groups / CUS;
+      const float rounds = sg_eu(wmode, R, xf) == 4 ? fill : ceilf(fill);  // two workgroups share a compute unit, or one has it
+      const float intake = rounds * (float)((per + chunk - 1) / chunk * chunk) * 32.f * (16.f * (float)R * wbytes + 32.f * (float)xf) / 52e3f;
+      const float stream = (float)NRG * 16.f * (float)KB * 32.f * wbytes / 6.2e6f;
+      const float us = (intake > stream ? intake + 0.25f * stream : stream + 0.25f * intake) + (ks > 1 ? 1.f : 0.f) + (members * ks > 1 ? 3.f + (float)(ks * R * (xf == 4 ? 2 : 1)) * 1024.f / 52e3f : 0.f);
+      if ((R == 1 && ks == 1) || us < least) {
+        least = us;
+        best = {R, ks, per};
+      }
+    }
+  return best;
+}
+
+// Which GEMMs of a step of M tokens run here (us per launch against skinny_gemm_kernel; 8B shape 1, 12, 24 sequences, 1B shape
+// 4 and 32): QKV 13.5 / 15.5, 15.3 / 16.0, 17.7 / 17.9, 8.4 / 11.2, 11.7 / 13.9; O 8.5 / 12.3, 10.5 / 12.4, 11.6 / 14.1, 5.0 / 8.7,
+// 8.0 / 10.0; down 22.4 / 25.8, 24.8 / 26.5, 26.4 / 28.0, 11.1 / 15.5, 14.0 / 17.5; output head 168 / 174 and 172 / 182 (1B: equal);
+// int4, 5 sequences: QKV 10.8 / 13.0, O 6.8 / 10.4, gate/up 18.0 / 24.4, down 13.2 / 17.7, head 56 / 67.  Not the gate/up GEMM
+// of the other formats, which has rows for every compute unit without a split (39.0 / 37.6, with FP8 24.6 / 21.9; 1B shape with up
+// to 8 tokens 13.4 / 14.6), and none whose k range leaves half of the wavefronts without a chunk (tiny shape, 4 sequences: 75 us a
+// step, 72 with the other kernel; 20 sequences: 80 against 84).
+bool small_gemm_takes(const www_model* m, int epi, int NRG, int KB, int M) {
+  if (KB < 16 && M <= 16) return false;
+  if (epi == EPI_QKV || epi == EPI_RESID) return M <= 32;
+  if (M > 16) return false;
+  if (epi == EPI_LOGITS || m->int4_group || m->wsplit) return true;
+  return M <= 8 && NRG <= 4 * decode_wg_target();
+}
+
+uint64_t small_gemm_partial_bytes(int NRG) { return (uint64_t)NRG * 8 * 2 * 1024; }  // [split][row group][2 token groups]
+
+template <int EPI>
+void launch_small_gemm(www_model* m, GemmP& p, hipStream_t st) {
+  const int xf = p.M <= 8 ? 1 : p.M <= 16 ? 2 : 4;
+  SmallShape s = {2, 1, (p.KB + 3) / 4 * 4};
+  int RW = 1;
+  if (m->wsplit) {  // two planes: two row groups fit the registers; whole heads, so that nothing is handed over
+    if (EPI == EPI_QKV) RW = p.hd / 32;
+  } else if (EPI == EPI_QKV || EPI == EPI_RESID) {
+    s = small_shape(EPI, p.NRG, p.KB, p.hd, xf, m->int4_group ? WMODE_INT4 : m->fp8 ? WMODE_FP8 : WMODE_F16);
+  } else {  // one round of workgroups where the rows allow it
+    s.R = 4;
+    while (RW < (EPI == EPI_LOGITS ? 8 : 2) && (p.NRG + 4 * RW - 1) / (4 * RW) > decode_wg_target()) RW *= 2;
+  }
+  p.ksplit = s.ks;
+  p.kb_per_split = s.per;
+  p.MT = xf == 4 ? 2 : 1;
+  p.partial = m->partial;
+  p.counters = m->counters;
+  p.fault_flag = m->fault_dev;
+  p.fence_handover = m->handover_fence;
+  if (p.wfactor == 0.f) p.wfactor = 1.f;  // not set: an unscaled matrix
+  const int hrg = EPI == EPI_QKV ? p.hd / 16 : s.R * RW;
+  p.row_tiles = (p.NRG + hrg - 1) / hrg;
+  p.zbs = p.ksplit * (EPI == EPI_QKV ? hrg / (s.R * RW) : 1);
+  const dim3 grid(8 * ((p.row_tiles + 7) / 8) * p.zbs), block(64 * SG_NW);
+#define LAUNCH(WM_, R_, RW_, XF_) hipLaunchKernelGGL((small_gemm_kernel<WM_, EPI, R_, RW_, XF_>), grid, block, 0, st, p)
+#define LAUNCHX(WM_, R_, RW_) { if (xf == 1) LAUNCH(WM_, R_, RW_, 1); else if (xf == 2) LAUNCH(WM_, R_, RW_, 2); else if constexpr (NARROW) LAUNCH(WM_, R_, RW_, 4); }
+#define LAUNCHW(R_, RW_)                                       \
+  {                                                            \
+    if (m->int4_group) LAUNCHX(WMODE_INT4, R_, RW_)            \
+    else if (m->fp8) LAUNCHX(WMODE_FP8, R_, RW_)               \
+    else LAUNCHX(WMODE_F16, R_, RW_)                           \
+  }
+  constexpr bool NARROW = EPI == EPI_QKV || EPI == EPI_RESID;
+  if constexpr (NARROW) {
+    if (m->wsplit) { if constexpr (EPI == EPI_QKV) { if (RW == 2) LAUNCHX(WMODE_SPLIT, 2, 2) else LAUNCHX(WMODE_SPLIT, 2, 4) } else LAUNCHX(WMODE_SPLIT, 2, 1) }
+    else if (s.R == 1) LAUNCHW(1, 1)
+    else if (s.R == 2) LAUNCHW(2, 1)
+    else LAUNCHW(4, 1)
+  } else {
+    if (m->wsplit) LAUNCHX(WMODE_SPLIT, 2, 1)
+    else if (RW == 1) LAUNCHW(4, 1)
+    else if (RW == 2) LAUNCHW(4, 2)
+    else if constexpr (EPI == EPI_LOGITS) { if (RW == 4) LAUNCHW(4, 4) else LAUNCHW(4, 8) }
+  }
+#undef LAUNCHW
+#undef LAUNCHX
+#undef LAUNCH
+}
+template void launch_small_gemm<EPI_QKV>(www_model*, GemmP&, hipStream_t);
+template void launch_small_gemm<EPI_RESID>(www_model*, GemmP&, hipStream_t);
+template void launch_small_gemm<EPI_SWIGLU>(www_model*, GemmP&, hipStream_t);
+template void launch_small_gemm<EPI_LOGITS>(www_model*, GemmP&, hipStream_t);

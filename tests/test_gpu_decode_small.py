@@ -1,0 +1,41 @@
+"""GPU: the decode GEMMs of steps of up to 32 sequences, at the edges of their token groups (8, 16 and 32 columns), with k ranges
+that end inside a chunk, row groups that do not fill a tile, split k ranges, and every weight format.  Bounds of the parity tests."""
+import dataclasses
+
+import pytest
+
+from paper_2603_20661_amd import synth
+from test_gpu_parity import WIDE8B, WIDE8B_FP8, WIDE8B_Q128, check, run_job
+
+pytestmark = pytest.mark.gpu
+
+# 20 k blocks in the QKV GEMM, 129 (132 for int4) in the down projection, 514 row groups in the gate/up GEMM
+H128 = synth.ModelShape("small128", 1, 640, 4, 1, 128, 4112, 528, 1e-5, 1e4, synth.WDTYPE_BF16, seed=501)
+H64 = dataclasses.replace(H128, name="small64", n_q_heads=8, n_kv_heads=2, head_dim=64, seed=502)
+FORMATS = [H128, H64, dataclasses.replace(H128, name="small128qk", qk_norm=1, seed=503), dataclasses.replace(H64, name="small64qk", qk_norm=1, seed=504),
+           dataclasses.replace(H128, name="small128fp8", weight_dtype=synth.WDTYPE_FP8WO, seed=505),
+           dataclasses.replace(H64, name="small64int4", ffn_dim=4224, weight_dtype=synth.WDTYPE_INT4WO_128, seed=506),
+           dataclasses.replace(H128, name="small128int4", ffn_dim=4128, weight_dtype=synth.WDTYPE_INT4WO_32, seed=507),
+           dataclasses.replace(H128, name="small128f32", weight_dtype=synth.WDTYPE_F32, seed=508),
+           dataclasses.replace(H64, name="small64f32", weight_dtype=synth.WDTYPE_F32, seed=509)]
+
+
+@pytest.mark.parametrize("batch", [1, 8, 9, 17, 32])
+@pytest.mark.parametrize("shape", FORMATS, ids=lambda s: s.name)
+def test_formats_and_token_groups(shape, batch):
+    lens = 2 + synth.uniform_i32(batch, 9, batch, 20)
+    check(run_job(shape, lens, 2, seed=510 + batch), f"{shape.name} batch {batch}")
+
+
+@pytest.mark.parametrize("shape,batch", [(WIDE8B_Q128, 5), (WIDE8B, 12), (WIDE8B_FP8, 24)], ids=lambda v: getattr(v, "name", str(v)))
+def test_full_width_tiles(shape, batch):
+    """several row groups per wavefront, k splits in all narrow GEMMs, two and eight wavefronts side by side in the wide ones"""
+    lens = 2 + synth.uniform_i32(batch, 9, batch, 20)
+    check(run_job(dataclasses.replace(shape, n_layers=1), lens, 2, seed=540 + batch), f"{shape.name} batch {batch}")
+
+
+def test_widest_sums_of_squares():
+    """d_model = 8192: 512 entries per token, twice what the kernels request up front"""
+    shape = dataclasses.replace(H128, name="small8192", d_model=8192, n_q_heads=2, n_kv_heads=2, ffn_dim=528, vocab=272, seed=520)
+    for batch in (3, 20):
+        check(run_job(shape, 2 + synth.uniform_i32(batch, 9, batch, 6), 2, seed=560 + batch), f"d_model 8192 batch {batch}")

@@ -207,8 +207,9 @@ static void make_plan(const www_config* c, Plan& p) {
       }
   }
   for (int n : {s.QKVN, s.d}) part = part > small_gemm_partial_bytes(n / 16) ? part : small_gemm_partial_bytes(n / 16);
-  const uint64_t pre[4] = {prefill_partial_bytes(s.maxT, s.QKVN / 16, s.d / 32), prefill_partial_bytes(s.maxT, s.d / 16, s.QD / 32),
-                           prefill_partial_bytes(s.maxT, 2 * s.F / 16, s.d / 32), prefill_partial_bytes(s.maxT, s.d / 16, s.Fp / 32)};
+  const int maxR = s.wsplit ? s.maxT : prefill_rows(s.maxT, s.maxB);  // rows of a prefill GEMM: tokens, and the last positions that ride along
+  const uint64_t pre[4] = {prefill_partial_bytes(maxR, s.QKVN / 16, s.d / 32), prefill_partial_bytes(maxR, s.d / 16, s.QD / 32),
+                           prefill_partial_bytes(maxR, 2 * s.F / 16, s.d / 32), prefill_partial_bytes(maxR, s.d / 16, s.Fp / 32)};
   for (uint64_t b : pre) part = part > b ? part : b;
   const uint64_t states = prefill_attn_part_bytes(s.hd, s.Hkv, s.G, s.maxT, s.maxB, s.max_pos);  // same buffer, other kernels
   part = part > states ? part : states;
@@ -224,15 +225,15 @@ static void make_plan(const www_config* c, Plan& p) {
   p.attn_pref = take(((uint64_t)s.maxB + 1) * 4);
   p.argmax_val = take((uint64_t)s.maxB * 32 * 4);
   p.argmax_idx = take((uint64_t)s.maxB * 32 * 4);
-  const uint64_t Tpad = ((uint64_t)s.maxT + 255) / 256 * 256;  // packed activation buffers hold whole 256-token tiles
+  const uint64_t Tpad = ((uint64_t)maxR + 255) / 256 * 256;  // packed activation buffers hold whole 256-token tiles
   p.hp = take(Tpad * (((uint64_t)s.d + 255) / 256 * 256) * 4);  // residual stream in whole 256 x 256 blocks (accumulator order)
   p.ssq_p = take(Tpad * (uint64_t)PSSQ * 4);
   p.xn = take(Tpad * s.d * 2);
   p.qp = take((uint64_t)s.maxT * s.QD * 2);
   p.op = take(Tpad * s.QD * 2);
   p.ap = take(Tpad * s.Fp * 2);
-  p.row_seq = take((uint64_t)s.maxT * 4);
-  p.row_pos = take((uint64_t)s.maxT * 4);
+  p.row_seq = take((uint64_t)maxR * 4);
+  p.row_pos = take((uint64_t)maxR * 4);
   const uint64_t max_tiles = (uint64_t)s.maxT / 64 + s.maxB + 1;
   p.tile_seq = take(max_tiles * 4);
   p.tile_q0 = take(max_tiles * 4);
@@ -518,10 +519,12 @@ WWW_EXPORT int www_prefill(www_model* m, const int32_t* tokens_dev, const int32_
   hipStream_t st = (hipStream_t)hip_stream;
   if (m->validate)
     if (int rcv = validate_device_args(m, tokens_dev, total_q_tokens, q_lens_dev, seq_lens_dev, block_table_dev, batch, st)) return rcv;
-  int rc = run_prefill(m, tokens_dev, q_lens_dev, seq_lens_dev, block_table_dev, batch, total_q_tokens, st);
+  const bool rides = prefill_rides(m, total_q_tokens, batch);
+  int rc = run_prefill(m, tokens_dev, q_lens_dev, seq_lens_dev, block_table_dev, batch, total_q_tokens, rides, st);
   if (rc) return rc;
-  // the last new position of every sequence goes through the decode path (hi/lo activations), which also yields the logits
-  return run_decode(m, m->last_tok, seq_lens_dev, block_table_dev, batch, logits_dev, next_tokens_dev, st);
+  // the last new position of every sequence goes through the decode path (hi/lo activations), which also yields the logits;
+  // where it rode along with the prefill, only the rest of the last layer and the output head are left
+  return run_decode(m, m->last_tok, seq_lens_dev, block_table_dev, batch, logits_dev, next_tokens_dev, rides, st);
 }
 
 WWW_EXPORT int www_decode_step(www_model* m, const int32_t* last_tokens_dev, const int32_t* seq_lens_dev, const int32_t* block_table_dev,
@@ -536,7 +539,7 @@ WWW_EXPORT int www_decode_step(www_model* m, const int32_t* last_tokens_dev, con
   if (m->validate)
     if (int rcv = validate_device_args(m, last_tokens_dev, batch, nullptr, seq_lens_dev, block_table_dev, batch, st)) return rcv;
   if (!m->use_graph || st == nullptr || (m->prof && m->prof->on))  // the legacy default stream cannot be captured
-    return run_decode(m, last_tokens_dev, seq_lens_dev, block_table_dev, batch, logits_dev, next_tokens_dev, st);
+    return run_decode(m, last_tokens_dev, seq_lens_dev, block_table_dev, batch, logits_dev, next_tokens_dev, false, st);
 
   for (int i = 0; i < m->n_graphs; ++i) {
     GraphEntry& g = m->graphs[i];
@@ -549,7 +552,7 @@ WWW_EXPORT int www_decode_step(www_model* m, const int32_t* last_tokens_dev, con
   // capture one step; pointers and grid sizes are frozen, lengths / tables / tokens are read from device memory at replay
   hipGraph_t graph = nullptr;
   HIP_TRY(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-  int rc = run_decode(m, last_tokens_dev, seq_lens_dev, block_table_dev, batch, logits_dev, next_tokens_dev, st);
+  int rc = run_decode(m, last_tokens_dev, seq_lens_dev, block_table_dev, batch, logits_dev, next_tokens_dev, false, st);
   hipError_t ec = hipStreamEndCapture(st, &graph);
   if (rc) { if (graph) (void)hipGraphDestroy(graph); return rc; }
   if (ec != hipSuccess) { set_error("hipStreamEndCapture failed: %s", hipGetErrorString(ec)); return WWW_E_HIP; }

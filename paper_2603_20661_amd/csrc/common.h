@@ -238,10 +238,16 @@ int launch_pack_qk_gain(const float* q_src, const float* k_src, int hd, float* o
 int launch_pack_fp8(const void* src, int N, int K, int KB, int mode, int hd, int n_rot_rows, int F, uint8_t* out, hipStream_t st);
 int decode_attn_resident_waves(int hd, int G);
 int decode_probe_placement(int32_t* scratch_dev, int n, hipStream_t st);
+// from_last_qkv: everything up to the last layer's QKV product (and the plan of the attention) has run as rows of a prefill call
 int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int32_t* table, int batch, float* logits, int32_t* next,
-               hipStream_t st);
+               bool from_last_qkv, hipStream_t st);
+void launch_attn_plan(www_model* m, const int32_t* lens, int batch, hipStream_t st);
+// decode attention of one layer, into packed decode activations of MT token groups, or (first_row >= 0) rows of a prefill operand
+void launch_decode_attn(www_model* m, int l, const int32_t* lens, const int32_t* table, int batch, uint16_t* out, int MT, int first_row, hipStream_t st);
+int prefill_rows(int T, int batch);
+bool prefill_rides(const www_model* m, int T, int batch);
 int run_prefill(www_model* m, const int32_t* tok, const int32_t* qlens, const int32_t* lens, const int32_t* table, int batch, int T,
-                hipStream_t st);
+                bool rides, hipStream_t st);
 int launch_pack_matrix(const void* src, int src_dtype, int N, int K, int KB, int mode, int hd, int n_rot_rows, int F, uint16_t* hi, uint16_t* lo,
                        hipStream_t st);
 int launch_debug_slots(const int32_t* row, const int32_t* pos, int n, int64_t* out, hipStream_t st);

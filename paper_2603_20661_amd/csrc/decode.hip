@@ -717,6 +717,12 @@ __device__ __forceinline__ void split_codes4(uint32_t w0, uint32_t w1, uint32_t 
 }
 __device__ __forceinline__ void split_codes8(u32x4 w, f16x8& hi, f16x8& lo) { split_codes4(w.x, w.y, w.z, w.w, hi, lo); }
 
+// Where column k of sequence b's attention output goes: the decode path's packed operand of the O projection, or (first_row >= 0)
+// the rows of a prefill call that its last position rides in (K16 = columns / 16)
+__device__ __forceinline__ int64_t attn_out_offset(int k, int b, int hl, int MT, int first_row, int K16) {
+  return first_row < 0 ? packed_x_offset(k, b, MT, hl) : packed_p_offset(first_row + (b >> 4) * 32 + hl * 16 + (b & 15), k, K16);
+}
+
 // ------------------------------------------------------------------------------------------------
 // Decode attention.  Each wavefront walks its chunk of the plan above, segment by segment:
 //   S^T = K Q^T (keys x heads), online softmax per head along the key axis with cross-lane shuffles,
@@ -730,7 +736,7 @@ __global__ __launch_bounds__(256) void decode_attn_kernel(const uint16_t* __rest
                                                            const int32_t* __restrict__ seq_lens,
                                                            const int32_t* __restrict__ table, int batch, int mbs, int Hq, int Hkv,
                                                            const int32_t* __restrict__ hdr, const int32_t* __restrict__ start,
-                                                           float* __restrict__ part, uint16_t* __restrict__ xo, int MT) {
+                                                           float* __restrict__ part, uint16_t* __restrict__ xo, int MT, int first_row) {
   constexpr int NKF = HD / 32;  // K fragments per block
   constexpr int NVF = HD / 16;  // V fragments per block
   constexpr int PSTRIDE = HD + 4;  // floats per (record, head): o[HD], m, l, pad
@@ -936,8 +942,8 @@ __global__ __launch_bounds__(256) void decode_attn_kernel(const uint16_t* __rest
 #pragma unroll
           for (int i = 0; i < 4; ++i) split_f16(oacc[f][i] * inv, hi.s[i], lo.s[i]);
           const int k = (j * G + n) * HD + f * 16 + g * 4;
-          *reinterpret_cast<u32x2*>(xo + packed_x_offset(k, b, MT, 0)) = hi.v;
-          *reinterpret_cast<u32x2*>(xo + packed_x_offset(k, b, MT, 1)) = lo.v;
+          *reinterpret_cast<u32x2*>(xo + attn_out_offset(k, b, 0, MT, first_row, Hq * HD / 16)) = hi.v;
+          *reinterpret_cast<u32x2*>(xo + attn_out_offset(k, b, 1, MT, first_row, Hq * HD / 16)) = lo.v;
         }
       }
     } else {
@@ -975,7 +981,7 @@ template <int HD, int G>
 __global__ __launch_bounds__(64 * MERGE_WAVES) void decode_attn_merge_kernel(const int32_t* __restrict__ seq_lens, int Hkv,
                                                                      const int32_t* __restrict__ hdr, const int32_t* __restrict__ pref,
                                                                      const float* __restrict__ part,
-                                                                     uint16_t* __restrict__ xo, int MT) {
+                                                                     uint16_t* __restrict__ xo, int MT, int first_row) {
   constexpr int PSTRIDE = HD + 4, NS = MERGE_WAVES;
   const int j = blockIdx.x, b = blockIdx.y, lane = threadIdx.x & 63, v = threadIdx.x >> 6;
   const int C = hdr[1];
@@ -1057,8 +1063,8 @@ __global__ __launch_bounds__(64 * MERGE_WAVES) void decode_attn_merge_kernel(con
       const int k = (j * G + hh) * HD + lane + 64 * i;
       uint16_t hi, lo;
       split_f16(oh[hh][i] * inv, hi, lo);
-      xo[packed_x_offset(k, b, MT, 0)] = hi;
-      xo[packed_x_offset(k, b, MT, 1)] = lo;
+      xo[attn_out_offset(k, b, 0, MT, first_row, Hkv * G * HD / 16)] = hi;
+      xo[attn_out_offset(k, b, 1, MT, first_row, Hkv * G * HD / 16)] = lo;
     }
   }
 }
@@ -1248,29 +1254,54 @@ int decode_probe_placement(int32_t* scratch_dev, int n, hipStream_t st) {
 
 int decode_MT(int batch) { return batch <= 16 ? 1 : batch <= 32 ? 2 : batch <= 64 ? 4 : ((batch + 127) / 128) * 8; }
 
+void launch_attn_plan(www_model* m, const int32_t* lens, int batch, hipStream_t st) {
+  hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(256), (size_t)(batch + 2) * 4, st, lens, batch, m->Hkv, m->attn_waves, m->attn_hdr,
+                     m->attn_start, m->attn_pref);
+}
+
+void launch_decode_attn(www_model* m, int l, const int32_t* lens, const int32_t* table, int batch, uint16_t* out, int MT, int first_row, hipStream_t st) {
+  const uint16_t *kplane = m->kv + (int64_t)(2 * l) * m->kv_plane, *vplane = m->kv + (int64_t)(2 * l + 1) * m->kv_plane;
+  const float* kvscale = m->kv_scales + (int64_t)l * m->kv_scale_plane;
+#define ATTN(HD_, G_)                                                                                                              \
+  {                                                                                                                                \
+    hipLaunchKernelGGL((decode_attn_kernel<HD_, G_>), dim3(m->attn_waves / 4), dim3(256), 0, st, m->q_hi, m->q_lo, kplane, vplane,  \
+                       kvscale, lens, table, batch, (int)m->cfg.max_blocks_per_seq, m->Hq, m->Hkv, m->attn_hdr, m->attn_start,      \
+                       m->attn_part, out, MT, first_row);                                                                           \
+    hipLaunchKernelGGL((decode_attn_merge_kernel<HD_, G_>), dim3(m->Hkv, batch), dim3(64 * MERGE_WAVES), 0, st, lens, m->Hkv,      \
+                       m->attn_hdr, m->attn_pref, m->attn_part, out, MT, first_row);                                                \
+  }
+  if (m->hd == 128) {
+    if (m->G == 1) ATTN(128, 1) else if (m->G == 2) ATTN(128, 2) else if (m->G == 4) ATTN(128, 4) else ATTN(128, 8)
+  } else {
+    if (m->G == 1) ATTN(64, 1) else if (m->G == 2) ATTN(64, 2) else if (m->G == 4) ATTN(64, 4) else ATTN(64, 8)
+  }
+#undef ATTN
+}
+
 int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int32_t* table, int batch, float* logits, int32_t* next,
-               hipStream_t st) {
+               bool from_last_qkv, hipStream_t st) {
   const int MT = decode_MT(batch);
   const int d = m->d;
   float* const ssq = MT <= 2 ? m->ssq_rows : m->ssq;
-  prof_mark(m, PK_EMBED, st);
-  if (m->cfg.weight_dtype == WWW_DTYPE_F32)
-    hipLaunchKernelGGL(embed_pack_kernel<float>, dim3(batch), dim3(256), 0, st, tok, (const float*)m->embed, d, m->layers[0].attn_norm,
-                       m->h, ssq, (uint16_t*)m->xq, MT);
-  else
-    hipLaunchKernelGGL(embed_pack_kernel<uint16_t>, dim3(batch), dim3(256), 0, st, tok, (const uint16_t*)m->embed, d,
-                       m->layers[0].attn_norm, m->h, ssq, (uint16_t*)m->xq, MT);
-  hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(256), (size_t)(batch + 2) * 4, st, lens, batch, m->Hkv, m->attn_waves, m->attn_hdr,
-                     m->attn_start, m->attn_pref);
+  if (!from_last_qkv) {
+    prof_mark(m, PK_EMBED, st);
+    if (m->cfg.weight_dtype == WWW_DTYPE_F32)
+      hipLaunchKernelGGL(embed_pack_kernel<float>, dim3(batch), dim3(256), 0, st, tok, (const float*)m->embed, d, m->layers[0].attn_norm,
+                         m->h, ssq, (uint16_t*)m->xq, MT);
+    else
+      hipLaunchKernelGGL(embed_pack_kernel<uint16_t>, dim3(batch), dim3(256), 0, st, tok, (const uint16_t*)m->embed, d,
+                         m->layers[0].attn_norm, m->h, ssq, (uint16_t*)m->xq, MT);
+    launch_attn_plan(m, lens, batch, st);
+  }
   int n_ssq = 1;  // entries per token of the sum-of-squares table: one per row group or per row tile of the GEMM that wrote it
   auto resid_entries = [&](int KB) { return small_gemm_takes(m, EPI_RESID, d / 16, KB, batch) ? d / 16 : (d / 16 + 7) / 8; };
   const float qscale = 1.4426950408889634f / sqrtf((float)m->hd);
-  for (int l = 0; l < m->L; ++l) {
+  for (int l = from_last_qkv ? m->L - 1 : 0; l < m->L; ++l) {
     const LayerW& w = m->layers[l];
     uint16_t* kplane = (uint16_t*)m->kv + (int64_t)(2 * l) * m->kv_plane;
     uint16_t* vplane = (uint16_t*)m->kv + (int64_t)(2 * l + 1) * m->kv_plane;
     float* kvscale = m->kv_scales + (int64_t)l * m->kv_scale_plane;
-    {
+    if (!from_last_qkv) {
       GemmP p = {};
       p.W = (const u32x4*)(w.wqkv8 ? (const void*)w.wqkv8 : (const void*)w.wqkv); p.Wlo = (const u32x4*)w.wqkv_lo; p.wfactor = w.sqkv; p.Wscale = (const u32x2*)w.gqkv;
       p.NRG = m->QKVN / 16; p.KB = d / 32;
@@ -1281,23 +1312,8 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
       prof_mark(m, PK_QKV, st);
       launch_gemm<EPI_QKV>(m, p, MT, st);
     }
-    {
-      prof_mark(m, PK_ATTN, st);
-#define ATTN(HD_, G_)                                                                                                              \
-  {                                                                                                                                \
-    hipLaunchKernelGGL((decode_attn_kernel<HD_, G_>), dim3(m->attn_waves / 4), dim3(256), 0, st, m->q_hi, m->q_lo, kplane, vplane,  \
-                       kvscale, lens, table, batch, (int)m->cfg.max_blocks_per_seq, m->Hq, m->Hkv, m->attn_hdr, m->attn_start,            \
-                       m->attn_part, (uint16_t*)m->xo, MT);                                                                        \
-    hipLaunchKernelGGL((decode_attn_merge_kernel<HD_, G_>), dim3(m->Hkv, batch), dim3(64 * MERGE_WAVES), 0, st, lens, m->Hkv,      \
-                       m->attn_hdr, m->attn_pref, m->attn_part, (uint16_t*)m->xo, MT);                                             \
-  }
-      if (m->hd == 128) {
-        if (m->G == 1) ATTN(128, 1) else if (m->G == 2) ATTN(128, 2) else if (m->G == 4) ATTN(128, 4) else ATTN(128, 8)
-      } else {
-        if (m->G == 1) ATTN(64, 1) else if (m->G == 2) ATTN(64, 2) else if (m->G == 4) ATTN(64, 4) else ATTN(64, 8)
-      }
-#undef ATTN
-    }
+    prof_mark(m, PK_ATTN, st);
+    launch_decode_attn(m, l, lens, table, batch, (uint16_t*)m->xo, MT, -1, st);
     {
       GemmP p = {};
       p.W = (const u32x4*)(w.wo8 ? (const void*)w.wo8 : (const void*)w.wo); p.Wlo = (const u32x4*)w.wo_lo; p.wfactor = w.so; p.Wscale = (const u32x2*)w.go;

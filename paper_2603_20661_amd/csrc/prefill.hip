@@ -1,8 +1,8 @@
 // Prefill path (many new tokens per sequence): ragged-batch bookkeeping, embedding, RMSNorm,
 // LDS-tiled fp16 MFMA GEMM with rotary + KV-cache write / residual / SwiGLU epilogues, and causal
 // paged flash attention over cached prefix + new tokens.  This pass fills the KV cache; the logits
-// of each sequence's last position are produced afterwards by the decode path, which keeps the
-// activations of that one row in hi/lo precision.
+// come from each sequence's last position, whose activations are kept in hi/lo precision: either the whole
+// position runs through the decode path afterwards, or it rides along as rows of its own (below).
 #include <type_traits>
 
 #include "common.h"
@@ -13,6 +13,16 @@ __device__ __forceinline__ f16x8 as_f16x8(u32x4 v) { return __builtin_bit_cast(f
 
 #define ATTN_TQ 64  // query rows per attention workgroup
 
+// Last positions as rows of a prefill call.  The decode pass that follows a prefill reads every weight a second time (8B shape, one
+// sequence: 3.3 of the 11 ms of a 333-token prompt).  Where the GEMMs take the rows without further rounds (prefill_rides), the
+// last position of sequence s travels through all layers but the rest of the last one as two more rows of the same GEMMs:
+// the hi parts of its activations are row first_last + 32 (s / 16) + s % 16, the lo parts 16 rows behind, so both are columns
+// of one 32-token group and a lane finds the other part 16 lanes away.  The epilogues add the two products and write the
+// residual (fp32, m->h), hi and lo operands, queries and cache codes that the decode path's kernels would have written; the
+// ordinary row of that position still runs along, but leaves the cache alone.  Attention at those positions is the
+// decode path's kernel in every layer, and that path takes over behind the last layer's QKV product.
+__host__ __device__ __forceinline__ int last_row_of(int first_last, int s) { return first_last + (s >> 4) * 32 + (s & 15); }
+
 // ------------------------------------------------------------------------------------------------
 // Ragged batch bookkeeping (one workgroup).  meta[0] = number of attention tiles.
 __global__ __launch_bounds__(1024) void prefill_meta_kernel(const int32_t* __restrict__ tokens, const int32_t* __restrict__ q_lens,
@@ -20,7 +30,8 @@ __global__ __launch_bounds__(1024) void prefill_meta_kernel(const int32_t* __res
                                                              int32_t* __restrict__ row_seq, int32_t* __restrict__ row_pos,
                                                              int32_t* __restrict__ tile_seq, int32_t* __restrict__ tile_q0,
                                                              int32_t* __restrict__ meta, int32_t* __restrict__ last_tok,
-                                                             int32_t* __restrict__ cum /* [2*(batch+1)] scratch */) {
+                                                             int32_t* __restrict__ cum /* [2*(batch+1)] scratch */,
+                                                             int first_last, int rows /* 0, T: the last positions do not ride along */) {
   int32_t* cum_rows = cum;
   int32_t* cum_tiles = cum + batch + 1;
   if (threadIdx.x == 0) {
@@ -42,8 +53,14 @@ __global__ __launch_bounds__(1024) void prefill_meta_kernel(const int32_t* __res
       int mid = (lo + hi + 1) >> 1;
       if (cum_rows[mid] <= r) lo = mid; else hi = mid - 1;
     }
-    row_seq[r] = lo;
+    // (the sign marks an ordinary row whose cache entry is written by the rows of its last position)
+    row_seq[r] = first_last && r == cum_rows[lo + 1] - 1 ? lo | (int)0x80000000 : lo;
     row_pos[r] = seq_lens[lo] - q_lens[lo] + (r - cum_rows[lo]);
+  }
+  for (int r = T + threadIdx.x; r < rows; r += blockDim.x) {  // padding, then the rows of the last positions
+    const int s = r < first_last ? 0 : min(((r - first_last) >> 5) * 16 + (r & 15), batch - 1);
+    row_seq[r] = s;
+    row_pos[r] = seq_lens[s] - 1;
   }
   for (int b = threadIdx.x; b < batch; b += blockDim.x) {
     int nt = cum_tiles[b + 1] - cum_tiles[b];
@@ -75,25 +92,31 @@ __device__ __forceinline__ int64_t hp_image_offset_of(int64_t t, int n, int n_rt
 
 // Embedding rows: residual stream h = E[token] (fp32), the first GEMM operand fp16(h * gain) in the packed prefill
 // layout, and the row's sum of squares.  RMSNorm's 1/rms factor is applied by the consuming GEMM's epilogue.
+// Workgroups past the T tokens: the last position of a sequence, residual row in h_last and operands hi and lo.
 template <typename ET>
 __global__ __launch_bounds__(256) void embed_rows_kernel(const int32_t* __restrict__ tokens, const ET* __restrict__ embed, int d,
                                                           const float* __restrict__ gain, float* __restrict__ hp,
-                                                          uint16_t* __restrict__ xn, float* __restrict__ ssq) {
-  int64_t r = blockIdx.x;
-  const ET* row = embed + (int64_t)tokens[r] * d;
+                                                          uint16_t* __restrict__ xn, float* __restrict__ ssq, int T, int first_last,
+                                                          const int32_t* __restrict__ last_tok, float* __restrict__ h_last) {
+  const bool last = (int)blockIdx.x >= T;
+  const int seq = (int)blockIdx.x - T;
+  const int64_t r = last ? last_row_of(first_last, seq) : (int)blockIdx.x;
+  const ET* row = embed + (int64_t)(last ? last_tok[seq] : tokens[r]) * d;
   float local = 0.f;
   for (int k = threadIdx.x * 4; k < d; k += blockDim.x * 4) {
-    union { uint16_t s[4]; u32x2 v; } o;
+    union { uint16_t s[4]; u32x2 v; } o, lo;
     float x[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       if constexpr (sizeof(ET) == 4) x[e] = (float)row[k + e];
       else x[e] = bf16_bits_to_float(((const uint16_t*)row)[k + e]);
       local += x[e] * x[e];
-      o.s[e] = f32_to_f16_sat(x[e] * gain[k + e]);
+      split_f16(x[e] * gain[k + e], o.s[e], lo.s[e]);
     }
-    *reinterpret_cast<float4*>(hp + hp_image_offset_of(r, k, (d + 255) >> 8)) = make_float4(x[0], x[1], x[2], x[3]);
+    float* h = last ? h_last + (int64_t)seq * d + k : hp + hp_image_offset_of(r, k, (d + 255) >> 8);
+    *reinterpret_cast<float4*>(h) = make_float4(x[0], x[1], x[2], x[3]);
     *reinterpret_cast<u32x2*>(xn + packed_p_offset(r, k, d >> 4)) = o.v;
+    if (last) *reinterpret_cast<u32x2*>(xn + packed_p_offset(r + 16, k, d >> 4)) = lo.v;
   }
   __shared__ float red[256];
   red[threadIdx.x] = local;
@@ -103,6 +126,7 @@ __global__ __launch_bounds__(256) void embed_rows_kernel(const int32_t* __restri
     __syncthreads();
   }
   if (threadIdx.x == 0) ssq[(int64_t)r * PSSQ] = red[0];  // row r of the [token][PSSQ] table, one entry in use
+  if (threadIdx.x == 0 && last) ssq[(int64_t)(r + 16) * PSSQ] = red[0];
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -113,14 +137,21 @@ __global__ __launch_bounds__(256) void embed_rows_kernel(const int32_t* __restri
 enum { PEPI_QKV = 0, PEPI_RESID = 1, PEPI_SWIGLU = 2 };
 #define PGEMM_NB 4  // stage buffers of the prefill GEMM (32 KiB each)
 #define PGEMM_LDS_BYTES (PGEMM_NB * 2048 * 16)
+#define PGEMM_LAST_LDS_BYTES ((128 + 16 * 512) * 16)  // with last positions: sums of squares and 16 parked groups behind the loop
 
 struct PGemmP {
   const u32x4* W;  // packed weights
   float wfactor;   // scale of the matrix (FP8 weight-only sources; 1 otherwise), applied to the result
   int NRG, KB;
   const u32x4* X;  // packed activations
-  int T;
+  int T;           // rows of X
   int n_tt, n_rt;  // token tiles, row tiles of 256 x 256
+  // last positions that ride along (kernels with LAST): ordinary tokens, first row of the last positions, their number, their
+  // residual rows and (QKV) queries
+  int T_new, first_last, n_last;
+  float* h_last;
+  uint16_t *q_hi, *q_lo;
+  float qscale;
   // QKV epilogue
   const float* qk_gain;  // models with normalised query / key heads: [2][hd] gains in packed row order; null otherwise
   uint16_t* qp;
@@ -185,7 +216,8 @@ __host__ __device__ __forceinline__ void pgemm_tile_of(int id, int n_tt, int n_r
 // groups tb0 .. tb0 + TB - 1 of token half wt of the 256 x 256 tile (tt, rt).
 //   acc[rb][tb][i] = Y^T[row][token]: row = (rg_w + rb*2)*16 + (i/4)*8 + (lane/32)*4 + i%4, token = t_w + tb*32 + lane%32
 // sum_out(tb, s) receives the sum of squares of a token's new residual over the wavefront's rows (residual epilogue).
-template <int EPI, bool QKN, int TB, typename SUM>
+// LAST: the call's last token groups hold last positions; they are left to last_epilogue, what is computed of them here is dropped.
+template <int EPI, bool QKN, int TB, bool LAST, typename SUM>
 __device__ __forceinline__ void pgemm_epilogue(const PGemmP& p, f32x16 (&acc)[4][TB], int tt, int rt, int wn, int wt, int tb0, SUM sum_out) {
   const int lane = threadIdx.x & 63, wave = wn * 2 + wt;  // (position of the wavefront's rows and tokens in the 256 x 256 tile)
   const int rg_w = rt * 16 + wn * 8, t_w = tt * 256 + wt * 128 + tb0 * 32;
@@ -198,14 +230,16 @@ __device__ __forceinline__ void pgemm_epilogue(const PGemmP& p, f32x16 (&acc)[4]
   bool tok_ok[TB];
   float scale[TB];
   int pos[TB], blk[TB];
+  bool keep_cache[TB];  // (LAST) ordinary row of a last position
 #pragma unroll
   for (int tb = 0; tb < TB; ++tb) {
     const int t = t_w + tb * 32 + (lane & 31);
-    tok_ok[tb] = t < p.T;
+    tok_ok[tb] = t < (LAST ? p.T_new : p.T);
     tcl[tb] = min(t, p.T - 1);
     scale[tb] = p.wfactor;
     pos[tb] = 0;
     blk[tb] = 0;
+    keep_cache[tb] = false;
   }
   if constexpr (EPI != PEPI_RESID) {
     if constexpr (EPI == PEPI_QKV) {
@@ -214,6 +248,10 @@ __device__ __forceinline__ void pgemm_epilogue(const PGemmP& p, f32x16 (&acc)[4]
       for (int tb = 0; tb < TB; ++tb) {
         pos[tb] = p.row_pos[tcl[tb]];
         seq[tb] = p.row_seq[tcl[tb]];
+        if constexpr (LAST) {
+          keep_cache[tb] = seq[tb] < 0;
+          seq[tb] &= 0x7fffffff;
+        }
       }
 #pragma unroll
       for (int tb = 0; tb < TB; ++tb) blk[tb] = kv_block_id(p.table + (int64_t)seq[tb] * p.mbs, pos[tb]);
@@ -393,7 +431,7 @@ __device__ __forceinline__ void pgemm_epilogue(const PGemmP& p, f32x16 (&acc)[4]
 #pragma unroll
               for (int i = 0; i < 4; ++i) o.s[i] = f32_to_f16_sat(v4[i]);  // queries feed the fp16 attention kernel
               *reinterpret_cast<u32x2*>(p.qp + (int64_t)t * (p.Hq * p.hd) + n0) = o.v;
-            } else {
+            } else if (!LAST || !keep_cache[tb]) {
               // keys and values go to the cache as 16-bit codes with the scale of their (token, head) vector
               const bool is_v = head >= p.Hq + p.Hkv;
               const int j = head - p.Hq - (is_v ? p.Hkv : 0);
@@ -420,9 +458,173 @@ __device__ __forceinline__ void pgemm_epilogue(const PGemmP& p, f32x16 (&acc)[4]
   }
 }
 
+// Epilogue of the token groups of last positions.  Before the epilogue above, a wavefront adds the hi and lo products of its
+// groups and parks the sums in LDS, [group][4 rows][sequence] in units of 16 bytes (park_last); behind it, when the accumulators
+// are free, it takes one group after the other from there (lane = sequence lane % 16 and row quads 4 q + lane / 16) and writes
+// what the decode path's GEMMs write.  (In one with the epilogue above the 256 x 256 tiles spill up to 290 registers.)
+#define LAST_UNITS 512  // of one group
+template <int TB>
+__device__ __forceinline__ void park_last(const PGemmP& p, f32x16 (&acc)[4][TB], int t_w, f32x4* lds) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int tb = 0; tb < TB; ++tb) {
+    if (t_w + tb * 32 < p.first_last) continue;
+#pragma unroll
+    for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        f32x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = acc[rb][tb][q4 * 4 + e] + __shfl_xor(acc[rb][tb][q4 * 4 + e], 16);
+        if (!(lane & 16)) lds[tb * LAST_UNITS + (rb * 8 + q4 * 2 + (lane >> 5)) * 16 + (lane & 15)] = v;
+      }
+  }
+}
+// sum_out(tb, column, s): sum of squares of a sequence's new residual over the wavefront's rows, for both of its columns.
+template <int EPI, bool QKN, int TB, typename SUM>
+__device__ __forceinline__ void last_epilogue(const PGemmP& p, int rg_w, int t_w, const f32x4* lds, SUM sum_out) {
+  const int lane = threadIdx.x & 63, s16 = lane & 15, part = lane >> 4;
+#pragma unroll 1
+  for (int tb = 0; tb < TB; ++tb, lds += LAST_UNITS) {
+    const int at = t_w + tb * 32 - p.first_last;
+    if (at < 0 || (at >> 1) >= p.n_last) continue;
+    const int seq = (at >> 1) + s16;
+    const bool ok = seq < p.n_last;
+    const int sc = min(seq, p.n_last - 1), row = last_row_of(p.first_last, sc);
+    float scale = p.wfactor;
+    if (EPI != PEPI_RESID && p.ssq_in) {
+      float ss = 0.f;
+      for (int e0 = 0; e0 < p.n_ssq_in; e0 += 32) {
+        f32x4 sq[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) sq[c] = *reinterpret_cast<const f32x4*>(p.ssq_in + (int64_t)row * PSSQ + e0 + c * 4);
+#pragma unroll
+        for (int c = 0; c < 8; ++c)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) ss += e0 + c * 4 + e < p.n_ssq_in ? sq[c][e] : 0.f;
+      }
+      scale *= rsqrtf(ss * p.inv_dim + p.eps);
+    }
+    auto value = [&](int quad) __attribute__((always_inline)) { return lds[quad * 16 + s16] * scale; };
+    auto split4 = [&](f32x4 v, u32x2& hi, u32x2& lo) __attribute__((always_inline)) {
+      union { uint16_t s[4]; u32x2 v; } h, l;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) split_f16(v[e], h.s[e], l.s[e]);
+      hi = h.v;
+      lo = l.v;
+    };
+    u32x2 hi, lo;
+    if constexpr (EPI == PEPI_SWIGLU) {
+#pragma unroll
+      for (int rb = 0; rb < 4; ++rb) {
+        const f32x4 g = value(rb * 8 + part), u = value(rb * 8 + 4 + part);
+        f32x4 a;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a[e] = g[e] / (1.f + __expf(-g[e])) * u[e];
+        split4(a, hi, lo);
+        if (!ok || rg_w + rb * 2 + 1 >= p.NRG) continue;
+        const int f0 = ((rg_w >> 1) + rb) * 16 + part * 4;
+        *reinterpret_cast<u32x2*>(p.ap + packed_p_offset(row, f0, p.Fp >> 4)) = hi;
+        *reinterpret_cast<u32x2*>(p.ap + packed_p_offset(row + 16, f0, p.Fp >> 4)) = lo;
+      }
+    } else if constexpr (EPI == PEPI_RESID) {
+      float ss = 0.f;
+      f32x4 hv[8], gv[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int n0 = min(rg_w + q, p.NRG - 1) * 16 + part * 4;
+        hv[q] = *reinterpret_cast<const f32x4*>(p.h_last + (int64_t)sc * p.d + n0);
+        gv[q] = *reinterpret_cast<const f32x4*>(p.gain_next + n0);
+      }
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {  // row group rg_w + q
+        if (rg_w + q >= p.NRG) break;
+        const int n0 = (rg_w + q) * 16 + part * 4;
+        const f32x4 hn = hv[q] + value(q * 4 + part);
+        ss += hn[0] * hn[0] + hn[1] * hn[1] + hn[2] * hn[2] + hn[3] * hn[3];
+        split4(hn * gv[q], hi, lo);
+        if (!ok) continue;
+        *reinterpret_cast<f32x4*>(p.h_last + (int64_t)sc * p.d + n0) = hn;
+        *reinterpret_cast<u32x2*>(p.xn_out + packed_p_offset(row, n0, p.d >> 4)) = hi;
+        *reinterpret_cast<u32x2*>(p.xn_out + packed_p_offset(row + 16, n0, p.d >> 4)) = lo;
+      }
+      ss += __shfl_xor(ss, 16);
+      ss += __shfl_xor(ss, 32);
+      if (lane < 32) sum_out(tb, lane, ss);
+    } else {
+      const int pos = p.row_pos[row];
+      const int64_t slot = kv_slot(p.table + (int64_t)sc * p.mbs, pos), blk = slot / KV_BS;
+      const int tok = (int)(slot % KV_BS);
+      f32x4 v[8];
+      float ss[2] = {0.f, 0.f}, amax[2] = {0.f, 0.f};  // a head of 128, or two of 64
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        v[q] = value(q * 4 + part);
+        if constexpr (QKN) ss[q >> 2] += v[q][0] * v[q][0] + v[q][1] * v[q][1] + v[q][2] * v[q][2] + v[q][3] * v[q][3];
+      }
+      if constexpr (QKN) {
+        if (p.hd == 128) ss[0] = ss[1] = ss[0] + ss[1];
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh) {
+          ss[hh] += __shfl_xor(ss[hh], 16);
+          ss[hh] += __shfl_xor(ss[hh], 32);
+          ss[hh] = rsqrtf(ss[hh] / (float)p.hd + p.eps);
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int n0 = min(rg_w + q, p.NRG - 1) * 16 + part * 4;
+        if (n0 < (p.Hq + p.Hkv) * p.hd) {
+          if constexpr (QKN) v[q] *= *reinterpret_cast<const f32x4*>(p.qk_gain + (n0 / p.hd < p.Hq ? 0 : p.hd) + n0 % p.hd) * ss[q >> 2];
+          const f32x4 cs = *reinterpret_cast<const f32x4*>(p.rope + (int64_t)pos * (p.hd / 2) + ((n0 % p.hd) >> 1));
+#pragma unroll
+          for (int pr = 0; pr < 2; ++pr) {
+            const float a = v[q][2 * pr], b = v[q][2 * pr + 1];
+            v[q][2 * pr] = a * cs[2 * pr] - b * cs[2 * pr + 1];
+            v[q][2 * pr + 1] = b * cs[2 * pr] + a * cs[2 * pr + 1];
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) amax[q >> 2] = fmaxf(amax[q >> 2], __builtin_fabsf(v[q][e]));
+      }
+      if (p.hd == 128) amax[0] = amax[1] = fmaxf(amax[0], amax[1]);
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh) {
+        amax[hh] = fmaxf(amax[hh], __shfl_xor(amax[hh], 16));
+        amax[hh] = fmaxf(amax[hh], __shfl_xor(amax[hh], 32));
+      }
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        if (!ok || rg_w + q >= p.NRG) continue;
+        const int n0 = (rg_w + q) * 16 + part * 4, head = n0 / p.hd, c0 = n0 % p.hd;
+        if (head < p.Hq) {  // pre-scaled, for the decode attention
+          split4(v[q] * p.qscale, hi, lo);
+          *reinterpret_cast<u32x2*>(p.q_hi + (int64_t)sc * (p.Hq * p.hd) + n0) = hi;
+          *reinterpret_cast<u32x2*>(p.q_lo + (int64_t)sc * (p.Hq * p.hd) + n0) = lo;
+          continue;
+        }
+        const bool is_v = head >= p.Hq + p.Hkv;
+        const int j = head - p.Hq - (is_v ? p.Hkv : 0);
+        const float am = amax[q >> 2], inv = kv_code_inv(am);
+        union { uint16_t s[4]; u32x2 v; } o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o.s[e] = kv_code(v[q][e], inv);
+        uint16_t* dst = (is_v ? p.vplane : p.kplane) + (blk * p.Hkv + j) * (int64_t)(KV_BS * p.hd);
+        if (!is_v) {
+          *reinterpret_cast<u32x2*>(dst + k_cache_offset(tok, c0)) = o.v;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dst[v_cache_offset(tok, c0 + e)] = o.s[e];
+        }
+        if (c0 == 0) p.kvscale[kv_scale_offset(blk, p.Hkv, j) + (is_v ? 16 : 0) + tok] = kv_code_scale(am);
+      }
+    }
+  }
+}
+
 // QKN: the QKV epilogue also normalises the query and key heads (an instantiation of its own, so that the plain model's
 // kernel carries none of its registers)
-template <int EPI, bool QKN = false>
+template <int EPI, bool QKN, bool LAST>
 __global__ __launch_bounds__(256) void prefill_gemm_kernel(const PGemmP p) {
   // PGEMM_NB stage buffers of 2048 sixteen-byte units: 0..1023 weights [16 row groups][64], 1024..2047 activations [8 token groups][2 k16][64]
   extern __shared__ u32x4 smem[];
@@ -552,9 +754,17 @@ __global__ __launch_bounds__(256) void prefill_gemm_kernel(const PGemmP p) {
   float(*red_ssq)[256] = reinterpret_cast<float(*)[256]>(smem);
   (void)red_ssq;
 
-  pgemm_epilogue<EPI, QKN, 4>(p, acc, tt, rt, wn, wt, 0, [&](int tb, float ssq_tok) __attribute__((always_inline)) {
-    if (lane < 32) red_ssq[wn][wt * 128 + tb * 32 + lane] = ssq_tok;  // (slots of tokens past the end are never read)
+  const int t_w = __builtin_amdgcn_readfirstlane(tt * 256 + wt * 128);
+  f32x4* parked = reinterpret_cast<f32x4*>(smem + 128 + wave * 4 * LAST_UNITS);
+  if constexpr (LAST) park_last(p, acc, t_w, parked);
+  pgemm_epilogue<EPI, QKN, 4, LAST>(p, acc, tt, rt, wn, wt, 0, [&](int tb, float ssq_tok) __attribute__((always_inline)) {
+    const int at = wt * 128 + tb * 32 + lane;
+    if (lane < 32 && (!LAST || tt * 256 + at < p.first_last)) red_ssq[wn][at] = ssq_tok;  // (slots of tokens past the end are never read)
   });
+  if constexpr (LAST) {
+    __syncthreads();
+    last_epilogue<EPI, QKN, 4>(p, rt * 16 + wn * 8, t_w, parked, [&](int tb, int c, float s) __attribute__((always_inline)) { red_ssq[wn][wt * 128 + tb * 32 + c] = s; });
+  }
   if constexpr (EPI == PEPI_RESID) {
     // per (row tile, token) sum of squares of the new residual, the two row halves added in a fixed order
     __syncthreads();
@@ -579,7 +789,7 @@ __global__ __launch_bounds__(256) void prefill_gemm_kernel(const PGemmP p) {
 #define PSG_NB 8  // stage buffers of 64 columns of the tile's weights (16 KiB each)
 #define PSG_D 8
 #define PSG_LDS_BYTES (PSG_NB * 1024 * 16)
-template <int EPI, bool QKN, int TB>
+template <int EPI, bool QKN, int TB, bool LAST>
 __global__ __launch_bounds__(256, 1) void prefill_gemm_small_kernel(const PGemmP p) {
   extern __shared__ u32x4 smem[];  // per stage 1024 units: [2 k blocks][8 row groups][64]
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -753,9 +963,18 @@ __global__ __launch_bounds__(256, 1) void prefill_gemm_small_kernel(const PGemmP
   }
   if (n_act == 0) return;
   const int g32 = tt1 * 4 * TB + wave * TB;  // the wavefront's first group of 32 tokens; 8 of them make a 256-token tile
-  pgemm_epilogue<EPI, QKN, TB>(p, acc, g32 >> 3, rt1 >> 1, rt1 & 1, (g32 >> 2) & 1, g32 & 3, [&](int tb, float ssq_tok) __attribute__((always_inline)) {
-    if (lane < 32 && t_w + tb * 32 + lane < p.T) p.ssq_out[(int64_t)(t_w + tb * 32 + lane) * PSSQ + rt1] = ssq_tok;
+  f32x4* parked = reinterpret_cast<f32x4*>(smem + 64 + wave * TB * LAST_UNITS);  // (its own: no barrier needed; behind s_last)
+  if constexpr (LAST) park_last(p, acc, t_w, parked);
+  pgemm_epilogue<EPI, QKN, TB, LAST>(p, acc, g32 >> 3, rt1 >> 1, rt1 & 1, (g32 >> 2) & 1, g32 & 3, [&](int tb, float ssq_tok) __attribute__((always_inline)) {
+    const int t = t_w + tb * 32 + lane;
+    if (lane < 32 && t < (LAST ? p.T_new : p.T)) p.ssq_out[(int64_t)t * PSSQ + rt1] = ssq_tok;
   });
+  if constexpr (LAST) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    last_epilogue<EPI, QKN, TB>(p, rg_tile, t_w, parked, [&](int tb, int c, float s) __attribute__((always_inline)) { p.ssq_out[(int64_t)(t_w + tb * 32 + c) * PSSQ + rt1] = s; });
+  }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1121,12 +1340,11 @@ __global__ __launch_bounds__(256 * HG) void prefill_attn_merge_kernel(const int3
 // 28 (128, 2 splits), gate/up 91 / 91 (256 x 256), down 256 / 59 (256 tokens, 4 splits); 1024 tokens 106 / 67, 93 / 44,
 // 195 / 195, 261 / 117; 2048 tokens O 108 / 71, down 282 / 204; 8192 tokens: always 256 x 256 (gate/up 1388, the others 1660
 // and 2030).
-struct PGemmChoice { int tb, ks; };
+struct PGemmChoice { int tb, ks; float us; };
 static PGemmChoice choose_pgemm(int T, int NRG, int KB) {
   constexpr int CUS = 256;
   const float per_kb[3] = {0.76f, 0.29f, 0.43f}, per_round[3] = {12.f, 5.f, 8.f}, hand0[3] = {0.f, 7.f, 9.f}, hand1[3] = {0.f, 1.4f, 3.f};
-  PGemmChoice best = {0, 1};
-  float least = 0.f;
+  PGemmChoice best = {0, 1, 0.f};
   for (int tb = 0; tb <= 2; ++tb) {
     const int rows = tb ? 8 : 16, tokens = tb ? 128 * tb : 256;
     const int64_t tiles = (int64_t)((T + tokens - 1) / tokens) * ((NRG + rows - 1) / rows);
@@ -1134,10 +1352,7 @@ static PGemmChoice choose_pgemm(int T, int NRG, int KB) {
       if (ks > 1 && (!tb || tiles * ks > CUS || KB < 8 * ks)) break;  // (parked tiles and counters are sized by this line)
       const float us = (float)((tiles * ks + CUS - 1) / CUS) * (per_kb[tb] * (float)((KB + ks - 1) / ks) + per_round[tb]) +
                        (ks > 1 ? hand0[tb] + hand1[tb] * ks : 0.f);
-      if ((!tb && ks == 1) || us < least) {
-        least = us;
-        best = {tb, ks};
-      }
+      if ((!tb && ks == 1) || us < best.us) best = {tb, ks, us};
     }
   }
   return best;
@@ -1157,35 +1372,55 @@ uint64_t prefill_partial_bytes(int maxT, int NRG, int KB) {
   return most;
 }
 
+// rows of X of a call whose last positions ride along
+int prefill_rows(int T, int batch) { return (T + 31) / 32 * 32 + (batch + 15) / 16 * 32; }
+
+// Do the last positions of a call ride along as rows of its GEMMs?  Where that costs less, by the fit above, than the four
+// products of the decode pass, which stream their weights at about 6 TB/s and take about 3 us, and 0.16 us per sequence, besides.
+// Not for models with two weight planes, whose prefill reads the first alone.
+bool prefill_rides(const www_model* m, int T, int batch) {
+  if (m->wsplit || m->L < 2) return false;
+  const float per_weight = m->int4_group ? 0.5f + 2.f / 32 : m->fp8 ? 1.f : 2.f;
+  const int N[4] = {m->QKVN, m->d, 2 * m->F, m->d}, K[4] = {m->d, m->QD, m->d, m->Fp};
+  float saved = 0.f, added = 0.f;
+  for (int i = 0; i < 4; ++i) {
+    saved += (float)N[i] * (float)K[i] * per_weight / 6e6f + 3.f + 0.16f * (float)batch;
+    added += choose_pgemm(prefill_rows(T, batch), N[i] / 16, K[i] / 32).us - choose_pgemm(T, N[i] / 16, K[i] / 32).us;
+  }
+  return added < saved;
+}
+
 // Announces the GEMM kernels, which use more than 64 KiB of dynamic LDS, to the current device (when a model is loaded there).
-template <int EPI, bool QKN>
+template <int EPI, bool QKN, bool LAST>
 static hipError_t allow_pgemm_lds() {
   auto allow = [](const void* kernel, int bytes) { return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); };
-  hipError_t e = allow(reinterpret_cast<const void*>(&prefill_gemm_kernel<EPI, QKN>), PGEMM_LDS_BYTES);
-  if (e == hipSuccess) e = allow(reinterpret_cast<const void*>(&prefill_gemm_small_kernel<EPI, QKN, 1>), PSG_LDS_BYTES);
-  if (e == hipSuccess) e = allow(reinterpret_cast<const void*>(&prefill_gemm_small_kernel<EPI, QKN, 2>), PSG_LDS_BYTES);
+  hipError_t e = allow(reinterpret_cast<const void*>(&prefill_gemm_kernel<EPI, QKN, LAST>), LAST ? PGEMM_LAST_LDS_BYTES : PGEMM_LDS_BYTES);
+  if (e == hipSuccess) e = allow(reinterpret_cast<const void*>(&prefill_gemm_small_kernel<EPI, QKN, 1, LAST>), PSG_LDS_BYTES);
+  if (e == hipSuccess) e = allow(reinterpret_cast<const void*>(&prefill_gemm_small_kernel<EPI, QKN, 2, LAST>), PSG_LDS_BYTES);
+  return e;
+}
+template <bool LAST>
+static hipError_t allow_all_pgemm_lds() {
+  hipError_t e = allow_pgemm_lds<PEPI_QKV, false, LAST>();
+  if (e == hipSuccess) e = allow_pgemm_lds<PEPI_QKV, true, LAST>();
+  if (e == hipSuccess) e = allow_pgemm_lds<PEPI_RESID, false, LAST>();
+  if (e == hipSuccess) e = allow_pgemm_lds<PEPI_SWIGLU, false, LAST>();
   return e;
 }
 hipError_t prefill_allow_lds() {
-  hipError_t e = allow_pgemm_lds<PEPI_QKV, false>();
-  if (e == hipSuccess) e = allow_pgemm_lds<PEPI_QKV, true>();
-  if (e == hipSuccess) e = allow_pgemm_lds<PEPI_RESID, false>();
-  if (e == hipSuccess) e = allow_pgemm_lds<PEPI_SWIGLU, false>();
-  return e;
+  const hipError_t e = allow_all_pgemm_lds<false>();
+  return e == hipSuccess ? allow_all_pgemm_lds<true>() : e;
 }
 
 // returns the number of entries per token a residual epilogue wrote into the sum-of-squares table
-template <int EPI, bool QKN = false>
-static int launch_pgemm(www_model* m, PGemmP& p, hipStream_t st) {
-  if constexpr (EPI == PEPI_QKV && !QKN) {
-    if (p.qk_gain) return launch_pgemm<EPI, true>(m, p, st);
-  }
+template <int EPI, bool QKN, bool LAST>
+static int launch_pgemm_as(www_model* m, PGemmP& p, hipStream_t st) {
   p.n_tt = (p.T + 255) / 256;
   p.n_rt = (p.NRG + 15) / 16;
   if (p.wfactor == 0.f) p.wfactor = 1.f;  // not set: an unscaled matrix
   const PGemmChoice c = choose_pgemm(p.T, p.NRG, p.KB);
   if (c.tb == 0) {
-    hipLaunchKernelGGL((prefill_gemm_kernel<EPI, QKN>), dim3(p.n_tt * p.n_rt), dim3(256), PGEMM_LDS_BYTES, st, p);
+    hipLaunchKernelGGL((prefill_gemm_kernel<EPI, QKN, LAST>), dim3(p.n_tt * p.n_rt), dim3(256), LAST ? PGEMM_LAST_LDS_BYTES : PGEMM_LDS_BYTES, st, p);
     return p.n_rt;
   }
   p.n_ttS = (p.T + 128 * c.tb - 1) / (128 * c.tb);
@@ -1194,9 +1429,16 @@ static int launch_pgemm(www_model* m, PGemmP& p, hipStream_t st) {
   p.ksplit = (p.KB + p.kb_per_split - 1) / p.kb_per_split;
   p.partial = m->partial; p.counters = m->counters; p.fence_handover = m->handover_fence; p.fault_flag = m->fault_dev;
   const dim3 grid(8 * ((p.n_rt128 + 7) / 8) * p.ksplit * p.n_ttS);
-  if (c.tb == 1) hipLaunchKernelGGL((prefill_gemm_small_kernel<EPI, QKN, 1>), grid, dim3(256), PSG_LDS_BYTES, st, p);
-  else hipLaunchKernelGGL((prefill_gemm_small_kernel<EPI, QKN, 2>), grid, dim3(256), PSG_LDS_BYTES, st, p);
+  if (c.tb == 1) hipLaunchKernelGGL((prefill_gemm_small_kernel<EPI, QKN, 1, LAST>), grid, dim3(256), PSG_LDS_BYTES, st, p);
+  else hipLaunchKernelGGL((prefill_gemm_small_kernel<EPI, QKN, 2, LAST>), grid, dim3(256), PSG_LDS_BYTES, st, p);
   return p.n_rt128;
+}
+template <int EPI>
+static int launch_pgemm(www_model* m, PGemmP& p, hipStream_t st) {
+  if constexpr (EPI == PEPI_QKV) {
+    if (p.qk_gain) return p.n_last ? launch_pgemm_as<EPI, true, true>(m, p, st) : launch_pgemm_as<EPI, true, false>(m, p, st);
+  }
+  return p.n_last ? launch_pgemm_as<EPI, false, true>(m, p, st) : launch_pgemm_as<EPI, false, false>(m, p, st);
 }
 
 // Shape of the attention workgroups: two query heads per wavefront pass, since their accumulators and operands fit 256
@@ -1255,51 +1497,60 @@ static void launch_pattn(www_model* m, const uint16_t* kplane, const uint16_t* v
 }
 
 int run_prefill(www_model* m, const int32_t* tok, const int32_t* qlens, const int32_t* lens, const int32_t* table, int batch, int T,
-                hipStream_t st) {
+                bool rides, hipStream_t st) {
   const int d = m->d;
   int32_t* cum = m->meta + 16;
+  const int first_last = rides ? (T + 31) / 32 * 32 : 0, n_last = rides ? batch : 0, rows = rides ? prefill_rows(T, batch) : T;
   hipLaunchKernelGGL(prefill_meta_kernel, dim3(1), dim3(1024), 0, st, tok, qlens, lens, batch, T, m->row_seq, m->row_pos, m->tile_seq,
-                     m->tile_q0, m->meta, m->last_tok, cum);
+                     m->tile_q0, m->meta, m->last_tok, cum, first_last, rows);
+  if (rides) launch_attn_plan(m, lens, batch, st);
   if (m->cfg.weight_dtype == WWW_DTYPE_F32)
-    hipLaunchKernelGGL(embed_rows_kernel<float>, dim3(T), dim3(256), 0, st, tok, (const float*)m->embed, d, m->layers[0].attn_norm, m->hp,
-                       (uint16_t*)m->xn, m->ssq_p);
+    hipLaunchKernelGGL(embed_rows_kernel<float>, dim3(T + n_last), dim3(256), 0, st, tok, (const float*)m->embed, d, m->layers[0].attn_norm, m->hp,
+                       (uint16_t*)m->xn, m->ssq_p, T, first_last, m->last_tok, m->h);
   else
-    hipLaunchKernelGGL(embed_rows_kernel<uint16_t>, dim3(T), dim3(256), 0, st, tok, (const uint16_t*)m->embed, d, m->layers[0].attn_norm,
-                       m->hp, (uint16_t*)m->xn, m->ssq_p);
+    hipLaunchKernelGGL(embed_rows_kernel<uint16_t>, dim3(T + n_last), dim3(256), 0, st, tok, (const uint16_t*)m->embed, d, m->layers[0].attn_norm,
+                       m->hp, (uint16_t*)m->xn, m->ssq_p, T, first_last, m->last_tok, m->h);
   int n_ssq = 1;
   const int max_tiles = T / ATTN_TQ + batch;
+  auto gemm = [&]() {
+    PGemmP p = {};
+    p.T = rows; p.T_new = T; p.first_last = first_last; p.n_last = n_last; p.h_last = m->h;
+    return p;
+  };
   for (int l = 0; l < m->L; ++l) {
     const LayerW& w = m->layers[l];
     uint16_t* kplane = (uint16_t*)m->kv + (int64_t)(2 * l) * m->kv_plane;
     uint16_t* vplane = (uint16_t*)m->kv + (int64_t)(2 * l + 1) * m->kv_plane;
     float* kvscale = m->kv_scales + (int64_t)l * m->kv_scale_plane;
     {
-      PGemmP p = {};
-      p.W = (const u32x4*)w.wqkv; p.wfactor = w.sqkv; p.NRG = m->QKVN / 16; p.KB = d / 32; p.X = (const u32x4*)m->xn; p.T = T;
+      PGemmP p = gemm();
+      p.W = (const u32x4*)w.wqkv; p.wfactor = w.sqkv; p.NRG = m->QKVN / 16; p.KB = d / 32; p.X = (const u32x4*)m->xn;
       p.ssq_in = m->ssq_p; p.n_ssq_in = n_ssq; p.inv_dim = 1.f / d; p.eps = m->cfg.rms_eps;
       p.qp = (uint16_t*)m->qp; p.kplane = kplane; p.vplane = vplane; p.kvscale = kvscale; p.row_seq = m->row_seq; p.row_pos = m->row_pos; p.table = table;
       p.mbs = m->cfg.max_blocks_per_seq; p.hd = m->hd; p.Hq = m->Hq; p.Hkv = m->Hkv; p.rope = m->rope; p.qk_gain = w.qk_gain;
+      p.q_hi = m->q_hi; p.q_lo = m->q_lo; p.qscale = 1.4426950408889634f / sqrtf((float)m->hd);
       launch_pgemm<PEPI_QKV>(m, p, st);
     }
-    if (l == m->L - 1) break;  // only this layer's keys and values are still needed
+    if (l == m->L - 1) break;  // only this layer's keys and values (and the last positions' queries) are still needed
+    if (rides) launch_decode_attn(m, l, lens, table, batch, (uint16_t*)m->op, 0, first_last, st);
     if (m->hd == 128) launch_pattn<128>(m, kplane, vplane, kvscale, qlens, lens, table, max_tiles, st);
     else launch_pattn<64>(m, kplane, vplane, kvscale, qlens, lens, table, max_tiles, st);
     {
-      PGemmP p = {};
-      p.W = (const u32x4*)w.wo; p.wfactor = w.so; p.NRG = d / 16; p.KB = m->QD / 32; p.X = (const u32x4*)m->op; p.T = T;
+      PGemmP p = gemm();
+      p.W = (const u32x4*)w.wo; p.wfactor = w.so; p.NRG = d / 16; p.KB = m->QD / 32; p.X = (const u32x4*)m->op;
       p.hp = m->hp; p.d = d; p.gain_next = w.ffn_norm; p.xn_out = (uint16_t*)m->xn; p.ssq_out = m->ssq_p;
       n_ssq = launch_pgemm<PEPI_RESID>(m, p, st);
     }
     {
-      PGemmP p = {};
-      p.W = (const u32x4*)w.wgu; p.wfactor = w.sgu; p.NRG = 2 * m->F / 16; p.KB = d / 32; p.X = (const u32x4*)m->xn; p.T = T;
+      PGemmP p = gemm();
+      p.W = (const u32x4*)w.wgu; p.wfactor = w.sgu; p.NRG = 2 * m->F / 16; p.KB = d / 32; p.X = (const u32x4*)m->xn;
       p.ssq_in = m->ssq_p; p.n_ssq_in = n_ssq; p.inv_dim = 1.f / d; p.eps = m->cfg.rms_eps;
       p.ap = (uint16_t*)m->ap; p.Fp = m->Fp;
       launch_pgemm<PEPI_SWIGLU>(m, p, st);
     }
     {
-      PGemmP p = {};
-      p.W = (const u32x4*)w.wd; p.wfactor = w.sd; p.NRG = d / 16; p.KB = m->Fp / 32; p.X = (const u32x4*)m->ap; p.T = T;
+      PGemmP p = gemm();
+      p.W = (const u32x4*)w.wd; p.wfactor = w.sd; p.NRG = d / 16; p.KB = m->Fp / 32; p.X = (const u32x4*)m->ap;
       p.hp = m->hp; p.d = d; p.gain_next = m->layers[l + 1].attn_norm; p.xn_out = (uint16_t*)m->xn; p.ssq_out = m->ssq_p;
       n_ssq = launch_pgemm<PEPI_RESID>(m, p, st);
     }

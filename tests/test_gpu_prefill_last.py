@@ -1,0 +1,37 @@
+"""GPU: prefill calls whose last positions ride along as rows of the GEMMs (hi and lo parts in one group of 32 columns): one to
+several such groups, full and nearly empty ones, token counts around a group and a tile, chunks over a cached prefix, every weight
+format that rides, both tile kernels and k splits.  The rule is evaluated on the host, so which calls ride follows from the sizes;
+the cache entries of the last positions are checked by the decode steps behind.  Bounds of the parity tests."""
+import dataclasses
+
+import pytest
+
+from paper_2603_20661_amd import synth
+from test_gpu_parity import WIDE8B, check, run_job
+
+pytestmark = pytest.mark.gpu
+
+H64 = synth.ModelShape("last64", 3, 256, 6, 3, 64, 352, 512, 1e-5, 1e4, synth.WDTYPE_BF16, seed=601)
+H128 = synth.ModelShape("last128", 2, 384, 4, 1, 128, 4112, 512, 1e-5, 1e4, synth.WDTYPE_BF16, seed=602)   # k splits
+FORMATS = [H64, H128, dataclasses.replace(H64, name="last64qk", qk_norm=1, seed=603), dataclasses.replace(H128, name="last128qk", qk_norm=1, seed=604),
+           dataclasses.replace(H128, name="last128fp8", weight_dtype=synth.WDTYPE_FP8WO, seed=605),
+           dataclasses.replace(H64, name="last64int4", ffn_dim=384, weight_dtype=synth.WDTYPE_INT4WO_32, seed=606)]
+
+
+@pytest.mark.parametrize("batch,total", [(1, 1), (1, 32), (3, 97), (16, 16), (17, 160), (33, 250), (70, 300)], ids=str)
+@pytest.mark.parametrize("shape", FORMATS, ids=lambda s: s.name)
+def test_groups_of_last_positions(shape, batch, total):
+    lens = [total // batch + (i < total % batch) for i in range(batch)]
+    check(run_job(shape, lens, 2, seed=610 + batch + total), f"{shape.name} {batch} sequences, {total} tokens")
+
+
+@pytest.mark.parametrize("shape", FORMATS[:4], ids=lambda s: s.name)
+def test_chunks_over_a_prefix(shape):
+    """every chunk's last position rides, the cache entry it leaves is read by the next chunk"""
+    check(run_job(shape, [150, 33, 1, 96], 2, seed=640, chunk=32), f"{shape.name} chunks of 32")
+
+
+@pytest.mark.parametrize("lens", [[200], [100, 60, 64], [300, 2]], ids=str)
+def test_large_tiles(lens):
+    """full-width matrices: the gate/up product takes the 256 x 256 tiles, the others the smaller ones, some with split k ranges"""
+    check(run_job(dataclasses.replace(WIDE8B, n_layers=2), lens, 1, seed=650 + len(lens)), f"{WIDE8B.name} {lens}")

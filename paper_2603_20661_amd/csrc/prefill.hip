@@ -757,7 +757,7 @@ __global__ __launch_bounds__(256) void prefill_gemm_kernel(const PGemmP p) {
   const int t_w = __builtin_amdgcn_readfirstlane(tt * 256 + wt * 128);
   f32x4* parked = reinterpret_cast<f32x4*>(smem + 128 + wave * 4 * LAST_UNITS);
   if constexpr (LAST) park_last(p, acc, t_w, parked);
-  pgemm_epilogue<EPI, QKN, 4, LAST>(p, acc, tt, rt, wn, wt, 0, [&](int tb, float ssq_tok) __attribute__((always_inline)) {
+  if (!LAST || t_w < p.first_last) pgemm_epilogue<EPI, QKN, 4, LAST>(p, acc, tt, rt, wn, wt, 0, [&](int tb, float ssq_tok) __attribute__((always_inline)) {
     const int at = wt * 128 + tb * 32 + lane;
     if (lane < 32 && (!LAST || tt * 256 + at < p.first_last)) red_ssq[wn][at] = ssq_tok;  // (slots of tokens past the end are never read)
   });
@@ -965,7 +965,7 @@ __global__ __launch_bounds__(256, 1) void prefill_gemm_small_kernel(const PGemmP
   const int g32 = tt1 * 4 * TB + wave * TB;  // the wavefront's first group of 32 tokens; 8 of them make a 256-token tile
   f32x4* parked = reinterpret_cast<f32x4*>(smem + 64 + wave * TB * LAST_UNITS);  // (its own: no barrier needed; behind s_last)
   if constexpr (LAST) park_last(p, acc, t_w, parked);
-  pgemm_epilogue<EPI, QKN, TB, LAST>(p, acc, g32 >> 3, rt1 >> 1, rt1 & 1, (g32 >> 2) & 1, g32 & 3, [&](int tb, float ssq_tok) __attribute__((always_inline)) {
+  if (!LAST || t_w < p.first_last) pgemm_epilogue<EPI, QKN, TB, LAST>(p, acc, g32 >> 3, rt1 >> 1, rt1 & 1, (g32 >> 2) & 1, g32 & 3, [&](int tb, float ssq_tok) __attribute__((always_inline)) {
     const int t = t_w + tb * 32 + lane;
     if (lane < 32 && t < (LAST ? p.T_new : p.T)) p.ssq_out[(int64_t)t * PSSQ + rt1] = ssq_tok;
   });
@@ -1403,7 +1403,7 @@ template <bool LAST>
 static hipError_t allow_all_pgemm_lds() {
   hipError_t e = allow_pgemm_lds<PEPI_QKV, false, LAST>();
   if (e == hipSuccess) e = allow_pgemm_lds<PEPI_QKV, true, LAST>();
-  if (e == hipSuccess) e = allow_pgemm_lds<PEPI_RESID, false, LAST>();
+  if constexpr (LAST) if (e == hipSuccess) e = allow_pgemm_lds<PEPI_RESID, false, true>();
   if (e == hipSuccess) e = allow_pgemm_lds<PEPI_SWIGLU, false, LAST>();
   return e;
 }
@@ -1438,7 +1438,10 @@ static int launch_pgemm(www_model* m, PGemmP& p, hipStream_t st) {
   if constexpr (EPI == PEPI_QKV) {
     if (p.qk_gain) return p.n_last ? launch_pgemm_as<EPI, true, true>(m, p, st) : launch_pgemm_as<EPI, true, false>(m, p, st);
   }
-  return p.n_last ? launch_pgemm_as<EPI, false, true>(m, p, st) : launch_pgemm_as<EPI, false, false>(m, p, st);
+  // The residual GEMMs always run the kernel that can carry last positions: their 256 x 256 epilogue spills 4 registers there and
+  // 63 without (8B shape, calls of 16 000 tokens: the two of a layer 2 x 1407 against 2 x 1467 us).
+  if constexpr (EPI == PEPI_RESID) return launch_pgemm_as<EPI, false, true>(m, p, st);
+  else return p.n_last ? launch_pgemm_as<EPI, false, true>(m, p, st) : launch_pgemm_as<EPI, false, false>(m, p, st);
 }
 
 // Shape of the attention workgroups: two query heads per wavefront pass, since their accumulators and operands fit 256
@@ -1514,7 +1517,7 @@ int run_prefill(www_model* m, const int32_t* tok, const int32_t* qlens, const in
   const int max_tiles = T / ATTN_TQ + batch;
   auto gemm = [&]() {
     PGemmP p = {};
-    p.T = rows; p.T_new = T; p.first_last = first_last; p.n_last = n_last; p.h_last = m->h;
+    p.T = rows; p.T_new = T; p.first_last = rides ? first_last : 0x7fffffff; p.n_last = n_last; p.h_last = m->h;
     return p;
   };
   for (int l = 0; l < m->L; ++l) {

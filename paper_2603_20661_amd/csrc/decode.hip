@@ -971,8 +971,8 @@ __global__ __launch_bounds__(256) void decode_attn_kernel(const uint16_t* __rest
 }
 
 // Merges the records of one (sequence, kv head) and writes the packed hi/lo operand of the O projection.  MERGE_WAVES wavefronts
-// per (kv head, sequence): wavefront v merges, in key order, the v-th run of consecutive records, and wavefront 0 then
-// adds the intermediate records, in key order again (a fixed order).  Sequences that were a single segment were
+// per (kv head, sequence): wavefront v merges, in key order, the v-th run of consecutive records; the intermediate records
+// are then added in key order again (a fixed order), one query head and 64 of its dims per wavefront.  Sequences that were a single segment were
 // finished by the attention kernel itself.  Bound by dependent memory round trips; eight wavefronts reading four records
 // at a time take a sequence of 32 records in one of them (8B shape, graph replay, against one wavefront: one sequence of
 // 8192 tokens 4800 -> 3800 us a step, 64 sequences 6450 -> 6395, 16 sequences with FP8 weights 3095 -> 2963).
@@ -1036,7 +1036,7 @@ __global__ __launch_bounds__(64 * MERGE_WAVES) void decode_attn_merge_kernel(con
     }
   }
   __shared__ float mid[NS][G][PSTRIDE];
-  if (v > 0 && v * per < nrec) {
+  if (v * per < nrec) {
 #pragma unroll
     for (int hh = 0; hh < G; ++hh) {
       if (lane == 0) { mid[v][hh][HD] = Mh[hh]; mid[v][hh][HD + 1] = Lh[hh]; }
@@ -1045,27 +1045,30 @@ __global__ __launch_bounds__(64 * MERGE_WAVES) void decode_attn_merge_kernel(con
     }
   }
   __syncthreads();
-  if (v > 0) return;
-  for (int u = 1; u < NS && u * per < nrec; ++u) {
+  const int n_mid = (nrec + per - 1) / per;
+  for (int q = v; q < G * NE; q += NS) {
+    const int hh = q / NE, c = lane + 64 * (q % NE);
+    float mv[NS], lv[NS], ov[NS];
 #pragma unroll
-    for (int hh = 0; hh < G; ++hh) {
-      float ov[NE];
-#pragma unroll
-      for (int i = 0; i < NE; ++i) ov[i] = mid[u][hh][lane + 64 * i];
-      take(hh, mid[u][hh][HD], mid[u][hh][HD + 1], ov);
+    for (int u = 0; u < NS; ++u) {
+      const int w = min(u, n_mid - 1);
+      mv[u] = mid[w][hh][HD]; lv[u] = mid[w][hh][HD + 1]; ov[u] = mid[w][hh][c];
     }
-  }
+    float M = mv[0], L = lv[0], o = ov[0];
 #pragma unroll
-  for (int hh = 0; hh < G; ++hh) {
-    const float inv = 1.f / Lh[hh];
-#pragma unroll
-    for (int i = 0; i < NE; ++i) {
-      const int k = (j * G + hh) * HD + lane + 64 * i;
-      uint16_t hi, lo;
-      split_f16(oh[hh][i] * inv, hi, lo);
-      xo[attn_out_offset(k, b, 0, MT, first_row, Hkv * G * HD / 16)] = hi;
-      xo[attn_out_offset(k, b, 1, MT, first_row, Hkv * G * HD / 16)] = lo;
+    for (int u = 1; u < NS; ++u) {
+      if (u >= n_mid) break;
+      const float Mn = fmaxf(M, mv[u]), ref = Mn == NEG_INF ? 0.f : Mn;
+      const float a = __builtin_amdgcn_exp2f(M - ref), w = __builtin_amdgcn_exp2f(mv[u] - ref);
+      L = L * a + lv[u] * w;
+      o = o * a + ov[u] * w;
+      M = Mn;
     }
+    const int k = (j * G + hh) * HD + c;
+    uint16_t hi, lo;
+    split_f16(o * (1.f / L), hi, lo);
+    xo[attn_out_offset(k, b, 0, MT, first_row, Hkv * G * HD / 16)] = hi;
+    xo[attn_out_offset(k, b, 1, MT, first_row, Hkv * G * HD / 16)] = lo;
   }
 }
 

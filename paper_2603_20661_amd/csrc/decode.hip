@@ -9,12 +9,95 @@
 #include "decode_gemm.h"
 
 // ------------------------------------------------------------------------------------------------
-// Embedding gather: h = E[token]; sum of squares; packed (h * gain) for the first QKV GEMM.
+// Plan of the decode attention, built once per step and used by every layer.
+//
+// The keys of the batch are counted in pairs of 16-key blocks.  All (sequence b, kv head j, pair) triples, in that
+// order, form one long list of T = Hkv * sum_b P_b entries (P_b = pairs of sequence b); the attention kernel runs W
+// wavefronts and wavefront w takes the entries [w*C, (w+1)*C), C = ceil(T / W), at least min(16, ceil(longest P / 64)).  Every wavefront therefore
+// streams the same number of bytes and all of them finish together, whatever the mix of sequence lengths.  A chunk may
+// end inside a (b, j) sequence and continue into the next one; each piece is a segment with its own softmax state,
+// parked as a record and merged afterwards.  Only the first and the last segment of a chunk can be part of a longer
+// sequence, so wavefront w owns the records 2w (the segment its chunk begins with) and 2w + 1 (a later one).
+// The cut points depend on the lengths of all sequences of the batch: results are reproducible for a given batch
+// but the rounding of a sequence's attention output may differ between batches of different composition.
+// C has no other lower bound: with few tokens in the batch a chunk is a single pair, and the whole GPU works on it.  (At
+// least 16 pairs a chunk, one sequence of 1041 tokens had 17 wavefronts: 32 us per layer of the 8B shape against 6; a
+// step took 4197 us, 3835 with at least 8 pairs, 3661 with 4, 3543 with 1.)  A sequence of up to 32 768 tokens is cut into
+// at most 64 full chunks, because the merge reads 32 records per memory round trip (a step of one sequence with 64 chunks
+// and with one per wavefront, us: 4096 tokens 3762 / 3877, 8192 3862 / 4014, 16 384 4058 / 4120, 32 768 4467 / 4475).  Beyond, the
+// wavefronts that this leaves without work cost more than a round trip (65 536: 5325 / 5122, 131 072: 7027 / 6410), so chunks
+// of 16 pairs are long enough.
+//   hdr[0] = T, hdr[1] = C;  start[w] = (b, j, first pair, length of b) of wavefront w, b = -1 if it has no work;
+//   pref[b] = sum of P over the sequences before b
+struct AttnPlan {
+  const int32_t* seq_lens;
+  int batch, Hkv, W;
+  int32_t *hdr, *start, *pref;
+};
+__device__ __forceinline__ void attn_plan(const AttnPlan& a, int* pref /* LDS: [batch + 1] and the longest P */) {
+  const int32_t* __restrict__ const seq_lens = a.seq_lens;
+  int32_t *__restrict__ const hdr = a.hdr, *__restrict__ const start = a.start, *__restrict__ const pref_out = a.pref;
+  const int batch = a.batch, Hkv = a.Hkv, W = a.W;
+  const int tid = threadIdx.x, lane = tid & 63;
+  if (tid < 64) {
+    int carry = 0, top = 0;
+    if (lane == 0) pref[0] = 0;
+    for (int c = 0; c < batch; c += 64) {
+      const int bb = c + lane;
+      const int P = bb < batch ? max(0, (seq_lens[bb] + 31) / 32) : 0;
+      int inc = P;
+      top = max(top, P);
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int up = __shfl_up(inc, o);
+        if (lane >= o) inc += up;
+      }
+      if (bb < batch) pref[bb + 1] = carry + inc;
+      carry += __shfl(inc, 63);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) top = max(top, __shfl_xor(top, o));
+    if (lane == 0) pref[batch + 1] = top;
+  }
+  __syncthreads();
+  const int T = pref[batch] * Hkv, longest = pref[batch + 1];
+  const int C = max(1, max((T + W - 1) / W, min(16, (longest + 63) / 64)));
+  if (tid == 0) { hdr[0] = T; hdr[1] = C; }
+  for (int i = tid; i <= batch; i += 256) pref_out[i] = pref[i];
+  for (int w = tid; w < W; w += 256) {
+    const int64_t x0 = (int64_t)w * C;
+    int sb = -1, sj = 0, sp = 0, sctx = 0;
+    if (x0 < T) {
+      int lo = 0, hi = batch - 1;  // largest b with Hkv * pref[b] <= x0
+      while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if ((int64_t)pref[mid] * Hkv <= x0) lo = mid; else hi = mid - 1;
+      }
+      const int P = max(1, pref[lo + 1] - pref[lo]);  // (never 0 for the sequence that holds entry x0 < T)
+      const int r = (int)(x0 - (int64_t)pref[lo] * Hkv);
+      sb = lo; sj = r / P; sp = r % P; sctx = seq_lens[lo];
+    }
+    start[4 * w] = sb; start[4 * w + 1] = sj; start[4 * w + 2] = sp; start[4 * w + 3] = sctx;
+  }
+}
+__global__ __launch_bounds__(256) void attn_plan_kernel(const AttnPlan a) {
+  extern __shared__ int plan_lds[];
+  attn_plan(a, plan_lds);
+}
+
+// ------------------------------------------------------------------------------------------------
+// Embedding gather: h = E[token]; sum of squares; packed (h * gain) for the first QKV GEMM.  Workgroup 0 makes the attention's
+// plan meanwhile, which needs none of it (a launch of its own: 4.6 us of a step of the tiny shape's 74).
 template <typename ET>
 __global__ __launch_bounds__(256) void embed_pack_kernel(const int32_t* __restrict__ tokens, const ET* __restrict__ embed, int d,
                                                           const float* __restrict__ gain, float* __restrict__ h,
-                                                          float* __restrict__ ssq, uint16_t* __restrict__ xq, int MT) {
-  int t = blockIdx.x;
+                                                          float* __restrict__ ssq, uint16_t* __restrict__ xq, int MT, const AttnPlan plan) {
+  extern __shared__ int plan_lds[];  // the plan's, or 256 partial sums
+  if (blockIdx.x == 0) {
+    attn_plan(plan, plan_lds);
+    return;
+  }
+  int t = blockIdx.x - 1;
   const ET* row = embed + (int64_t)tokens[t] * d;
   float local = 0.f;
   for (int o = threadIdx.x; o < d / 8; o += blockDim.x) {
@@ -32,7 +115,7 @@ __global__ __launch_bounds__(256) void embed_pack_kernel(const int32_t* __restri
     *reinterpret_cast<u32x4*>(xq + packed_x_offset(k, t, MT, 0)) = hi.v;
     *reinterpret_cast<u32x4*>(xq + packed_x_offset(k, t, MT, 1)) = lo.v;
   }
-  __shared__ float red[256];
+  float* red = reinterpret_cast<float*>(plan_lds);
   red[threadIdx.x] = local;
   __syncthreads();
   for (int s = 128; s > 0; s >>= 1) {
@@ -628,73 +711,6 @@ __global__ __launch_bounds__(256 * KH, MTK == 8 ? 1 : 2 / KH) void skinny_gemm_k
 }
 
 // ------------------------------------------------------------------------------------------------
-// Plan of the decode attention, built once per step and used by every layer.
-//
-// The keys of the batch are counted in pairs of 16-key blocks.  All (sequence b, kv head j, pair) triples, in that
-// order, form one long list of T = Hkv * sum_b P_b entries (P_b = pairs of sequence b); the attention kernel runs W
-// wavefronts and wavefront w takes the entries [w*C, (w+1)*C), C = ceil(T / W), at least min(16, ceil(longest P / 64)).  Every wavefront therefore
-// streams the same number of bytes and all of them finish together, whatever the mix of sequence lengths.  A chunk may
-// end inside a (b, j) sequence and continue into the next one; each piece is a segment with its own softmax state,
-// parked as a record and merged afterwards.  Only the first and the last segment of a chunk can be part of a longer
-// sequence, so wavefront w owns the records 2w (the segment its chunk begins with) and 2w + 1 (a later one).
-// The cut points depend on the lengths of all sequences of the batch: results are reproducible for a given batch
-// but the rounding of a sequence's attention output may differ between batches of different composition.
-// C has no other lower bound: with few tokens in the batch a chunk is a single pair, and the whole GPU works on it.  (At
-// least 16 pairs a chunk, one sequence of 1041 tokens had 17 wavefronts: 32 us per layer of the 8B shape against 6; a
-// step took 4197 us, 3835 with at least 8 pairs, 3661 with 4, 3543 with 1.)  A sequence of up to 32 768 tokens is cut into
-// at most 64 full chunks, because the merge reads 32 records per memory round trip (a step of one sequence with 64 chunks
-// and with one per wavefront, us: 4096 tokens 3762 / 3877, 8192 3862 / 4014, 16 384 4058 / 4120, 32 768 4467 / 4475).  Beyond, the
-// wavefronts that this leaves without work cost more than a round trip (65 536: 5325 / 5122, 131 072: 7027 / 6410), so chunks
-// of 16 pairs are long enough.
-//   hdr[0] = T, hdr[1] = C;  start[w] = (b, j, first pair, length of b) of wavefront w, b = -1 if it has no work;
-//   pref[b] = sum of P over the sequences before b
-__global__ __launch_bounds__(256) void attn_plan_kernel(const int32_t* __restrict__ seq_lens, int batch, int Hkv, int W,
-                                                        int32_t* __restrict__ hdr, int32_t* __restrict__ start,
-                                                        int32_t* __restrict__ pref_out) {
-  extern __shared__ int pref[];  // [batch + 1] and the longest P
-  const int tid = threadIdx.x, lane = tid & 63;
-  if (tid < 64) {
-    int carry = 0, top = 0;
-    if (lane == 0) pref[0] = 0;
-    for (int c = 0; c < batch; c += 64) {
-      const int bb = c + lane;
-      const int P = bb < batch ? max(0, (seq_lens[bb] + 31) / 32) : 0;
-      int inc = P;
-      top = max(top, P);
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int up = __shfl_up(inc, o);
-        if (lane >= o) inc += up;
-      }
-      if (bb < batch) pref[bb + 1] = carry + inc;
-      carry += __shfl(inc, 63);
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) top = max(top, __shfl_xor(top, o));
-    if (lane == 0) pref[batch + 1] = top;
-  }
-  __syncthreads();
-  const int T = pref[batch] * Hkv, longest = pref[batch + 1];
-  const int C = max(1, max((T + W - 1) / W, min(16, (longest + 63) / 64)));
-  if (tid == 0) { hdr[0] = T; hdr[1] = C; }
-  for (int i = tid; i <= batch; i += 256) pref_out[i] = pref[i];
-  for (int w = tid; w < W; w += 256) {
-    const int64_t x0 = (int64_t)w * C;
-    int sb = -1, sj = 0, sp = 0, sctx = 0;
-    if (x0 < T) {
-      int lo = 0, hi = batch - 1;  // largest b with Hkv * pref[b] <= x0
-      while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if ((int64_t)pref[mid] * Hkv <= x0) lo = mid; else hi = mid - 1;
-      }
-      const int P = max(1, pref[lo + 1] - pref[lo]);  // (never 0 for the sequence that holds entry x0 < T)
-      const int r = (int)(x0 - (int64_t)pref[lo] * Hkv);
-      sb = lo; sj = r / P; sp = r % P; sctx = seq_lens[lo];
-    }
-    start[4 * w] = sb; start[4 * w + 1] = sj; start[4 * w + 2] = sp; start[4 * w + 3] = sctx;
-  }
-}
-
 // Two 16-bit codes (one 32-bit word, offset binary u = x + 32768) as two pairs of fp16 numbers a, b with x = 256 a + b,
 // a in [-128, 127], b in [0, 255] - both exact in fp16, so the matrix cores multiply the codes without losing a bit.
 // The high and low bytes of u are planted in the mantissa of the fp16 number 1024 (0x6400 | n = 1024 + n) and
@@ -1257,9 +1273,12 @@ int decode_probe_placement(int32_t* scratch_dev, int n, hipStream_t st) {
 
 int decode_MT(int batch) { return batch <= 16 ? 1 : batch <= 32 ? 2 : batch <= 64 ? 4 : ((batch + 127) / 128) * 8; }
 
+static AttnPlan plan_of(const www_model* m, const int32_t* lens, int batch) {
+  return {lens, batch, m->Hkv, m->attn_waves, m->attn_hdr, m->attn_start, m->attn_pref};
+}
+static size_t plan_lds_bytes(int batch) { return batch + 2 < 256 ? 1024 : (size_t)(batch + 2) * 4; }
 void launch_attn_plan(www_model* m, const int32_t* lens, int batch, hipStream_t st) {
-  hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(256), (size_t)(batch + 2) * 4, st, lens, batch, m->Hkv, m->attn_waves, m->attn_hdr,
-                     m->attn_start, m->attn_pref);
+  hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(256), plan_lds_bytes(batch), st, plan_of(m, lens, batch));
 }
 
 void launch_decode_attn(www_model* m, int l, const int32_t* lens, const int32_t* table, int batch, uint16_t* out, int MT, int first_row, hipStream_t st) {
@@ -1289,12 +1308,11 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
   if (!from_last_qkv) {
     prof_mark(m, PK_EMBED, st);
     if (m->cfg.weight_dtype == WWW_DTYPE_F32)
-      hipLaunchKernelGGL(embed_pack_kernel<float>, dim3(batch), dim3(256), 0, st, tok, (const float*)m->embed, d, m->layers[0].attn_norm,
-                         m->h, ssq, (uint16_t*)m->xq, MT);
+      hipLaunchKernelGGL(embed_pack_kernel<float>, dim3(batch + 1), dim3(256), plan_lds_bytes(batch), st, tok, (const float*)m->embed, d, m->layers[0].attn_norm,
+                         m->h, ssq, (uint16_t*)m->xq, MT, plan_of(m, lens, batch));
     else
-      hipLaunchKernelGGL(embed_pack_kernel<uint16_t>, dim3(batch), dim3(256), 0, st, tok, (const uint16_t*)m->embed, d,
-                         m->layers[0].attn_norm, m->h, ssq, (uint16_t*)m->xq, MT);
-    launch_attn_plan(m, lens, batch, st);
+      hipLaunchKernelGGL(embed_pack_kernel<uint16_t>, dim3(batch + 1), dim3(256), plan_lds_bytes(batch), st, tok, (const uint16_t*)m->embed, d,
+                         m->layers[0].attn_norm, m->h, ssq, (uint16_t*)m->xq, MT, plan_of(m, lens, batch));
   }
   int n_ssq = 1;  // entries per token of the sum-of-squares table: one per row group or per row tile of the GEMM that wrote it
   auto resid_entries = [&](int KB) { return small_gemm_takes(m, EPI_RESID, d / 16, KB, batch) ? d / 16 : (d / 16 + 7) / 8; };

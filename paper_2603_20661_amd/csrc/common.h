@@ -144,6 +144,31 @@ __device__ __forceinline__ bool arrive_last(unsigned long long* counter, int ksp
   return last;
 }
 
+// Adds n parked partial tiles in order: load(slot, i) requests tile i into one of W register sets, add(slot) adds it.  The set
+// just added takes the next tile, so that W requests stay on their way and a range of 8 splits costs one memory latency, not two.
+template <int W, typename LOAD, typename ADD>
+__device__ __forceinline__ void add_in_order(int n, LOAD load, ADD add) {
+#pragma unroll
+  for (int u = 0; u < W; ++u) load(u, min(u, n - 1));
+  int i = W;
+  for (; i + W <= n; i += W) {
+#pragma unroll
+    for (int u = 0; u < W; ++u) {
+      add(u);
+      load(u, i + u);
+    }
+  }
+  // sets 0 .. W-1 hold tiles i-W .. i-1; n - i < W are left
+#pragma unroll
+  for (int u = 0; u < W; ++u) {
+    if (i - W + u < n) add(u);
+    if (i + u < n) load(u, i + u);
+  }
+#pragma unroll
+  for (int u = 0; u < W - 1; ++u)
+    if (i + u < n) add(u);
+}
+
 // ------------------------------------------------------------------------------------------------
 struct LayerW {
   const uint16_t *wqkv, *wqkv_lo, *wo, *wo_lo, *wgu, *wgu_lo, *wd, *wd_lo;  // packed fp16 (lo planes only for fp32 sources)

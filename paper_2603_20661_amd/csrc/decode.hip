@@ -502,28 +502,22 @@ __global__ __launch_bounds__(256 * KH, MTK == 8 ? 1 : 2 / KH) void skinny_gemm_k
     for (int r = 0; r < R; ++r)
 #pragma unroll
       for (int tb = 0; tb < MTK; ++tb) acc[r][tb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // partial tiles are added in split order (reproducible); loads are issued four splits at a time so that
-    // the reduction is not one memory round trip per split
+    // partial tiles are added in split order (reproducible), four on their way at a time
     constexpr int NSP = 4;
-    for (int s0 = 0; s0 < p.ksplit; s0 += NSP) {
-      f32x4 pv[NSP][R][MTK];
+    f32x4 pv[NSP][R][MTK];
+    add_in_order<NSP>(p.ksplit,
+        [&](int u, int sp) __attribute__((always_inline)) {
 #pragma unroll
-      for (int u = 0; u < NSP; ++u) {
-        const int sidx = min(s0 + u, p.ksplit - 1);
+          for (int r = 0; r < R; ++r)
 #pragma unroll
-        for (int r = 0; r < R; ++r)
+            for (int tb = 0; tb < MTK; ++tb) pv[u][r][tb] = load_shared_f32x4(prs, punit(sp, r, tb));
+        },
+        [&](int u) __attribute__((always_inline)) {
 #pragma unroll
-          for (int tb = 0; tb < MTK; ++tb) pv[u][r][tb] = load_shared_f32x4(prs, punit(sidx, r, tb));
-      }
+          for (int r = 0; r < R; ++r)
 #pragma unroll
-      for (int u = 0; u < NSP; ++u) {
-        if (s0 + u >= p.ksplit) break;
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-          for (int tb = 0; tb < MTK; ++tb) acc[r][tb] += pv[u][r][tb];
-      }
-    }
+            for (int tb = 0; tb < MTK; ++tb) acc[r][tb] += pv[u][r][tb];
+        });
   }
 
   float ssq_local[MTK];

@@ -270,18 +270,16 @@ __global__ __launch_bounds__(64 * SG_NW, sg_eu(WMODE, R, XF)) void small_gemm_ke
       if (wave < n_fin) {
 #pragma unroll
         for (int tb = 0; tb < TB; ++tb) v[tb] = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int s0 = 0; s0 < p.ksplit; s0 += 4) {
-          f32x4 pv[4][TB];
+        f32x4 pv[4][TB];
+        add_in_order<4>(p.ksplit,
+            [&](int u, int sp) __attribute__((always_inline)) {
 #pragma unroll
-          for (int u = 0; u < 4; ++u)
+              for (int tb = 0; tb < TB; ++tb) pv[u][tb] = load_shared_f32x4(prs, unit(sp, frgc, tb));
+            },
+            [&](int u) __attribute__((always_inline)) {
 #pragma unroll
-            for (int tb = 0; tb < TB; ++tb) pv[u][tb] = load_shared_f32x4(prs, unit(min(s0 + u, p.ksplit - 1), frgc, tb));
-#pragma unroll
-          for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int tb = 0; tb < TB; ++tb)
-              if (s0 + u < p.ksplit) v[tb] += pv[u][tb];
-        }
+              for (int tb = 0; tb < TB; ++tb) v[tb] += pv[u][tb];
+            });
       }
     }
   }

@@ -936,7 +936,7 @@ __global__ __launch_bounds__(256, 1) void prefill_gemm_small_kernel(const PGemmP
     if (!*s_last) return;
     if (p.fence_handover) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     if (tid == 0) __hip_atomic_store(&p.counters[tile], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // added in split order (reproducible), the loads of two splits in flight together
+    // added in split order (reproducible), three on their way at a time
 #pragma unroll
     for (int tb = 0; tb < TB; ++tb) {
       if (tb >= n_act) break;
@@ -944,21 +944,18 @@ __global__ __launch_bounds__(256, 1) void prefill_gemm_small_kernel(const PGemmP
       for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[rb][tb][i] = 0.f;
-      for (int s0 = 0; s0 < p.ksplit; s0 += 2) {
-        f32x4 pv[2][16];
+      f32x4 pv[3][16];
+      add_in_order<3>(p.ksplit,
+          [&](int w, int sp) __attribute__((always_inline)) {
 #pragma unroll
-        for (int w = 0; w < 2; ++w)
+            for (int u = 0; u < 16; ++u) pv[w][u] = load_shared_f32x4(prs, punit(sp, tb, u));
+          },
+          [&](int w) __attribute__((always_inline)) {
 #pragma unroll
-          for (int u = 0; u < 16; ++u) pv[w][u] = load_shared_f32x4(prs, punit(min(s0 + w, p.ksplit - 1), tb, u));
+            for (int u = 0; u < 16; ++u)
 #pragma unroll
-        for (int w = 0; w < 2; ++w) {
-          if (s0 + w >= p.ksplit) break;
-#pragma unroll
-          for (int u = 0; u < 16; ++u)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[u >> 2][tb][(u & 3) * 4 + e] += pv[w][u][e];
-        }
-      }
+              for (int e = 0; e < 4; ++e) acc[u >> 2][tb][(u & 3) * 4 + e] += pv[w][u][e];
+          });
     }
   }
   if (n_act == 0) return;

@@ -447,12 +447,15 @@ static SmallShape small_shape(int epi, int NRG, int KB, int hd, int xf, int wmod
 // 8.0 / 10.0; down 22.4 / 25.8, 24.8 / 26.5, 26.4 / 28.0, 11.1 / 15.5, 14.0 / 17.5; output head 168 / 174 and 172 / 182 (1B: equal);
 // int4, 5 sequences: QKV 10.8 / 13.0, O 6.8 / 10.4, gate/up 18.0 / 24.4, down 13.2 / 17.7, head 56 / 67.  Not the gate/up GEMM
 // of the other formats, which has rows for every compute unit without a split (39.0 / 37.6, with FP8 24.6 / 21.9; 1B shape with up
-// to 8 tokens 13.4 / 14.6), and none whose k range leaves half of the wavefronts without a chunk (tiny shape, 4 sequences: 75 us a
-// step, 72 with the other kernel; 20 sequences: 80 against 84).
+// to 8 tokens 13.4 / 14.6), unless 64 rows per workgroup fill the chip in one round: then up to 8 tokens and, where the other kernel
+// has to split k, from 17 on (1B shape, 32 tokens 15.4 / 16.9; a step of 24 sequences with FP8 weights 880 / 896; of 12 and 16
+// sequences 904 / 899 and 916 / 911, with FP8 767 / 770 and 776 / 781: within 0.6 %, so those stay).
+// None whose k range leaves half of the wavefronts without a chunk (tiny shape, 4 sequences: 75 us a step, 72 with the other
+// kernel; 20 sequences: 80 against 84).
 bool small_gemm_takes(const www_model* m, int epi, int NRG, int KB, int M) {
   if (KB < 16 && M <= 16) return false;
   if (epi == EPI_QKV || epi == EPI_RESID) return M <= 32;
-  if (M > 16) return false;
+  if (M > 16) return M <= 32 && epi == EPI_SWIGLU && !m->wsplit && !m->int4_group && NRG <= 4 * decode_wg_target();
   if (epi == EPI_LOGITS || m->int4_group || m->wsplit) return true;
   return M <= 8 && NRG <= 4 * decode_wg_target();
 }
@@ -485,7 +488,7 @@ void launch_small_gemm(www_model* m, GemmP& p, hipStream_t st) {
   p.zbs = p.ksplit * (EPI == EPI_QKV ? hrg / (s.R * RW) : 1);
   const dim3 grid(8 * ((p.row_tiles + 7) / 8) * p.zbs), block(64 * SG_NW);
 #define LAUNCH(WM_, R_, RW_, XF_) hipLaunchKernelGGL((small_gemm_kernel<WM_, EPI, R_, RW_, XF_>), grid, block, 0, st, p)
-#define LAUNCHX(WM_, R_, RW_) { if (xf == 1) LAUNCH(WM_, R_, RW_, 1); else if (xf == 2) LAUNCH(WM_, R_, RW_, 2); else if constexpr (NARROW) LAUNCH(WM_, R_, RW_, 4); }
+#define LAUNCHX(WM_, R_, RW_) { if (xf == 1) LAUNCH(WM_, R_, RW_, 1); else if (xf == 2) LAUNCH(WM_, R_, RW_, 2); else if constexpr (NARROW || (EPI == EPI_SWIGLU && (WM_ == WMODE_F16 || WM_ == WMODE_FP8) && RW_ == 1)) LAUNCH(WM_, R_, RW_, 4); }
 #define LAUNCHW(R_, RW_)                                       \
   {                                                            \
     if (m->int4_group) LAUNCHX(WMODE_INT4, R_, RW_)            \

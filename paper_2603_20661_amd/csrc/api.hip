@@ -225,7 +225,7 @@ static void make_plan(const www_config* c, Plan& p) {
   p.attn_pref = take(((uint64_t)s.maxB + 1) * 4);
   p.argmax_val = take((uint64_t)s.maxB * 32 * 4);
   p.argmax_idx = take((uint64_t)s.maxB * 32 * 4);
-  const uint64_t Tpad = ((uint64_t)maxR + 255) / 256 * 256;  // packed activation buffers hold whole 256-token tiles
+  const uint64_t Tpad = (((uint64_t)maxR + 191) / 192 * 192 + 255) / 256 * 256;  // packed activation buffers hold whole tiles of 192 and 256 tokens
   p.hp = take(Tpad * (((uint64_t)s.d + 255) / 256 * 256) * 4);  // residual stream in whole 256 x 256 blocks (accumulator order)
   p.ssq_p = take(Tpad * (uint64_t)PSSQ * 4);
   p.xn = take(Tpad * s.d * 2);

@@ -222,6 +222,15 @@ __device__ __forceinline__ void pgemm_epilogue(const PGemmP& p, f32x16 (&acc)[4]
   const int lane = threadIdx.x & 63, wave = wn * 2 + wt;  // (position of the wavefront's rows and tokens in the 256 x 256 tile)
   const int rg_w = rt * 16 + wn * 8, t_w = tt * 256 + wt * 128 + tb0 * 32;
   const int hsel = lane >> 5;
+  // the residual stream's image, whose blocks are 256 tokens: three groups of 32 may cross into the next half or block
+  auto image = [&](int tb, int rb, int q4) __attribute__((always_inline)) {
+    if constexpr (TB == 3) {
+      const int g = tt * 8 + wt * 4 + tb0 + tb;
+      return hp_image_offset(g >> 3, rt, p.n_rt, wn * 2 + ((g >> 2) & 1), rb, g & 3, q4, lane);
+    } else {
+      return hp_image_offset(tt, rt, p.n_rt, wave, rb, tb0 + tb, q4, lane);
+    }
+  };
   // Everything the epilogue needs from memory per token is requested up front for all token groups (one memory
   // round trip, two for the KV block ids), and the per-element operands of a token group (residual rows, rotary
   // factors) in one batch per group: a wavefront has no partner on its SIMD to hide a chain of dependent loads behind.
@@ -258,7 +267,7 @@ __device__ __forceinline__ void pgemm_epilogue(const PGemmP& p, f32x16 (&acc)[4]
     }
     // the tokens' rows of the sum-of-squares table, [token][PSSQ], two token groups and 32 entries at a time (64
     // registers); entries past n_ssq_in are masked, the rest is added in tile order
-    constexpr int TH = TB < 2 ? TB : 2;
+    constexpr int TH = TB % 2 ? 1 : 2;
 #pragma unroll
     for (int t0 = 0; t0 < TB; t0 += TH) {
       if (!p.ssq_in) break;  // no normalisation requested: the scales stay 1
@@ -320,7 +329,7 @@ __device__ __forceinline__ void pgemm_epilogue(const PGemmP& p, f32x16 (&acc)[4]
           const int rg = min(rg_w + rb * 2 + (q4 >> 1), p.NRG - 1);
           const int n0 = rg * 16 + (q4 & 1) * 8 + hsel * 4;
           if constexpr (EPI == PEPI_RESID)  // (whole tiles are allocated: in bounds also for tokens and rows past the end)
-            pre[rb][q4] = *reinterpret_cast<const f32x4*>(p.hp + hp_image_offset(tt, rt, p.n_rt, wave, rb, tb0 + tb, q4, lane));
+            pre[rb][q4] = *reinterpret_cast<const f32x4*>(p.hp + image(tb, rb, q4));
           else pre[rb][q4] = *reinterpret_cast<const f32x4*>(p.rope + (int64_t)pos[tb] * (p.hd / 2) + ((n0 % p.hd) >> 1));
         }
     }
@@ -414,7 +423,7 @@ __device__ __forceinline__ void pgemm_epilogue(const PGemmP& p, f32x16 (&acc)[4]
           if constexpr (EPI == PEPI_RESID) {
             const f32x4 hv = pre[rb][q4], g4 = gv[rb][q4];
             const float hn[4] = {hv[0] + v4[0], hv[1] + v4[1], hv[2] + v4[2], hv[3] + v4[3]};
-            *reinterpret_cast<float4*>(p.hp + hp_image_offset(tt, rt, p.n_rt, wave, rb, tb0 + tb, q4, lane)) = make_float4(hn[0], hn[1], hn[2], hn[3]);
+            *reinterpret_cast<float4*>(p.hp + image(tb, rb, q4)) = make_float4(hn[0], hn[1], hn[2], hn[3]);
             union { uint16_t s[4]; u32x2 v; } o;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -624,9 +633,15 @@ __device__ __forceinline__ void last_epilogue(const PGemmP& p, int rg_w, int t_w
 
 // QKN: the QKV epilogue also normalises the query and key heads (an instantiation of its own, so that the plain model's
 // kernel carries none of its registers)
-template <int EPI, bool QKN, bool LAST>
+// TB: groups of 32 tokens per wavefront, 4 (256 tokens per tile) or 3 (192).  A k block of 32 columns takes 0.73 - 0.76 us with 256
+// tokens and 0.53 (one round of workgroups) to 0.60 with 192, in either case about what the matrix cores need at the clock the
+// power limit leaves them; the narrower tile serves calls whose tokens or rounds of workgroups it fits better (choose_pgemm): 8B
+// shape, gate/up of 333 tokens 93 -> 78 us, whole prompts of 333, 700, 1100 and 3000 tokens 8525 -> 8240, 14 222 -> 13 590, 19 645
+// -> 19 100 and 44 880 -> 42 120; 2000 tokens, five rounds against four of 256, 27 230 -> 27 340, so those keep the wide tile.
+template <int EPI, bool QKN, bool LAST, int TB>
 __global__ __launch_bounds__(256) void prefill_gemm_kernel(const PGemmP p) {
-  // PGEMM_NB stage buffers of 2048 sixteen-byte units: 0..1023 weights [16 row groups][64], 1024..2047 activations [8 token groups][2 k16][64]
+  // PGEMM_NB stage buffers of SB sixteen-byte units: 0..1023 weights [16 row groups][64], from 1024 on activations [2 TB token groups][2 k16][64]
+  constexpr int SB = 1024 + 256 * TB, U = 4 + TB;  // U: units of 64 that each wavefront copies per block
   extern __shared__ u32x4 smem[];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int wn = wave >> 1, wt = wave & 1;
@@ -637,11 +652,11 @@ __global__ __launch_bounds__(256) void prefill_gemm_kernel(const PGemmP p) {
   const int rg_tile = rt * 16;
   const int K16 = p.KB * 2;
 
-  f32x16 acc[4][4];
+  f32x16 acc[4][TB];
 #pragma unroll
   for (int a = 0; a < 4; ++a)
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
+    for (int b = 0; b < TB; ++b)
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
 
@@ -655,42 +670,42 @@ __global__ __launch_bounds__(256) void prefill_gemm_kernel(const PGemmP p) {
   constexpr int NB = PGEMM_NB;
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   const u32x4* srcA[4];
-  const u32x4* srcB[4];
+  const u32x4* srcB[TB];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int f = wave_u + 4 * i;  // fragment unit 0..15 handled by this wavefront
+    const int f = wave_u + 4 * i;  // fragment unit handled by this wavefront: 0..15, activations 0 .. 4 TB - 1
     srcA[i] = p.W + (int64_t)min(rg_tile + f, p.NRG - 1) * 64;
-    srcB[i] = p.X + ((int64_t)(tt * 8 + (f >> 1)) * K16 + (f & 1)) * 64;
+    if (i < TB) srcB[i] = p.X + ((int64_t)(tt * (2 * TB) + (f >> 1)) * K16 + (f & 1)) * 64;
   }
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)smem;
   const uint32_t voff = lane * 16;
-  u32x4 fa0[4], fb0[4], fa1[4], fb1[4];
+  u32x4 fa0[4], fb0[TB], fa1[4], fb1[TB];
   const int fm = lane & 31, fh = lane >> 5;
   auto dma16 = [&](const u32x4* g, uint32_t lds_addr) __attribute__((always_inline)) {
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(g), "s"(lds_addr) : "memory", "m0");
   };
-  // unit i = 0..7 of this wavefront's share of a k block: even = weights, odd = activations
+  // unit i = 0 .. U - 1 of this wavefront's share of a k block: even = weights, odd = activations
   auto stage1 = [&](int kbc, int buf, int i) __attribute__((always_inline)) {
     const int q = i >> 1;
-    if (i & 1) dma16(srcB[q] + (int64_t)kbc * 128, lds0 + (uint32_t)(buf * 2048 + 1024 + (wave_u + 4 * q) * 64) * 16u);
-    else dma16(srcA[q] + (int64_t)kbc * p.NRG * 64, lds0 + (uint32_t)(buf * 2048 + (wave_u + 4 * q) * 64) * 16u);
+    if (i & 1) dma16(srcB[q] + (int64_t)kbc * 128, lds0 + (uint32_t)(buf * SB + 1024 + (wave_u + 4 * q) * 64) * 16u);
+    else dma16(srcA[q] + (int64_t)kbc * p.NRG * 64, lds0 + (uint32_t)(buf * SB + (wave_u + 4 * q) * 64) * 16u);
   };
   auto stage = [&](int kb, int buf) __attribute__((always_inline)) {
     const int kbc = min(kb, p.KB - 1);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) stage1(kbc, buf, i);
+    for (int i = 0; i < U; ++i) stage1(kbc, buf, i);
   };
-  // fragment read i = 0..7 of a 16-column half: 0..3 weights (row blocks), 4..7 activations (token blocks)
-  auto fetch1 = [&](u32x4(&fa)[4], u32x4(&fb)[4], int buf, int k16, int i) __attribute__((always_inline)) {
-    if (i < 4) fa[i] = smem[buf * 2048 + (wn * 8 + i * 2 + (fm >> 4)) * 64 + ((k16 * 2 + fh) << 4) + (fm & 15)];
-    else fb[i - 4] = smem[buf * 2048 + 1024 + ((wt * 4 + (i - 4)) * 2 + k16) * 64 + lane];
+  // fragment read i = 0 .. U - 1 of a 16-column half: 0..3 weights (row blocks), then activations (token blocks)
+  auto fetch1 = [&](u32x4(&fa)[4], u32x4(&fb)[TB], int buf, int k16, int i) __attribute__((always_inline)) {
+    if (i < 4) fa[i] = smem[buf * SB + (wn * 8 + i * 2 + (fm >> 4)) * 64 + ((k16 * 2 + fh) << 4) + (fm & 15)];
+    else fb[i - 4] = smem[buf * SB + 1024 + ((wt * TB + (i - 4)) * 2 + k16) * 64 + lane];
   };
-  auto fetch = [&](u32x4(&fa)[4], u32x4(&fb)[4], int buf, int k16) __attribute__((always_inline)) {
+  auto fetch = [&](u32x4(&fa)[4], u32x4(&fb)[TB], int buf, int k16) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) fetch1(fa, fb, buf, k16, i);
+    for (int i = 0; i < U; ++i) fetch1(fa, fb, buf, k16, i);
   };
-  auto mfma1 = [&](u32x4(&fa)[4], u32x4(&fb)[4], int i) __attribute__((always_inline)) {
-    const int rb = i >> 2, tb = i & 3;
+  auto mfma1 = [&](u32x4(&fa)[4], u32x4(&fb)[TB], int i) __attribute__((always_inline)) {
+    const int rb = i / TB, tb = i % TB;
     acc[rb][tb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_f16x8(fa[rb]), as_f16x8(fb[tb]), acc[rb][tb], 0, 0, 0);
   };
   auto lds_barrier = [&]() __attribute__((always_inline)) {
@@ -699,37 +714,37 @@ __global__ __launch_bounds__(256) void prefill_gemm_kernel(const PGemmP p) {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
   };
   // k block s sits in buffer r = s mod NB; two fragment sets carry the LDS reads of its two 16-column halves.  The
-  // instruction order is fixed by hand: one LDS read behind each of the first eight MFMAs of a half (half 1 of block s
+  // instruction order is fixed by hand: one LDS read behind each of the first U MFMAs of a half (half 1 of block s
   // in the first half, half 0 of block s+1 in the second, each 8 to 16 MFMAs before its data is needed) and one stage
-  // copy behind every fourth MFMA, so that the requests of the four wavefronts reach the memory pipeline evenly spread.
+  // copy behind every fourth MFMA (TB in the first half of a block, four in the second), so that the requests of the four wavefronts reach the memory pipeline evenly spread.
   // The copies of block s+NB-1 go to the buffer of block s-1, which nobody reads any more once the barrier of block
   // s-1 has been passed.  One barrier per k block, in the middle: in front of it a wavefront waits until its own units
-  // of block s+1 have landed (at most (NB-3) blocks of 8 units and the 4 units of block s+NB-1 requested so far may
+  // of block s+1 have landed (at most (NB-3) blocks of U units and the TB units of block s+NB-1 requested so far may
   // still be outstanding); behind it everybody's have.  Past the last k block the copies are redirected to the last
   // block; nobody reads them.
   // s_waitcnt immediates for "at most n memory requests outstanding": a 6-bit count split over bits 3:0 and 15:14, the
   // other counters unconstrained
-  constexpr int VM_MID = (NB - 3) * 8 + 4;
+  constexpr int VM_MID = (NB - 3) * U + TB;
   constexpr int WAIT_MID = 0x0F70 | (VM_MID & 15) | ((VM_MID >> 4) << 14);
-  constexpr int VM_PRO = (NB - 2) * 8;
+  constexpr int VM_PRO = (NB - 2) * U;
   constexpr int WAIT_PRO = 0x0F70 | (VM_PRO & 15) | ((VM_PRO >> 4) << 14);
   auto k_block = [&](int s, int r) __attribute__((always_inline)) {
     const int buf1 = r == NB - 1 ? 0 : r + 1, bufp = r == 0 ? NB - 1 : r - 1;
     const int kbc = min(s + NB - 1, p.KB - 1);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
+    for (int i = 0; i < 4 * TB; ++i) {
       mfma1(fa0, fb0, i);
-      if (i < 8) fetch1(fa1, fb1, r, 1, i);
+      if (i < U) fetch1(fa1, fb1, r, 1, i);
       if ((i & 3) == 3) stage1(kbc, bufp, i >> 2);
       __builtin_amdgcn_sched_barrier(0);
     }
     __builtin_amdgcn_s_waitcnt(WAIT_MID);  // this wavefront's units of block s+1 have landed
     lds_barrier();                         // ... everybody's
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
+    for (int i = 0; i < 4 * TB; ++i) {
       mfma1(fa1, fb1, i);
-      if (i < 8) fetch1(fa0, fb0, buf1, 0, i);
-      if ((i & 3) == 3) stage1(kbc, bufp, 4 + (i >> 2));
+      if (i < U) fetch1(fa0, fb0, buf1, 0, i);
+      if (i % TB == TB - 1) stage1(kbc, bufp, TB + i / TB);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
@@ -754,22 +769,22 @@ __global__ __launch_bounds__(256) void prefill_gemm_kernel(const PGemmP p) {
   float(*red_ssq)[256] = reinterpret_cast<float(*)[256]>(smem);
   (void)red_ssq;
 
-  const int t_w = __builtin_amdgcn_readfirstlane(tt * 256 + wt * 128);
-  f32x4* parked = reinterpret_cast<f32x4*>(smem + 128 + wave * 4 * LAST_UNITS);
+  const int t_w = __builtin_amdgcn_readfirstlane((tt * 2 + wt) * 32 * TB), g32 = (tt * 2 + wt) * TB;  // first token, group of 32
+  f32x4* parked = reinterpret_cast<f32x4*>(smem + 128 + wave * TB * LAST_UNITS);
   if constexpr (LAST) park_last(p, acc, t_w, parked);
-  if (!LAST || t_w < p.first_last) pgemm_epilogue<EPI, QKN, 4, LAST>(p, acc, tt, rt, wn, wt, 0, [&](int tb, float ssq_tok) __attribute__((always_inline)) {
-    const int at = wt * 128 + tb * 32 + lane;
-    if (lane < 32 && (!LAST || tt * 256 + at < p.first_last)) red_ssq[wn][at] = ssq_tok;  // (slots of tokens past the end are never read)
+  if (!LAST || t_w < p.first_last) pgemm_epilogue<EPI, QKN, TB, LAST>(p, acc, g32 >> 3, rt, wn, (g32 >> 2) & 1, g32 & 3, [&](int tb, float ssq_tok) __attribute__((always_inline)) {
+    const int at = (wt * TB + tb) * 32 + lane;
+    if (lane < 32 && (!LAST || tt * 64 * TB + at < p.first_last)) red_ssq[wn][at] = ssq_tok;  // (slots of tokens past the end are never read)
   });
   if constexpr (LAST) {
     __syncthreads();
-    last_epilogue<EPI, QKN, 4>(p, rt * 16 + wn * 8, t_w, parked, [&](int tb, int c, float s) __attribute__((always_inline)) { red_ssq[wn][wt * 128 + tb * 32 + c] = s; });
+    last_epilogue<EPI, QKN, TB>(p, rt * 16 + wn * 8, t_w, parked, [&](int tb, int c, float s) __attribute__((always_inline)) { red_ssq[wn][(wt * TB + tb) * 32 + c] = s; });
   }
   if constexpr (EPI == PEPI_RESID) {
     // per (row tile, token) sum of squares of the new residual, the two row halves added in a fixed order
     __syncthreads();
-    const int t = tt * 256 + tid;
-    if (t < p.T) p.ssq_out[(int64_t)t * PSSQ + rt] = red_ssq[0][tid] + red_ssq[1][tid];
+    const int t = tt * 64 * TB + tid;
+    if (tid < 64 * TB && t < p.T) p.ssq_out[(int64_t)t * PSSQ + rt] = red_ssq[0][tid] + red_ssq[1][tid];
   }
 }
 
@@ -1328,25 +1343,25 @@ __global__ __launch_bounds__(256 * HG) void prefill_attn_merge_kernel(const int3
 // ------------------------------------------------------------------------------------------------
 // Host side
 
-// Which kernel a prefill GEMM of T tokens, NRG row groups and KB k blocks uses: tb = 0: 256 x 256 tiles, otherwise tiles of
-// 128 rows x 128 tb tokens whose k range is shared by ks workgroups.  The choice is the least of the times in us that a
-// fit of all three kernels gives: rounds of one workgroup per compute unit, a time per k block, a fixed time per round
+// Which kernel a prefill GEMM of T tokens, NRG row groups and KB k blocks uses: tb = 0: 256 x 256 tiles, 3: 256 rows x 192 tokens,
+// 1 and 2: tiles of 128 rows x 128 tb tokens whose k range is shared by ks workgroups.  The choice is the least of the times in us that a
+// fit of all kernels gives: rounds of one workgroup per compute unit, a time per k block, a fixed time per round
 // (fill and epilogue) and, for a split range, the hand-over, whose last workgroup reads ks partial tiles.  Large calls
 // keep the 256 x 256 tiles, which read least per product; small ones would leave most compute units idle with them.
 // Measured at the 8B shape (us, 256 x 256 tiles against the choice): 333 tokens QKV 100 / 41 (128 tokens, no split), O 91 /
-// 28 (128, 2 splits), gate/up 91 / 91 (256 x 256), down 256 / 59 (256 tokens, 4 splits); 1024 tokens 106 / 67, 93 / 44,
+// 28 (128, 2 splits), gate/up 93 / 78 (192), down 256 / 59 (256 tokens, 4 splits); 1024 tokens 106 / 67, 93 / 44,
 // 195 / 195, 261 / 117; 2048 tokens O 108 / 71, down 282 / 204; 8192 tokens: always 256 x 256 (gate/up 1388, the others 1660
 // and 2030).
 struct PGemmChoice { int tb, ks; float us; };
 static PGemmChoice choose_pgemm(int T, int NRG, int KB) {
   constexpr int CUS = 256;
-  const float per_kb[3] = {0.76f, 0.29f, 0.43f}, per_round[3] = {12.f, 5.f, 8.f}, hand0[3] = {0.f, 7.f, 9.f}, hand1[3] = {0.f, 1.4f, 3.f};
+  const float per_kb[4] = {0.76f, 0.29f, 0.43f, 0.60f}, per_round[4] = {12.f, 5.f, 8.f, 11.f}, hand0[3] = {0.f, 7.f, 9.f}, hand1[3] = {0.f, 1.4f, 3.f};
   PGemmChoice best = {0, 1, 0.f};
-  for (int tb = 0; tb <= 2; ++tb) {
-    const int rows = tb ? 8 : 16, tokens = tb ? 128 * tb : 256;
+  for (int tb = 0; tb <= 3; ++tb) {
+    const int rows = tb % 3 ? 8 : 16, tokens = tb == 3 ? 192 : tb ? 128 * tb : 256;
     const int64_t tiles = (int64_t)((T + tokens - 1) / tokens) * ((NRG + rows - 1) / rows);
     for (int ks = 1; ks <= 8; ++ks) {
-      if (ks > 1 && (!tb || tiles * ks > CUS || KB < 8 * ks)) break;  // (parked tiles and counters are sized by this line)
+      if (ks > 1 && (tb % 3 == 0 || tiles * ks > CUS || KB < 8 * ks)) break;  // (parked tiles and counters are sized by this line)
       const float us = (float)((tiles * ks + CUS - 1) / CUS) * (per_kb[tb] * (float)((KB + ks - 1) / ks) + per_round[tb]) +
                        (ks > 1 ? hand0[tb] + hand1[tb] * ks : 0.f);
       if ((!tb && ks == 1) || us < best.us) best = {tb, ks, us};
@@ -1391,7 +1406,8 @@ bool prefill_rides(const www_model* m, int T, int batch) {
 template <int EPI, bool QKN, bool LAST>
 static hipError_t allow_pgemm_lds() {
   auto allow = [](const void* kernel, int bytes) { return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); };
-  hipError_t e = allow(reinterpret_cast<const void*>(&prefill_gemm_kernel<EPI, QKN, LAST>), LAST ? PGEMM_LAST_LDS_BYTES : PGEMM_LDS_BYTES);
+  hipError_t e = allow(reinterpret_cast<const void*>(&prefill_gemm_kernel<EPI, QKN, LAST, 4>), LAST ? PGEMM_LAST_LDS_BYTES : PGEMM_LDS_BYTES);
+  if (e == hipSuccess) e = allow(reinterpret_cast<const void*>(&prefill_gemm_kernel<EPI, QKN, LAST, 3>), LAST ? PGEMM_LAST_LDS_BYTES : PGEMM_LDS_BYTES);
   if (e == hipSuccess) e = allow(reinterpret_cast<const void*>(&prefill_gemm_small_kernel<EPI, QKN, 1, LAST>), PSG_LDS_BYTES);
   if (e == hipSuccess) e = allow(reinterpret_cast<const void*>(&prefill_gemm_small_kernel<EPI, QKN, 2, LAST>), PSG_LDS_BYTES);
   return e;
@@ -1417,7 +1433,12 @@ static int launch_pgemm_as(www_model* m, PGemmP& p, hipStream_t st) {
   if (p.wfactor == 0.f) p.wfactor = 1.f;  // not set: an unscaled matrix
   const PGemmChoice c = choose_pgemm(p.T, p.NRG, p.KB);
   if (c.tb == 0) {
-    hipLaunchKernelGGL((prefill_gemm_kernel<EPI, QKN, LAST>), dim3(p.n_tt * p.n_rt), dim3(256), LAST ? PGEMM_LAST_LDS_BYTES : PGEMM_LDS_BYTES, st, p);
+    hipLaunchKernelGGL((prefill_gemm_kernel<EPI, QKN, LAST, 4>), dim3(p.n_tt * p.n_rt), dim3(256), LAST ? PGEMM_LAST_LDS_BYTES : PGEMM_LDS_BYTES, st, p);
+    return p.n_rt;
+  }
+  if (c.tb == 3) {
+    p.n_tt = (p.T + 191) / 192;
+    hipLaunchKernelGGL((prefill_gemm_kernel<EPI, QKN, LAST, 3>), dim3(p.n_tt * p.n_rt), dim3(256), LAST ? PGEMM_LAST_LDS_BYTES : PGEMM_LDS_BYTES, st, p);
     return p.n_rt;
   }
   p.n_ttS = (p.T + 128 * c.tb - 1) / (128 * c.tb);

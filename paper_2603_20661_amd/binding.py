@@ -21,7 +21,7 @@ EXPORTS = ("www_query_sizes", "www_model_load", "www_prefill", "www_decode_step"
            "www_judge_verdict", "www_ledger_create", "www_ledger_free", "www_ledger_stakes", "www_pos_sample", "www_ledger_serve",
            "www_ledger_duel", "www_ledger_num_ops", "www_ledger_read_ops",
            "www_sched_create", "www_sched_free", "www_sched_submit", "www_sched_plan", "www_sched_table_row", "www_sched_commit",
-           "www_get_stats", "www_sample_top_p", "www_sample_top_p_static", "www_check", "www_debug_mfma_loop", "www_debug_prefill_tile")
+           "www_get_stats", "www_sample_top_p", "www_sample_top_p_static", "www_check", "www_debug_mfma_loop", "www_debug_prefill_tile", "www_debug_route")
 FLAG_QK_NORM = 1
 OP_BASE_REWARD, OP_DUEL_REWARD, OP_DUEL_PENALTY, OP_JUDGE_REWARD = 0, 1, 2, 3
 
@@ -83,6 +83,8 @@ def _load_library():
     L.www_debug_mfma_loop.restype = ctypes.c_int
     L.www_debug_prefill_tile.argtypes = [i32, i32, i32, ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32)]
     L.www_debug_prefill_tile.restype = ctypes.c_int
+    L.www_debug_route.argtypes = [cfgp, i32, i32, i32, ctypes.POINTER(ctypes.c_int32)]
+    L.www_debug_route.restype = ctypes.c_int
     L.www_check.argtypes = [vp, vp]
     L.www_check.restype = ctypes.c_int
     L.www_debug_slots.argtypes = [vp, vp, i32, vp, vp]
@@ -214,6 +216,17 @@ def www_debug_prefill_tile(workgroup: int, token_tiles: int, row_tiles: int):
     tt, rt = ctypes.c_int32(), ctypes.c_int32()
     _check(lib.www_debug_prefill_tile(workgroup, token_tiles, row_tiles, ctypes.byref(tt), ctypes.byref(rt)))
     return tt.value, rt.value
+
+
+GEMMS = ("qkv", "o", "gate_up", "down", "lm_head")
+ROUTE_KERNELS = ("decode", "decode_small", "prefill", "prefill_small")
+
+
+def www_debug_route(cfg: WwwConfig, gemm: str, batch: int, total_q_tokens: int = 0):
+    """(kernel, tokens per workgroup, rows per workgroup, k splits, last positions ride) of one GEMM of a call; host only"""
+    out = (ctypes.c_int32 * 5)()
+    _check(lib.www_debug_route(ctypes.byref(cfg), total_q_tokens, batch, GEMMS.index(gemm), out))
+    return ROUTE_KERNELS[out[0]], out[1], out[2], out[3], bool(out[4])
 
 
 def www_check(model: Model, stream=None):

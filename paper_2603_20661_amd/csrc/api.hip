@@ -19,6 +19,8 @@ hipError_t prefill_allow_lds();
 uint64_t prefill_partial_bytes(int maxT, int NRG, int KB);
 uint64_t prefill_attn_part_bytes(int hd, int Hkv, int G, int maxT, int maxB, int max_pos);
 int decode_MT(int batch);
+void decode_route(const www_model* m, int which, int batch, int32_t out[4]);
+void prefill_route(const www_model* m, int which, int T, int batch, int32_t out[5]);
 
 static thread_local char g_err[512] = "";
 
@@ -143,6 +145,15 @@ static Dims dims_of(const www_config* c) {
   s.qk_norm = (c->flags & WWW_FLAG_QK_NORM) != 0;
   s.int4_group = c->weight_dtype == WWW_DTYPE_INT4WO_128 ? 128 : c->weight_dtype == WWW_DTYPE_INT4WO_32 ? 32 : 0;
   return s;
+}
+
+static void set_dims(www_model* m, const www_config* cfg, const Dims& s) {
+  m->cfg = *cfg;
+  m->L = s.L; m->d = s.d; m->Hq = s.Hq; m->Hkv = s.Hkv; m->hd = s.hd; m->G = s.G; m->F = s.F; m->Fp = s.Fp; m->V = s.V;
+  m->QKVN = s.QKVN; m->QD = s.QD; m->KD = s.KD; m->max_pos = s.max_pos; m->maxB = s.maxB; m->MTmax = s.MTmax; m->maxT = s.maxT;
+  m->wsplit = s.wsplit;
+  m->fp8 = s.fp8;
+  m->int4_group = s.int4_group;
 }
 
 static void make_plan(const www_config* c, Plan& p) {
@@ -358,12 +369,7 @@ WWW_EXPORT int www_model_load(const www_config* cfg, const void* weights_dev, vo
 
   www_model* m = new www_model();
   memset(m, 0, sizeof(*m));
-  m->cfg = *cfg;
-  m->L = s.L; m->d = s.d; m->Hq = s.Hq; m->Hkv = s.Hkv; m->hd = s.hd; m->G = s.G; m->F = s.F; m->Fp = s.Fp; m->V = s.V;
-  m->QKVN = s.QKVN; m->QD = s.QD; m->KD = s.KD; m->max_pos = s.max_pos; m->maxB = s.maxB; m->MTmax = s.MTmax; m->maxT = s.maxT;
-  m->wsplit = s.wsplit;
-  m->fp8 = s.fp8;
-  m->int4_group = s.int4_group;
+  set_dims(m, cfg, s);
   m->layers = new LayerW[s.L];
   memset(m->layers, 0, sizeof(LayerW) * s.L);
   m->graphs = new GraphEntry[MAX_GRAPHS];
@@ -611,6 +617,19 @@ WWW_EXPORT int www_debug_read(www_model* m, int32_t which, float* dst_host, uint
   HIP_TRY(hipStreamSynchronize((hipStream_t)hip_stream));
   HIP_TRY(hipMemcpy(dst_host, src, n_floats * 4, hipMemcpyDeviceToHost));
   return check_placement_fault(m);  // the work is complete: a violation found by its kernels is reported now, not by the next call
+}
+
+WWW_EXPORT int www_debug_route(const www_config* cfg, int32_t total_q_tokens, int32_t batch, int32_t gemm, int32_t* route_out) {
+  if (int rc = check_config(cfg)) return rc;
+  if (!route_out || batch < 1 || total_q_tokens < 0 || gemm < 0 || gemm > (total_q_tokens ? 3 : 4)) { set_error("bad argument"); return WWW_E_INVALID_ARG; }
+  if (batch > (int64_t)cfg->max_batch || total_q_tokens > (int64_t)cfg->max_prefill_tokens) { set_error("the call exceeds the configuration's capacities"); return WWW_E_CAPACITY; }
+  www_model m;
+  memset(&m, 0, sizeof(m));
+  set_dims(&m, cfg, dims_of(cfg));
+  route_out[4] = 0;
+  if (total_q_tokens) prefill_route(&m, gemm, total_q_tokens, batch, route_out);
+  else decode_route(&m, gemm, batch, route_out);
+  return WWW_OK;
 }
 
 WWW_EXPORT int www_debug_profile(www_model* m, int32_t enable) {

@@ -1148,6 +1148,8 @@ int decode_wg_target() {
   return v;
 }
 
+int decode_MT(int batch) { return batch <= 16 ? 1 : batch <= 32 ? 2 : batch <= 64 ? 4 : ((batch + 127) / 128) * 8; }
+
 static void choose_split(int row_tiles, int zb, int KB, int* ksplit, int* kb_per_split) {
   int want = decode_wg_target() / (row_tiles * zb);
   if (want < 1) want = 1;
@@ -1171,10 +1173,10 @@ int decode_gemm_ksplit(int NRG, int KB, int MT) {
   return most;
 }
 
-template <int EPI>
-static void launch_gemm(www_model* m, GemmP& p, int MT, hipStream_t st) {
-  if (small_gemm_takes(m, EPI, p.NRG, p.KB, p.M)) return launch_small_gemm<EPI>(m, p, st);
-  const int row_tiles = (p.NRG + 7) / 8;
+// Tokens per workgroup (16 mtk), workgroups per row tile (zb) and split of the k range of skinny_gemm_kernel
+struct SkinnyShape { int mtk, zb, ksplit, kb_per_split; };
+static SkinnyShape skinny_shape(const www_model* m, int epi, int NRG, int KB, int M) {
+  const int row_tiles = (NRG + 7) / 8, MT = decode_MT(M);
   // Above 64 tokens the two wide GEMMs may take 128 tokens per workgroup: every compute unit takes in about 55 KB per us, and
   // 128 rows x 128 tokens need 24 KB per k block where two workgroups of 64 tokens need 32 (with FP8 weights 20 and 24).
   // A round of 128 tokens on all compute units takes about 1.75 (FP8: 1.9) times as long as one of 64 (8B shape, gate/up 73
@@ -1183,21 +1185,32 @@ static void launch_gemm(www_model* m, GemmP& p, int MT, hipStream_t st) {
   // sequences 1456 -> 1530.  The split-K GEMMs, whose epilogues then exceed the registers, are slower that way (QKV
   // 36 -> 52 us), and so are int4 weights (a step of 100 sequences 7250 -> 7700 us).  A range of k is never split there: more
   // than half of the compute units have a row tile each, or there would be no round to save.
+  auto rounds = [&](int tokens) { return (float)((row_tiles * ((M + tokens - 1) / tokens) + decode_wg_target() - 1) / decode_wg_target()); };
+  const bool wide = (epi == EPI_SWIGLU || epi == EPI_LOGITS) && !m->int4_group && !m->wsplit && rounds(128) * (m->fp8 ? 1.9f : 1.75f) < rounds(64);
+  SkinnyShape s;
+  s.mtk = MT < 8 ? MT : wide ? 8 : 4;
+  s.zb = MT < 8 ? 1 : (M + 16 * s.mtk - 1) / (16 * s.mtk);  // (not MT / mtk: the last 64 tokens may all be padding)
+  choose_split(row_tiles, s.zb, KB, &s.ksplit, &s.kb_per_split);
+  return s;
+}
+
+template <int EPI>
+static void launch_gemm(www_model* m, GemmP& p, hipStream_t st) {
+  if (small_gemm_takes(m, EPI, p.NRG, p.KB, p.M)) return launch_small_gemm<EPI>(m, p, st);
   constexpr bool wide_epi = EPI == EPI_SWIGLU || EPI == EPI_LOGITS;
-  auto rounds = [&](int tokens) { return (float)((row_tiles * ((p.M + tokens - 1) / tokens) + decode_wg_target() - 1) / decode_wg_target()); };
-  const bool wide = wide_epi && !m->int4_group && !m->wsplit && rounds(128) * (m->fp8 ? 1.9f : 1.75f) < rounds(64);
-  const int mtk = MT < 8 ? MT : wide ? 8 : 4;
-  const int zb = MT < 8 ? 1 : (p.M + 16 * mtk - 1) / (16 * mtk);  // (not MT / mtk: the last 64 tokens may all be padding)
-  choose_split(row_tiles, zb, p.KB, &p.ksplit, &p.kb_per_split);
-  p.MT = MT;
+  const SkinnyShape s = skinny_shape(m, EPI, p.NRG, p.KB, p.M);
+  const int mtk = s.mtk, zb = s.zb;
+  p.ksplit = s.ksplit;
+  p.kb_per_split = s.kb_per_split;
+  p.MT = decode_MT(p.M);
   p.partial = m->partial;
   p.counters = m->counters;
   p.fault_flag = m->fault_dev;
-  p.row_tiles = row_tiles;
+  p.row_tiles = (p.NRG + 7) / 8;
   p.zbs = zb;
   p.fence_handover = m->handover_fence;
   if (p.wfactor == 0.f) p.wfactor = 1.f;  // not set: an unscaled matrix
-  dim3 grid(8 * ((row_tiles + 7) / 8) * p.ksplit * zb);
+  dim3 grid(8 * ((p.row_tiles + 7) / 8) * p.ksplit * zb);
 #define LAUNCH(MTK_, WM_, KH_) hipLaunchKernelGGL((skinny_gemm_kernel<MTK_, WM_, EPI, KH_>), grid, dim3(256 * KH_), 0, st, p);
 #define LAUNCH2(WM_, KH_) { if constexpr (wide_epi) LAUNCH(2, WM_, KH_) }  // (the others: small_gemm_kernel)
 #define LAUNCH8(WM_) { if constexpr (wide_epi) LAUNCH(8, WM_, 2) }
@@ -1226,6 +1239,21 @@ static void launch_gemm(www_model* m, GemmP& p, int MT, hipStream_t st) {
 #undef LAUNCH2
 #undef LAUNCH8
 #undef LAUNCH
+}
+
+// Kernel (0: skinny_gemm_kernel, 1: small_gemm_kernel), tokens and rows per workgroup and k splits of GEMM `which` (0 QKV, 1 O,
+// 2 gate/up, 3 down, 4 output head) of a decode step
+void decode_route(const www_model* m, int which, int batch, int32_t out[4]) {
+  const int epi[5] = {EPI_QKV, EPI_RESID, EPI_SWIGLU, EPI_RESID, EPI_LOGITS};
+  const int NRG = (which == 0 ? m->QKVN : which == 2 ? 2 * m->F : which == 4 ? m->V : m->d) / 16;
+  const int KB = (which == 1 ? m->QD : which == 3 ? m->Fp : m->d) / 32;
+  if (small_gemm_takes(m, epi[which], NRG, KB, batch)) {
+    const SmallShape s = small_gemm_shape(m, epi[which], NRG, KB, batch);
+    out[0] = 1; out[1] = s.xf == 1 ? 8 : s.xf == 2 ? 16 : 32; out[2] = 16 * s.R * s.RW; out[3] = s.ks;
+  } else {
+    const SkinnyShape s = skinny_shape(m, epi[which], NRG, KB, batch);
+    out[0] = 0; out[1] = 16 * s.mtk; out[2] = GEMM_TILE_ROWS; out[3] = s.ksplit;
+  }
 }
 
 // wavefronts the decode attention kernel keeps resident on the whole device (its grid), a multiple of 4
@@ -1264,8 +1292,6 @@ int decode_probe_placement(int32_t* scratch_dev, int n, hipStream_t st) {
     if (h[i] != h[i & 7]) return 0;
   return 1;
 }
-
-int decode_MT(int batch) { return batch <= 16 ? 1 : batch <= 32 ? 2 : batch <= 64 ? 4 : ((batch + 127) / 128) * 8; }
 
 static AttnPlan plan_of(const www_model* m, const int32_t* lens, int batch) {
   return {lens, batch, m->Hkv, m->attn_waves, m->attn_hdr, m->attn_start, m->attn_pref};
@@ -1325,7 +1351,7 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
       p.q_hi = m->q_hi; p.q_lo = m->q_lo; p.qscale = qscale; p.kplane = kplane; p.vplane = vplane; p.kvscale = kvscale; p.seq_lens = lens; p.table = table; p.mbs = m->cfg.max_blocks_per_seq;
       p.hd = m->hd; p.Hq = m->Hq; p.Hkv = m->Hkv; p.rope = m->rope; p.qk_gain = w.qk_gain;
       prof_mark(m, PK_QKV, st);
-      launch_gemm<EPI_QKV>(m, p, MT, st);
+      launch_gemm<EPI_QKV>(m, p, st);
     }
     prof_mark(m, PK_ATTN, st);
     launch_decode_attn(m, l, lens, table, batch, (uint16_t*)m->xo, MT, -1, st);
@@ -1336,7 +1362,7 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
       p.X = (const u32x4*)m->xo; p.M = batch;
       p.h = m->h; p.gain_next = w.ffn_norm; p.xnext = (uint16_t*)m->xq; p.ssq_out = ssq; p.d = d;
       prof_mark(m, PK_OPROJ, st);
-      launch_gemm<EPI_RESID>(m, p, MT, st);
+      launch_gemm<EPI_RESID>(m, p, st);
       n_ssq = resid_entries(m->QD / 32);
     }
     {
@@ -1347,7 +1373,7 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
       p.ssq_in = ssq; p.n_ssq_in = n_ssq; p.inv_dim = 1.f / d; p.eps = m->cfg.rms_eps;
       p.xa = (uint16_t*)m->xa; p.F = m->F;
       prof_mark(m, PK_GATEUP, st);
-      launch_gemm<EPI_SWIGLU>(m, p, MT, st);
+      launch_gemm<EPI_SWIGLU>(m, p, st);
     }
     {
       GemmP p = {};
@@ -1357,7 +1383,7 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
       p.h = m->h; p.gain_next = (l + 1 < m->L) ? m->layers[l + 1].attn_norm : m->final_norm;
       p.xnext = (uint16_t*)m->xq; p.ssq_out = ssq; p.d = d;
       prof_mark(m, PK_DOWN, st);
-      launch_gemm<EPI_RESID>(m, p, MT, st);
+      launch_gemm<EPI_RESID>(m, p, st);
       n_ssq = resid_entries(m->Fp / 32);
     }
   }
@@ -1370,7 +1396,7 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
     p.ssq_in = ssq; p.n_ssq_in = n_ssq; p.inv_dim = 1.f / d; p.eps = m->cfg.rms_eps;
     p.logits = lg; p.V = m->V;
     prof_mark(m, PK_LMHEAD, st);
-    launch_gemm<EPI_LOGITS>(m, p, MT, st);
+    launch_gemm<EPI_LOGITS>(m, p, st);
   }
   if (next) prof_mark(m, PK_ARGMAX, st);
   if (next) {

@@ -89,8 +89,10 @@ __device__ __forceinline__ f16x8 int4x8_to_f16x8(uint32_t w, f16x2 scale) {
 // four k blocks (one chunk) per 16-byte unit, widened and multiplied by their group's scale in registers
 enum { WMODE_F16 = 0, WMODE_SPLIT = 1, WMODE_FP8 = 2, WMODE_INT4 = 3 };
 
-// decode_small.hip: the GEMMs of a step of up to 16 tokens
+// decode_small.hip: GEMMs of a step of up to 32 tokens
 int decode_wg_target();  // compute units (decode.hip)
 bool small_gemm_takes(const www_model* m, int epi, int NRG, int KB, int M);
+struct SmallShape { int R, RW, xf, ks, per; };  // 16 R RW rows a workgroup, XF, k splits, k blocks of one
+SmallShape small_gemm_shape(const www_model* m, int epi, int NRG, int KB, int M);
 template <int EPI>
 void launch_small_gemm(www_model* m, GemmP& p, hipStream_t st);

@@ -417,12 +417,11 @@ __global__ __launch_bounds__(64 * SG_NW, sg_eu(WMODE, R, XF)) void small_gemm_ke
 // over (4 us with split k ranges).  Many rows save activations, few rows or more splits keep every compute unit at work.
 // 8B shape, us: down projection of FP8 weights, 16 tokens, 1 row group without splits 21.4, 2 x 2 splits 19.7, 4 x 4 16.6; O
 // projection of fp16 weights, 1 token, 1 x 1 8.5, 2 x 2 9.8, 4 x 4 11.2; QKV, 16 tokens, FP8: 1 x 1 15.8, 2 x 1 14.5, 4 x 2 12.5.
-struct SmallShape { int R, ks, per; };
-static SmallShape small_shape(int epi, int NRG, int KB, int hd, int xf, int wmode) {
+static SmallShape narrow_shape(int epi, int NRG, int KB, int hd, int xf, int wmode) {
   const float CUS = (float)decode_wg_target();
   const float wbytes = wmode == WMODE_INT4 ? 0.5f + 2.f / 32 : wmode == WMODE_FP8 ? 1.f : 2.f;
   const int chunk = SG_NW * sg_kc(wmode, xf);  // k blocks of one chunk of every wavefront: an unfilled round costs a whole one
-  SmallShape best = {1, 1, (KB + 3) / 4 * 4};
+  SmallShape best = {1, 1, xf, 1, (KB + 3) / 4 * 4};
   float least = 0.f;
   for (int R = 1; R <= 4; R *= 2)
     for (int ks = 1; ks <= 8; ++ks) {
@@ -436,7 +435,7 @@ static SmallShape small_shape(int epi, int NRG, int KB, int hd, int xf, int wmod
       const float us = (intake > stream ? intake + 0.25f * stream : stream + 0.25f * intake) + (ks > 1 ? 1.f : 0.f) + (members * ks > 1 ? 3.f + (float)(ks * R * (xf == 4 ? 2 : 1)) * 1024.f / 52e3f : 0.f);
       if ((R == 1 && ks == 1) || us < least) {
         least = us;
-        best = {R, ks, per};
+        best = {R, 1, xf, ks, per};
       }
     }
   return best;
@@ -462,19 +461,24 @@ bool small_gemm_takes(const www_model* m, int epi, int NRG, int KB, int M) {
 
 uint64_t small_gemm_partial_bytes(int NRG) { return (uint64_t)NRG * 8 * 2 * 1024; }  // [split][row group][2 token groups]
 
-template <int EPI>
-void launch_small_gemm(www_model* m, GemmP& p, hipStream_t st) {
-  const int xf = p.M <= 8 ? 1 : p.M <= 16 ? 2 : 4;
-  SmallShape s = {2, 1, (p.KB + 3) / 4 * 4};
-  int RW = 1;
+SmallShape small_gemm_shape(const www_model* m, int epi, int NRG, int KB, int M) {
+  const int xf = M <= 8 ? 1 : M <= 16 ? 2 : 4;
+  const bool narrow = epi == EPI_QKV || epi == EPI_RESID;
+  if (narrow && !m->wsplit) return narrow_shape(epi, NRG, KB, m->hd, xf, m->int4_group ? WMODE_INT4 : m->fp8 ? WMODE_FP8 : WMODE_F16);
+  SmallShape s = {2, 1, xf, 1, (KB + 3) / 4 * 4};
   if (m->wsplit) {  // two planes: two row groups fit the registers; whole heads, so that nothing is handed over
-    if (EPI == EPI_QKV) RW = p.hd / 32;
-  } else if (EPI == EPI_QKV || EPI == EPI_RESID) {
-    s = small_shape(EPI, p.NRG, p.KB, p.hd, xf, m->int4_group ? WMODE_INT4 : m->fp8 ? WMODE_FP8 : WMODE_F16);
+    if (epi == EPI_QKV) s.RW = m->hd / 32;
   } else {  // one round of workgroups where the rows allow it
     s.R = 4;
-    while (RW < (EPI == EPI_LOGITS ? 8 : 2) && (p.NRG + 4 * RW - 1) / (4 * RW) > decode_wg_target()) RW *= 2;
+    while (s.RW < (epi == EPI_LOGITS ? 8 : 2) && (NRG + 4 * s.RW - 1) / (4 * s.RW) > decode_wg_target()) s.RW *= 2;
   }
+  return s;
+}
+
+template <int EPI>
+void launch_small_gemm(www_model* m, GemmP& p, hipStream_t st) {
+  const SmallShape s = small_gemm_shape(m, EPI, p.NRG, p.KB, p.M);
+  const int xf = s.xf, RW = s.RW;
   p.ksplit = s.ks;
   p.kb_per_split = s.per;
   p.MT = xf == 4 ? 2 : 1;

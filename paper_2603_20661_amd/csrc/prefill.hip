@@ -1402,6 +1402,16 @@ bool prefill_rides(const www_model* m, int T, int batch) {
   return added < saved;
 }
 
+// Kernel (2: prefill_gemm_kernel, 3: prefill_gemm_small_kernel), tokens and rows per tile and k splits of GEMM `which` (0 QKV, 1 O,
+// 2 gate/up, 3 down) of a prefill call, and whether its last positions ride along
+void prefill_route(const www_model* m, int which, int T, int batch, int32_t out[5]) {
+  const int N[4] = {m->QKVN, m->d, 2 * m->F, m->d}, K[4] = {m->d, m->QD, m->d, m->Fp};
+  const bool rides = prefill_rides(m, T, batch);
+  const PGemmChoice c = choose_pgemm(rides ? prefill_rows(T, batch) : T, N[which] / 16, K[which] / 32);
+  const bool small = c.tb == 1 || c.tb == 2;
+  out[0] = small ? 3 : 2; out[1] = c.tb == 0 ? 256 : c.tb == 3 ? 192 : 128 * c.tb; out[2] = small ? 128 : 256; out[3] = c.ks; out[4] = rides;
+}
+
 // Announces the GEMM kernels, which use more than 64 KiB of dynamic LDS, to the current device (when a model is loaded there).
 template <int EPI, bool QKN, bool LAST>
 static hipError_t allow_pgemm_lds() {

@@ -84,3 +84,16 @@ def test_prefill_gemm_tile_order_visits_every_tile_once():
     for bad in ((-1, 4, 4), (16, 4, 4), (0, 0, 4), (0, 4, 0)):
         with pytest.raises(Exception):
             B.www_debug_prefill_tile(*bad)
+
+
+def test_route_hook():
+    """the rules that pick a call's kernels, evaluated without a GPU (256 compute units)"""
+    cfg = B.make_config(synth.M8B, 64, 272, 81920, 6000)
+    assert B.www_debug_route(cfg, "qkv", 1)[0] == "decode_small" and B.www_debug_route(cfg, "gate_up", 64) == ("decode", 64, 128, 1, False)
+    assert B.www_debug_route(cfg, "gate_up", 64, 80231)[:4] == ("prefill", 256, 256, 1)
+    assert B.www_debug_route(cfg, "down", 1, 16)[0] == "prefill_small" and B.www_debug_route(cfg, "down", 1, 16)[3] > 1
+    for gemm, batch, total, code in ((4, 1, 16, B.E_INVALID_ARG), (5, 1, 0, B.E_INVALID_ARG), (0, 0, 0, B.E_INVALID_ARG), (0, 1, -1, B.E_INVALID_ARG),
+                                     (0, 65, 0, B.E_CAPACITY), (0, 1, 81921, B.E_CAPACITY)):
+        out = (ctypes.c_int32 * 5)()
+        assert B.lib.www_debug_route(ctypes.byref(cfg), total, batch, gemm, out) == code
+    assert B.lib.www_debug_route(ctypes.byref(cfg), 0, 1, 0, None) == B.E_INVALID_ARG

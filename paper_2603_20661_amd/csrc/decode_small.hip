@@ -451,11 +451,22 @@ static SmallShape narrow_shape(int epi, int NRG, int KB, int hd, int xf, int wmo
 // sequences 904 / 899 and 916 / 911, with FP8 767 / 770 and 776 / 781: within 0.6 %, so those stay).
 // None whose k range leaves half of the wavefronts without a chunk (tiny shape, 4 sequences: 75 us a step, 72 with the other
 // kernel; 20 sequences: 80 against 84).
+// fp32 sources: two planes double a workgroup's weights, it has two row groups of the residual and wide products and a whole head of
+// the QKV product, and its k range is never split.  So only while its rows times k blocks are few (us against skinny_gemm_kernel, models of 4
+// layers; residual products, 4 / 12 / 20 / 32 sequences: 16 k blocks 7.9 / 8.7, 8.3 / 8.8, 8.0 / 10.2, 8.4 / 10.4; 32 8.6 / 9.3, 9.7 / 10.0,
+// 9.2 / 10.7, 9.9 / 11.1; 64 (1B shape) 11.9 / 11.4, 12.9 / 11.4, 14.3 / 12.8, 15.1 / 13.0; 256 30 / 21, 34 / 21, 38 / 22, 41 / 22.  QKV,
+// heads of 64: 32 k blocks 9.9 / 11.1, 11.0 / 11.3, 13.4 / 13.7, 14.2 / 14.2, 48 14.9 / 12.7, 16.5 / 12.6, 19.0 / 14.5, 20.7 / 15.1;
+// heads of 128: 16 9.1 / 10.8, 10.2 / 10.8, 12.1 / 13.1, 12.9 / 13.2, 32 13.5 / 11.5, 15.8 / 11.3, 19.1 / 13.6, 21.7 / 14.2.  Wide ones in
+// one round, 4 and 12 sequences: gate/up 16 8.7 / 9.0, 9.1 / 9.1, 32 11.5 / 11.8, 12.2 / 11.8; in two rounds 48 21.4 / 18.6, 23.1 / 18.6).
 bool small_gemm_takes(const www_model* m, int epi, int NRG, int KB, int M) {
   if (KB < 16 && M <= 16) return false;
+  if (m->wsplit) {
+    if (epi == EPI_QKV) return M <= 32 && m->hd * KB <= 64 * 32;
+    return KB <= 48 && (epi == EPI_RESID ? M <= 32 : M <= 8 && NRG <= 2 * decode_wg_target());
+  }
   if (epi == EPI_QKV || epi == EPI_RESID) return M <= 32;
-  if (M > 16) return M <= 32 && epi == EPI_SWIGLU && !m->wsplit && !m->int4_group && NRG <= 4 * decode_wg_target();
-  if (epi == EPI_LOGITS || m->int4_group || m->wsplit) return true;
+  if (M > 16) return M <= 32 && epi == EPI_SWIGLU && !m->int4_group && NRG <= 4 * decode_wg_target();
+  if (epi == EPI_LOGITS || m->int4_group) return true;
   return M <= 8 && NRG <= 4 * decode_wg_target();
 }
 

@@ -1150,7 +1150,7 @@ int decode_wg_target() {
 
 int decode_MT(int batch) { return batch <= 16 ? 1 : batch <= 32 ? 2 : batch <= 64 ? 4 : ((batch + 127) / 128) * 8; }
 
-static void choose_split(int row_tiles, int zb, int KB, int* ksplit, int* kb_per_split) {
+void choose_split(int row_tiles, int zb, int KB, int* ksplit, int* kb_per_split) {
   int want = decode_wg_target() / (row_tiles * zb);
   if (want < 1) want = 1;
   if (want > MAX_KSPLIT) want = MAX_KSPLIT;
@@ -1212,7 +1212,7 @@ static void launch_gemm(www_model* m, GemmP& p, hipStream_t st) {
   if (p.wfactor == 0.f) p.wfactor = 1.f;  // not set: an unscaled matrix
   dim3 grid(8 * ((p.row_tiles + 7) / 8) * p.ksplit * zb);
 #define LAUNCH(MTK_, WM_, KH_) hipLaunchKernelGGL((skinny_gemm_kernel<MTK_, WM_, EPI, KH_>), grid, dim3(256 * KH_), 0, st, p);
-#define LAUNCH2(WM_, KH_) { if constexpr (wide_epi || WM_ == WMODE_SPLIT) LAUNCH(2, WM_, KH_) }  // (the others: small_gemm_kernel)
+#define LAUNCH2(WM_, KH_) { if constexpr (wide_epi || WM_ != WMODE_INT4) LAUNCH(2, WM_, KH_) }  // (int4, narrow: small_gemm_kernel)
 #define LAUNCH8(WM_) { if constexpr (wide_epi) LAUNCH(8, WM_, 2) }
   // With more than 32 tokens the MFMAs of a chunk take a third of a wavefront's time; in the gate/up GEMM (no split-K,
   // 32 chunks per workgroup) two wavefronts per SIMD (KH = 2) hide them behind each other's waits: 53 -> 49.5 us at 64

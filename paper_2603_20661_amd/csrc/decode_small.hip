@@ -417,28 +417,36 @@ __global__ __launch_bounds__(64 * SG_NW, sg_eu(WMODE, R, XF)) void small_gemm_ke
 // over (4 us with split k ranges).  Many rows save activations, few rows or more splits keep every compute unit at work.
 // 8B shape, us: down projection of FP8 weights, 16 tokens, 1 row group without splits 21.4, 2 x 2 splits 19.7, 4 x 4 16.6; O
 // projection of fp16 weights, 1 token, 1 x 1 8.5, 2 x 2 9.8, 4 x 4 11.2; QKV, 16 tokens, FP8: 1 x 1 15.8, 2 x 1 14.5, 4 x 2 12.5.
+// Where two workgroups fit a compute unit, a partial second round counts as its part from one and a half rounds on only: with less
+// a few units that have two hold up all others (4 tokens, 320 row groups of 432 k blocks, 1 x 1: 38.7; the other kernel 31.8).
 static SmallShape narrow_shape(int epi, int NRG, int KB, int hd, int xf, int wmode) {
   const float CUS = (float)decode_wg_target();
   const float wbytes = wmode == WMODE_INT4 ? 0.5f + 2.f / 32 : wmode == WMODE_FP8 ? 1.f : 2.f;
   const int chunk = SG_NW * sg_kc(wmode, xf);  // k blocks of one chunk of every wavefront: an unfilled round costs a whole one
-  SmallShape best = {1, 1, xf, 1, (KB + 3) / 4 * 4};
-  float least = 0.f;
+  SmallShape best = {1, 1, xf, 1, (KB + 3) / 4 * 4, 0.f};
   for (int R = 1; R <= 4; R *= 2)
     for (int ks = 1; ks <= 8; ++ks) {
       const int per = ((KB + ks - 1) / ks + 3) / 4 * 4, members = epi == EPI_QKV ? hd / 16 / R : 1;
       if ((KB + per - 1) / per != ks || members < 1 || members * ks > 31) continue;  // (arrivals of a group: 5 bits per XCD)
       if (ks > 1 && (per < chunk || (NRG + R - 1) / R * ks > decode_wg_target())) break;
       const float groups = (float)((NRG + R - 1) / R) * (float)ks, fill = groups < CUS ? 1.f : groups / CUS;
-      const float rounds = sg_eu(wmode, R, xf) == 4 ? fill : ceilf(fill);  // two workgroups share a compute unit, or one has it
+      const float rounds = sg_eu(wmode, R, xf) == 4 && fill >= 1.5f ? fill : ceilf(fill);  // two workgroups share a compute unit, or one has it
       const float intake = rounds * (float)((per + chunk - 1) / chunk * chunk) * 32.f * (16.f * (float)R * wbytes + 32.f * (float)xf) / 52e3f;
       const float stream = (float)NRG * 16.f * (float)KB * 32.f * wbytes / 6.2e6f;
       const float us = (intake > stream ? intake + 0.25f * stream : stream + 0.25f * intake) + (ks > 1 ? 1.f : 0.f) + (members * ks > 1 ? 3.f + (float)(ks * R * (xf == 4 ? 2 : 1)) * 1024.f / 52e3f : 0.f);
-      if ((R == 1 && ks == 1) || us < least) {
-        least = us;
-        best = {R, 1, xf, ks, per};
-      }
+      if ((R == 1 && ks == 1) || us < best.us) best = {R, 1, xf, ks, per, us};
     }
   return best;
+}
+
+// The same estimate for skinny_gemm_kernel: row tiles of 8 row groups, activations of whole groups of 16 tokens
+static float general_us(int NRG, int KB, int M, float wbytes) {
+  const int row_tiles = (NRG + 7) / 8, MT = M <= 16 ? 1 : 2, cus = decode_wg_target();
+  int ks, per;
+  choose_split(row_tiles, 1, KB, &ks, &per);
+  const float intake = (float)((row_tiles * ks + cus - 1) / cus * per) * 32.f * (128.f * wbytes + 64.f * (float)MT) / 52e3f;
+  const float stream = (float)NRG * 16.f * (float)KB * 32.f * wbytes / 6.2e6f;
+  return (intake > stream ? intake + 0.25f * stream : stream + 0.25f * intake) + (ks > 1 ? 4.f + (float)(ks * 8 * MT) * 1024.f / 52e3f : 0.f);
 }
 
 // Which GEMMs of a step of M tokens run here (us per launch against skinny_gemm_kernel; 8B shape 1, 12, 24 sequences, 1B shape
@@ -449,6 +457,13 @@ static SmallShape narrow_shape(int epi, int NRG, int KB, int hd, int xf, int wmo
 // to 8 tokens 13.4 / 14.6), unless 64 rows per workgroup fill the chip in one round: then up to 8 tokens and, where the other kernel
 // has to split k, from 17 on (1B shape, 32 tokens 15.4 / 16.9; a step of 24 sequences with FP8 weights 880 / 896; of 12 and 16
 // sequences 904 / 899 and 916 / 911, with FP8 767 / 770 and 776 / 781: within 0.6 %, so those stay).
+// FP16 and FP8 weights of other widths: the narrow products by the estimate above against the same for 128 rows a workgroup, with 2.5 us
+// for that kernel's shorter pipeline.  Few k splits fit beside many rows and a long k range then reads the activations
+// once per 64 rows: 8192 columns, QKV of 640 row groups, 16 and 32 tokens 41.5 / 36.0 and 50.4 / 38.5, with FP8 weights 28.7 / 24.5 and 37.7 /
+// 29.5, down projection of 896 k blocks at 32 tokens 86.9 / 81.8 and 59.5 / 51.5; int4 codes cost more to unpack there (down 38.1 / 45.0 at
+// 9 tokens).  The output head only where its row tiles are more than one round (32 000 tokens, 4 sequences: 64 k blocks 27.4 / 25.6,
+// 160 58.5 / 57.0, with FP8 weights 16 sequences 18.2 / 16.3 and 35.5 / 31.9; 128 256 tokens: above), with FP8 weights also up to 8
+// tokens (1B shape 16.7 / 17.4).
 // None whose k range leaves half of the wavefronts without a chunk (tiny shape, 4 sequences: 75 us a step, 72 with the other
 // kernel; 20 sequences: 80 against 84).
 // fp32 sources: two planes double a workgroup's weights, it has two row groups of the residual and wide products and a whole head of
@@ -464,9 +479,13 @@ bool small_gemm_takes(const www_model* m, int epi, int NRG, int KB, int M) {
     if (epi == EPI_QKV) return M <= 32 && m->hd * KB <= 64 * 32;
     return KB <= 48 && (epi == EPI_RESID ? M <= 32 : M <= 8 && NRG <= 2 * decode_wg_target());
   }
-  if (epi == EPI_QKV || epi == EPI_RESID) return M <= 32;
+  if (epi == EPI_QKV || epi == EPI_RESID) {
+    if (M > 32 || m->int4_group) return M <= 32;
+    return small_gemm_shape(m, epi, NRG, KB, M).us <= general_us(NRG, KB, M, m->fp8 ? 1.f : 2.f) + 2.5f;
+  }
   if (M > 16) return M <= 32 && epi == EPI_SWIGLU && !m->int4_group && NRG <= 4 * decode_wg_target();
-  if (epi == EPI_LOGITS || m->int4_group) return true;
+  if (m->int4_group) return true;
+  if (epi == EPI_LOGITS) return (NRG + 7) / 8 > decode_wg_target() || (m->fp8 && M <= 8);
   return M <= 8 && NRG <= 4 * decode_wg_target();
 }
 
@@ -476,7 +495,7 @@ SmallShape small_gemm_shape(const www_model* m, int epi, int NRG, int KB, int M)
   const int xf = M <= 8 ? 1 : M <= 16 ? 2 : 4;
   const bool narrow = epi == EPI_QKV || epi == EPI_RESID;
   if (narrow && !m->wsplit) return narrow_shape(epi, NRG, KB, m->hd, xf, m->int4_group ? WMODE_INT4 : m->fp8 ? WMODE_FP8 : WMODE_F16);
-  SmallShape s = {2, 1, xf, 1, (KB + 3) / 4 * 4};
+  SmallShape s = {2, 1, xf, 1, (KB + 3) / 4 * 4, 0.f};
   if (m->wsplit) {  // two planes: two row groups fit the registers; whole heads, so that nothing is handed over
     if (epi == EPI_QKV) s.RW = m->hd / 32;
   } else {  // one round of workgroups where the rows allow it

@@ -196,7 +196,7 @@ int www_debug_prefill_tile(int32_t workgroup, int32_t token_tiles, int32_t row_t
  * 4 output head (decode only).  route_out[5] (host): kernel (0 and 1 decode, 2 and 3 prefill: the general one and the one for
  * small calls), tokens and rows of the matrix per workgroup, splits of the k range, and 1 if the call's last positions run as
  * rows of the prefill GEMMs.  Without a GPU the rules assume 256 compute units.  Errors: INVALID_ARG, ABI_MISMATCH, BAD_CONFIG,
- * CAPACITY. */
+ * CAPACITY, HIP (the rules lead to a kernel that does not exist). */
 int www_debug_route(const www_config* cfg, int32_t total_q_tokens, int32_t batch, int32_t gemm, int32_t* route_out);
 
 /* ------------------------------------------------------------------------------------------------

@@ -19,7 +19,7 @@ hipError_t prefill_allow_lds();
 uint64_t prefill_partial_bytes(int maxT, int NRG, int KB);
 uint64_t prefill_attn_part_bytes(int hd, int Hkv, int G, int maxT, int maxB, int max_pos);
 int decode_MT(int batch);
-void decode_route(const www_model* m, int which, int batch, int32_t out[4]);
+bool decode_route(const www_model* m, int which, int batch, int32_t out[4]);
 void prefill_route(const www_model* m, int which, int T, int batch, int32_t out[5]);
 
 static thread_local char g_err[512] = "";
@@ -628,7 +628,7 @@ WWW_EXPORT int www_debug_route(const www_config* cfg, int32_t total_q_tokens, in
   set_dims(&m, cfg, dims_of(cfg));
   route_out[4] = 0;
   if (total_q_tokens) prefill_route(&m, gemm, total_q_tokens, batch, route_out);
-  else decode_route(&m, gemm, batch, route_out);
+  else if (!decode_route(&m, gemm, batch, route_out)) { set_error("decode: no kernel for the shape chosen for a GEMM"); return WWW_E_HIP; }
   return WWW_OK;
 }
 

@@ -1219,8 +1219,10 @@ static SkinnyShape skinny_shape(const www_model* m, int epi, int NRG, int KB, in
   return s;
 }
 
+// false: the shape the rules chose has no kernel, nothing was launched
 template <int EPI>
-static void launch_gemm(www_model* m, GemmP& p, hipStream_t st) {
+static bool launch_gemm(www_model* m, GemmP& p, hipStream_t st) {
+  bool launched = false;
   if (small_gemm_takes(m, EPI, p.NRG, p.KB, p.M)) return launch_small_gemm<EPI>(m, p, st);
   constexpr bool wide_epi = EPI == EPI_SWIGLU || EPI == EPI_LOGITS;
   const SkinnyShape s = skinny_shape(m, EPI, p.NRG, p.KB, p.M);
@@ -1236,7 +1238,7 @@ static void launch_gemm(www_model* m, GemmP& p, hipStream_t st) {
   p.fence_handover = m->handover_fence;
   if (p.wfactor == 0.f) p.wfactor = 1.f;  // not set: an unscaled matrix
   dim3 grid(8 * ((p.row_tiles + 7) / 8) * p.ksplit * zb);
-#define LAUNCH(MTK_, WM_, KH_) hipLaunchKernelGGL((skinny_gemm_kernel<MTK_, WM_, EPI, KH_>), grid, dim3(256 * KH_), 0, st, p);
+#define LAUNCH(MTK_, WM_, KH_) { hipLaunchKernelGGL((skinny_gemm_kernel<MTK_, WM_, EPI, KH_>), grid, dim3(256 * KH_), 0, st, p); launched = true; }
 #define LAUNCH2(WM_, KH_) { if constexpr (wide_epi || WM_ != WMODE_INT4) LAUNCH(2, WM_, KH_) }  // (int4, narrow: small_gemm_kernel)
 #define LAUNCH8(WM_) { if constexpr (wide_epi) LAUNCH(8, WM_, 2) }
   // With more than 32 tokens the MFMAs of a chunk take a third of a wavefront's time; in the gate/up GEMM (no split-K,
@@ -1264,20 +1266,23 @@ static void launch_gemm(www_model* m, GemmP& p, hipStream_t st) {
 #undef LAUNCH2
 #undef LAUNCH8
 #undef LAUNCH
+  return launched;
 }
 
 // Kernel (0: skinny_gemm_kernel, 1: small_gemm_kernel), tokens and rows per workgroup and k splits of GEMM `which` (0 QKV, 1 O,
-// 2 gate/up, 3 down, 4 output head) of a decode step
-void decode_route(const www_model* m, int which, int batch, int32_t out[4]) {
+// 2 gate/up, 3 down, 4 output head) of a decode step; false: there is no such kernel
+bool decode_route(const www_model* m, int which, int batch, int32_t out[4]) {
   const int epi[5] = {EPI_QKV, EPI_RESID, EPI_SWIGLU, EPI_RESID, EPI_LOGITS};
   const int NRG = (which == 0 ? m->QKVN : which == 2 ? 2 * m->F : which == 4 ? m->V : m->d) / 16;
   const int KB = (which == 1 ? m->QD : which == 3 ? m->Fp : m->d) / 32;
   if (small_gemm_takes(m, epi[which], NRG, KB, batch)) {
     const SmallShape s = small_gemm_shape(m, epi[which], NRG, KB, batch);
     out[0] = 1; out[1] = s.xf == 1 ? 8 : s.xf == 2 ? 16 : 32; out[2] = 16 * s.R * s.RW; out[3] = s.ks;
+    return small_gemm_built(m, epi[which], s);
   } else {
     const SkinnyShape s = skinny_shape(m, epi[which], NRG, KB, batch);
     out[0] = 0; out[1] = 16 * s.mtk; out[2] = GEMM_TILE_ROWS; out[3] = s.ksplit;
+    return s.mtk != 2 || !m->int4_group || which == 2 || which == 4;  // (narrow int4 products of 17 to 32 tokens: the other kernel)
   }
 }
 
@@ -1359,6 +1364,7 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
       hipLaunchKernelGGL(embed_pack_kernel<uint16_t>, dim3(batch + 1), dim3(256), plan_lds_bytes(batch), st, tok, (const uint16_t*)m->embed, d,
                          m->layers[0].attn_norm, m->h, ssq, (uint16_t*)m->xq, MT, plan_of(m, lens, batch));
   }
+  bool launched = true;
   int n_ssq = 1;  // entries per token of the sum-of-squares table: one per row group or per row tile of the GEMM that wrote it
   auto resid_entries = [&](int KB) { return small_gemm_takes(m, EPI_RESID, d / 16, KB, batch) ? d / 16 : (d / 16 + 7) / 8; };
   const float qscale = 1.4426950408889634f / sqrtf((float)m->hd);
@@ -1376,7 +1382,7 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
       p.q_hi = m->q_hi; p.q_lo = m->q_lo; p.qscale = qscale; p.kplane = kplane; p.vplane = vplane; p.kvscale = kvscale; p.seq_lens = lens; p.table = table; p.mbs = m->cfg.max_blocks_per_seq;
       p.hd = m->hd; p.Hq = m->Hq; p.Hkv = m->Hkv; p.rope = m->rope; p.qk_gain = w.qk_gain;
       prof_mark(m, PK_QKV, st);
-      launch_gemm<EPI_QKV>(m, p, st);
+      launched &= launch_gemm<EPI_QKV>(m, p, st);
     }
     prof_mark(m, PK_ATTN, st);
     launch_decode_attn(m, l, lens, table, batch, (uint16_t*)m->xo, MT, -1, st);
@@ -1387,7 +1393,7 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
       p.X = (const u32x4*)m->xo; p.M = batch;
       p.h = m->h; p.gain_next = w.ffn_norm; p.xnext = (uint16_t*)m->xq; p.ssq_out = ssq; p.d = d;
       prof_mark(m, PK_OPROJ, st);
-      launch_gemm<EPI_RESID>(m, p, st);
+      launched &= launch_gemm<EPI_RESID>(m, p, st);
       n_ssq = resid_entries(m->QD / 32);
     }
     {
@@ -1398,7 +1404,7 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
       p.ssq_in = ssq; p.n_ssq_in = n_ssq; p.inv_dim = 1.f / d; p.eps = m->cfg.rms_eps;
       p.xa = (uint16_t*)m->xa; p.F = m->F;
       prof_mark(m, PK_GATEUP, st);
-      launch_gemm<EPI_SWIGLU>(m, p, st);
+      launched &= launch_gemm<EPI_SWIGLU>(m, p, st);
     }
     {
       GemmP p = {};
@@ -1408,7 +1414,7 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
       p.h = m->h; p.gain_next = (l + 1 < m->L) ? m->layers[l + 1].attn_norm : m->final_norm;
       p.xnext = (uint16_t*)m->xq; p.ssq_out = ssq; p.d = d;
       prof_mark(m, PK_DOWN, st);
-      launch_gemm<EPI_RESID>(m, p, st);
+      launched &= launch_gemm<EPI_RESID>(m, p, st);
       n_ssq = resid_entries(m->Fp / 32);
     }
   }
@@ -1421,7 +1427,7 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
     p.ssq_in = ssq; p.n_ssq_in = n_ssq; p.inv_dim = 1.f / d; p.eps = m->cfg.rms_eps;
     p.logits = lg; p.V = m->V;
     prof_mark(m, PK_LMHEAD, st);
-    launch_gemm<EPI_LOGITS>(m, p, st);
+    launched &= launch_gemm<EPI_LOGITS>(m, p, st);
   }
   if (next) prof_mark(m, PK_ARGMAX, st);
   if (next) {
@@ -1429,6 +1435,10 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
     hipLaunchKernelGGL(argmax_final_kernel, dim3(batch), dim3(64), 0, st, m->argmax_val, m->argmax_idx, next);
   }
   prof_mark(m, -1, st);
+  if (!launched) {
+    set_error("decode: no kernel for the shape chosen for a GEMM");
+    return WWW_E_HIP;
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
     set_error("decode launch failed: %s", hipGetErrorString(e));

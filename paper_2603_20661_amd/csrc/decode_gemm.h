@@ -95,5 +95,6 @@ void choose_split(int row_tiles, int zb, int KB, int* ksplit, int* kb_per_split)
 bool small_gemm_takes(const www_model* m, int epi, int NRG, int KB, int M);
 struct SmallShape { int R, RW, xf, ks, per; float us; };  // 16 R RW rows a workgroup, XF, k splits, k blocks of one; narrow ones: estimate
 SmallShape small_gemm_shape(const www_model* m, int epi, int NRG, int KB, int M);
+bool small_gemm_built(const www_model* m, int epi, const SmallShape& s);
 template <int EPI>
-void launch_small_gemm(www_model* m, GemmP& p, hipStream_t st);
+bool launch_small_gemm(www_model* m, GemmP& p, hipStream_t st);  // false: the shape has no kernel, nothing was launched

@@ -505,47 +505,60 @@ SmallShape small_gemm_shape(const www_model* m, int epi, int NRG, int KB, int M)
   return s;
 }
 
+// The kernels there are: those that small_gemm_takes and small_gemm_shape lead to (fp16 and FP8 gate/up products take one round of
+// workgroups and not 9 to 16 tokens, output heads of theirs more than one round of row tiles but for FP8 up to 8 tokens).
+static constexpr bool sg_built(int epi, int wmode, int R, int RW, int xf) {
+  const bool narrow = epi == EPI_QKV || epi == EPI_RESID;
+  if (wmode == WMODE_SPLIT) return R == 2 && (epi == EPI_QKV ? RW == 2 || RW == 4 : RW == 1) && (narrow || xf == 1);
+  if (narrow) return RW == 1;
+  if (R != 4 || (xf == 4 && (epi == EPI_LOGITS || wmode == WMODE_INT4))) return false;
+  if (epi == EPI_SWIGLU) return wmode == WMODE_INT4 ? RW <= 2 : RW == 1 && xf != 2;
+  return wmode == WMODE_INT4 || RW >= 4 || (wmode == WMODE_FP8 && xf == 1);
+}
+static int sg_wmode(const www_model* m) { return m->wsplit ? WMODE_SPLIT : m->int4_group ? WMODE_INT4 : m->fp8 ? WMODE_FP8 : WMODE_F16; }
+bool small_gemm_built(const www_model* m, int epi, const SmallShape& s) { return sg_built(epi, sg_wmode(m), s.R, s.RW, s.xf); }
+
+template <int EPI, int WMODE, int R, int RW, int XF>
+static bool launch_small_as(const GemmP& p, hipStream_t st) {
+  if constexpr (sg_built(EPI, WMODE, R, RW, XF))
+    hipLaunchKernelGGL((small_gemm_kernel<WMODE, EPI, R, RW, XF>), dim3(8 * ((p.row_tiles + 7) / 8) * p.zbs), dim3(64 * SG_NW), 0, st, p);
+  return sg_built(EPI, WMODE, R, RW, XF);
+}
+template <int EPI, int WMODE, int R, int RW>
+static bool launch_small_xf(const GemmP& p, int xf, hipStream_t st) {
+  return xf == 1 ? launch_small_as<EPI, WMODE, R, RW, 1>(p, st) : xf == 2 ? launch_small_as<EPI, WMODE, R, RW, 2>(p, st) : launch_small_as<EPI, WMODE, R, RW, 4>(p, st);
+}
+template <int EPI, int WMODE>
+static bool launch_small_rows(const GemmP& p, const SmallShape& s, hipStream_t st) {
+  if (s.R == 1) return s.RW == 1 && launch_small_xf<EPI, WMODE, 1, 1>(p, s.xf, st);
+  if (s.R == 2) return s.RW == 1 ? launch_small_xf<EPI, WMODE, 2, 1>(p, s.xf, st) : s.RW == 2 ? launch_small_xf<EPI, WMODE, 2, 2>(p, s.xf, st) : s.RW == 4 && launch_small_xf<EPI, WMODE, 2, 4>(p, s.xf, st);
+  if (s.R != 4) return false;
+  return s.RW == 1 ? launch_small_xf<EPI, WMODE, 4, 1>(p, s.xf, st) : s.RW == 2 ? launch_small_xf<EPI, WMODE, 4, 2>(p, s.xf, st)
+       : s.RW == 4 ? launch_small_xf<EPI, WMODE, 4, 4>(p, s.xf, st) : s.RW == 8 && launch_small_xf<EPI, WMODE, 4, 8>(p, s.xf, st);
+}
+
 template <int EPI>
-void launch_small_gemm(www_model* m, GemmP& p, hipStream_t st) {
+bool launch_small_gemm(www_model* m, GemmP& p, hipStream_t st) {
   const SmallShape s = small_gemm_shape(m, EPI, p.NRG, p.KB, p.M);
-  const int xf = s.xf, RW = s.RW;
   p.ksplit = s.ks;
   p.kb_per_split = s.per;
-  p.MT = xf == 4 ? 2 : 1;
+  p.MT = s.xf == 4 ? 2 : 1;
   p.partial = m->partial;
   p.counters = m->counters;
   p.fault_flag = m->fault_dev;
   p.fence_handover = m->handover_fence;
   if (p.wfactor == 0.f) p.wfactor = 1.f;  // not set: an unscaled matrix
-  const int hrg = EPI == EPI_QKV ? p.hd / 16 : s.R * RW;
+  const int hrg = EPI == EPI_QKV ? p.hd / 16 : s.R * s.RW;
   p.row_tiles = (p.NRG + hrg - 1) / hrg;
-  p.zbs = p.ksplit * (EPI == EPI_QKV ? hrg / (s.R * RW) : 1);
-  const dim3 grid(8 * ((p.row_tiles + 7) / 8) * p.zbs), block(64 * SG_NW);
-#define LAUNCH(WM_, R_, RW_, XF_) hipLaunchKernelGGL((small_gemm_kernel<WM_, EPI, R_, RW_, XF_>), grid, block, 0, st, p)
-#define LAUNCHX(WM_, R_, RW_) { if (xf == 1) LAUNCH(WM_, R_, RW_, 1); else if (xf == 2) LAUNCH(WM_, R_, RW_, 2); else if constexpr (NARROW || (EPI == EPI_SWIGLU && (WM_ == WMODE_F16 || WM_ == WMODE_FP8) && RW_ == 1)) LAUNCH(WM_, R_, RW_, 4); }
-#define LAUNCHW(R_, RW_)                                       \
-  {                                                            \
-    if (m->int4_group) LAUNCHX(WMODE_INT4, R_, RW_)            \
-    else if (m->fp8) LAUNCHX(WMODE_FP8, R_, RW_)               \
-    else LAUNCHX(WMODE_F16, R_, RW_)                           \
+  p.zbs = p.ksplit * (EPI == EPI_QKV ? hrg / (s.R * s.RW) : 1);
+  switch (sg_wmode(m)) {
+    case WMODE_SPLIT: return launch_small_rows<EPI, WMODE_SPLIT>(p, s, st);
+    case WMODE_INT4: return launch_small_rows<EPI, WMODE_INT4>(p, s, st);
+    case WMODE_FP8: return launch_small_rows<EPI, WMODE_FP8>(p, s, st);
+    default: return launch_small_rows<EPI, WMODE_F16>(p, s, st);
   }
-  constexpr bool NARROW = EPI == EPI_QKV || EPI == EPI_RESID;
-  if constexpr (NARROW) {
-    if (m->wsplit) { if constexpr (EPI == EPI_QKV) { if (RW == 2) LAUNCHX(WMODE_SPLIT, 2, 2) else LAUNCHX(WMODE_SPLIT, 2, 4) } else LAUNCHX(WMODE_SPLIT, 2, 1) }
-    else if (s.R == 1) LAUNCHW(1, 1)
-    else if (s.R == 2) LAUNCHW(2, 1)
-    else LAUNCHW(4, 1)
-  } else {
-    if (m->wsplit) LAUNCHX(WMODE_SPLIT, 2, 1)
-    else if (RW == 1) LAUNCHW(4, 1)
-    else if (RW == 2) LAUNCHW(4, 2)
-    else if constexpr (EPI == EPI_LOGITS) { if (RW == 4) LAUNCHW(4, 4) else LAUNCHW(4, 8) }
-  }
-#undef LAUNCHW
-#undef LAUNCHX
-#undef LAUNCH
 }
-template void launch_small_gemm<EPI_QKV>(www_model*, GemmP&, hipStream_t);
-template void launch_small_gemm<EPI_RESID>(www_model*, GemmP&, hipStream_t);
-template void launch_small_gemm<EPI_SWIGLU>(www_model*, GemmP&, hipStream_t);
-template void launch_small_gemm<EPI_LOGITS>(www_model*, GemmP&, hipStream_t);
+template bool launch_small_gemm<EPI_QKV>(www_model*, GemmP&, hipStream_t);
+template bool launch_small_gemm<EPI_RESID>(www_model*, GemmP&, hipStream_t);
+template bool launch_small_gemm<EPI_SWIGLU>(www_model*, GemmP&, hipStream_t);
+template bool launch_small_gemm<EPI_LOGITS>(www_model*, GemmP&, hipStream_t);

@@ -1413,11 +1413,16 @@ void prefill_route(const www_model* m, int which, int T, int batch, int32_t out[
 }
 
 // Announces the GEMM kernels, which use more than 64 KiB of dynamic LDS, to the current device (when a model is loaded there).
+// The residual GEMMs of large tiles always run the kernel that can carry last positions: their 256 x 256 epilogue spills 4 registers
+// there and 63 without (8B shape, calls of 16 000 tokens: the two of a layer 2 x 1407 against 2 x 1467 us).  Not those of smaller tiles
+// (8B shape, 512 tokens, down projection 76.0 us with it against 74.7; 1B shape, 1024 tokens, 49.2 against 47.6).
+constexpr bool large_tiles_last(int epi, bool last) { return last || epi == PEPI_RESID; }
 template <int EPI, bool QKN, bool LAST>
 static hipError_t allow_pgemm_lds() {
+  constexpr bool LL = large_tiles_last(EPI, LAST);
   auto allow = [](const void* kernel, int bytes) { return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); };
-  hipError_t e = allow(reinterpret_cast<const void*>(&prefill_gemm_kernel<EPI, QKN, LAST, 4>), LAST ? PGEMM_LAST_LDS_BYTES : PGEMM_LDS_BYTES);
-  if (e == hipSuccess) e = allow(reinterpret_cast<const void*>(&prefill_gemm_kernel<EPI, QKN, LAST, 3>), LAST ? PGEMM_LAST_LDS_BYTES : PGEMM_LDS_BYTES);
+  hipError_t e = allow(reinterpret_cast<const void*>(&prefill_gemm_kernel<EPI, QKN, LL, 4>), LL ? PGEMM_LAST_LDS_BYTES : PGEMM_LDS_BYTES);
+  if (e == hipSuccess) e = allow(reinterpret_cast<const void*>(&prefill_gemm_kernel<EPI, QKN, LL, 3>), LL ? PGEMM_LAST_LDS_BYTES : PGEMM_LDS_BYTES);
   if (e == hipSuccess) e = allow(reinterpret_cast<const void*>(&prefill_gemm_small_kernel<EPI, QKN, 1, LAST>), PSG_LDS_BYTES);
   if (e == hipSuccess) e = allow(reinterpret_cast<const void*>(&prefill_gemm_small_kernel<EPI, QKN, 2, LAST>), PSG_LDS_BYTES);
   return e;
@@ -1426,7 +1431,7 @@ template <bool LAST>
 static hipError_t allow_all_pgemm_lds() {
   hipError_t e = allow_pgemm_lds<PEPI_QKV, false, LAST>();
   if (e == hipSuccess) e = allow_pgemm_lds<PEPI_QKV, true, LAST>();
-  if constexpr (LAST) if (e == hipSuccess) e = allow_pgemm_lds<PEPI_RESID, false, true>();
+  if (e == hipSuccess) e = allow_pgemm_lds<PEPI_RESID, false, LAST>();
   if (e == hipSuccess) e = allow_pgemm_lds<PEPI_SWIGLU, false, LAST>();
   return e;
 }
@@ -1442,13 +1447,12 @@ static int launch_pgemm_as(www_model* m, PGemmP& p, hipStream_t st) {
   p.n_rt = (p.NRG + 15) / 16;
   if (p.wfactor == 0.f) p.wfactor = 1.f;  // not set: an unscaled matrix
   const PGemmChoice c = choose_pgemm(p.T, p.NRG, p.KB);
-  if (c.tb == 0) {
-    hipLaunchKernelGGL((prefill_gemm_kernel<EPI, QKN, LAST, 4>), dim3(p.n_tt * p.n_rt), dim3(256), LAST ? PGEMM_LAST_LDS_BYTES : PGEMM_LDS_BYTES, st, p);
-    return p.n_rt;
-  }
-  if (c.tb == 3) {
-    p.n_tt = (p.T + 191) / 192;
-    hipLaunchKernelGGL((prefill_gemm_kernel<EPI, QKN, LAST, 3>), dim3(p.n_tt * p.n_rt), dim3(256), LAST ? PGEMM_LAST_LDS_BYTES : PGEMM_LDS_BYTES, st, p);
+  if (c.tb % 3 == 0) {
+    constexpr bool LL = large_tiles_last(EPI, LAST);
+    if (c.tb == 3) p.n_tt = (p.T + 191) / 192;
+    const dim3 grid(p.n_tt * p.n_rt);
+    if (c.tb == 0) hipLaunchKernelGGL((prefill_gemm_kernel<EPI, QKN, LL, 4>), grid, dim3(256), LL ? PGEMM_LAST_LDS_BYTES : PGEMM_LDS_BYTES, st, p);
+    else hipLaunchKernelGGL((prefill_gemm_kernel<EPI, QKN, LL, 3>), grid, dim3(256), LL ? PGEMM_LAST_LDS_BYTES : PGEMM_LDS_BYTES, st, p);
     return p.n_rt;
   }
   p.n_ttS = (p.T + 128 * c.tb - 1) / (128 * c.tb);
@@ -1466,10 +1470,7 @@ static int launch_pgemm(www_model* m, PGemmP& p, hipStream_t st) {
   if constexpr (EPI == PEPI_QKV) {
     if (p.qk_gain) return p.n_last ? launch_pgemm_as<EPI, true, true>(m, p, st) : launch_pgemm_as<EPI, true, false>(m, p, st);
   }
-  // The residual GEMMs always run the kernel that can carry last positions: their 256 x 256 epilogue spills 4 registers there and
-  // 63 without (8B shape, calls of 16 000 tokens: the two of a layer 2 x 1407 against 2 x 1467 us).
-  if constexpr (EPI == PEPI_RESID) return launch_pgemm_as<EPI, false, true>(m, p, st);
-  else return p.n_last ? launch_pgemm_as<EPI, false, true>(m, p, st) : launch_pgemm_as<EPI, false, false>(m, p, st);
+  return p.n_last ? launch_pgemm_as<EPI, false, true>(m, p, st) : launch_pgemm_as<EPI, false, false>(m, p, st);
 }
 
 // Shape of the attention workgroups: two query heads per wavefront pass, since their accumulators and operands fit 256

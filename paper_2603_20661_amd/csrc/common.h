@@ -144,8 +144,9 @@ __device__ __forceinline__ bool arrive_last(unsigned long long* counter, int ksp
   return last;
 }
 
-// Adds n parked partial tiles in order: load(slot, i) requests tile i into one of W register sets, add(slot) adds it.  The set
-// just added takes the next tile, so that W requests stay on their way and a range of 8 splits costs one memory latency, not two.
+// Adds n parked partial tiles in order: load(slot, i) requests tile i into one of W register sets, add(slot) adds it.  The set just
+// added takes the next tile at once, so the requests of the next W tiles go out one behind the other while these are added, instead of
+// all together behind the last of them; more than W tiles still take a second memory latency, less the time of the additions.
 template <int W, typename LOAD, typename ADD>
 __device__ __forceinline__ void add_in_order(int n, LOAD load, ADD add) {
 #pragma unroll

@@ -14,7 +14,7 @@ __device__ __forceinline__ f16x8 as_f16x8(u32x4 v) { return __builtin_bit_cast(f
 #define ATTN_TQ 64  // query rows per attention workgroup
 
 // Last positions as rows of a prefill call.  The decode pass that follows a prefill reads every weight a second time (8B shape, one
-// sequence: 3.3 of the 11 ms of a 333-token prompt).  Where the GEMMs take the rows without further rounds (prefill_rides), the
+// sequence: 3.3 of the 11 ms of a 333-token prompt).  Where the rows cost the GEMMs less than that pass (prefill_rides), the
 // last position of sequence s travels through all layers but the rest of the last one as two more rows of the same GEMMs:
 // the hi parts of its activations are row first_last + 32 (s / 16) + s % 16, the lo parts 16 rows behind, so both are columns
 // of one 32-token group and a lane finds the other part 16 lanes away.  The epilogues add the two products and write the
@@ -1390,6 +1390,8 @@ int prefill_rows(int T, int batch) { return (T + 31) / 32 * 32 + (batch + 15) / 
 
 // Do the last positions of a call ride along as rows of its GEMMs?  Where that costs less, by the fit above, than the four
 // products of the decode pass, which stream their weights at about 6 TB/s and take about 3 us, and 0.16 us per sequence, besides.
+// One decision for all four products of a layer: calls whose tokens fill their tiles exactly would open another round of them and keep
+// the pass (8B shape, one prompt: 333, 640, 768, 1500 and 3000 tokens ride, 512, 1024, 2048, 4096 and 8192 do not).
 // Not for models with two weight planes, whose prefill reads the first alone.
 bool prefill_rides(const www_model* m, int T, int batch) {
   if (m->wsplit || m->L < 2) return false;

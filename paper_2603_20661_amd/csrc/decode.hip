@@ -1221,9 +1221,9 @@ static SkinnyShape skinny_shape(const www_model* m, int epi, int NRG, int KB, in
 
 // false: the shape the rules chose has no kernel, nothing was launched
 template <int EPI>
-static bool launch_gemm(www_model* m, GemmP& p, hipStream_t st) {
+static bool launch_gemm(www_model* m, GemmP& p, const SmallShape& small, hipStream_t st) {
+  if (small.R) return launch_small_gemm<EPI>(m, p, small, st);
   bool launched = false;
-  if (small_gemm_takes(m, EPI, p.NRG, p.KB, p.M)) return launch_small_gemm<EPI>(m, p, st);
   constexpr bool wide_epi = EPI == EPI_SWIGLU || EPI == EPI_LOGITS;
   const SkinnyShape s = skinny_shape(m, EPI, p.NRG, p.KB, p.M);
   const int mtk = s.mtk, zb = s.zb;
@@ -1275,14 +1275,13 @@ bool decode_route(const www_model* m, int which, int batch, int32_t out[4]) {
   const int epi[5] = {EPI_QKV, EPI_RESID, EPI_SWIGLU, EPI_RESID, EPI_LOGITS};
   const int NRG = (which == 0 ? m->QKVN : which == 2 ? 2 * m->F : which == 4 ? m->V : m->d) / 16;
   const int KB = (which == 1 ? m->QD : which == 3 ? m->Fp : m->d) / 32;
-  if (small_gemm_takes(m, epi[which], NRG, KB, batch)) {
-    const SmallShape s = small_gemm_shape(m, epi[which], NRG, KB, batch);
+  if (const SmallShape s = small_gemm_route(m, epi[which], NRG, KB, batch); s.R) {
     out[0] = 1; out[1] = s.xf == 1 ? 8 : s.xf == 2 ? 16 : 32; out[2] = 16 * s.R * s.RW; out[3] = s.ks;
     return small_gemm_built(m, epi[which], s);
   } else {
-    const SkinnyShape s = skinny_shape(m, epi[which], NRG, KB, batch);
-    out[0] = 0; out[1] = 16 * s.mtk; out[2] = GEMM_TILE_ROWS; out[3] = s.ksplit;
-    return s.mtk != 2 || !m->int4_group || which == 2 || which == 4;  // (narrow int4 products of 17 to 32 tokens: the other kernel)
+    const SkinnyShape k = skinny_shape(m, epi[which], NRG, KB, batch);
+    out[0] = 0; out[1] = 16 * k.mtk; out[2] = GEMM_TILE_ROWS; out[3] = k.ksplit;
+    return k.mtk != 2 || !m->int4_group || which == 2 || which == 4;  // (narrow int4 products of 17 to 32 tokens: the other kernel)
   }
 }
 
@@ -1366,7 +1365,10 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
   }
   bool launched = true;
   int n_ssq = 1;  // entries per token of the sum-of-squares table: one per row group or per row tile of the GEMM that wrote it
-  auto resid_entries = [&](int KB) { return small_gemm_takes(m, EPI_RESID, d / 16, KB, batch) ? d / 16 : (d / 16 + 7) / 8; };
+  auto resid_entries = [&](const SmallShape& s) { return s.R ? d / 16 : (d / 16 + 7) / 8; };
+  // the same in every layer
+  const SmallShape s_qkv = small_gemm_route(m, EPI_QKV, m->QKVN / 16, d / 32, batch), s_o = small_gemm_route(m, EPI_RESID, d / 16, m->QD / 32, batch);
+  const SmallShape s_gu = small_gemm_route(m, EPI_SWIGLU, 2 * m->F / 16, d / 32, batch), s_down = small_gemm_route(m, EPI_RESID, d / 16, m->Fp / 32, batch);
   const float qscale = 1.4426950408889634f / sqrtf((float)m->hd);
   for (int l = from_last_qkv ? m->L - 1 : 0; l < m->L; ++l) {
     const LayerW& w = m->layers[l];
@@ -1382,7 +1384,7 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
       p.q_hi = m->q_hi; p.q_lo = m->q_lo; p.qscale = qscale; p.kplane = kplane; p.vplane = vplane; p.kvscale = kvscale; p.seq_lens = lens; p.table = table; p.mbs = m->cfg.max_blocks_per_seq;
       p.hd = m->hd; p.Hq = m->Hq; p.Hkv = m->Hkv; p.rope = m->rope; p.qk_gain = w.qk_gain;
       prof_mark(m, PK_QKV, st);
-      launched &= launch_gemm<EPI_QKV>(m, p, st);
+      launched &= launch_gemm<EPI_QKV>(m, p, s_qkv, st);
     }
     prof_mark(m, PK_ATTN, st);
     launch_decode_attn(m, l, lens, table, batch, (uint16_t*)m->xo, MT, -1, st);
@@ -1393,8 +1395,8 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
       p.X = (const u32x4*)m->xo; p.M = batch;
       p.h = m->h; p.gain_next = w.ffn_norm; p.xnext = (uint16_t*)m->xq; p.ssq_out = ssq; p.d = d;
       prof_mark(m, PK_OPROJ, st);
-      launched &= launch_gemm<EPI_RESID>(m, p, st);
-      n_ssq = resid_entries(m->QD / 32);
+      launched &= launch_gemm<EPI_RESID>(m, p, s_o, st);
+      n_ssq = resid_entries(s_o);
     }
     {
       GemmP p = {};
@@ -1404,7 +1406,7 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
       p.ssq_in = ssq; p.n_ssq_in = n_ssq; p.inv_dim = 1.f / d; p.eps = m->cfg.rms_eps;
       p.xa = (uint16_t*)m->xa; p.F = m->F;
       prof_mark(m, PK_GATEUP, st);
-      launched &= launch_gemm<EPI_SWIGLU>(m, p, st);
+      launched &= launch_gemm<EPI_SWIGLU>(m, p, s_gu, st);
     }
     {
       GemmP p = {};
@@ -1414,8 +1416,8 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
       p.h = m->h; p.gain_next = (l + 1 < m->L) ? m->layers[l + 1].attn_norm : m->final_norm;
       p.xnext = (uint16_t*)m->xq; p.ssq_out = ssq; p.d = d;
       prof_mark(m, PK_DOWN, st);
-      launched &= launch_gemm<EPI_RESID>(m, p, st);
-      n_ssq = resid_entries(m->Fp / 32);
+      launched &= launch_gemm<EPI_RESID>(m, p, s_down, st);
+      n_ssq = resid_entries(s_down);
     }
   }
   float* lg = logits ? logits : m->logits_buf;
@@ -1427,7 +1429,7 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
     p.ssq_in = ssq; p.n_ssq_in = n_ssq; p.inv_dim = 1.f / d; p.eps = m->cfg.rms_eps;
     p.logits = lg; p.V = m->V;
     prof_mark(m, PK_LMHEAD, st);
-    launched &= launch_gemm<EPI_LOGITS>(m, p, st);
+    launched &= launch_gemm<EPI_LOGITS>(m, p, small_gemm_route(m, EPI_LOGITS, m->V / 16, d / 32, batch), st);
   }
   if (next) prof_mark(m, PK_ARGMAX, st);
   if (next) {

@@ -92,9 +92,9 @@ enum { WMODE_F16 = 0, WMODE_SPLIT = 1, WMODE_FP8 = 2, WMODE_INT4 = 3 };
 // decode_small.hip: GEMMs of a step of up to 32 tokens
 int decode_wg_target();  // compute units (decode.hip)
 void choose_split(int row_tiles, int zb, int KB, int* ksplit, int* kb_per_split);  // k splits of skinny_gemm_kernel
-bool small_gemm_takes(const www_model* m, int epi, int NRG, int KB, int M);
-struct SmallShape { int R, RW, xf, ks, per; float us; };  // 16 R RW rows a workgroup, XF, k splits, k blocks of one; narrow ones: estimate
-SmallShape small_gemm_shape(const www_model* m, int epi, int NRG, int KB, int M);
+// 16 R RW rows a workgroup, XF, k splits, k blocks of one; narrow ones: estimate.  R = 0: the GEMM runs in skinny_gemm_kernel
+struct SmallShape { int R, RW, xf, ks, per; float us; };
+SmallShape small_gemm_route(const www_model* m, int epi, int NRG, int KB, int M);
 bool small_gemm_built(const www_model* m, int epi, const SmallShape& s);
 template <int EPI>
-bool launch_small_gemm(www_model* m, GemmP& p, hipStream_t st);  // false: the shape has no kernel, nothing was launched
+bool launch_small_gemm(www_model* m, GemmP& p, const SmallShape& s, hipStream_t st);  // false: the shape has no kernel, nothing was launched

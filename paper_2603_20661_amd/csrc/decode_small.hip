@@ -473,17 +473,14 @@ static float general_us(int NRG, int KB, int M, float wbytes) {
 // heads of 64: 32 k blocks 9.9 / 11.1, 11.0 / 11.3, 13.4 / 13.7, 14.2 / 14.2, 48 14.9 / 12.7, 16.5 / 12.6, 19.0 / 14.5, 20.7 / 15.1;
 // heads of 128: 16 9.1 / 10.8, 10.2 / 10.8, 12.1 / 13.1, 12.9 / 13.2, 32 13.5 / 11.5, 15.8 / 11.3, 19.1 / 13.6, 21.7 / 14.2.  Wide ones in
 // one round, 4 and 12 sequences: gate/up 16 8.7 / 9.0, 9.1 / 9.1, 32 11.5 / 11.8, 12.2 / 11.8; in two rounds 48 21.4 / 18.6, 23.1 / 18.6).
-bool small_gemm_takes(const www_model* m, int epi, int NRG, int KB, int M) {
+static bool small_gemm_takes(const www_model* m, int epi, int NRG, int KB, int M, const SmallShape& s) {
   if (KB < 16 && M <= 16) return false;
   if (m->wsplit) {
-    if (epi == EPI_QKV) return M <= 32 && m->hd * KB <= 64 * 32;
-    return KB <= 48 && (epi == EPI_RESID ? M <= 32 : M <= 8 && NRG <= 2 * decode_wg_target());
+    if (epi == EPI_QKV) return m->hd * KB <= 64 * 32;
+    return KB <= 48 && (epi == EPI_RESID || (M <= 8 && NRG <= 2 * decode_wg_target()));
   }
-  if (epi == EPI_QKV || epi == EPI_RESID) {
-    if (M > 32 || m->int4_group) return M <= 32;
-    return small_gemm_shape(m, epi, NRG, KB, M).us <= general_us(NRG, KB, M, m->fp8 ? 1.f : 2.f) + 2.5f;
-  }
-  if (M > 16) return M <= 32 && epi == EPI_SWIGLU && !m->int4_group && NRG <= 4 * decode_wg_target();
+  if (epi == EPI_QKV || epi == EPI_RESID) return m->int4_group || s.us <= general_us(NRG, KB, M, m->fp8 ? 1.f : 2.f) + 2.5f;
+  if (M > 16) return epi == EPI_SWIGLU && !m->int4_group && NRG <= 4 * decode_wg_target();
   if (m->int4_group) return true;
   if (epi == EPI_LOGITS) return (NRG + 7) / 8 > decode_wg_target() || (m->fp8 && M <= 8);
   return M <= 8 && NRG <= 4 * decode_wg_target();
@@ -491,7 +488,7 @@ bool small_gemm_takes(const www_model* m, int epi, int NRG, int KB, int M) {
 
 uint64_t small_gemm_partial_bytes(int NRG) { return (uint64_t)NRG * 8 * 2 * 1024; }  // [split][row group][2 token groups]
 
-SmallShape small_gemm_shape(const www_model* m, int epi, int NRG, int KB, int M) {
+static SmallShape small_gemm_shape(const www_model* m, int epi, int NRG, int KB, int M) {
   const int xf = M <= 8 ? 1 : M <= 16 ? 2 : 4;
   const bool narrow = epi == EPI_QKV || epi == EPI_RESID;
   if (narrow && !m->wsplit) return narrow_shape(epi, NRG, KB, m->hd, xf, m->int4_group ? WMODE_INT4 : m->fp8 ? WMODE_FP8 : WMODE_F16);
@@ -502,6 +499,14 @@ SmallShape small_gemm_shape(const www_model* m, int epi, int NRG, int KB, int M)
     s.R = 4;
     while (s.RW < (epi == EPI_LOGITS ? 8 : 2) && (NRG + 4 * s.RW - 1) / (4 * s.RW) > decode_wg_target()) s.RW *= 2;
   }
+  return s;
+}
+
+SmallShape small_gemm_route(const www_model* m, int epi, int NRG, int KB, int M) {
+  SmallShape s = {0, 0, 0, 0, 0, 0.f};
+  if (M > 32) return s;
+  s = small_gemm_shape(m, epi, NRG, KB, M);
+  if (!small_gemm_takes(m, epi, NRG, KB, M, s)) s.R = 0;
   return s;
 }
 
@@ -538,8 +543,7 @@ static bool launch_small_rows(const GemmP& p, const SmallShape& s, hipStream_t s
 }
 
 template <int EPI>
-bool launch_small_gemm(www_model* m, GemmP& p, hipStream_t st) {
-  const SmallShape s = small_gemm_shape(m, EPI, p.NRG, p.KB, p.M);
+bool launch_small_gemm(www_model* m, GemmP& p, const SmallShape& s, hipStream_t st) {
   p.ksplit = s.ks;
   p.kb_per_split = s.per;
   p.MT = s.xf == 4 ? 2 : 1;
@@ -558,7 +562,7 @@ bool launch_small_gemm(www_model* m, GemmP& p, hipStream_t st) {
     default: return launch_small_rows<EPI, WMODE_F16>(p, s, st);
   }
 }
-template bool launch_small_gemm<EPI_QKV>(www_model*, GemmP&, hipStream_t);
-template bool launch_small_gemm<EPI_RESID>(www_model*, GemmP&, hipStream_t);
-template bool launch_small_gemm<EPI_SWIGLU>(www_model*, GemmP&, hipStream_t);
-template bool launch_small_gemm<EPI_LOGITS>(www_model*, GemmP&, hipStream_t);
+template bool launch_small_gemm<EPI_QKV>(www_model*, GemmP&, const SmallShape&, hipStream_t);
+template bool launch_small_gemm<EPI_RESID>(www_model*, GemmP&, const SmallShape&, hipStream_t);
+template bool launch_small_gemm<EPI_SWIGLU>(www_model*, GemmP&, const SmallShape&, hipStream_t);
+template bool launch_small_gemm<EPI_LOGITS>(www_model*, GemmP&, const SmallShape&, hipStream_t);

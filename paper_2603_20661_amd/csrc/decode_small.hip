@@ -452,7 +452,9 @@ static float general_us(int NRG, int KB, int M, float wbytes) {
 // Which GEMMs of a step of M tokens run here (us per launch against skinny_gemm_kernel; 8B shape 1, 12, 24 sequences, 1B shape
 // 4 and 32): QKV 13.5 / 15.5, 15.3 / 16.0, 17.7 / 17.9, 8.4 / 11.2, 11.7 / 13.9; O 8.5 / 12.3, 10.5 / 12.4, 11.6 / 14.1, 5.0 / 8.7,
 // 8.0 / 10.0; down 22.4 / 25.8, 24.8 / 26.5, 26.4 / 28.0, 11.1 / 15.5, 14.0 / 17.5; output head 168 / 174 and 172 / 182 (1B: equal);
-// int4, 5 sequences: QKV 10.8 / 13.0, O 6.8 / 10.4, gate/up 18.0 / 24.4, down 13.2 / 17.7, head 56 / 67.  Not the gate/up GEMM
+// int4, 5 sequences: QKV 10.8 / 13.0, O 6.8 / 10.4, gate/up 18.0 / 24.4, down 13.2 / 17.7, head 56 / 67; the narrow int4 products
+// also from 17 to 32 tokens (steps of up to 6 layers, 17 and 32 sequences: 8B shape 667 / 719 and 736 / 782, 1B shape at 20 and
+// 32 380 / 443 and 412 / 468, 8192 columns and 4 layers 906 / 928 and 966 / 988).  Not the gate/up GEMM
 // of the other formats, which has rows for every compute unit without a split (39.0 / 37.6, with FP8 24.6 / 21.9; 1B shape with up
 // to 8 tokens 13.4 / 14.6), unless 64 rows per workgroup fill the chip in one round: then up to 8 tokens and, where the other kernel
 // has to split k, from 17 on (1B shape, 32 tokens 15.4 / 16.9; a step of 24 sequences with FP8 weights 880 / 896; of 12 and 16

@@ -50,25 +50,25 @@ HBM_PEAK_GBS = 8000.0      # MI355X HBM3E
 CALIB_COPY_BYTES = 1 << 28  # size of the counter-calibration copy
 
 # HBM traffic of the decode kernel classes, from two `rocprofv3 --pmc` runs of this file (FETCH_SIZE, then WRITE_SIZE;
-# profiles/decode_kernels_8b_traffic.md).  Counter units per launch, averaged over the 256 launches per class of those runs
+# profiles/decode_kernels_8b_traffic.md).  Counter units per launch, averaged over the 224 to 256 launches per class of those runs
 # (8 for the output head); scale = KiB per unit, from what the same counter read for the calibration copy above (131 087.1
 # units of FETCH_SIZE for 262 144 KiB read, 262 144.0 units of WRITE_SIZE for 262 144 KiB written).  The attention
 # reading is rescaled linearly to the reported launch's context (its traffic is proportional to it); the GEMMs' bytes do
-# not depend on the step.  Valid only for the kernels it was taken with: the hash covers the text of decode.hip and
-# common.h; every reading is reported as null when that text has changed.
+# not depend on the step.  Valid only for the kernels it was taken with: the hash covers the text of the decode path's
+# sources; every reading is reported as null when that text has changed.
 TRAFFIC = {
     "workload": "8b",
     "fetch_scale": 262144.0 / 131087.1, "write_scale": 1.0,
     "classes": {   # class: (FETCH_SIZE units, WRITE_SIZE units, algorithmic bytes of the measured launches or None = this run's)
-        "decode_attention": (165304.6 + 1669.0, 3107.2 + 1024.0, 80383 * 4160),
-        "qkv_gemm": (32960.2, 9513.0, None),
-        "o_gemm": (25222.0, 10313.0, None),
-        "gate_up_gemm": (118939.6, 3584.0, None),
-        "down_gemm": (76424.4, 10313.0, None),
-        "lm_head_gemm": (529392.8, 32068.2, None),
+        "decode_attention": (165371.5 + 1578.3, 3108.6 + 1024.0, 80383 * 4160),
+        "qkv_gemm": (32980.4, 9513.0, None),
+        "o_gemm": (25239.6, 10313.0, None),
+        "gate_up_gemm": (118926.5, 3584.0, None),
+        "down_gemm": (76439.9, 10313.0, None),
+        "lm_head_gemm": (529503.9, 32067.8, None),
     },
-    "sources": ("paper_2603_20661_amd/csrc/decode.hip", "paper_2603_20661_amd/csrc/common.h"),
-    "sha256": "342b09e6dd9f9cefa0e384a9223eea53e53d2bd049cfa55c14bb3eb7a7807254",
+    "sources": tuple("paper_2603_20661_amd/csrc/" + f for f in ("decode.hip", "decode_small.hip", "decode_gemm.h", "common.h")),
+    "sha256": "b6510288cda3a89cd0057954b20c66964a46d04587333026823ad514a9dbd0eb",
 }
 
 

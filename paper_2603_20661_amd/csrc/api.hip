@@ -234,8 +234,8 @@ static void make_plan(const www_config* c, Plan& p) {
   p.attn_hdr = take(16);
   p.attn_start = take((uint64_t)MAX_ATTN_WAVES * 16);
   p.attn_pref = take(((uint64_t)s.maxB + 1) * 4);
-  p.argmax_val = take((uint64_t)s.maxB * 32 * 4);
-  p.argmax_idx = take((uint64_t)s.maxB * 32 * 4);
+  p.argmax_val = take((uint64_t)s.maxB * ((s.V + 31) / 32) * 4);
+  p.argmax_idx = take((uint64_t)s.maxB * ((s.V + 31) / 32) * 4);
   const uint64_t Tpad = (((uint64_t)maxR + 191) / 192 * 192 + 255) / 256 * 256;  // packed activation buffers hold whole tiles of 192 and 256 tokens
   p.hp = take(Tpad * (((uint64_t)s.d + 255) / 256 * 256) * 4);  // residual stream in whole 256 x 256 blocks (accumulator order)
   p.ssq_p = take(Tpad * (uint64_t)PSSQ * 4);

@@ -218,7 +218,7 @@ struct www_model {
   float* partial;  // split-K partial tiles
   float* attn_part;
   int *attn_hdr, *attn_start, *attn_pref;  // per-step plan of the decode attention: totals, per-wavefront start, prefix of pair counts
-  float* argmax_val;  // [maxB][32] per-slice maxima of the logits and
+  float* argmax_val;  // [token][workgroups over the rows of the output head, of 32 rows at least] largest logits and
   int* argmax_idx;    // their indices
   unsigned long long* counters;  // split-K arrival counters
   int* fault_host;  // pinned host words: [0] set by the kernels when the placement rule of the split-K hand-over is violated,

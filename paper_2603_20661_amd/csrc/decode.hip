@@ -548,6 +548,8 @@ __global__ __launch_bounds__(256 * KH, MTK == 8 ? 1 : 2 / KH) void skinny_gemm_k
   float ssq_local[MTK];
 #pragma unroll
   for (int tb = 0; tb < MTK; ++tb) ssq_local[tb] = 0.f;
+  float best[EPI == EPI_LOGITS ? MTK : 1];
+  int best_at[EPI == EPI_LOGITS ? MTK : 1];
 
   // Normalised query / key heads: 1 / rms of each token's head vector.  A row tile holds whole heads (128 rows: one head
   // of 128, or two of 64 owned by wavefronts 0,1 and 2,3); a wavefront adds the squares of its 32 rows per token (lanes,
@@ -638,6 +640,7 @@ __global__ __launch_bounds__(256 * KH, MTK == 8 ? 1 : 2 / KH) void skinny_gemm_k
     const bool tok_ok = t < p.M;
     const float scale = scale_pre[tb];
 
+    if constexpr (EPI == EPI_LOGITS) { best[tb] = NEG_INF; best_at[tb] = 0x7fffffff; }
     if constexpr (EPI == EPI_SWIGLU) {
       if (tok_ok && rg0 + 1 < p.NRG) {
         int f0 = (rg0 >> 1) * 16 + rsub;
@@ -662,6 +665,8 @@ __global__ __launch_bounds__(256 * KH, MTK == 8 ? 1 : 2 / KH) void skinny_gemm_k
 
         if constexpr (EPI == EPI_LOGITS) {
           *reinterpret_cast<float4*>(p.logits + (int64_t)t * p.V + n0) = make_float4(v[0], v[1], v[2], v[3]);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) argmax_take(best[tb], best_at[tb], v[i], n0 + i);
         } else if constexpr (EPI == EPI_RESID) {
           const f32x4 hv = hv_pre[r][tb], gv = gv_pre[r];
           float hn[4] = {hv[0] + v[0], hv[1] + v[1], hv[2] + v[2], hv[3] + v[3]};
@@ -712,6 +717,25 @@ __global__ __launch_bounds__(256 * KH, MTK == 8 ? 1 : 2 / KH) void skinny_gemm_k
     }
   }
 
+  if constexpr (EPI == EPI_LOGITS) {  // the largest of this row tile per token, for argmax_kernel
+    if (!p.best_val) return;
+    int(*at)[MTK * 16] = reinterpret_cast<int(*)[MTK * 16]>(red + 4);
+#pragma unroll
+    for (int tb = 0; tb < MTK; ++tb) {
+      argmax_of_rows(best[tb], best_at[tb]);
+      if (lane < 16) { red[wave][tb * 16 + lane] = best[tb]; at[wave][tb * 16 + lane] = best_at[tb]; }
+    }
+    __syncthreads();
+    const int t = tb0 * 16 + tid;
+    if (tid < MTK * 16 && t < p.M) {
+      float b = red[0][tid];
+      int i = at[0][tid];
+#pragma unroll
+      for (int w = 1; w < 4; ++w) argmax_take(b, i, red[w][tid], at[w][tid]);
+      p.best_val[(int64_t)t * p.row_tiles + tile] = b;
+      p.best_idx[(int64_t)t * p.row_tiles + tile] = i;
+    }
+  }
   if constexpr (EPI == EPI_RESID) {
     // per (row tile, token) sum of squares of the new residual, reduced in a fixed order
 #pragma unroll
@@ -1108,46 +1132,26 @@ __global__ __launch_bounds__(64 * MERGE_WAVES) void decode_attn_merge_kernel(con
 }
 
 // ------------------------------------------------------------------------------------------------
-// Greedy next token: index of the largest logit, the lowest index winning ties.  Two stages: ARGMAX_CHUNKS
-// workgroups per row each scan a contiguous slice with 16-byte loads, then one wavefront per row combines them.
-#define ARGMAX_CHUNKS 32
-__device__ __forceinline__ void argmax_take(float& best, int& bi, float v, int i) {
-  if (v > best || (v == best && i < bi)) { best = v; bi = i; }
-}
-__global__ __launch_bounds__(256) void argmax_partial_kernel(const float* __restrict__ logits, int V, float* __restrict__ pval,
-                                                             int* __restrict__ pidx) {
-  const float* row = logits + (int64_t)blockIdx.y * V;
-  const int nq = V / 4, per = (nq + ARGMAX_CHUNKS - 1) / ARGMAX_CHUNKS;
-  const int q0 = blockIdx.x * per, q1 = min(nq, q0 + per);
+// Greedy next token: index of the largest logit, the lowest index winning ties.  The output head's workgroups leave the largest of their rows
+// per token (a kernel of its own that read the logits again: 4.8 us a step, 9 with 64 sequences); one workgroup per token combines these.
+__global__ __launch_bounds__(256) void argmax_kernel(const float* __restrict__ val, const int* __restrict__ idx, int n, int32_t* __restrict__ out) {
+  const int tid = threadIdx.x;
   float best = NEG_INF;
   int bi = 0x7fffffff;
-  for (int q = q0 + threadIdx.x; q < q1; q += 256) {
-    const f32x4 v = *reinterpret_cast<const f32x4*>(row + 4 * q);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) argmax_take(best, bi, v[e], 4 * q + e);
-  }
+#pragma unroll 4
+  for (int q = tid; q < n; q += 256) argmax_take(best, bi, val[(int64_t)blockIdx.x * n + q], idx[(int64_t)blockIdx.x * n + q]);
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) argmax_take(best, bi, __shfl_xor(best, o), __shfl_xor(bi, o));
   __shared__ float sv[4];
   __shared__ int si[4];
-  if ((threadIdx.x & 63) == 0) { sv[threadIdx.x >> 6] = best; si[threadIdx.x >> 6] = bi; }
+  if ((tid & 63) == 0) { sv[tid >> 6] = best; si[tid >> 6] = bi; }
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (tid == 0) {
 #pragma unroll
     for (int w = 1; w < 4; ++w) argmax_take(best, bi, sv[w], si[w]);
-    pval[blockIdx.y * ARGMAX_CHUNKS + blockIdx.x] = best;
-    pidx[blockIdx.y * ARGMAX_CHUNKS + blockIdx.x] = bi;
+    // a row without any ordered value (all NaN) has no largest element: token 0, never an index outside the vocabulary
+    out[blockIdx.x] = bi == 0x7fffffff ? 0 : bi;
   }
-}
-__global__ __launch_bounds__(64) void argmax_final_kernel(const float* __restrict__ pval, const int* __restrict__ pidx,
-                                                          int32_t* __restrict__ out) {
-  const int lane = threadIdx.x;
-  float best = lane < ARGMAX_CHUNKS ? pval[blockIdx.x * ARGMAX_CHUNKS + lane] : NEG_INF;
-  int bi = lane < ARGMAX_CHUNKS ? pidx[blockIdx.x * ARGMAX_CHUNKS + lane] : 0x7fffffff;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) argmax_take(best, bi, __shfl_xor(best, o), __shfl_xor(bi, o));
-  // a row without any ordered value (all NaN) has no largest element: token 0, never an index outside the vocabulary
-  if (lane == 0) out[blockIdx.x] = bi == 0x7fffffff ? 0 : bi;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1429,12 +1433,12 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
     p.ssq_in = ssq; p.n_ssq_in = n_ssq; p.inv_dim = 1.f / d; p.eps = m->cfg.rms_eps;
     p.logits = lg; p.V = m->V;
     prof_mark(m, PK_LMHEAD, st);
+    if (next) { p.best_val = m->argmax_val; p.best_idx = m->argmax_idx; }
     launched &= launch_gemm<EPI_LOGITS>(m, p, small_gemm_route(m, EPI_LOGITS, m->V / 16, d / 32, batch), st);
-  }
-  if (next) prof_mark(m, PK_ARGMAX, st);
-  if (next) {
-    hipLaunchKernelGGL(argmax_partial_kernel, dim3(ARGMAX_CHUNKS, batch), dim3(256), 0, st, lg, m->V, m->argmax_val, m->argmax_idx);
-    hipLaunchKernelGGL(argmax_final_kernel, dim3(batch), dim3(64), 0, st, m->argmax_val, m->argmax_idx, next);
+    if (next) {
+      prof_mark(m, PK_ARGMAX, st);
+      hipLaunchKernelGGL(argmax_kernel, dim3(batch), dim3(256), 0, st, m->argmax_val, m->argmax_idx, p.row_tiles, next);
+    }
   }
   prof_mark(m, -1, st);
   if (!launched) {

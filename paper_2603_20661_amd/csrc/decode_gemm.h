@@ -53,7 +53,19 @@ struct GemmP {
   // logits epilogue
   float* logits;
   int V;
+  float* best_val;  // [token][workgroups over the rows] largest logit of a workgroup's rows and its index; null: nobody asks for the tokens
+  int* best_idx;
 };
+
+// the larger of two logits, the lowest index winning ties (a NaN is never taken)
+__device__ __forceinline__ void argmax_take(float& best, int& bi, float v, int i) {
+  if (v > best || (v == best && i < bi)) { best = v; bi = i; }
+}
+// ... of a token over the four lanes l, l ^ 16, l ^ 32 and l ^ 48
+__device__ __forceinline__ void argmax_of_rows(float& best, int& bi) {
+  argmax_take(best, bi, __shfl_xor(best, 16), __shfl_xor(bi, 16));
+  argmax_take(best, bi, __shfl_xor(best, 32), __shfl_xor(bi, 32));
+}
 
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 

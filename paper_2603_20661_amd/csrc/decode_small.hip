@@ -232,13 +232,38 @@ __global__ __launch_bounds__(64 * SG_NW, sg_eu(WMODE, R, XF)) void small_gemm_ke
   auto valid_token = [&](int tb) __attribute__((always_inline)) { return tlow == tsub && tb * 16 + tlow < p.M; };
 
   if constexpr (EPI == EPI_LOGITS) {
+    float best[TB];
+    int best_at[TB];
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) { best[tb] = NEG_INF; best_at[tb] = 0x7fffffff; }
     for (int q = wave; q < RT; q += SG_NW) {
 #pragma unroll
       for (int tb = 0; tb < TB; ++tb) {
-        const f32x4 o = sum(q, tb);
-        if (valid_token(tb) && rg0 + q < p.NRG)
-          *reinterpret_cast<f32x4*>(p.logits + (int64_t)(tb * 16 + tlow) * p.V + (rg0 + q) * 16 + rsub) = o * s_scale[tb * 16 + tlow];
+        const f32x4 o = sum(q, tb) * s_scale[tb * 16 + tlow];
+        const int n = (rg0 + q) * 16 + rsub;
+        if (valid_token(tb) && rg0 + q < p.NRG) {
+          *reinterpret_cast<f32x4*>(p.logits + (int64_t)(tb * 16 + tlow) * p.V + n) = o;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) argmax_take(best[tb], best_at[tb], o[e], n + e);
+        }
       }
+    }
+    if (!p.best_val) return;  // the largest of this workgroup per token, for argmax_kernel
+    __shared__ float s_best[SG_NW][16 * TB];
+    __shared__ int s_at[SG_NW][16 * TB];
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) {
+      argmax_of_rows(best[tb], best_at[tb]);
+      if (lane < 16) { s_best[wave][tb * 16 + lane] = best[tb]; s_at[wave][tb * 16 + lane] = best_at[tb]; }
+    }
+    __syncthreads();
+    if (tid < 16 * TB && tid < p.M) {
+      float b = s_best[0][tid];
+      int at = s_at[0][tid];
+#pragma unroll
+      for (int w = 1; w < SG_NW; ++w) argmax_take(b, at, s_best[w][tid], s_at[w][tid]);
+      p.best_val[(int64_t)tid * p.row_tiles + group] = b;
+      p.best_idx[(int64_t)tid * p.row_tiles + group] = at;
     }
     return;
   }

@@ -79,19 +79,20 @@ __device__ __forceinline__ f16x8 fp8x8_to_f16x8(uint32_t lo, uint32_t hi) {
 
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 
-// 8 four-bit codes (one 32-bit word, the code of column e in nibble e) -> 8 fp16 values (code - 8) * scale.  A code n
-// is planted in the mantissa of the fp16 number 1024 (0x6400 | n = 1024 + n, exact), 1032 is subtracted and the result
-// multiplied by the group's scale, two values per instruction; with a scale of 8 significant bits (bf16) the product
-// is exact.
+// 8 four-bit codes (one 32-bit word, the codes of columns 2 i and 2 i + 1 in nibbles i and i + 4: one per half) -> 8 fp16 values
+// (code - 8) * scale.  A code n is planted in the mantissa of the fp16 numbers 1024 (0x6400 | n = 1024 + n) or 64 (0x5400 | n << 4 = 64 + n),
+// both exact; 1032 or 72 is subtracted and the result multiplied by the group's scale, two values per instruction; with a scale of 8
+// significant bits (bf16) the product is exact.  13 instructions for 8 weights; with the codes in column order 19, two nibbles of a pair
+// being brought together by a byte permutation.
 __device__ __forceinline__ f16x8 int4x8_to_f16x8(uint32_t w, f16x2 scale) {
-  const uint32_t even = w & 0x0F0F0F0Fu, odd = (w >> 4) & 0x0F0F0F0Fu;  // codes of columns 0,2,4,6 / 1,3,5,7, one per byte
-  const f16x2 off = {(_Float16)1032.f, (_Float16)1032.f};
+  const f16x2 off[2] = {{(_Float16)1032.f, (_Float16)1032.f}, {(_Float16)72.f, (_Float16)72.f}};
   f16x2 v[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    // low half: byte i of `even`, high half: byte i of `odd`
-    const uint32_t pair = __builtin_amdgcn_perm(odd, even, 0x0C040C00u + 0x00010001u * i) | 0x64006400u;
-    v[i] = (__builtin_bit_cast(f16x2, pair) - off) * scale;
+    uint32_t pair;  // one instruction: of (w & mask) | bits with two literals the compiler makes two
+    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(pair) : "v"(w), "s"(i & 1 ? 0x00F000F0u : 0x000F000Fu), "v"(i & 1 ? 0x54005400u : 0x64006400u));
+    v[i] = (__builtin_bit_cast(f16x2, pair) - off[i & 1]) * scale;
+    if (i == 1) w >>= 8;
   }
   return __builtin_shufflevector(__builtin_shufflevector(v[0], v[1], 0, 1, 2, 3), __builtin_shufflevector(v[2], v[3], 0, 1, 2, 3), 0, 1, 2, 3, 4, 5, 6, 7);
 }

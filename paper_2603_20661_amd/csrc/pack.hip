@@ -144,7 +144,7 @@ __global__ void pack_int4_f16_kernel(const uint8_t* __restrict__ codes, const ui
 }
 
 // Decode order: 16-byte unit ((chunk j of 4 k blocks, row group rg), lane) holds the lane's 8 codes of k blocks 4j .. 4j+3,
-// one 32-bit word per k block, the code of the lane's e-th column in nibble e; zero weights (code 8) past K.
+// one 32-bit word per k block, the code of the lane's e-th column in nibble e / 2 + 4 (e % 2) (int4x8_to_f16x8); zero weights (code 8) past K.
 // Group scales for the decode GEMM: fp16, [chunk][packed row][4] = the scale of each of the chunk's 4 k blocks.
 __global__ void pack_int4_kernel(const uint8_t* __restrict__ codes, const uint16_t* __restrict__ scales, int N, int K, int KB, int group,
                                  int mode, int hd, int n_rot_rows, int F, uint8_t* __restrict__ out, uint16_t* __restrict__ sc_out) {
@@ -162,7 +162,7 @@ __global__ void pack_int4_kernel(const uint8_t* __restrict__ codes, const uint16
     const int k0 = (kb4 * 4 + j) * 32 + (lane >> 4) * 8;
     uint32_t v = 0;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v |= (uint32_t)((k0 + e < K) ? int4_code(codes, srow, K, k0 + e) : 8) << (4 * e);
+    for (int e = 0; e < 8; ++e) v |= (uint32_t)((k0 + e < K) ? int4_code(codes, srow, K, k0 + e) : 8) << (4 * (e / 2) + 16 * (e % 2));
     w[j] = v;
   }
   *reinterpret_cast<uint4*>(out + idx * 16) = make_uint4(w[0], w[1], w[2], w[3]);

@@ -1029,105 +1029,99 @@ __global__ __launch_bounds__(256) void decode_attn_kernel(const uint16_t* __rest
   }
 }
 
-// Merges the records of one (sequence, kv head) and writes the packed hi/lo operand of the O projection.  MERGE_WAVES wavefronts
-// per (kv head, sequence): wavefront v merges, in key order, the v-th run of consecutive records; the intermediate records
-// are then added in key order again (a fixed order), one query head and 64 of its dims per wavefront.  Sequences that were a single segment were
-// finished by the attention kernel itself.  Bound by dependent memory round trips; eight wavefronts reading four records
-// at a time take a sequence of 32 records in one of them (8B shape, graph replay, against one wavefront: one sequence of
-// 8192 tokens 4800 -> 3800 us a step, 64 sequences 6450 -> 6395, 16 sequences with FP8 weights 3095 -> 2963).
+// Merges the records of one (sequence, kv head) and writes the packed hi/lo operand of the O projection.  A wavefront merges records
+// of one query head: 16-byte loads, two (four with 64-wide heads) records per instruction, eight instructions on their way; wavefronts
+// v, v + G, ... share the records of head v in blocks of 16 (32), what they have is combined through LDS in that order.  Sequences that
+// were a single segment were finished by the attention kernel itself.
+// Bound by the launch, two memory round trips (plan, records) and instruction fetch.  With a wavefront for all query heads of a run of
+// records (4-byte loads, four records on their way, one exponential more per record) 8B shape, us: one sequence of 1041 tokens
+// 6.5 -> 4.9, of 8192 8.5 -> 6.2, three of 2000 to 8000 7.7 -> 5.5, 64 of the usual mix 5.0 -> 4.8.
 #define MERGE_WAVES 8
 template <int HD, int G>
-__global__ __launch_bounds__(64 * MERGE_WAVES) void decode_attn_merge_kernel(const int32_t* __restrict__ seq_lens, int Hkv,
-                                                                     const int32_t* __restrict__ hdr, const int32_t* __restrict__ pref,
-                                                                     const float* __restrict__ part,
-                                                                     uint16_t* __restrict__ xo, int MT, int first_row) {
-  constexpr int PSTRIDE = HD + 4, NS = MERGE_WAVES;
-  const int j = blockIdx.x, b = blockIdx.y, lane = threadIdx.x & 63, v = threadIdx.x >> 6;
+__global__ __launch_bounds__(64 * MERGE_WAVES) void decode_attn_merge_kernel(const int32_t* __restrict__ seq_lens, int Hkv, const int32_t* __restrict__ hdr,
+                                                                  const int32_t* __restrict__ pref, const float* __restrict__ part,
+                                                                  uint16_t* __restrict__ xo, int MT, int first_row) {
+  constexpr int PSTRIDE = HD + 4, LR = HD / 4, RI = 64 / LR, U = 8;  // lanes of a record, records per load, loads on their way
+  const int j = blockIdx.x, b = blockIdx.y, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int hh = wave % G, v = wave / G, sharers = MERGE_WAVES / G;
   const int C = hdr[1];
   const int P = max(0, (seq_lens[b] + 31) / 32);
   const int S = pref[b] * Hkv + j * P;  // list position of this sequence's first pair
   const int first_w = S / C;
   const int nrec = (S + P - 1) / C - first_w + 1;
   if (nrec <= 1) return;
+  const int n_mid = min(sharers, (nrec + U * RI - 1) / (U * RI));
+  if (v >= n_mid) return;  // (the barrier below counts the wavefronts that are left)
   const int first_slot = 2 * first_w + (S == first_w * C ? 0 : 1);  // later wavefronts begin with this sequence: even records
-  // Lane owns head-dim elements lane + 64*i of every head; records are read four at a time so the merge is not one
-  // memory round trip per record.
-  constexpr int NE = HD / 64;
-  float Mh[G], Lh[G], oh[G][NE];
-#pragma unroll
-  for (int hh = 0; hh < G; ++hh) {
-    Mh[hh] = NEG_INF;
-    Lh[hh] = 0.f;
-#pragma unroll
-    for (int i = 0; i < NE; ++i) oh[hh][i] = 0.f;
-  }
-  auto take = [&](int hh, float mv, float lv, const float(&ov)[NE]) __attribute__((always_inline)) {
-    const float Mn = fmaxf(Mh[hh], mv);
-    const float ref = Mn == NEG_INF ? 0.f : Mn;
-    const float a = __builtin_amdgcn_exp2f(Mh[hh] - ref), w = __builtin_amdgcn_exp2f(mv - ref);
-    Lh[hh] = Lh[hh] * a + lv * w;
-#pragma unroll
-    for (int i = 0; i < NE; ++i) oh[hh][i] = oh[hh][i] * a + ov[i] * w;
-    Mh[hh] = Mn;
-  };
-  const int per = (nrec + NS - 1) / NS;
-  const int r_end = min(nrec, (v + 1) * per);
-  for (int s0 = v * per; s0 < r_end; s0 += 4) {
-    float mv[4][G], lv[4][G], ov[4][G][NE];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int sidx = min(s0 + u, r_end - 1);
-      const int slot = sidx == 0 ? first_slot : 2 * (first_w + sidx);
-#pragma unroll
-      for (int hh = 0; hh < G; ++hh) {
-        const float* r = part + ((int64_t)slot * G + hh) * PSTRIDE;
-        mv[u][hh] = r[HD];
-        lv[u][hh] = r[HD + 1];
-#pragma unroll
-        for (int i = 0; i < NE; ++i) ov[u][hh][i] = r[lane + 64 * i];
+  const int sub = lane / LR, c = (lane % LR) * 4;
+  float M = NEG_INF, L = 0.f;
+  f32x4 o = {0.f, 0.f, 0.f, 0.f};
+  for (int s0 = v * U * RI; s0 < nrec; s0 += n_mid * U * RI) {
+    f32x4 ov[U];
+    float2 ml[U];
+    auto request = [&](int u) __attribute__((always_inline)) {
+      const int r = min(s0 + u * RI + sub, nrec - 1);
+      const float* rec = part + ((int64_t)(r == 0 ? first_slot : 2 * (first_w + r)) * G + hh) * PSTRIDE;
+      ml[u] = *reinterpret_cast<const float2*>(rec + HD);
+      ov[u] = *reinterpret_cast<const f32x4*>(rec + c);
+    };
+    // (with many sequences most have two or three records: eight loads for them cost 1.2 us of a launch with 128 sequences)
+    request(0);
+    if (s0 + RI < nrec) {
+      request(1);
+      if (s0 + 2 * RI < nrec) {
+        request(2);
+        request(3);
+        if (s0 + 4 * RI < nrec) { request(4); request(5); request(6); request(7); }
       }
     }
+    float Mn = M;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (s0 + u >= r_end) break;
+    for (int u = 0; u < U; ++u) {
+      if (s0 + u * RI >= nrec) break;
+      Mn = fmaxf(Mn, ml[u].x);  // (lanes past the end have the last record once more)
+    }
+    const float ref = Mn == NEG_INF ? 0.f : Mn, a = __builtin_amdgcn_exp2f(M - ref);
+    L *= a;
+    o *= a;
+    M = Mn;
 #pragma unroll
-      for (int hh = 0; hh < G; ++hh) take(hh, mv[u][hh], lv[u][hh], ov[u][hh]);
+    for (int u = 0; u < U; ++u) {
+      if (s0 + u * RI >= nrec) break;
+      if (s0 + u * RI + sub < nrec) {
+        const float w = __builtin_amdgcn_exp2f(ml[u].x - ref);
+        L += ml[u].y * w;
+        o += ov[u] * w;
+      }
     }
   }
-  __shared__ float mid[NS][G][PSTRIDE];
-  if (v * per < nrec) {
+  auto take = [&](float mv, float lv, f32x4 ov) __attribute__((always_inline)) {
+    const float Mn = fmaxf(M, mv), ref = Mn == NEG_INF ? 0.f : Mn;
+    const float a = __builtin_amdgcn_exp2f(M - ref), w = __builtin_amdgcn_exp2f(mv - ref);
+    L = L * a + lv * w;
+    o = o * a + ov * w;
+    M = Mn;
+  };
 #pragma unroll
-    for (int hh = 0; hh < G; ++hh) {
-      if (lane == 0) { mid[v][hh][HD] = Mh[hh]; mid[v][hh][HD + 1] = Lh[hh]; }
-#pragma unroll
-      for (int i = 0; i < NE; ++i) mid[v][hh][lane + 64 * i] = oh[hh][i];
+  for (int x = LR; x < 64; x <<= 1) take(__shfl_xor(M, x), __shfl_xor(L, x), f32x4{__shfl_xor(o[0], x), __shfl_xor(o[1], x), __shfl_xor(o[2], x), __shfl_xor(o[3], x)});
+  if (n_mid > 1) {
+    __shared__ float mid[MERGE_WAVES][PSTRIDE];
+    if (lane < LR) {
+      *reinterpret_cast<f32x4*>(&mid[wave][c]) = o;
+      if (lane == 0) { mid[wave][HD] = M; mid[wave][HD + 1] = L; }
     }
+    __syncthreads();
+    if (v > 0) return;
+    for (int w = wave + G; w < n_mid * G; w += G) take(mid[w][HD], mid[w][HD + 1], *reinterpret_cast<const f32x4*>(&mid[w][c]));
   }
-  __syncthreads();
-  const int n_mid = (nrec + per - 1) / per;
-  for (int q = v; q < G * NE; q += NS) {
-    const int hh = q / NE, c = lane + 64 * (q % NE);
-    float mv[NS], lv[NS], ov[NS];
+  if (lane < LR) {
+    const float inv = 1.f / L;
+    union { uint16_t s[4]; u32x2 v; } hi, lo;
 #pragma unroll
-    for (int u = 0; u < NS; ++u) {
-      const int w = min(u, n_mid - 1);
-      mv[u] = mid[w][hh][HD]; lv[u] = mid[w][hh][HD + 1]; ov[u] = mid[w][hh][c];
-    }
-    float M = mv[0], L = lv[0], o = ov[0];
-#pragma unroll
-    for (int u = 1; u < NS; ++u) {
-      if (u >= n_mid) break;
-      const float Mn = fmaxf(M, mv[u]), ref = Mn == NEG_INF ? 0.f : Mn;
-      const float a = __builtin_amdgcn_exp2f(M - ref), w = __builtin_amdgcn_exp2f(mv[u] - ref);
-      L = L * a + lv[u] * w;
-      o = o * a + ov[u] * w;
-      M = Mn;
-    }
+    for (int i = 0; i < 4; ++i) split_f16(o[i] * inv, hi.s[i], lo.s[i]);
     const int k = (j * G + hh) * HD + c;
-    uint16_t hi, lo;
-    split_f16(o * (1.f / L), hi, lo);
-    xo[attn_out_offset(k, b, 0, MT, first_row, Hkv * G * HD / 16)] = hi;
-    xo[attn_out_offset(k, b, 1, MT, first_row, Hkv * G * HD / 16)] = lo;
+    *reinterpret_cast<u32x2*>(xo + attn_out_offset(k, b, 0, MT, first_row, Hkv * G * HD / 16)) = hi.v;
+    *reinterpret_cast<u32x2*>(xo + attn_out_offset(k, b, 1, MT, first_row, Hkv * G * HD / 16)) = lo.v;
   }
 }
 

@@ -67,7 +67,7 @@ TRAFFIC = {
         "down_gemm": (76439.9, 10313.0, None),
         "lm_head_gemm": (529503.9, 32067.8, None),
     },
-    "sources": tuple("paper_2603_20661_amd/csrc/" + f for f in ("decode.hip", "decode_small.hip", "decode_gemm.h", "common.h")),
+    "sources": tuple("paper_2603_20661_amd/csrc/" + f for f in ("decode.hip", "decode_small.hip", "decode_mid.hip", "decode_gemm.h", "common.h")),
     "sha256": "b6510288cda3a89cd0057954b20c66964a46d04587333026823ad514a9dbd0eb",
 }
 

@@ -14,6 +14,7 @@
 #define WWW_EXPORT extern "C" __attribute__((visibility("default")))
 
 uint64_t small_gemm_partial_bytes(int NRG);
+uint64_t mid_gemm_partial_bytes(int NRG);
 int decode_gemm_ksplit(int NRG, int KB, int MT);
 hipError_t prefill_allow_lds();
 uint64_t prefill_partial_bytes(int maxT, int NRG, int KB);
@@ -218,6 +219,7 @@ static void make_plan(const www_config* c, Plan& p) {
       }
   }
   for (int n : {s.QKVN, s.d}) part = part > small_gemm_partial_bytes(n / 16) ? part : small_gemm_partial_bytes(n / 16);
+  if (s.maxB > 32 && part < mid_gemm_partial_bytes(s.d / 16)) part = mid_gemm_partial_bytes(s.d / 16);
   const int maxR = s.wsplit ? s.maxT : prefill_rows(s.maxT, s.maxB);  // rows of a prefill GEMM: tokens, and the last positions that ride along
   const uint64_t pre[4] = {prefill_partial_bytes(maxR, s.QKVN / 16, s.d / 32), prefill_partial_bytes(maxR, s.d / 16, s.QD / 32),
                            prefill_partial_bytes(maxR, 2 * s.F / 16, s.d / 32), prefill_partial_bytes(maxR, s.d / 16, s.Fp / 32)};

@@ -1219,8 +1219,9 @@ static SkinnyShape skinny_shape(const www_model* m, int epi, int NRG, int KB, in
 
 // false: the shape the rules chose has no kernel, nothing was launched
 template <int EPI>
-static bool launch_gemm(www_model* m, GemmP& p, const SmallShape& small, hipStream_t st) {
+static bool launch_gemm(www_model* m, GemmP& p, const SmallShape& small, hipStream_t st, const MidShape& mid = {0, 0, 0}) {
   if (small.R) return launch_small_gemm<EPI>(m, p, small, st);
+  if (mid.R) return launch_mid_gemm(m, p, mid, st);
   bool launched = false;
   constexpr bool wide_epi = EPI == EPI_SWIGLU || EPI == EPI_LOGITS;
   const SkinnyShape s = skinny_shape(m, EPI, p.NRG, p.KB, p.M);
@@ -1267,7 +1268,7 @@ static bool launch_gemm(www_model* m, GemmP& p, const SmallShape& small, hipStre
   return launched;
 }
 
-// Kernel (0: skinny_gemm_kernel, 1: small_gemm_kernel), tokens and rows per workgroup and k splits of GEMM `which` (0 QKV, 1 O,
+// Kernel (0: skinny_gemm_kernel, with 32 or 64 rows mid_gemm_kernel, 1: small_gemm_kernel), tokens and rows per workgroup and k splits of GEMM `which` (0 QKV, 1 O,
 // 2 gate/up, 3 down, 4 output head) of a decode step; false: there is no such kernel
 bool decode_route(const www_model* m, int which, int batch, int32_t out[4]) {
   const int epi[5] = {EPI_QKV, EPI_RESID, EPI_SWIGLU, EPI_RESID, EPI_LOGITS};
@@ -1276,6 +1277,9 @@ bool decode_route(const www_model* m, int which, int batch, int32_t out[4]) {
   if (const SmallShape s = small_gemm_route(m, epi[which], NRG, KB, batch); s.R) {
     out[0] = 1; out[1] = s.xf == 1 ? 8 : s.xf == 2 ? 16 : 32; out[2] = 16 * s.R * s.RW; out[3] = s.ks;
     return small_gemm_built(m, epi[which], s);
+  } else if (const MidShape g = mid_gemm_route(m, epi[which], NRG, KB, batch); g.R) {
+    out[0] = 0; out[1] = 64; out[2] = 16 * g.R; out[3] = g.ks;
+    return g.R == 2 || g.R == 4;
   } else {
     const SkinnyShape k = skinny_shape(m, epi[which], NRG, KB, batch);
     out[0] = 0; out[1] = 16 * k.mtk; out[2] = GEMM_TILE_ROWS; out[3] = k.ksplit;
@@ -1363,10 +1367,11 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
   }
   bool launched = true;
   int n_ssq = 1;  // entries per token of the sum-of-squares table: one per row group or per row tile of the GEMM that wrote it
-  auto resid_entries = [&](const SmallShape& s) { return s.R ? d / 16 : (d / 16 + 7) / 8; };
+  auto resid_entries = [&](const SmallShape& s, const MidShape& g) { const int rg = s.R ? 1 : g.R ? g.R : 8; return (d / 16 + rg - 1) / rg; };
   // the same in every layer
   const SmallShape s_qkv = small_gemm_route(m, EPI_QKV, m->QKVN / 16, d / 32, batch), s_o = small_gemm_route(m, EPI_RESID, d / 16, m->QD / 32, batch);
   const SmallShape s_gu = small_gemm_route(m, EPI_SWIGLU, 2 * m->F / 16, d / 32, batch), s_down = small_gemm_route(m, EPI_RESID, d / 16, m->Fp / 32, batch);
+  const MidShape m_o = mid_gemm_route(m, EPI_RESID, d / 16, m->QD / 32, batch), m_down = mid_gemm_route(m, EPI_RESID, d / 16, m->Fp / 32, batch);
   const float qscale = 1.4426950408889634f / sqrtf((float)m->hd);
   for (int l = from_last_qkv ? m->L - 1 : 0; l < m->L; ++l) {
     const LayerW& w = m->layers[l];
@@ -1393,8 +1398,8 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
       p.X = (const u32x4*)m->xo; p.M = batch;
       p.h = m->h; p.gain_next = w.ffn_norm; p.xnext = (uint16_t*)m->xq; p.ssq_out = ssq; p.d = d;
       prof_mark(m, PK_OPROJ, st);
-      launched &= launch_gemm<EPI_RESID>(m, p, s_o, st);
-      n_ssq = resid_entries(s_o);
+      launched &= launch_gemm<EPI_RESID>(m, p, s_o, st, m_o);
+      n_ssq = resid_entries(s_o, m_o);
     }
     {
       GemmP p = {};
@@ -1414,8 +1419,8 @@ int run_decode(www_model* m, const int32_t* tok, const int32_t* lens, const int3
       p.h = m->h; p.gain_next = (l + 1 < m->L) ? m->layers[l + 1].attn_norm : m->final_norm;
       p.xnext = (uint16_t*)m->xq; p.ssq_out = ssq; p.d = d;
       prof_mark(m, PK_DOWN, st);
-      launched &= launch_gemm<EPI_RESID>(m, p, s_down, st);
-      n_ssq = resid_entries(s_down);
+      launched &= launch_gemm<EPI_RESID>(m, p, s_down, st, m_down);
+      n_ssq = resid_entries(s_down, m_down);
     }
   }
   float* lg = logits ? logits : m->logits_buf;

@@ -60,15 +60,15 @@ TRAFFIC = {
     "workload": "8b",
     "fetch_scale": 262144.0 / 131087.1, "write_scale": 1.0,
     "classes": {   # class: (FETCH_SIZE units, WRITE_SIZE units, algorithmic bytes of the measured launches or None = this run's)
-        "decode_attention": (165371.5 + 1578.3, 3108.6 + 1024.0, 80383 * 4160),
-        "qkv_gemm": (32980.4, 9513.0, None),
-        "o_gemm": (25239.6, 10313.0, None),
-        "gate_up_gemm": (118926.5, 3584.0, None),
-        "down_gemm": (76439.9, 10313.0, None),
-        "lm_head_gemm": (529503.9, 32067.8, None),
+        "decode_attention": (165370.9 + 1570.1, 3108.5 + 1024.0, 80383 * 4160),
+        "qkv_gemm": (32977.1, 9513.0, None),
+        "o_gemm": (23116.1, 6282.0, None),
+        "gate_up_gemm": (118936.0, 3584.0, None),
+        "down_gemm": (76433.4, 10313.0, None),
+        "lm_head_gemm": (529444.8, 36547.9, None),
     },
     "sources": tuple("paper_2603_20661_amd/csrc/" + f for f in ("decode.hip", "decode_small.hip", "decode_mid.hip", "decode_gemm.h", "common.h")),
-    "sha256": "b6510288cda3a89cd0057954b20c66964a46d04587333026823ad514a9dbd0eb",
+    "sha256": "2f32a6629cce43a9e11125799e528661ccf973fac8c0f53e330e7675b616c70a",
 }
 
 

@@ -68,7 +68,7 @@ TRAFFIC = {
         "lm_head_gemm": (529444.8, 36547.9, None),
     },
     "sources": tuple("paper_2603_20661_amd/csrc/" + f for f in ("decode.hip", "decode_small.hip", "decode_mid.hip", "decode_gemm.h", "common.h")),
-    "sha256": "2f32a6629cce43a9e11125799e528661ccf973fac8c0f53e330e7675b616c70a",
+    "sha256": "4152e7b584f56bbdbd20b2f63f97935e6d957b07c5e76dc71c3d68256283de76",
 }
 
 

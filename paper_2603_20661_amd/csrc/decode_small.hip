@@ -479,7 +479,9 @@ static float general_us(int NRG, int KB, int M, float wbytes) {
 // 8.0 / 10.0; down 22.4 / 25.8, 24.8 / 26.5, 26.4 / 28.0, 11.1 / 15.5, 14.0 / 17.5; output head 168 / 174 and 172 / 182 (1B: equal);
 // int4, 5 sequences: QKV 10.8 / 13.0, O 6.8 / 10.4, gate/up 18.0 / 24.4, down 13.2 / 17.7, head 56 / 67; the narrow int4 products
 // also from 17 to 32 tokens (steps of up to 6 layers, 17 and 32 sequences: 8B shape 667 / 719 and 736 / 782, 1B shape at 20 and
-// 32 380 / 443 and 412 / 468, 8192 columns and 4 layers 906 / 928 and 966 / 988).  Not the gate/up GEMM
+// 32 380 / 443 and 412 / 468, 8192 columns and 4 layers 906 / 928 and 966 / 988), and their gate/up product where 128 rows a workgroup
+// are one round (24 sequences, 8B shape 27.4 / 29.1; with the other kernel's longer unpacking of then, 2048 columns 11.4 / 13.2, 3072
+// 14.8 / 16.7, 5120 32.9 / 38.8, 1024 8.5 / 8.6).  Not the gate/up GEMM
 // of the other formats, which has rows for every compute unit without a split (39.0 / 37.6, with FP8 24.6 / 21.9; 1B shape with up
 // to 8 tokens 13.4 / 14.6), unless 64 rows per workgroup fill the chip in one round: then up to 8 tokens and, where the other kernel
 // has to split k, from 17 on (1B shape, 32 tokens 15.4 / 16.9; a step of 24 sequences with FP8 weights 880 / 896; of 12 and 16
@@ -507,7 +509,7 @@ static bool small_gemm_takes(const www_model* m, int epi, int NRG, int KB, int M
     return KB <= 48 && (epi == EPI_RESID || (M <= 8 && NRG <= 2 * decode_wg_target()));
   }
   if (epi == EPI_QKV || epi == EPI_RESID) return m->int4_group || s.us <= general_us(NRG, KB, M, m->fp8 ? 1.f : 2.f) + 2.5f;
-  if (M > 16) return epi == EPI_SWIGLU && !m->int4_group && NRG <= 4 * decode_wg_target();
+  if (M > 16) return epi == EPI_SWIGLU && NRG <= (m->int4_group ? 8 : 4) * decode_wg_target();
   if (m->int4_group) return true;
   if (epi == EPI_LOGITS) return (NRG + 7) / 8 > decode_wg_target() || (m->fp8 && M <= 8);
   return M <= 8 && NRG <= 4 * decode_wg_target();
@@ -538,12 +540,13 @@ SmallShape small_gemm_route(const www_model* m, int epi, int NRG, int KB, int M)
 }
 
 // The kernels there are: those that small_gemm_takes and small_gemm_shape lead to (fp16 and FP8 gate/up products take one round of
-// workgroups and not 9 to 16 tokens, output heads of theirs more than one round of row tiles but for FP8 up to 8 tokens).
+// workgroups and not 9 to 16 tokens, int4 ones one round from 17 tokens on, output heads of fp16 and FP8 weights more than one round of
+// row tiles but for FP8 up to 8 tokens).
 static constexpr bool sg_built(int epi, int wmode, int R, int RW, int xf) {
   const bool narrow = epi == EPI_QKV || epi == EPI_RESID;
   if (wmode == WMODE_SPLIT) return R == 2 && (epi == EPI_QKV ? RW == 2 || RW == 4 : RW == 1) && (narrow || xf == 1);
   if (narrow) return RW == 1;
-  if (R != 4 || (xf == 4 && (epi == EPI_LOGITS || wmode == WMODE_INT4))) return false;
+  if (R != 4 || (xf == 4 && epi == EPI_LOGITS)) return false;
   if (epi == EPI_SWIGLU) return wmode == WMODE_INT4 ? RW <= 2 : RW == 1 && xf != 2;
   return wmode == WMODE_INT4 || RW >= 4 || (wmode == WMODE_FP8 && xf == 1);
 }

@@ -47,6 +47,13 @@ def test_full_width_tiles(shape, batch, expected):
     check(run_job(dataclasses.replace(shape, n_layers=1), lens, 2, seed=540 + batch), f"{shape.name} batch {batch}")
 
 
+def test_int4_gate_up_of_two_token_groups():
+    """128 rows a workgroup; the formats above have its 64"""
+    assert route(WIDE8B_Q128, "gate_up", 20)[:4] == ("decode_small", 32, 128, 1)
+    lens = 2 + synth.uniform_i32(20, 9, 20, 20)
+    check(run_job(dataclasses.replace(WIDE8B_Q128, n_layers=1), lens, 2, seed=575), "int4 gate/up, 20 sequences")
+
+
 def test_widest_sums_of_squares():
     """d_model = 8192: 512 entries per token, twice what the kernels request up front"""
     shape = dataclasses.replace(H128, name="small8192", d_model=8192, n_q_heads=2, n_kv_heads=2, ffn_dim=528, vocab=272, seed=520)

@@ -268,17 +268,21 @@ __device__ __forceinline__ float logit_of(uint32_t key) {
   if (key <= 0x00800000u) return -INFINITY;  // (keys of -inf and below)
   return __uint_as_float(key & 0x80000000u ? key & 0x7FFFFFFFu : 0u - key);
 }
+// The least float that is no smaller than n, |n| < 2^30: a score t, a float, has floor(t) >= n exactly where t >= at_least(n).  (Beyond 2^24
+// a whole number need not be a float, and between 2^22 and 2^23 floats are halves: the next float after a bin's own is not its end there.)
+__device__ __forceinline__ float at_least(int n) {
+  const float f = (float)n;
+  return (int)f < n ? __uint_as_float(f > 0.f ? __float_as_uint(f) + 1u : __float_as_uint(f) - 1u) : f;
+}
 // bin_of(x, c) == bin, compared as scores; bottom and top: everything below or above belongs to it too (a NaN does not: it has no mass)
 struct InBin {
   float scale, lo, hi;
   bool open;
   __device__ __forceinline__ InBin(int bin, bool bottom, bool top, float c) {
-    const float at = (float)bin;  // (exact: the bin of a score, which is a float)
     scale = c * (float)(1 << BINS_PER_OCTAVE_LOG2);
-    lo = bottom || bin <= -536870912 ? -INFINITY : at;
+    lo = bottom || bin <= -536870912 ? -INFINITY : at_least(bin);
+    hi = at_least(bin + 1);
     open = top || bin >= 536870912;
-    // the next bin, or where floats are whole numbers the next float
-    hi = fabsf(at) < 8388608.f ? at + 1.f : __uint_as_float(at > 0.f ? __float_as_uint(at) + 1u : __float_as_uint(at) - 1u);
   }
   __device__ __forceinline__ float above() const { return open ? NAN : hi; }  // scores from here on lie above (none, if it is open)
   __device__ __forceinline__ bool operator()(float x) const {

@@ -150,3 +150,46 @@ def test_members_of_the_decisive_bin_in_some_chunks_only(vocab):
     lg[3, :3000] = 0.125
     for u in (0.01, 0.5, 0.999):
         check(lg, 1.0, 0.6, np.full(4, u, np.float32))
+
+
+def scores_in_bins(logit, temperature):
+    """the kernels' scores, in eighths of an octave: fp32, as in sample.hip"""
+    c = np.float32(1.4426950408889634) / np.float32(temperature)
+    return np.float32(logit) * (c * np.float32(8))
+
+
+@pytest.mark.parametrize("vocab", [512, CHUNKS])
+def test_the_bin_where_floats_stop_being_halves(vocab):
+    """scores of -2^23 and half above it share a bin, the one that decides: five members, not nine"""
+    values = np.array([-508772.0, -508772.21875, -508772.25], np.float32)
+    assert scores_in_bins(values[1:], 0.7).tolist() == [-8388607.5, -8388608.0]
+    lg = np.full((4, vocab), -600000.0, np.float32)
+    lg[:, 7] = values[0]
+    lg[:, [9, 100, 300, 400]] = values[1]
+    lg[:2, vocab - 4:] = values[2]
+    lg[2:, [1, 8, 101, vocab - 5]] = values[2]
+    tok = check(lg, 0.7, 0.5295, U)
+    assert set(tok.tolist()) <= {7, 9, 100, 300, 400}
+
+
+@pytest.mark.parametrize("vocab", [8192, CHUNKS])
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_the_lowest_bin_where_no_float_is_its_number(vocab, sign):
+    """Beyond 2^24 the bin 255 below the largest has an odd number.  It holds the last 1300 tokens; 1500 lie in the bin above it, the others higher
+    still.  A token of the lowest bin is 2^-32 of the largest, so that the last 2^-24 of the whole mass are some 250 of them."""
+    line = np.float32(sign * 1.4e6) + np.arange(-600, 600, dtype=np.float32) * np.float32(0.125)
+    t = scores_in_bins(line, 0.7).astype(np.int64)
+    assert (np.abs(t) > 1 << 24).all() and (np.abs(t) < 1 << 25).all() and (t % 2 == 0).all()
+    at = {int(v): x for v, x in zip(t, line)}
+    top = max(v for v in at if v % 4 == 2 and {v - 252, v - 254, v - 256} <= set(at))
+    lg = np.full((1, vocab), at[top - 252], np.float32)
+    lg[0, 1:vocab - 1300:(vocab - 1300) // 1500] = at[top - 254]
+    lg[0, vocab - 1300:] = at[top - 256]
+    lg[0, 0] = at[top]
+    tok, _ = run(lg, 0.7, 1.0, np.array([1.0 - 2.0 ** -24], np.float32))
+    _, e, mask, cum, target = S.sample(lg[0], float(np.float32(0.7)), 1.0, 1.0 - 2.0 ** -24)
+    # masses are whole multiples of 2^-44 of up to twice the largest, each off by up to one of its 2048 at least and, as derived above, by
+    # 32 * 1.3e-7: 5e-4 of what follows the largest
+    rest = cum[-1] - cum[0]
+    assert mask.all() and cum[tok[0] - 1] - 5e-4 * rest <= target <= cum[tok[0]] + 5e-4 * rest
+    assert tok[0] >= vocab - 300

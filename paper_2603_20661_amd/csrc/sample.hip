@@ -62,8 +62,11 @@ constexpr int H_RUNS = H_BINS + 2 * BINS;
 constexpr int RESERVED = 4096;
 __device__ __host__ constexpr int head_of(int runs) { return H_RUNS + 2 * runs; }
 __device__ __host__ constexpr int cand_max(int runs) { return (RESERVED - head_of(runs)) / 2; }
-constexpr int ROW_CAND = 4096;       // candidates of a row that are looked at in LDS (two workgroups to a compute unit), and of a row of more than 2^19
-constexpr int LONG_ROW_CAND = 9216;  // tokens (2 097 152 normal logits of standard deviation 3, top_p 0.9: 5150, and 947 us where they do not fit, 81 where they do)
+// Candidates of a row that are looked at in LDS, two workgroups to a compute unit.  With more the chunks' lists are read, once per round (128 256
+// normal logits of standard deviation 0.4 to 1, top_p 0.8 and 0.9: 4000 to 9000; 1, 16 and 64 rows 30 to 35, 31 to 39 and 54 to 66 us, where a list
+// of 8192 in LDS took 70 to 90 and the row itself 123 to 175).  A list of 9216 is slower where it is needed: 2 000 000 tokens of standard deviation 3,
+// 5000 candidates, 1 and 4 rows 73.7 and 86.9, the chunks' lists 58.5 and 65.8.
+constexpr int ROW_CAND = 4096;
 
 typedef unsigned long long u64;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -280,7 +283,7 @@ struct InBin {
   bool open;
   __device__ __forceinline__ InBin(int bin, bool bottom, bool top, float c) {
     scale = c * (float)(1 << BINS_PER_OCTAVE_LOG2);
-    lo = bottom || bin <= -536870912 ? -INFINITY : at_least(bin);
+    lo = bottom || bin <= -536870912 ? -INFINITY : (float)bin;  // (any but the lowest is the bin of a score, which is a float)
     hi = at_least(bin + 1);
     open = top || bin >= 536870912;
   }
@@ -614,15 +617,14 @@ struct DrawLds {
   double need;
   int reached[2 * WAVES];
   uint32_t klo, khi;
-  int bin, count, overflow, last;
-  // behind it the lists, of as many entries as the host chose: masses (or copies of bins), keys, runs of the candidates, counted through the row
-  __device__ __forceinline__ u64* mass() { return reinterpret_cast<u64*>(this + 1); }
-  __device__ __forceinline__ uint32_t* keys(int most) { return reinterpret_cast<uint32_t*>(mass() + most); }
-  __device__ __forceinline__ uint16_t* run(int most) { return reinterpret_cast<uint16_t*>(keys(most) + most); }
+  int bin, count, where, last;
+  // candidates: masses (or copies of bins), keys, and the runs they lie in, counted through the row
+  u64 mass[ROW_CAND];
+  uint32_t keys[ROW_CAND];
+  uint16_t run[ROW_CAND];
 };
-constexpr size_t draw_lds(int most) { return sizeof(DrawLds) + (size_t)most * 14; }
-static_assert(2 * draw_lds(ROW_CAND) <= 160 * 1024 && draw_lds(LONG_ROW_CAND) <= 160 * 1024, "two workgroups to a compute unit, and one");
-static_assert(ROW_CAND >= BINS * COPIES, "what shares the lists' space");
+static_assert(2 * sizeof(DrawLds) <= 160 * 1024, "two workgroups to a compute unit");
+static_assert(ROW_CAND >= BINS * COPIES, "what shares the masses' space");
 
 // The elements of a chunk in runs of `length` (a multiple of 256), `per_chunk` of them, of which a row has at most MAX_RUNS: masses by run lead to the token
 // without another look at a chunk
@@ -646,8 +648,10 @@ struct Refs {
   }
 };
 
-// Where the lists do not do (a row that is flat to within a tenth of an octave), the row itself is read: by one wavefront per chunk, or
-// several where there are fewer chunks (512 rows of 32 000 near-equal tokens: 163 us)
+// Where the row's list in LDS does not do.  LISTS: the chunks' lists hold all members of bin b, too many of them together (128 256 normal logits
+// of a standard deviation up to 1: 4000 to 8000).  ROW: one of them does not (a row that is flat to within a tenth of an octave), and the row
+// itself is read: by one wavefront per chunk, or several where there are fewer chunks (512 rows of 32 000 near-equal tokens: 163 us)
+enum { IN_LDS = 0, LISTS = 1, ROW = 2 };
 struct RowReader {
   const float *lg_row, *row;
   int V, chunk, n_chunks;
@@ -658,6 +662,30 @@ struct RowReader {
     int t = 1;
     while (2 * t * n_chunks <= WAVES) t *= 2;
     return t;
+  }
+  // use(key, mass, place) of every entry of the chunks' lists, four a lane on their way
+  template <bool PLACES, typename U>
+  __device__ __forceinline__ void listed(const DrawLds& S, int list0, U&& use) const {
+    constexpr int F = 4;
+    const int t = team(), lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (int k = wave / t; k < n_chunks; k += WAVES / t) {
+      const float* list = row + (int64_t)k * chunk + list0;
+      const int cnt = S.chunk_at[k + 1] - S.chunk_at[k];
+      const Ref R = refs[k];
+#pragma unroll 1
+      for (int i0 = wave % t * (64 * F) + lane; i0 - lane < cnt; i0 += 64 * F * t) {
+        float v[F], at[F];
+#pragma unroll
+        for (int u = 0; u < F; ++u) {
+          const int i = min(i0 + 64 * u, cnt - 1);
+          v[u] = handed_on(list + 2 * i);
+          if constexpr (PLACES) at[u] = handed_on(list + 2 * i + 1);
+        }
+#pragma unroll
+        for (int u = 0; u < F; ++u)
+          if (i0 + 64 * u < cnt) use(key_of(v[u]), [&] { return shifted(mass_of(prob(v[u], c, R.m, R.r), unit), R.back); }, k, PLACES ? __float_as_int(at[u]) : 0);
+      }
+    }
   }
   // use(key, mass) of every member of bin b in chunk k, and done(i) behind every 256 elements from i on (one wavefront's)
   template <typename U, typename D>
@@ -678,15 +706,24 @@ struct RowReader {
       done(i);
     }
   }
-  // the keys of the bin are binned again, 256 linear bins at a time, until one is left; three or four passes over the row
-  __device__ __forceinline__ uint32_t tau(DrawLds& S, double need, uint32_t klo, uint32_t khi) const {
+  // the keys of the bin are binned again, 256 linear bins at a time, until one is left; three or four passes
+  __device__ __forceinline__ uint32_t tau(DrawLds& S, int where, int list0, double need, uint32_t klo, uint32_t khi) const {
     const int t = team();
     auto all = [&](auto&& use) __attribute__((always_inline)) {
-      for (int k = (threadIdx.x >> 6) / t; k < n_chunks; k += WAVES / t) members(k, t, use, [](int) {});
+      if (where == LISTS)
+        listed<false>(S, list0, [&](uint32_t key, auto&& mass, int, int) __attribute__((always_inline)) { use(key, mass); });
+      else
+        for (int k = (threadIdx.x >> 6) / t; k < n_chunks; k += WAVES / t) members(k, t, use, [](int) {});
     };
-    return search_keys(all, klo, khi, 0.f, need, S.mass(), S.hist, &S.bin, &S.need);  // (copies of the bins in the space of the lists)
+    return search_keys(all, klo, khi, 0.f, need, S.mass, S.hist, &S.bin, &S.need);  // (copies of the bins in the space of the masses)
   }
-  __device__ __forceinline__ void add_masses(DrawLds& S, uint32_t tau, RowRuns runs) const {  // of the bin's members that are in, to their runs
+  __device__ __forceinline__ void add_masses(DrawLds& S, int where, int list0, uint32_t tau, RowRuns runs) const {  // of the bin's members that are in, to their runs
+    if (where == LISTS) {
+      listed<true>(S, list0, [&](uint32_t key, auto&& mass, int k, int place) __attribute__((always_inline)) {
+        if (key >= tau) atomicAdd(&S.runs[k * runs.per_chunk + place / runs.length], mass());
+      });
+      return;
+    }
     const int t = team();
     for (int k = (threadIdx.x >> 6) / t; k < n_chunks; k += WAVES / t) {
       u64 q = 0;
@@ -700,15 +737,12 @@ struct RowReader {
 };
 
 // The workgroup of a row that finishes last: tau, the token, and the probabilities that the chunks' headers and lists stood in the way of.
-struct RowEnd { const float* u01; float* row; int32_t* tokens; float m; RowRuns runs; int row_cand; };
+struct RowEnd { const float* u01; float* row; int32_t* tokens; float m; RowRuns runs; };
 __device__ __forceinline__ void end_of_row(const RowReader& reader, const RowEnd& end, DrawLds& S) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n_chunks = reader.n_chunks, chunk = reader.chunk, V = reader.V;
   const int per_chunk = end.runs.per_chunk, n_runs = n_chunks * per_chunk, list0 = head_of(per_chunk), most = cand_max(per_chunk);
   const float *lg_row = reader.lg_row, c = reader.c, unit = reader.unit, m = end.m;
   float* const row = end.row;
-  u64* const mass_of_cand = S.mass();
-  uint32_t* const key_of_cand = S.keys(end.row_cand);
-  uint16_t* const run_of_cand = S.run(end.row_cand);
   // a thread looks after a run of the row
   const int run_chunk = min(tid / per_chunk, n_chunks - 1);
   u64 run_mass = 0;
@@ -726,17 +760,17 @@ __device__ __forceinline__ void end_of_row(const RowReader& reader, const RowEnd
       khi = __float_as_uint(handed_on(reg + H_KHI));
     }
     const uint32_t upto = wave_scan(mine);
-    const bool over = __any(mine > (uint32_t)most) || lane_of(upto, 63) > (uint32_t)end.row_cand;
+    const int where = __any(mine > (uint32_t)most) ? ROW : lane_of(upto, 63) > ROW_CAND ? LISTS : IN_LDS;
     S.chunk_at[lane + 1] = (int)upto;
     wave_range(klo, khi);
-    if (lane == 0) { S.chunk_at[0] = 0; S.overflow = over; S.klo = klo; S.khi = khi; }
+    if (lane == 0) { S.chunk_at[0] = 0; S.where = where; S.klo = klo; S.khi = khi; }
   }
   const float u = *end.u01;
   S.runs[tid] = shifted(run_mass, __shfl(reader.refs.lane.back, run_chunk));
   __syncthreads();
   const uint32_t klo = S.klo, khi = S.khi;
-  const bool listed = !S.overflow;
-  if (listed) {  // a wavefront looks after chunk number `wave` and every sixteenth from there
+  const int where = S.where;
+  if (__builtin_expect(where == IN_LDS, 1)) {  // a wavefront looks after chunk number `wave` and every sixteenth from there
 #pragma unroll 1
     for (int k = wave; k < n_chunks; k += WAVES) {
       const int at = S.chunk_at[k], cnt = S.chunk_at[k + 1] - at;
@@ -745,23 +779,23 @@ __device__ __forceinline__ void end_of_row(const RowReader& reader, const RowEnd
 #pragma unroll 1
       for (int i = lane; i < cnt; i += 64) {
         const float v = handed_on(reg + 2 * i);
-        run_of_cand[at + i] = (uint16_t)(k * per_chunk + __float_as_int(handed_on(reg + 2 * i + 1)) / end.runs.length);
-        key_of_cand[at + i] = key_of(v);
-        mass_of_cand[at + i] = shifted(mass_of(prob(v, c, R.m, R.r), unit), R.back);
+        S.run[at + i] = (uint16_t)(k * per_chunk + __float_as_int(handed_on(reg + 2 * i + 1)) / end.runs.length);
+        S.keys[at + i] = key_of(v);
+        S.mass[at + i] = shifted(mass_of(prob(v, c, R.m, R.r), unit), R.back);
       }
     }
   }
   __syncthreads();
   uint32_t tau;
-  if (listed) {
+  if (__builtin_expect(where == IN_LDS, 1)) {
     const int n = S.chunk_at[n_chunks];
-    tau = n ? find_tau(key_of_cand, mass_of_cand, n, S.need, klo, khi == 0xFFFFFFFFu ? khi : khi + 1u, S.reached) : 0u;
+    tau = n ? find_tau(S.keys, S.mass, n, S.need, klo, khi == 0xFFFFFFFFu ? khi : khi + 1u, S.reached) : 0u;
 #pragma unroll 1
     for (int i = tid; i < n; i += TPB)
-      if (key_of_cand[i] >= tau) atomicAdd(&S.runs[run_of_cand[i]], mass_of_cand[i]);
+      if (S.keys[i] >= tau) atomicAdd(&S.runs[S.run[i]], S.mass[i]);
   } else {
-    tau = reader.tau(S, S.need, klo, khi);
-    reader.add_masses(S, tau, end.runs);
+    tau = reader.tau(S, where, list0, S.need, klo, khi);
+    reader.add_masses(S, where, list0, tau, end.runs);
   }
   __syncthreads();
   // the run, in units of the row's reference; it is the owner of this thread's or of no thread (a row without any finite logit)
@@ -811,7 +845,7 @@ __device__ __forceinline__ void end_of_row(const RowReader& reader, const RowEnd
 
 template <int PER>
 __global__ __launch_bounds__(TPB, 8) void sample_draw_kernel(const float* __restrict__ logits, int V, int chunk, int n_chunks, float c, float unit, float top_p,
-                                                          const float* __restrict__ u01, float* scratch, int32_t* __restrict__ tokens, int row_cand) {
+                                                          const float* __restrict__ u01, float* scratch, int32_t* __restrict__ tokens) {
   extern __shared__ __align__(16) char smem[];
   DrawLds& S = *reinterpret_cast<DrawLds*>(smem);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), own = blockIdx.y;
@@ -911,7 +945,7 @@ __global__ __launch_bounds__(TPB, 8) void sample_draw_kernel(const float* __rest
   __syncthreads();
   if (!S.last) return;
   const RowReader reader{lg_row, row, V, chunk, n_chunks, c, unit, top, b, refs};
-  const RowEnd end{u01 + blockIdx.x, row, tokens + blockIdx.x, m, runs, row_cand};
+  const RowEnd end{u01 + blockIdx.x, row, tokens + blockIdx.x, m, runs};
   end_of_row(reader, end, S);
 }
 
@@ -942,8 +976,8 @@ int allow_lds() {
   if (g_lds_allowed[dev]) return WWW_OK;
   auto allow = [](const void* kernel, size_t bytes) { return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes); };
   hipError_t e = allow(reinterpret_cast<const void*>(&sample_row_kernel<2, 2>), sizeof(SmallLds));
-  if (e == hipSuccess) e = allow(reinterpret_cast<const void*>(&sample_draw_kernel<2>), draw_lds(LONG_ROW_CAND));
-  if (e == hipSuccess) e = allow(reinterpret_cast<const void*>(&sample_draw_kernel<4>), draw_lds(LONG_ROW_CAND));
+  if (e == hipSuccess) e = allow(reinterpret_cast<const void*>(&sample_draw_kernel<2>), sizeof(DrawLds));
+  if (e == hipSuccess) e = allow(reinterpret_cast<const void*>(&sample_draw_kernel<4>), sizeof(DrawLds));
   if (e != hipSuccess) { set_error("hipFuncSetAttribute failed: %s", hipGetErrorString(e)); return WWW_E_HIP; }
   g_lds_allowed[dev] = true;
   return WWW_OK;
@@ -985,8 +1019,7 @@ WWW_EXPORT int www_sample_top_p(const float* logits_dev, int32_t batch, int32_t 
     auto bins = chunk > 8192 ? sample_bins_kernel<4> : sample_bins_kernel<2>;
     auto draw = chunk > 8192 ? sample_draw_kernel<4> : sample_draw_kernel<2>;
     hipLaunchKernelGGL(bins, grid, dim3(TPB), 0, st, logits_dev, vocab, chunk, c, unit, scratch_dev);
-    const int row_cand = vocab > 1 << 19 ? LONG_ROW_CAND : ROW_CAND;
-    hipLaunchKernelGGL(draw, grid, dim3(TPB), draw_lds(row_cand), st, logits_dev, vocab, chunk, n_chunks, c, unit, top_p, u01_dev, scratch_dev, tokens_dev, row_cand);
+    hipLaunchKernelGGL(draw, grid, dim3(TPB), sizeof(DrawLds), st, logits_dev, vocab, chunk, n_chunks, c, unit, top_p, u01_dev, scratch_dev, tokens_dev);
   }
   const hipError_t err = hipGetLastError();
   if (err != hipSuccess) { set_error("sampling kernel launch failed: %s", hipGetErrorString(err)); return WWW_E_HIP; }

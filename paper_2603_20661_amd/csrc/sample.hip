@@ -419,11 +419,12 @@ __device__ __forceinline__ void list_members(f32x4 (&x)[N], const InBin& in_bin,
 }
 
 // ---- rows of up to 16 N * TPB bytes: one workgroup per row, everything in registers and LDS
-constexpr int LIST = 8192;  // candidates looked at in LDS
+constexpr int LIST = 4 * ROW_PER * TPB;  // candidates looked at in LDS, where all of a row may be some (one workgroup to a compute unit)
+template <int CP>
 struct SmallLds {
   uint32_t keys[LIST];
   u64 mass[LIST];
-  u64 copies[BINS * COPIES];
+  u64 copies[BINS * CP];
   u64 hist[BINS];
   u64 part[ROW_PER * WAVES];
   double need;
@@ -433,27 +434,13 @@ struct SmallLds {
   int bin, count;
 };
 
-// more members of the decisive bin than the lists hold: the row is read again, once per round
-__device__ __forceinline__ uint32_t tau_of_row(const float* lg, int V, float c, float m, float unit, int top, SmallLds& S, uint32_t klo, uint32_t khi) {
-  const int b = S.bin;
-  auto members = [&](auto&& use) __attribute__((always_inline)) {
-#pragma unroll 1
-    for (int i = threadIdx.x * 4; i < V; i += 4 * TPB) {
-      const f32x4 v = load4(lg, i, V);
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (i + e < V && bin_number(top, bin_of(v[e], c)) == b) use(key_of(v[e]), [&] { return mass_of(prob(v[e], c, m, 0.f), unit); });
-    }
-  };
-  return search_keys(members, klo, khi, 0.f, S.need, S.copies, S.hist, &S.bin, &S.need);
-}
-
 // CP: sets of bins, so that the lanes of a wavefront seldom meet in one (clearing and adding them up costs short rows more than it gives)
 template <int N, int CP>
-__global__ __launch_bounds__(TPB, 8) void sample_row_kernel(const float* logits, int V, float c, float unit, float top_p, const float* __restrict__ u01,
+__global__ __launch_bounds__(TPB) void sample_row_kernel(const float* logits, int V, float c, float unit, float top_p, const float* __restrict__ u01,
                                                          float* scratch, int32_t* __restrict__ tokens) {
   extern __shared__ __align__(16) char smem[];
-  SmallLds& S = *reinterpret_cast<SmallLds*>(smem);
+  static_assert(4 * N * TPB <= LIST);
+  SmallLds<CP>& S = *reinterpret_cast<SmallLds<CP>*>(smem);
   const int tid = threadIdx.x, row = blockIdx.x;
   const bool in_place = scratch == logits;  // the probabilities then wait until the logits have been read for the last time
   const float* lg = logits + (int64_t)row * V;
@@ -485,18 +472,13 @@ __global__ __launch_bounds__(TPB, 8) void sample_row_kernel(const float* logits,
   __syncthreads();
   const InBin in_bin(top - S.bin, S.bin == BINS - 1, S.bin == 0, c);
   list_members(x, in_bin, V, &S.count, &S.klo, &S.khi, [&](int at, float v, int) __attribute__((always_inline)) {
-    if (at < LIST) {
-      S.keys[at] = key_of(v);
-      S.mass[at] = mass_of(prob(v, c, m, 0.f), unit);
-    }
+    S.keys[at] = key_of(v);
+    S.mass[at] = mass_of(prob(v, c, m, 0.f), unit);
   });
   __syncthreads();
   const uint32_t klo = S.klo, khi = S.khi;
   uint32_t tau = 0u;
-  if (S.count > LIST)  // (a row that is flat to within a tenth of an octave)
-    tau = tau_of_row(lg, V, c, m, unit, top, S, klo, khi);
-  else if (S.count)
-    tau = find_tau(S.keys, S.mass, S.count, S.need, klo, khi == 0xFFFFFFFFu ? khi : khi + 1u, S.reached);
+  if (S.count) tau = find_tau(S.keys, S.mass, S.count, S.need, klo, khi == 0xFFFFFFFFu ? khi : khi + 1u, S.reached);
   const Masses mass{c, m, 0.f, unit, logit_of(tau)};
   member_masses(x, mass, S.part);
   __syncthreads();
@@ -975,7 +957,7 @@ int allow_lds() {
   std::lock_guard<std::mutex> lock(g_device_mutex);
   if (g_lds_allowed[dev]) return WWW_OK;
   auto allow = [](const void* kernel, size_t bytes) { return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes); };
-  hipError_t e = allow(reinterpret_cast<const void*>(&sample_row_kernel<2, 2>), sizeof(SmallLds));
+  hipError_t e = allow(reinterpret_cast<const void*>(&sample_row_kernel<2, 2>), sizeof(SmallLds<2>));
   if (e == hipSuccess) e = allow(reinterpret_cast<const void*>(&sample_draw_kernel<2>), sizeof(DrawLds));
   if (e == hipSuccess) e = allow(reinterpret_cast<const void*>(&sample_draw_kernel<4>), sizeof(DrawLds));
   if (e != hipSuccess) { set_error("hipFuncSetAttribute failed: %s", hipGetErrorString(e)); return WWW_E_HIP; }
@@ -1005,7 +987,7 @@ WWW_EXPORT int www_sample_top_p(const float* logits_dev, int32_t batch, int32_t 
   const float unit = mass_unit(vocab);
   if (int rc = allow_lds()) return rc;
   if (vocab <= 8 * TPB) {
-    hipLaunchKernelGGL((sample_row_kernel<2, 2>), dim3(batch), dim3(TPB), sizeof(SmallLds), st, logits_dev, vocab, c, unit, top_p, u01_dev, scratch_dev, tokens_dev);
+    hipLaunchKernelGGL((sample_row_kernel<2, 2>), dim3(batch), dim3(TPB), sizeof(SmallLds<2>), st, logits_dev, vocab, c, unit, top_p, u01_dev, scratch_dev, tokens_dev);
   } else if (scratch_dev == logits_dev) {
     hipLaunchKernelGGL(sample_in_place_kernel, dim3(batch), dim3(TPB), 0, st, scratch_dev, vocab, c, unit, top_p, u01_dev, tokens_dev);
   } else {

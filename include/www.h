@@ -194,8 +194,8 @@ int www_debug_prefill_tile(int32_t workgroup, int32_t token_tiles, int32_t row_t
 /* Test hook, host only: which kernel and tile one GEMM of a call takes on a model of this configuration, by the library's own
  * rules.  total_q_tokens > 0: a www_prefill call; 0: a decode step of `batch` sequences.  gemm: 0 QKV, 1 O, 2 gate/up, 3 down,
  * 4 output head (decode only).  route_out[5] (host): kernel (0 and 1 decode, 2 and 3 prefill: the general one and the one for
- * small calls), tokens and rows of the matrix per workgroup, splits of the k range, and 1 if the call's last positions run as
- * rows of the prefill GEMMs.  Without a GPU the rules assume 256 compute units.  Errors: INVALID_ARG, ABI_MISMATCH, BAD_CONFIG,
+ * small calls; 4 decode, O and down products of 33 to 64 sequences), tokens and rows of the matrix per workgroup, splits of the
+ * k range, and 1 if the call's last positions run as rows of the prefill GEMMs.  Without a GPU the rules assume 256 compute units.  Errors: INVALID_ARG, ABI_MISMATCH, BAD_CONFIG,
  * CAPACITY, HIP (the rules lead to a kernel that does not exist). */
 int www_debug_route(const www_config* cfg, int32_t total_q_tokens, int32_t batch, int32_t gemm, int32_t* route_out);
 

@@ -219,7 +219,7 @@ def www_debug_prefill_tile(workgroup: int, token_tiles: int, row_tiles: int):
 
 
 GEMMS = ("qkv", "o", "gate_up", "down", "lm_head")
-ROUTE_KERNELS = ("decode", "decode_small", "prefill", "prefill_small")
+ROUTE_KERNELS = ("decode", "decode_small", "prefill", "prefill_small", "decode_mid")
 
 
 def www_debug_route(cfg: WwwConfig, gemm: str, batch: int, total_q_tokens: int = 0):

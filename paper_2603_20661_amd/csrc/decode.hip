@@ -1268,8 +1268,8 @@ static bool launch_gemm(www_model* m, GemmP& p, const SmallShape& small, hipStre
   return launched;
 }
 
-// Kernel (0: skinny_gemm_kernel, with 32 or 64 rows mid_gemm_kernel, 1: small_gemm_kernel), tokens and rows per workgroup and k splits of GEMM `which` (0 QKV, 1 O,
-// 2 gate/up, 3 down, 4 output head) of a decode step; false: there is no such kernel
+// Kernel (0: skinny_gemm_kernel, 1: small_gemm_kernel, 4: mid_gemm_kernel), tokens and rows per workgroup and k splits of GEMM `which`
+// (0 QKV, 1 O, 2 gate/up, 3 down, 4 output head) of a decode step; false: there is no such kernel
 bool decode_route(const www_model* m, int which, int batch, int32_t out[4]) {
   const int epi[5] = {EPI_QKV, EPI_RESID, EPI_SWIGLU, EPI_RESID, EPI_LOGITS};
   const int NRG = (which == 0 ? m->QKVN : which == 2 ? 2 * m->F : which == 4 ? m->V : m->d) / 16;
@@ -1278,8 +1278,8 @@ bool decode_route(const www_model* m, int which, int batch, int32_t out[4]) {
     out[0] = 1; out[1] = s.xf == 1 ? 8 : s.xf == 2 ? 16 : 32; out[2] = 16 * s.R * s.RW; out[3] = s.ks;
     return small_gemm_built(m, epi[which], s);
   } else if (const MidShape g = mid_gemm_route(m, epi[which], NRG, KB, batch); g.R) {
-    out[0] = 0; out[1] = 64; out[2] = 16 * g.R; out[3] = g.ks;
-    return g.R == 2 || g.R == 4;
+    out[0] = 4; out[1] = 64; out[2] = 16 * g.R; out[3] = g.ks;
+    return mid_gemm_built(m, g);
   } else {
     const SkinnyShape k = skinny_shape(m, epi[which], NRG, KB, batch);
     out[0] = 0; out[1] = 16 * k.mtk; out[2] = GEMM_TILE_ROWS; out[3] = k.ksplit;

@@ -115,4 +115,5 @@ bool launch_small_gemm(www_model* m, GemmP& p, const SmallShape& s, hipStream_t 
 // decode_mid.hip: residual GEMMs of a step of 33 to 64 tokens; 16 R rows a workgroup, k splits, k blocks of one.  R = 0: skinny_gemm_kernel
 struct MidShape { int R, ks, per; };
 MidShape mid_gemm_route(const www_model* m, int epi, int NRG, int KB, int M);
+bool mid_gemm_built(const www_model* m, const MidShape& s);
 bool launch_mid_gemm(www_model* m, GemmP& p, const MidShape& s, hipStream_t st);  // false: the shape has no kernel, nothing was launched

@@ -34,7 +34,7 @@ __global__ __launch_bounds__(64 * MG_NW, 2) void mid_gemm_kernel(const GemmP p) 
   // what this wavefront finishes: row group fr of the tile, token groups tbase, tbase + TSTEP ..
   constexpr int TSTEP = MG_NW / R, NT = TB / TSTEP;
   const int tsub = lane & 15, rsub = (lane >> 4) * 4, fr = wave % R, tbase = wave / R;
-  const int frg = rg0 + fr, frgc = min(frg, p.NRG - 1), n0 = frgc * 16 + rsub;
+  const int frg = rg0 + fr, n0 = frg * 16 + rsub;  // (p.NRG is a multiple of R)
 
   struct WSet { u32x4 w[R]; } ws[D];
   struct XSet { u32x4 x[TB][2]; } xs[D];
@@ -45,14 +45,11 @@ __global__ __launch_bounds__(64 * MG_NW, 2) void mid_gemm_kernel(const GemmP p) 
     const int g = min(tb, (p.M - 1) / 16);
     xo[tb] = g * 128 + (lane & 48) + min(tsub, p.M - 1 - g * 16);
   }
-  int rgc[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) rgc[r] = min(rg0 + r, p.NRG - 1);
   // (loads past the end of the k range are redirected to its last valid block, their products are skipped)
   auto load_w = [&](WSet& s, int i) __attribute__((always_inline)) {
     const int c = min(kb_begin / KC + wave + MG_NW * i, last / KC);  // (kb_begin is a multiple of 4)
 #pragma unroll
-    for (int r = 0; r < R; ++r) s.w[r] = p.W[((int64_t)c * p.NRG + rgc[r]) * 64 + lane];
+    for (int r = 0; r < R; ++r) s.w[r] = p.W[((int64_t)c * p.NRG + rg0 + r) * 64 + lane];
   };
   auto load_x = [&](XSet& s, int i, int j) __attribute__((always_inline)) {  // k block j of the wavefront's chunk i
     const u32x4* x = p.X + (int64_t)min(kb_begin + (wave + MG_NW * i) * KC + j, last) * (TB * 128);
@@ -131,11 +128,9 @@ __global__ __launch_bounds__(64 * MG_NW, 2) void mid_gemm_kernel(const GemmP p) 
   }
   // parked as [split][row group][tb][lane]; the workgroup of the tile that comes last adds the splits in order
   const __amdgpu_buffer_rsrc_t prs = shared_rsrc(p.partial);
-  auto unit = [&](int sp, int tb) __attribute__((always_inline)) { return (uint32_t)(((sp * p.NRG + frgc) * TB + tb) * 64 + lane) * 16u; };
-  if (frg < p.NRG) {
+  auto unit = [&](int sp, int tb) __attribute__((always_inline)) { return (uint32_t)(((sp * p.NRG + frg) * TB + tb) * 64 + lane) * 16u; };
 #pragma unroll
-    for (int q = 0; q < NT; ++q) store_shared_f32x4(prs, unit(split, tbase + q * TSTEP), v[q]);
-  }
+  for (int q = 0; q < NT; ++q) store_shared_f32x4(prs, unit(split, tbase + q * TSTEP), v[q]);
   wait_own_memory_ops();
   __syncthreads();
   if (tid == 0) s_last = arrive_last(&p.counters[tile], p.ksplit, p.fence_handover, p.fault_flag);
@@ -175,12 +170,12 @@ __global__ __launch_bounds__(64 * MG_NW, 2) void mid_gemm_kernel(const GemmP p) 
     }
     s += __shfl_xor(s, 16);
     s += __shfl_xor(s, 32);
-    if (t < p.M && frg < p.NRG) {
+    if (t < p.M) {
       *reinterpret_cast<f32x4*>(p.h + (int64_t)t * p.d + n0) = hn;
       *reinterpret_cast<u32x2*>(p.xnext + packed_x_offset(n0, t, TB, 0)) = hi.v;
       *reinterpret_cast<u32x2*>(p.xnext + packed_x_offset(n0, t, TB, 1)) = lo.v;
     }
-    if (lane < 16) s_sq[fr][(tbase + q * TSTEP) * 16 + lane] = frg < p.NRG ? s : 0.f;
+    if (lane < 16) s_sq[fr][(tbase + q * TSTEP) * 16 + lane] = s;
   }
   __syncthreads();
   if (tid < p.M) {  // one entry per token and tile, its row groups added in order
@@ -193,6 +188,11 @@ __global__ __launch_bounds__(64 * MG_NW, 2) void mid_gemm_kernel(const GemmP p) 
 
 // ------------------------------------------------------------------------------------------------
 // Host side
+// the kernels there are
+static constexpr bool mg_built(int wmode, int R) { return (R == 2 && (wmode == WMODE_F16 || wmode == WMODE_FP8)) || (R == 4 && wmode == WMODE_F16); }
+static int mg_wmode(const www_model* m) { return m->wsplit ? WMODE_SPLIT : m->int4_group ? WMODE_INT4 : m->fp8 ? WMODE_FP8 : WMODE_F16; }
+bool mid_gemm_built(const www_model* m, const MidShape& s) { return mg_built(mg_wmode(m), s.R); }
+
 static int mid_rows(int NRG) { return NRG > 128 ? 4 : 2; }  // a tile's sums of squares: SSQ_TILES entries up to 4096 columns
 static int mid_splits(int tiles) { return tiles ? min(8, decode_wg_target() / tiles) : 0; }
 
@@ -205,15 +205,22 @@ uint64_t mid_gemm_partial_bytes(int NRG) {
 // 64 tokens, us: 64 blocks 24.0 -> 22.8, 88 28.2 -> 27.7, 112 33 -> 35), and eight wavefronts with a chunk each at least.
 MidShape mid_gemm_route(const www_model* m, int epi, int NRG, int KB, int M) {
   MidShape s = {0, 0, 0};
-  if (epi != EPI_RESID || M <= 32 || M > 64 || m->wsplit || m->int4_group) return s;
-  const int R = mid_rows(NRG), tiles = (NRG + R - 1) / R, chunk = MG_NW * mg_kc(m->fp8 ? WMODE_FP8 : WMODE_F16);
+  const int R = mid_rows(NRG), tiles = NRG / R, chunk = MG_NW * mg_kc(mg_wmode(m));
+  if (epi != EPI_RESID || M <= 32 || M > 64 || NRG % R || !mg_built(mg_wmode(m), R)) return s;
   const int ks = min(mid_splits(tiles), KB / chunk), per = ks > 1 ? ((KB + ks - 1) / ks + 3) / 4 * 4 : 0;
-  if (tiles > SSQ_TILES || (m->fp8 && R > 2) || ks < 2 || per > 96) return s;
+  if (tiles > SSQ_TILES || ks < 2 || per > 96) return s;
   s = {R, (KB + per - 1) / per, per};
   return s;
 }
 
+template <int WMODE, int R>
+static bool launch_mid_as(const GemmP& p, hipStream_t st) {
+  if constexpr (mg_built(WMODE, R))
+    hipLaunchKernelGGL((mid_gemm_kernel<WMODE, R>), dim3(8 * ((p.row_tiles + 7) / 8) * p.ksplit), dim3(64 * MG_NW), 0, st, p);
+  return mg_built(WMODE, R);
+}
 bool launch_mid_gemm(www_model* m, GemmP& p, const MidShape& s, hipStream_t st) {
+  if (!mid_gemm_built(m, s) || p.NRG % s.R) return false;
   p.ksplit = s.ks;
   p.kb_per_split = s.per;
   p.partial = m->partial;
@@ -221,12 +228,7 @@ bool launch_mid_gemm(www_model* m, GemmP& p, const MidShape& s, hipStream_t st) 
   p.fault_flag = m->fault_dev;
   p.fence_handover = m->handover_fence;
   if (p.wfactor == 0.f) p.wfactor = 1.f;  // not set: an unscaled matrix
-  p.row_tiles = (p.NRG + s.R - 1) / s.R;
-  const dim3 grid(8 * ((p.row_tiles + 7) / 8) * p.ksplit), block(64 * MG_NW);
-#define MID(WM_, R_) hipLaunchKernelGGL((mid_gemm_kernel<WM_, R_>), grid, block, 0, st, p)
-  if (s.R == 4 && !m->fp8) MID(WMODE_F16, 4);
-  else if (s.R == 2) { if (m->fp8) MID(WMODE_FP8, 2); else MID(WMODE_F16, 2); }
-  else return false;
-#undef MID
-  return true;
+  p.row_tiles = p.NRG / s.R;
+  if (m->fp8) return s.R == 2 ? launch_mid_as<WMODE_FP8, 2>(p, st) : launch_mid_as<WMODE_FP8, 4>(p, st);
+  return s.R == 2 ? launch_mid_as<WMODE_F16, 2>(p, st) : launch_mid_as<WMODE_F16, 4>(p, st);
 }

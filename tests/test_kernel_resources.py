@@ -78,3 +78,20 @@ def test_every_route_has_a_kernel_and_every_small_decode_kernel_a_route():
                         reached.add((wm, epi[gemm], r, groups // r, {8: 1, 16: 2, 32: 4}[tokens]))
     built = {tuple(map(int, m.groups())) for m in (re.match(r"_Z17small_gemm_kernelILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)E", k) for k in _kernels()) if m}
     assert reached == built, (sorted(reached - built), sorted(built - reached))
+
+
+def test_every_decode_kernel_of_33_to_64_sequences_has_a_route():
+    """and is named by the route hook; their rows fill whole workgroups"""
+    wmode = {synth.WDTYPE_F32: 1, synth.WDTYPE_BF16: 0, synth.WDTYPE_FP8WO: 2, synth.WDTYPE_INT4WO_128: 3}
+    reached = set()
+    for shape in _shapes():
+        for wd, wm in wmode.items():
+            cfg = B.make_config(dataclasses.replace(shape, weight_dtype=wd), 64, 64, 64, 4096)
+            for gemm in B.GEMMS:
+                for batch in (32, 33, 64):
+                    kernel, tokens, rows, splits, _ = B.www_debug_route(cfg, gemm, batch)
+                    if kernel == "decode_mid":
+                        assert batch > 32 and gemm in ("o", "down") and tokens == 64 and splits > 1 and shape.d_model % rows == 0
+                        reached.add((wm, rows // 16))
+    built = {tuple(map(int, m.groups())) for m in (re.match(r"_Z15mid_gemm_kernelILi(\d+)ELi(\d+)E", k) for k in _kernels()) if m}
+    assert reached == built == {(0, 2), (0, 4), (2, 2)}

@@ -1033,9 +1033,12 @@ __global__ __launch_bounds__(256) void decode_attn_kernel(const uint16_t* __rest
 // of one query head: 16-byte loads, two (four with 64-wide heads) records per instruction, eight instructions on their way; wavefronts
 // v, v + G, ... share the records of head v in blocks of 16 (32), what they have is combined through LDS in that order.  Sequences that
 // were a single segment were finished by the attention kernel itself.
-// Bound by the launch, two memory round trips (plan, records) and instruction fetch.  With a wavefront for all query heads of a run of
-// records (4-byte loads, four records on their way, one exponential more per record) 8B shape, us: one sequence of 1041 tokens
-// 6.5 -> 4.9, of 8192 8.5 -> 6.2, three of 2000 to 8000 7.7 -> 5.5, 64 of the usual mix 5.0 -> 4.8.
+// Bound by the launch, memory round trips (the plan; records, 16 a round with 128-wide heads, of which a wavefront has up to 64 with eight
+// query heads, 32 with four) and instruction fetch.  With a wavefront for all query heads of a run of records (4-byte loads, four records on
+// their way, one exponential more per record) 8B shape, us: one sequence of 1041 tokens 6.5 -> 4.9, of 8192 8.5 -> 6.2, three of 2000 to 8000
+// 7.7 -> 5.5, 64 of the usual mix 5.0 -> 4.8.  Eight kv heads, one sequence of 1041, 8192 and 131 072 tokens, by query heads per kv head:
+// one 4.8 / 5.5 / 8.2 -> 4.8 / 4.8 / 4.8, two 5.4 / 5.7 / 9.4 -> 4.8 / 4.8 / 5.7, four 6.3 / 7.2 / 11.2 -> 4.5 / 5.5 / 7.9, eight
+// 8.7 / 10.9 / 17.5 -> 5.8 / 7.6 / 12.1 (one kv head, eight: 7.6 / 10.5 / 29.8 -> 4.9 / 7.0 / 20.0); 64-wide heads likewise, 64 and more sequences equal.
 #define MERGE_WAVES 8
 template <int HD, int G>
 __global__ __launch_bounds__(64 * MERGE_WAVES) void decode_attn_merge_kernel(const int32_t* __restrict__ seq_lens, int Hkv, const int32_t* __restrict__ hdr,
@@ -1127,7 +1130,10 @@ __global__ __launch_bounds__(64 * MERGE_WAVES) void decode_attn_merge_kernel(con
 
 // ------------------------------------------------------------------------------------------------
 // Greedy next token: index of the largest logit, the lowest index winning ties.  The output head's workgroups leave the largest of their rows
-// per token (a kernel of its own that read the logits again: 4.8 us a step, 9 with 64 sequences); one workgroup per token combines these.
+// per token; one workgroup per token combines these.  Two kernels that read the logits again took 9 us, 19 with 128 sequences; this one takes
+// 4.2, and the head as much longer as its records (4 bytes a line) and registers (FP8 17 to 32 tokens 130 for 128) cost: head and all behind it, 4096
+// columns and 128 256 rows, us, 1, 17, 32, 64 and 128 sequences 174.5 -> 173.0, 188.3 -> 187.4, 191.6 -> 191.3, 215.1 -> 210.0, 314.7 -> 315.3;
+// FP8 95.8 -> 91.4, 109.2 -> 106.3, 113.9 -> 110.1, 148.8 -> 144.7, 302.3 -> 301.3.
 __global__ __launch_bounds__(256) void argmax_kernel(const float* __restrict__ val, const int* __restrict__ idx, int n, int32_t* __restrict__ out) {
   const int tid = threadIdx.x;
   float best = NEG_INF;

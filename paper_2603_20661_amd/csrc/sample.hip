@@ -394,9 +394,13 @@ __device__ __forceinline__ u64 draw_target(float u, u64 nucleus) {
 }
 
 // put(place, logit, index) for every element of a block (of the n that are valid) that lies in a bin; places are counted in LDS, in no particular order, and
-// the range of the keys is kept
+// the range of the keys is kept: step by step, or with the larger blocks, which come where all compute units have several workgroups, once at the
+// end (128 256 tokens, 256 rows of standard deviation 2, top_p 0.8 125.7 -> 122.7 us, of 0.02 310 -> 292; but one row of 32 000, in smaller
+// blocks, 53.0 -> 55.7)
 template <int N, typename P>
 __device__ __forceinline__ void list_members(f32x4 (&x)[N], const InBin& in_bin, int n, int* count, uint32_t* klo, uint32_t* khi, P&& put) {
+  constexpr bool AT_END = N > ROW_PER;
+  uint32_t least = 0xFFFFFFFFu, largest = 0u;
   each_group(x, [&](f32x4 v, int k) __attribute__((always_inline)) {
     const int i = (k * TPB + (int)threadIdx.x) * 4;
     uint32_t mine = 0;
@@ -408,18 +412,32 @@ __device__ __forceinline__ void list_members(f32x4 (&x)[N], const InBin& in_bin,
       const int lane = threadIdx.x & 63, leader = __ffsll((long long)who) - 1, e = __ffs((int)mine) - 1;
       const float y = e == 0 ? v[0] : e == 1 ? v[1] : e == 2 ? v[2] : v[3];
       uint32_t lo = mine ? key_of(y) : 0xFFFFFFFFu, hi = mine ? key_of(y) : 0u;
-      wave_range(lo, hi);
+      if constexpr (AT_END) {
+        least = min(least, lo);
+        largest = max(largest, hi);
+      } else {
+        wave_range(lo, hi);
+      }
       int at = 0;
       if (lane == leader) {
         at = atomicAdd(count, __popcll(who));
-        atomicMin(klo, lo);
-        atomicMax(khi, hi);
+        if constexpr (!AT_END) {
+          atomicMin(klo, lo);
+          atomicMax(khi, hi);
+        }
       }
       at = __shfl(at, leader) + __popcll(who & ((1ull << lane) - 1));
       if (mine) put(at, y, i + e);
       mine &= mine - 1;
     }
   });
+  if (AT_END && __any(largest)) {
+    wave_range(least, largest);
+    if ((threadIdx.x & 63) == 0) {
+      atomicMin(klo, least);
+      atomicMax(khi, largest);
+    }
+  }
 }
 
 // ---- rows of up to 16 N * TPB bytes: one workgroup per row, everything in registers and LDS

@@ -23,7 +23,7 @@
 // C has no other lower bound: with few tokens in the batch a chunk is a single pair, and the whole GPU works on it.  (At
 // least 16 pairs a chunk, one sequence of 1041 tokens had 17 wavefronts: 32 us per layer of the 8B shape against 6; a
 // step took 4197 us, 3835 with at least 8 pairs, 3661 with 4, 3543 with 1.)  A sequence of up to 32 768 tokens is cut into
-// at most 64 full chunks, because the merge reads 32 records per memory round trip (a step of one sequence with 64 chunks
+// at most 64 full chunks, because the merge reads these in one or two memory round trips (a step of one sequence with 64 chunks
 // and with one per wavefront, us: 4096 tokens 3762 / 3877, 8192 3862 / 4014, 16 384 4058 / 4120, 32 768 4467 / 4475).  Beyond, the
 // wavefronts that this leaves without work cost more than a round trip (65 536: 5325 / 5122, 131 072: 7027 / 6410), so chunks
 // of 16 pairs are long enough.
@@ -1029,103 +1029,102 @@ __global__ __launch_bounds__(256) void decode_attn_kernel(const uint16_t* __rest
   }
 }
 
-// Merges the records of one (sequence, kv head) and writes the packed hi/lo operand of the O projection.  A wavefront merges records
-// of one query head: 16-byte loads, two (four with 64-wide heads) records per instruction, eight instructions on their way; wavefronts
-// v, v + G, ... share the records of head v in blocks of 16 (32), what they have is combined through LDS in that order.  Sequences that
-// were a single segment were finished by the attention kernel itself.
-// Bound by the launch, memory round trips (the plan; records, 16 a round with 128-wide heads, of which a wavefront has up to 64 with eight
-// query heads, 32 with four) and instruction fetch.  With a wavefront for all query heads of a run of records (4-byte loads, four records on
-// their way, one exponential more per record) 8B shape, us: one sequence of 1041 tokens 6.5 -> 4.9, of 8192 8.5 -> 6.2, three of 2000 to 8000
-// 7.7 -> 5.5, 64 of the usual mix 5.0 -> 4.8.  Eight kv heads, one sequence of 1041, 8192 and 131 072 tokens, by query heads per kv head:
-// one 4.8 / 5.5 / 8.2 -> 4.8 / 4.8 / 4.8, two 5.4 / 5.7 / 9.4 -> 4.8 / 4.8 / 5.7, four 6.3 / 7.2 / 11.2 -> 4.5 / 5.5 / 7.9, eight
-// 8.7 / 10.9 / 17.5 -> 5.8 / 7.6 / 12.1 (one kv head, eight: 7.6 / 10.5 / 29.8 -> 4.9 / 7.0 / 20.0); 64-wide heads likewise, 64 and more sequences equal.
-#define MERGE_WAVES 8
+// Merges the records of one (sequence, kv head) and writes the packed hi/lo operand of the O projection.  The records are cut into eight runs, in
+// key order; a run is added up record by record, then the runs one by one, so the order of all sums depends on the number of records alone: sums
+// split by the query heads that share a kv head moved the cache entries of a chunk's last position in their last bits, and with them, after 32
+// layers, a chunked prompt's logits by 2e-4.  A wavefront takes runs of one query head, two (four with 64-wide heads) side by side: 16-byte loads,
+// up to eight records of each run on their way.  Up to eight records are runs of one: the threads that write the result read them all, without LDS
+// (eight query heads, 33 and 128 sequences 5.5 -> 5.0, 5.6 -> 5.1 us).  Sequences that were a single segment were finished by the attention kernel.
+// Bound by the launch, memory round trips (plan, records) and instruction fetch.  Against a wavefront per run for all query heads (4-byte loads,
+// four records on their way), eight kv heads of 128, us by query heads per kv head: one sequence of 2000 and 40 000 tokens, two 6.3 -> 5.2, 6.8 ->
+// 5.2, four 7.2 -> 5.9, 8.1 -> 6.6, eight 11.2 -> 8.5, 12.3 -> 9.3; three of 4000 to 8000, four 6.1 -> 5.5, eight 9.0 -> 7.8; 16 to 128
+// sequences, up to four 4.7 to 4.9 on both sides, eight 5.1 to 7.8 -> 4.8 to 5.1; heads of 64, one sequence of 2000, four 6.9 -> 4.8, eight 8.7 -> 6.2.
+constexpr int MERGE_RUNS = 8;
 template <int HD, int G>
-__global__ __launch_bounds__(64 * MERGE_WAVES) void decode_attn_merge_kernel(const int32_t* __restrict__ seq_lens, int Hkv, const int32_t* __restrict__ hdr,
+__global__ __launch_bounds__(1024) void decode_attn_merge_kernel(const int32_t* __restrict__ seq_lens, int Hkv, const int32_t* __restrict__ hdr,
                                                                   const int32_t* __restrict__ pref, const float* __restrict__ part,
-                                                                  uint16_t* __restrict__ xo, int MT, int first_row) {
-  constexpr int PSTRIDE = HD + 4, LR = HD / 4, RI = 64 / LR, U = 8;  // lanes of a record, records per load, loads on their way
+                                                                  uint16_t* __restrict__ xo, int MT, int first_row, int waves) {
+  constexpr int PSTRIDE = HD + 4, LR = HD / 4, SIDE = 64 / LR, U = 8;  // lanes of a record, runs side by side, records of a run on their way
   const int j = blockIdx.x, b = blockIdx.y, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int hh = wave % G, v = wave / G, sharers = MERGE_WAVES / G;
   const int C = hdr[1];
   const int P = max(0, (seq_lens[b] + 31) / 32);
   const int S = pref[b] * Hkv + j * P;  // list position of this sequence's first pair
   const int first_w = S / C;
   const int nrec = (S + P - 1) / C - first_w + 1;
   if (nrec <= 1) return;
-  const int n_mid = min(sharers, (nrec + U * RI - 1) / (U * RI));
-  if (v >= n_mid) return;  // (the barrier below counts the wavefronts that are left)
   const int first_slot = 2 * first_w + (S == first_w * C ? 0 : 1);  // later wavefronts begin with this sequence: even records
-  const int sub = lane / LR, c = (lane % LR) * 4;
-  float M = NEG_INF, L = 0.f;
-  f32x4 o = {0.f, 0.f, 0.f, 0.f};
-  for (int s0 = v * U * RI; s0 < nrec; s0 += n_mid * U * RI) {
-    f32x4 ov[U];
-    float2 ml[U];
-    auto request = [&](int u) __attribute__((always_inline)) {
-      const int r = min(s0 + u * RI + sub, nrec - 1);
-      const float* rec = part + ((int64_t)(r == 0 ? first_slot : 2 * (first_w + r)) * G + hh) * PSTRIDE;
-      ml[u] = *reinterpret_cast<const float2*>(rec + HD);
-      ov[u] = *reinterpret_cast<const f32x4*>(rec + c);
-    };
-    // (with many sequences most have two or three records: eight loads for them cost 1.2 us of a launch with 128 sequences)
-    request(0);
-    if (s0 + RI < nrec) {
-      request(1);
-      if (s0 + 2 * RI < nrec) {
-        request(2);
-        request(3);
-        if (s0 + 4 * RI < nrec) { request(4); request(5); request(6); request(7); }
-      }
-    }
-    float Mn = M;
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (s0 + u * RI >= nrec) break;
-      Mn = fmaxf(Mn, ml[u].x);  // (lanes past the end have the last record once more)
-    }
-    const float ref = Mn == NEG_INF ? 0.f : Mn, a = __builtin_amdgcn_exp2f(M - ref);
-    L *= a;
-    o *= a;
-    M = Mn;
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (s0 + u * RI >= nrec) break;
-      if (s0 + u * RI + sub < nrec) {
-        const float w = __builtin_amdgcn_exp2f(ml[u].x - ref);
-        L += ml[u].y * w;
-        o += ov[u] * w;
-      }
-    }
-  }
+  const int per = (nrec + MERGE_RUNS - 1) / MERGE_RUNS, n_runs = (nrec + per - 1) / per;
+  float M, L;
+  f32x4 o;
   auto take = [&](float mv, float lv, f32x4 ov) __attribute__((always_inline)) {
     const float Mn = fmaxf(M, mv), ref = Mn == NEG_INF ? 0.f : Mn;
     const float a = __builtin_amdgcn_exp2f(M - ref), w = __builtin_amdgcn_exp2f(mv - ref);
-    L = L * a + lv * w;
-    o = o * a + ov * w;
+    L = __builtin_fmaf(L, a, lv * w);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i] = __builtin_fmaf(o[i], a, ov[i] * w);
     M = Mn;
   };
+  auto add_run = [&](int hh, int c, int r0, int r_end, int longest) __attribute__((always_inline)) {
+    M = NEG_INF;
+    L = 0.f;
+    o = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int s0 = 0; s0 < longest; s0 += U) {
+      f32x4 ov[U];
+      float2 ml[U];
+      auto request = [&](int u) __attribute__((always_inline)) {
+        const int r = min(r0 + s0 + u, nrec - 1);
+        const float* rec = part + ((int64_t)(r == 0 ? first_slot : 2 * (first_w + r)) * G + hh) * PSTRIDE;
+        ml[u] = *reinterpret_cast<const float2*>(rec + HD);
+        ov[u] = *reinterpret_cast<const f32x4*>(rec + c);
+      };
+      // (with many sequences most have two or three records: eight loads for them cost 1.2 us of a launch with 128 sequences)
+      request(0);
+      if (s0 + 1 < longest) {
+        request(1);
+        if (s0 + 2 < longest) {
+          request(2);
+          request(3);
+          if (s0 + 4 < longest) { request(4); request(5); request(6); request(7); }
+        }
+      }
 #pragma unroll
-  for (int x = LR; x < 64; x <<= 1) take(__shfl_xor(M, x), __shfl_xor(L, x), f32x4{__shfl_xor(o[0], x), __shfl_xor(o[1], x), __shfl_xor(o[2], x), __shfl_xor(o[3], x)});
-  if (n_mid > 1) {
-    __shared__ float mid[MERGE_WAVES][PSTRIDE];
-    if (lane < LR) {
-      *reinterpret_cast<f32x4*>(&mid[wave][c]) = o;
-      if (lane == 0) { mid[wave][HD] = M; mid[wave][HD + 1] = L; }
+      for (int u = 0; u < U; ++u) {
+        if (s0 + u >= longest) break;
+        if (r0 + s0 + u < r_end) take(ml[u].x, ml[u].y, ov[u]);
+      }
+    }
+  };
+  __shared__ float mid[MERGE_RUNS][G][PSTRIDE];
+  if (per > 1) {
+    const int hh = wave % G, sub = lane / LR, c = (lane % LR) * 4;
+    for (int run0 = wave / G * SIDE; run0 < n_runs; run0 += waves / G * SIDE) {
+      const int r0 = (run0 + sub) * per;
+      add_run(hh, c, r0, min(nrec, r0 + per), per);
+      if (run0 + sub < n_runs) {
+        float* out = mid[run0 + sub][hh];
+        *reinterpret_cast<f32x4*>(out + c) = o;
+        if (c == 0) *reinterpret_cast<float2*>(out + HD) = make_float2(M, L);
+      }
     }
     __syncthreads();
-    if (v > 0) return;
-    for (int w = wave + G; w < n_mid * G; w += G) take(mid[w][HD], mid[w][HD + 1], *reinterpret_cast<const f32x4*>(&mid[w][c]));
   }
-  if (lane < LR) {
-    const float inv = 1.f / L;
-    union { uint16_t s[4]; u32x2 v; } hi, lo;
+  const int hh = threadIdx.x / LR, c = (threadIdx.x % LR) * 4;
+  if (hh >= G) return;
+  if (per > 1) {
+    M = mid[0][hh][HD];
+    L = mid[0][hh][HD + 1];
+    o = *reinterpret_cast<const f32x4*>(&mid[0][hh][c]);
+    for (int u = 1; u < n_runs; ++u) take(mid[u][hh][HD], mid[u][hh][HD + 1], *reinterpret_cast<const f32x4*>(&mid[u][hh][c]));
+  } else {  // runs of one record
+    add_run(hh, c, 0, nrec, nrec);
+  }
+  const float inv = 1.f / L;
+  union { uint16_t s[4]; u32x2 v; } hi, lo;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) split_f16(o[i] * inv, hi.s[i], lo.s[i]);
-    const int k = (j * G + hh) * HD + c;
-    *reinterpret_cast<u32x2*>(xo + attn_out_offset(k, b, 0, MT, first_row, Hkv * G * HD / 16)) = hi.v;
-    *reinterpret_cast<u32x2*>(xo + attn_out_offset(k, b, 1, MT, first_row, Hkv * G * HD / 16)) = lo.v;
-  }
+  for (int i = 0; i < 4; ++i) split_f16(o[i] * inv, hi.s[i], lo.s[i]);
+  const int k = (j * G + hh) * HD + c;
+  *reinterpret_cast<u32x2*>(xo + attn_out_offset(k, b, 0, MT, first_row, Hkv * G * HD / 16)) = hi.v;
+  *reinterpret_cast<u32x2*>(xo + attn_out_offset(k, b, 1, MT, first_row, Hkv * G * HD / 16)) = lo.v;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1341,13 +1340,16 @@ void launch_attn_plan(www_model* m, const int32_t* lens, int batch, hipStream_t 
 void launch_decode_attn(www_model* m, int l, const int32_t* lens, const int32_t* table, int batch, uint16_t* out, int MT, int first_row, hipStream_t st) {
   const uint16_t *kplane = m->kv + (int64_t)(2 * l) * m->kv_plane, *vplane = m->kv + (int64_t)(2 * l + 1) * m->kv_plane;
   const float* kvscale = m->kv_scales + (int64_t)l * m->kv_scale_plane;
+  // all eight runs of a head side by side where a wavefront takes no more than one query head's at a time and every workgroup has a compute unit (8B
+  // shape, a layer of a step, us: one sequence of 2000 tokens 34.8 -> 34.2, 16 47.3 -> 47.0; 64 72.1 -> 72.9, 128 80.3 -> 82.3)
+  const int merge_waves = m->G * m->hd > 256 && m->Hkv * batch <= decode_wg_target() ? 16 : 8;
 #define ATTN(HD_, G_)                                                                                                              \
   {                                                                                                                                \
     hipLaunchKernelGGL((decode_attn_kernel<HD_, G_>), dim3(m->attn_waves / 4), dim3(256), 0, st, m->q_hi, m->q_lo, kplane, vplane,  \
                        kvscale, lens, table, batch, (int)m->cfg.max_blocks_per_seq, m->Hq, m->Hkv, m->attn_hdr, m->attn_start,      \
                        m->attn_part, out, MT, first_row);                                                                           \
-    hipLaunchKernelGGL((decode_attn_merge_kernel<HD_, G_>), dim3(m->Hkv, batch), dim3(64 * MERGE_WAVES), 0, st, lens, m->Hkv,      \
-                       m->attn_hdr, m->attn_pref, m->attn_part, out, MT, first_row);                                                \
+    hipLaunchKernelGGL((decode_attn_merge_kernel<HD_, G_>), dim3(m->Hkv, batch), dim3(64 * merge_waves), 0, st, lens, m->Hkv,               \
+                       m->attn_hdr, m->attn_pref, m->attn_part, out, MT, first_row, merge_waves);                                   \
   }
   if (m->hd == 128) {
     if (m->G == 1) ATTN(128, 1) else if (m->G == 2) ATTN(128, 2) else if (m->G == 4) ATTN(128, 4) else ATTN(128, 8)

@@ -1056,15 +1056,16 @@ __global__ __launch_bounds__(1024) void decode_attn_merge_kernel(const int32_t* 
   const int per = (nrec + MERGE_RUNS - 1) / MERGE_RUNS, n_runs = (nrec + per - 1) / per;
   float M, L;
   f32x4 o;
-  auto take = [&](float mv, float lv, f32x4 ov) __attribute__((always_inline)) {
+  // (one of the two products of a sum is rounded before it: which one is part of the order)
+  auto take = [&](float mv, float lv, f32x4 ov, bool old_rounded) __attribute__((always_inline)) {
     const float Mn = fmaxf(M, mv), ref = Mn == NEG_INF ? 0.f : Mn;
     const float a = __builtin_amdgcn_exp2f(M - ref), w = __builtin_amdgcn_exp2f(mv - ref);
     L = __builtin_fmaf(L, a, lv * w);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) o[i] = __builtin_fmaf(o[i], a, ov[i] * w);
+    for (int i = 0; i < 4; ++i) o[i] = old_rounded ? __builtin_fmaf(ov[i], w, o[i] * a) : __builtin_fmaf(o[i], a, ov[i] * w);
     M = Mn;
   };
-  auto add_run = [&](int hh, int c, int r0, int r_end, int longest) __attribute__((always_inline)) {
+  auto add_run = [&](int hh, int c, int r0, int r_end, int longest, bool old_rounded) __attribute__((always_inline)) {
     M = NEG_INF;
     L = 0.f;
     o = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -1090,7 +1091,7 @@ __global__ __launch_bounds__(1024) void decode_attn_merge_kernel(const int32_t* 
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         if (s0 + u >= longest) break;
-        if (r0 + s0 + u < r_end) take(ml[u].x, ml[u].y, ov[u]);
+        if (r0 + s0 + u < r_end) take(ml[u].x, ml[u].y, ov[u], old_rounded);
       }
     }
   };
@@ -1099,7 +1100,7 @@ __global__ __launch_bounds__(1024) void decode_attn_merge_kernel(const int32_t* 
     const int hh = wave % G, sub = lane / LR, c = (lane % LR) * 4;
     for (int run0 = wave / G * SIDE; run0 < n_runs; run0 += waves / G * SIDE) {
       const int r0 = (run0 + sub) * per;
-      add_run(hh, c, r0, min(nrec, r0 + per), per);
+      add_run(hh, c, r0, min(nrec, r0 + per), per, HD == 64);
       if (run0 + sub < n_runs) {
         float* out = mid[run0 + sub][hh];
         *reinterpret_cast<f32x4*>(out + c) = o;
@@ -1114,9 +1115,9 @@ __global__ __launch_bounds__(1024) void decode_attn_merge_kernel(const int32_t* 
     M = mid[0][hh][HD];
     L = mid[0][hh][HD + 1];
     o = *reinterpret_cast<const f32x4*>(&mid[0][hh][c]);
-    for (int u = 1; u < n_runs; ++u) take(mid[u][hh][HD], mid[u][hh][HD + 1], *reinterpret_cast<const f32x4*>(&mid[u][hh][c]));
+    for (int u = 1; u < n_runs; ++u) take(mid[u][hh][HD], mid[u][hh][HD + 1], *reinterpret_cast<const f32x4*>(&mid[u][hh][c]), false);
   } else {  // runs of one record
-    add_run(hh, c, 0, nrec, nrec);
+    add_run(hh, c, 0, nrec, nrec, false);
   }
   const float inv = 1.f / L;
   union { uint16_t s[4]; u32x2 v; } hi, lo;

@@ -1035,10 +1035,11 @@ __global__ __launch_bounds__(256) void decode_attn_kernel(const uint16_t* __rest
 // layers, a chunked prompt's logits by 2e-4.  A wavefront takes runs of one query head, two (four with 64-wide heads) side by side: 16-byte loads,
 // up to eight records of each run on their way.  Up to eight records are runs of one: the threads that write the result read them all, without LDS
 // (eight query heads, 33 and 128 sequences 5.5 -> 5.0, 5.6 -> 5.1 us).  Sequences that were a single segment were finished by the attention kernel.
-// Bound by the launch, memory round trips (plan, records) and instruction fetch.  Against a wavefront per run for all query heads (4-byte loads,
-// four records on their way), eight kv heads of 128, us by query heads per kv head: one sequence of 2000 and 40 000 tokens, two 6.3 -> 5.2, 6.8 ->
-// 5.2, four 7.2 -> 5.9, 8.1 -> 6.6, eight 11.2 -> 8.5, 12.3 -> 9.3; three of 4000 to 8000, four 6.1 -> 5.5, eight 9.0 -> 7.8; 16 to 128
-// sequences, up to four 4.7 to 4.9 on both sides, eight 5.1 to 7.8 -> 4.8 to 5.1; heads of 64, one sequence of 2000, four 6.9 -> 4.8, eight 8.7 -> 6.2.
+// Bound by the launch, memory round trips (plan, records), a compute unit's intake and instruction fetch.  Against a wavefront per run for all
+// query heads (4-byte loads, four records on their way), eight kv heads of 128, us by query heads per kv head: one sequence of 1041 tokens, four 6.5
+// -> 5.3; of 2000 and 40 000, two 6.2 -> 4.8, 6.8 -> 5.2, four 7.2 -> 6.1, 8.1 -> 6.6, eight 11.2 -> 8.2, 12.3 -> 9.2; three of 4000 to 8000, four 6.0
+// -> 5.1, eight 9.0 -> 6.8; 16 to 128 sequences, up to four 4.6 to 4.9 on both sides, eight 5.1 to 7.7 -> 4.8 to 5.1; heads of 64, one sequence of
+// 2000, four 7.0 -> 4.6, eight 8.7 -> 6.1.
 constexpr int MERGE_RUNS = 8;
 template <int HD, int G>
 __global__ __launch_bounds__(1024) void decode_attn_merge_kernel(const int32_t* __restrict__ seq_lens, int Hkv, const int32_t* __restrict__ hdr,
@@ -1078,15 +1079,11 @@ __global__ __launch_bounds__(1024) void decode_attn_merge_kernel(const int32_t* 
         ml[u] = *reinterpret_cast<const float2*>(rec + HD);
         ov[u] = *reinterpret_cast<const f32x4*>(rec + c);
       };
-      // (with many sequences most have two or three records: eight loads for them cost 1.2 us of a launch with 128 sequences)
-      request(0);
-      if (s0 + 1 < longest) {
-        request(1);
-        if (s0 + 2 < longest) {
-          request(2);
-          request(3);
-          if (s0 + 4 < longest) { request(4); request(5); request(6); request(7); }
-        }
+      // (no more than there are: two, four or eight at a time, 33 records of four query heads, 70 KB, took 6.1 us, and 128 sequences 1.2 more)
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (s0 + u >= longest) break;
+        request(u);
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
@@ -1131,9 +1128,11 @@ __global__ __launch_bounds__(1024) void decode_attn_merge_kernel(const int32_t* 
 // ------------------------------------------------------------------------------------------------
 // Greedy next token: index of the largest logit, the lowest index winning ties.  The output head's workgroups leave the largest of their rows
 // per token; one workgroup per token combines these.  Two kernels that read the logits again took 9 us, 19 with 128 sequences; this one takes
-// 4.2, and the head as much longer as its records (4 bytes a line) and registers (FP8 17 to 32 tokens 130 for 128) cost: head and all behind it, 4096
+// 4.2, and the head as much longer as it compares and exchanges (no shorter with the records of a workgroup side by side, which take 0.5 us more
+// to read here, nor with the registers of four wavefronts per SIMD where FP8 weights and 17 to 32 tokens have those of three): head and all behind it, 4096
 // columns and 128 256 rows, us, 1, 17, 32, 64 and 128 sequences 174.5 -> 173.0, 188.3 -> 187.4, 191.6 -> 191.3, 215.1 -> 210.0, 314.7 -> 315.3;
-// FP8 95.8 -> 91.4, 109.2 -> 106.3, 113.9 -> 110.1, 148.8 -> 144.7, 302.3 -> 301.3.
+// FP8 95.8 -> 91.4, 109.2 -> 106.3, 113.9 -> 110.1, 148.8 -> 144.7, 302.3 -> 301.3.  (With one narrow layer in front, 24, 32 and 100 sequences: 253.9 ->
+// 252.6, 264 -> 262.4, 389.8 -> 392.2; FP8 167.3 -> 169.3, 176.0 -> 177.7, 364.2 -> 369.6.)
 __global__ __launch_bounds__(256) void argmax_kernel(const float* __restrict__ val, const int* __restrict__ idx, int n, int32_t* __restrict__ out) {
   const int tid = threadIdx.x;
   float best = NEG_INF;

@@ -480,8 +480,8 @@ static float general_us(int NRG, int KB, int M, float wbytes) {
 // int4, 5 sequences: QKV 10.8 / 13.0, O 6.8 / 10.4, gate/up 18.0 / 24.4, down 13.2 / 17.7, head 56 / 67; the narrow int4 products
 // also from 17 to 32 tokens (steps of up to 6 layers, 17 and 32 sequences: 8B shape 667 / 719 and 736 / 782, 1B shape at 20 and
 // 32 380 / 443 and 412 / 468, 8192 columns and 4 layers 906 / 928 and 966 / 988), and their gate/up product where 128 rows a workgroup
-// are one round (24 sequences, 8B shape 27.4 / 29.1; with the other kernel's longer unpacking of then, 2048 columns 11.4 / 13.2, 3072
-// 14.8 / 16.7, 5120 32.9 / 38.8, 1024 8.5 / 8.6).  Not the gate/up GEMM
+// are one round (24 sequences, 8B shape 27.4 / 29.1; a layer of a step, 24 and 32 sequences, 1024 columns 41.3 / 41.8 and 43.2 / 43.2, 2048
+// 49.6 / 52.0 and 53.1 / 55.4, 3072 71.3 / 73.2 and 74.8 / 75.9, 4096 84.5 / 86.8 and 89.9 / 91.1, 5120 101.6 / 105.6 and 106.8 / 109.2).  Not the gate/up GEMM
 // of the other formats, which has rows for every compute unit without a split (39.0 / 37.6, with FP8 24.6 / 21.9; 1B shape with up
 // to 8 tokens 13.4 / 14.6), unless 64 rows per workgroup fill the chip in one round: then up to 8 tokens and, where the other kernel
 // has to split k, from 17 on (1B shape, 32 tokens 15.4 / 16.9; a step of 24 sequences with FP8 weights 880 / 896; of 12 and 16

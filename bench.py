@@ -51,24 +51,24 @@ CALIB_COPY_BYTES = 1 << 28  # size of the counter-calibration copy
 
 # HBM traffic of the decode kernel classes, from two `rocprofv3 --pmc` runs of this file (FETCH_SIZE, then WRITE_SIZE;
 # profiles/decode_kernels_8b_traffic.md).  Counter units per launch, averaged over the 224 to 256 launches per class of those runs
-# (8 for the output head); scale = KiB per unit, from what the same counter read for the calibration copy above (131 087.1
+# (8 for the output head); scale = KiB per unit, from what the same counter read for the calibration copy above (131 086.9
 # units of FETCH_SIZE for 262 144 KiB read, 262 144.0 units of WRITE_SIZE for 262 144 KiB written).  The attention
 # reading is rescaled linearly to the reported launch's context (its traffic is proportional to it); the GEMMs' bytes do
 # not depend on the step.  Valid only for the kernels it was taken with: the hash covers the text of the decode path's
 # sources; every reading is reported as null when that text has changed.
 TRAFFIC = {
     "workload": "8b",
-    "fetch_scale": 262144.0 / 131087.1, "write_scale": 1.0,
+    "fetch_scale": 262144.0 / 131086.9, "write_scale": 1.0,
     "classes": {   # class: (FETCH_SIZE units, WRITE_SIZE units, algorithmic bytes of the measured launches or None = this run's)
-        "decode_attention": (165370.9 + 1570.1, 3108.5 + 1024.0, 80383 * 4160),
-        "qkv_gemm": (32977.1, 9513.0, None),
-        "o_gemm": (23116.1, 6282.0, None),
-        "gate_up_gemm": (118936.0, 3584.0, None),
-        "down_gemm": (76433.4, 10313.0, None),
-        "lm_head_gemm": (529444.8, 36547.9, None),
+        "decode_attention": (165370.2 + 1574.6, 3108.7 + 1024.0, 80383 * 4160),
+        "qkv_gemm": (32968.8, 9513.0, None),
+        "o_gemm": (23123.6, 6282.0, None),
+        "gate_up_gemm": (118941.1, 3584.0, None),
+        "down_gemm": (76432.9, 10313.0, None),
+        "lm_head_gemm": (529411.9, 36527.1, None),
     },
     "sources": tuple("paper_2603_20661_amd/csrc/" + f for f in ("decode.hip", "decode_small.hip", "decode_mid.hip", "decode_gemm.h", "common.h")),
-    "sha256": "4152e7b584f56bbdbd20b2f63f97935e6d957b07c5e76dc71c3d68256283de76",
+    "sha256": "24bed9f7b20de5396c2623ce38b3a977d7ba20bc15b2a739b9d23780b13a7a64",
 }
 
 

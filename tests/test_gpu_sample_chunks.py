@@ -12,6 +12,27 @@ from test_gpu_sample_sizes import run
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("batch,vocab", [(4, 8193), (5, 16383), (4, 262145), (4, 300001), (90, 16385), (130, 16384), (70, 32769)])
+@pytest.mark.parametrize("std", [3.0, 0.05])
+def test_chunks_and_runs(batch, vocab, std):
+    lg = synth.normal_f32(91, vocab, batch * vocab, std=std).reshape(batch, vocab).copy()
+    for k, at in enumerate((0, 255, 256, vocab // 2 - 1, vocab // 2, vocab - 1)):    # certain tokens at the ends of runs and chunks
+        if k + 4 < batch:
+            lg[k + 4, at] = 60.0
+    u = np.linspace(0.0, 0.999, batch).astype(np.float32)
+    print(f"batch {batch} vocab {vocab} std {std}", flush=True)
+    keep = sorted({*range(min(batch, 12)), batch - 2, batch - 1})                     # rows that the oracle looks at
+
+    def some(lg_all, temperature, top_p, u_all):
+        tok, e = run(lg, temperature, top_p, u)
+        return tok[keep], e[keep]
+
+    tok = check(lg[keep], 1.0, 0.9, u[keep], some)
+    for k, at in enumerate((0, 255, 256, vocab // 2 - 1, vocab // 2, vocab - 1)):
+        if k + 4 < batch:
+            assert tok[keep.index(k + 4)] == at
+
+
 def edges(batch, vocab):
     """tokens in front of which a chunk, a run of tokens or a chunk's reserved head ends, by the launch rule of sample.hip"""
     shorter = -(-vocab // 8192)
@@ -24,21 +45,6 @@ def edges(batch, vocab):
 
 
 SIZES = [(4, 8193), (5, 16383), (4, 262145), (4, 300001), (90, 16385), (130, 16384), (70, 32769)]
-
-
-@pytest.mark.parametrize("batch,vocab", SIZES)
-@pytest.mark.parametrize("std", [3.0, 0.05])
-def test_chunks_and_runs(batch, vocab, std):
-    lg = synth.normal_f32(91, vocab, batch * vocab, std=std).reshape(batch, vocab).copy()
-    u = np.linspace(0.0, 0.999, batch).astype(np.float32)
-    print(f"batch {batch} vocab {vocab} std {std}", flush=True)
-    keep = sorted({*range(min(batch, 12)), batch - 2, batch - 1})                     # rows that the oracle looks at
-
-    def some(lg_all, temperature, top_p, u_all):
-        tok, e = run(lg, temperature, top_p, u)
-        return tok[keep], e[keep]
-
-    check(lg[keep], 1.0, 0.9, u[keep], some)
 
 
 @pytest.mark.parametrize("batch,vocab", SIZES)
